@@ -13,8 +13,8 @@
 //  * the matrix cores do the k-reduction (one 16x16 tile of logits per 1 KiB
 //    fragment pair); the streamers fold finished tiles into running softmax
 //    statistics, tiles split between two waves are summed by the service wave;
-//  * two more waves do everything that needs global round trips so that the
-//    streamers never drain their rings: a LayerNorm wave prepares the next
+//  * four more waves do everything that needs global round trips so that the
+//    streamers never drain their rings: three LayerNorm waves prepare the next
 //    head's rows in LDS (double buffered), and an exchange wave all-gathers
 //    the workgroups' partial statistics through tagged records, merges them
 //    and applies the threshold test (every workgroup reaches the same
@@ -36,7 +36,14 @@ namespace eh {
 namespace {
 
 constexpr int kStreamers = 8;
-constexpr int kThreads = (kStreamers + 2) * kWave;  // streamers + exchange wave + LayerNorm wave
+// LayerNorm waves.  Every workgroup normalises every live row of every head for itself, about 5 us
+// a row of 2048 by one wave (a trip to memory, then three fp64 sweeps): one wave is enough for a
+// row or two but took 40 us for 8 rows, longer than the head's weights take to arrive (30 us).
+// Three keep the workgroup at three waves per SIMD (a fourth would cost the streamers registers:
+// 128 instead of 168, and spills).  With the exchange of four rows per sweep (Service::pass), 8 rows
+// through 24 heads of d = 2048: 1144 us before, 826 now; 1 row is unchanged.
+constexpr int kLnW = 3;
+constexpr int kThreads = (kStreamers + 1 + kLnW) * kWave;  // streamers + exchange wave + LayerNorm waves
 constexpr int kRing = 4;              // fragments per ring buffer (two buffers per streamer wave)
 constexpr int kMaxLag = 3;            // heads the streamers may be ahead of the oldest open exchange
 constexpr int kSpinLimit = 1 << 22;   // polls of a flag of this workgroup (LDS) before giving up
@@ -430,6 +437,9 @@ __device__ __forceinline__ void streamer(const DecodeParams& p, const Smem& sm, 
 // are never written; a tag from an older launch never matches, so nothing has to
 // be reset between launches.
 struct Service {
+  static constexpr int kRadix = 16;                   // workgroups of a group, and groups
+  static constexpr int kWindow = 4;                   // heads in flight
+  static constexpr int kSweepRows = kWave / kRadix;   // rows of a head a sweep looks at
   const DecodeParams& p;
   const Smem sm;
   int lane;
@@ -486,24 +496,47 @@ struct Service {
     return ok;
   }
 
-  // Lane i < count holds (in `x`) the record of the i-th source of a round.  If
-  // every record is there they are merged in lane order (fixed tree), so every
-  // reader of the same records gets bitwise the same result, and true is
-  // returned; otherwise false (nothing is kept: the caller tries again later).
-  __device__ __forceinline__ bool merge_round(const Raw& x, int count, Stats& out) const {
+  // A sweep looks at up to kSweepRows rows of a round at once: lane 16*g + i holds (in `x`) the
+  // record of the i-th of `count` sources for the g-th of them (row < 0: group g has none).  Where
+  // all of a group's records are there they are merged in lane order (fixed tree), so every
+  // reader of the same records gets bitwise the same result in `out`, and the group's bit is set
+  // in the returned mask; otherwise nothing is kept (the caller tries again later).
+  // One row per sweep made the exchange of a head take a sweep (a trip to memory and a pause,
+  // about 4 us) per row and round, which for 8 rows is longer than the head's stream.
+  __device__ __forceinline__ unsigned merge_round(const Raw& x, int row, int count, Stats& out) const {
     Stats s;
     stats_init(s);
     bool have = true;
-    if (lane < count) have = decode_record(x, s);
-    if (!__all(have)) return false;
+    if (row >= 0 && (lane & 15) < count) have = decode_record(x, s);
+    const unsigned long long there = __ballot(have && row >= 0);
+    // lanes beyond `count` have nothing to wait for
+    unsigned ok = 0;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) s = stats_merge(s, stats_shfl_xor(s, o));
+    for (int g = 0; g < kSweepRows; ++g)
+      if (((there >> (16 * g)) & 0xffffu) == 0xffffu) ok |= 1u << g;
+    if (ok == 0u) return 0u;
+#pragma unroll
+    for (int o = 1; o < kRadix; o <<= 1) s = stats_merge(s, stats_shfl_xor(s, o));
     // the merge is not bitwise symmetric in its operands (fused multiply-adds), so
-    // lanes may differ in the last bit: everybody takes lane 0's result, which is
-    // computed from the same operands in the same order in every workgroup
-    out.m = __shfl(s.m, 0); out.S = __shfl(s.S, 0); out.U = __shfl(s.U, 0);
-    out.zb = __shfl(s.zb, 0); out.ib = __shfl(s.ib, 0);
-    return true;
+    // lanes may differ in the last bit: everybody takes the group's first lane's result,
+    // which is computed from the same operands in the same order in every workgroup
+    const int src = lane & 48;
+    out.m = __shfl(s.m, src); out.S = __shfl(s.S, src); out.U = __shfl(s.U, src);
+    out.zb = __shfl(s.zb, src); out.ib = __shfl(s.ib, src);
+    return ok;
+  }
+
+  // The lowest kSweepRows set bits of `todo` (-1 where there are fewer).
+  static __device__ __forceinline__ void pick_rows(unsigned todo, int (&rows)[4]) {
+#pragma unroll
+    for (int g = 0; g < kSweepRows; ++g) {
+      rows[g] = todo ? __ffs(todo) - 1 : -1;
+      todo &= todo - 1u;  // 0 stays 0
+    }
+  }
+  __device__ __forceinline__ int my_row(const int (&rows)[4]) const {
+    const int g = lane >> 4;
+    return g == 0 ? rows[0] : g == 1 ? rows[1] : g == 2 ? rows[2] : rows[3];
   }
 
   // A two-round all-gather with radix kRadix, then finalise and
@@ -521,8 +554,6 @@ struct Service {
   // rows whose round-1 record this workgroup has written; done1 the rows of head
   // c that are decided.  pass() makes one sweep and returns true if head c got
   // decided, with `live` then holding the rows that go on to head c+1.
-  static constexpr int kRadix = 16;
-  static constexpr int kWindow = 4;
   unsigned long long done0 = 0;
   unsigned done1 = 0, stay = 0;
   int c = 0, sent = 0;
@@ -533,76 +564,77 @@ struct Service {
     const int g0 = (me / kRadix) * kRadix;
     const int gsize = min(kRadix, grid - g0);
     const int ngroups = (grid + kRadix - 1) / kRadix;
-    const bool writer = me == 0 && lane == 0;
-    // One row per open head and round in a sweep (the lowest one that still needs
+    // Up to kSweepRows rows per open head and round in a sweep (the lowest ones that still need
     // work), with all loads of the sweep issued before any is looked at, so that a
     // sweep costs one memory round trip however many heads are open.
+    const int sub = lane & (kRadix - 1);
     Raw x0[kWindow], x1;
-    int row0[kWindow], row1 = -1;
+    int rows0[kWindow][kSweepRows], rows1[kSweepRows];
+    int row0[kWindow], row1 = -1;  // this lane's
 #pragma unroll
     for (int k = 0; k < kWindow; ++k) {
       const int h = c + k;
       const int sh = (h & (kWindow - 1)) * 16;
       const unsigned todo = (h < sent) ? (live & ~(unsigned)((done0 >> sh) & 0xffffu)) : 0u;
-      row0[k] = todo ? __ffs(todo) - 1 : -1;
-      if (row0[k] >= 0 && lane < gsize) x0[k] = load_record(record_ptr(p, 0, h, g0 + lane, row0[k]));
+      pick_rows(todo, rows0[k]);
+      row0[k] = my_row(rows0[k]);
+      if (row0[k] >= 0 && sub < gsize) x0[k] = load_record(record_ptr(p, 0, h, g0 + sub, row0[k]));
     }
     const int sc = (c & (kWindow - 1)) * 16;
-    if (c < sent) {
-      const unsigned todo = (unsigned)((done0 >> sc) & 0xffffu) & live & ~done1;
-      row1 = todo ? __ffs(todo) - 1 : -1;
-      if (row1 >= 0 && lane < ngroups) {
-        const int j = lane;
-        const int src = j * kRadix + min(member, min(kRadix, grid - j * kRadix) - 1);
-        x1 = load_record(record_ptr(p, 1, c, src, row1));
-      }
+    pick_rows(c < sent ? (unsigned)((done0 >> sc) & 0xffffu) & live & ~done1 : 0u, rows1);
+    row1 = my_row(rows1);
+    if (row1 >= 0 && sub < ngroups) {
+      const int src = sub * kRadix + min(member, min(kRadix, grid - sub * kRadix) - 1);
+      x1 = load_record(record_ptr(p, 1, c, src, row1));
     }
 #pragma unroll
     for (int k = 0; k < kWindow; ++k) {
-      if (row0[k] < 0) continue;
+      if (rows0[k][0] < 0) continue;
       const int h = c + k;
       Stats s;
-      if (merge_round(x0[k], gsize, s)) {
-        if (lane == 0) write_record(p, record_ptr(p, 1, h, me, row0[k]), s);
-        done0 |= 1ull << ((h & (kWindow - 1)) * 16 + row0[k]);
-      }
+      const unsigned ok = merge_round(x0[k], row0[k], gsize, s);
+      if (ok == 0u) continue;
+      if (sub == 0 && ((ok >> (lane >> 4)) & 1u)) write_record(p, record_ptr(p, 1, h, me, row0[k]), s);
+#pragma unroll
+      for (int g = 0; g < kSweepRows; ++g)
+        if ((ok >> g) & 1u) done0 |= 1ull << ((h & (kWindow - 1)) * 16 + rows0[k][g]);
     }
-    if (row1 >= 0) {
-      const int n = row1;
+    if (rows1[0] >= 0) {
       Stats s;
-      if (merge_round(x1, ngroups, s)) {
-        done1 |= 1u << n;
+      const unsigned ok = merge_round(x1, row1, ngroups, s);
+      if (ok != 0u) {
+        const bool mine = ((ok >> (lane >> 4)) & 1u) != 0u;  // this lane's row is complete
+        const bool writer = me == 0 && sub == 0 && mine;
         float H, lse;
         stats_finalize(s, H, lse);
+        bool leaves = false;
         if (p.decide) {
-          const bool leaves = (c == p.n_heads - 1) || (H < p.tau[c]);
-          if (!leaves) stay |= 1u << n;
+          leaves = (c == p.n_heads - 1) || (H < p.tau[c]);
           if (writer) {
             if (leaves) {
-              p.exit_layer[n] = c;
-              p.token[n] = stats_token(s);
+              p.exit_layer[row1] = c;
+              p.token[row1] = stats_token(s);
             }
-            if (p.H_out) p.H_out[(long long)c * p.n_rows + n] = H;
+            if (p.H_out) p.H_out[(long long)c * p.n_rows + row1] = H;
           }
         } else if (writer) {
-          if (p.H) p.H[n] = H;
-          if (p.lse) p.lse[n] = lse;
-          if (p.argmax) p.argmax[n] = stats_token(s);
+          if (p.H) p.H[row1] = H;
+          if (p.lse) p.lse[row1] = lse;
+          if (p.argmax) p.argmax[row1] = stats_token(s);
+        }
+        const unsigned long long left = __ballot(leaves);
+#pragma unroll
+        for (int g = 0; g < kSweepRows; ++g) {
+          if ((ok >> g) & 1u) {
+            done1 |= 1u << rows1[g];
+            if (p.decide && !((left >> (16 * g)) & 1u)) stay |= 1u << rows1[g];
+          }
         }
       }
     }
     if (c >= sent || done1 != live) return false;
-    if (writer && p.decide) {
-      if (p.n_evals) atomicAdd(p.n_evals, (unsigned long long)__popc(live));
-      if (p.H_out) {
-        for (int n = 0; n < p.n_rows; ++n)
-          if (!((live >> n) & 1u)) p.H_out[(long long)c * p.n_rows + n] = NAN;
-        if (stay == 0u || c == p.l1 - 1) {
-          const int total = (p.n_heads - (c + 1)) * p.n_rows;
-          for (int i = 0; i < total; ++i) p.H_out[(long long)(c + 1) * p.n_rows + i] = NAN;
-        }
-      }
-    }
+    // entries of H_out that no evaluation fills keep the NaN this workgroup preset them to
+    if (me == 0 && lane == 0 && p.decide && p.n_evals) atomicAdd(p.n_evals, (unsigned long long)__popc(live));
     live = p.decide ? stay : 0u;
     done0 &= ~(0xffffull << sc);
     done1 = stay = 0u;
@@ -610,11 +642,14 @@ struct Service {
     return true;
   }
 
+  // The live rows are dealt to the LayerNorm waves in turn (lnw = this one's index).
   template <typename DT>
-  __device__ __forceinline__ void layernorm_rows(int l, unsigned rows, lds_frag_t* ybuf) {
+  __device__ __forceinline__ void layernorm_rows(int l, unsigned rows, lds_frag_t* ybuf, int lnw) {
     const int esz = DT::ESZ;
+    int turn = 0;
     for (int n = 0; n < 16; ++n) {
       if (!((rows >> n) & 1u)) continue;
+      if (turn++ % kLnW != lnw) continue;
       const long long r = p.row_idx ? p.row_idx[n] : n;
       const char* row = (const char*)p.h + ((long long)l * p.layer_stride + r * p.row_stride) * esz;
       ln_row_to_lds<DT>(row, p.d, p.KS, p.gamma[l], p.beta[l], p.eps, lane, n, ybuf);
@@ -686,19 +721,19 @@ struct Service {
     }
   }
 
-  // LayerNorm wave: one head ahead of the streamers (speculative: a row that turns
+  // LayerNorm waves: one head ahead of the streamers (speculative: a row that turns
   // out to have exited only wastes its column).  The set of rows it normalises is
   // the one the exchange wave knew a window earlier, a superset of the live rows.
   template <typename DT>
-  __device__ __forceinline__ void run_layernorm() {
+  __device__ __forceinline__ void run_layernorm(int lnw) {
     live = initial_live();
-    layernorm_rows<DT>(p.l0, live, sm.ybuf(p.l0 & 1));
+    layernorm_rows<DT>(p.l0, live, sm.ybuf(p.l0 & 1), lnw);
     lds_barrier();  // B_{-1}
     for (int l = p.l0; l < p.l1; ++l) {
       const int par = l & 1;
       live = (unsigned)*sm.live_word(par ^ 1);
-      if (l + 1 < p.l1) layernorm_rows<DT>(l + 1, live, sm.ybuf(par ^ 1));
-      stamp(p, l, 7, lane);
+      if (l + 1 < p.l1) layernorm_rows<DT>(l + 1, live, sm.ybuf(par ^ 1), lnw);
+      if (lnw == 0) stamp(p, l, 7, lane);
       lds_barrier();  // B_l
       if (*sm.abort_flag(par)) return;
     }
@@ -753,7 +788,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(const DecodeParams 
   } else {
     Service sv{p, sm, lane, 0u};
     if (wave == kStreamers) sv.run_exchange();
-    else sv.template run_layernorm<DT>();
+    else sv.template run_layernorm<DT>(wave - kStreamers - 1);
   }
 }
 
@@ -777,7 +812,8 @@ hipError_t decode_prepare(eh_ctx* c) {
   if (e != hipSuccess || per_cu < 1) { (void)hipGetLastError(); return hipSuccess; }
   // the kernel waits on other workgroups, so all of them must be resident at once
   c->num_cu = prop.multiProcessorCount;
-  c->decode_grid = std::min(prop.multiProcessorCount, c->VT);
+  // (the exchange is two rounds of 16 records: at most 256 workgroups)
+  c->decode_grid = std::min(std::min(prop.multiProcessorCount, c->VT), 256);
   c->decode_smem = smem;
   return hipSuccess;
 }
