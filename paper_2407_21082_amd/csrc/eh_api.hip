@@ -47,8 +47,7 @@ hipError_t scratch_address(int device, void** out) {
   return hipSuccess;
 }
 
-constexpr int kMaxNB = 10;           // token blocks (of 16) one stream launch covers
-constexpr int kStreamGrid = 512;     // workgroups of the stream kernel (2 per CU)
+constexpr int kMaxParts = 512;       // partial statistics per row there is room for (one per workgroup over the vocabulary)
 
 struct DeviceGuard {
   int prev = -1;
@@ -100,22 +99,38 @@ void free_all(eh_ctx* ctx) {
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <typename DT, bool AO>
-void launch_stream(int nbc, const eh_ctx* c, int head, int nb0, const int* n_rows_dev, int n_rows,
-                   int R_pad, hipStream_t s, const frag_t* yf, Stats* partials) {
-  const frag_t* Wf = c->Wf[head];
-  const float* bias = c->bias.empty() ? nullptr : c->bias[head];
-  dim3 g(kStreamGrid), b(256);
-#define EH_LAUNCH(NB)                                                                           \
-  hipLaunchKernelGGL((stream_kernel<DT, NB, AO>), g, b, 0, s, Wf, yf, bias, c->VT, c->KS, c->V, \
-                     nb0, n_rows_dev, n_rows, R_pad, partials)
-  if (nbc <= 1) EH_LAUNCH(1);
-  else if (nbc <= 2) EH_LAUNCH(2);
-  else if (nbc <= 4) EH_LAUNCH(4);
-  else if (nbc <= 6) EH_LAUNCH(6);
-  else if (nbc <= 8) EH_LAUNCH(8);
-  else EH_LAUNCH(10);
-#undef EH_LAUNCH
+// The k-split kernel: heads with a bias vector, bf16 up to its 64 rows, fp32 up to 32 (beyond that
+// fp32 is bound by its matrix instructions, not by the weights, and gemm_launch's kernel, with
+// twice the rows per weight operand, is the better one: 432 against 472 us at 512 rows of d = 1024,
+// 47 against 48 at 64 of d = 512; at 32 rows 47 against 36).
+bool use_ksplit(const eh_ctx* c, int n_rows) {
+  return !c->bias.empty() || n_rows <= (c->dtype == EH_BF16 ? 64 : 32);
+}
+// Rows per block of the activations' operand order: 16 for gemm_launch's kernel, 32 for all others.
+int row_block(const eh_ctx* c, int n_rows) { return c->dtype == EH_BF16 || use_ksplit(c, n_rows) ? 32 : 16; }
+
+int round_up(int n, int to) { return (n + to - 1) / to * to; }
+
+// LayerNorm of a head's rows into yf, in the operand order of the kernel that n_rows rows go to.
+void launch_ln(const eh_ctx* c, int head, const void* h, int64_t row_stride, const int* row_idx, const int* n_rows_dev,
+               int n_rows, int R_pad, frag_t* yf, hipStream_t s) {
+#define EH_LN(DT, RB)                                                                                            \
+  hipLaunchKernelGGL((ln_pack_kernel<DT, RB>), dim3(R_pad), dim3(kLnThreads), 0, s, h, row_stride, row_idx,      \
+                     n_rows_dev, n_rows, R_pad, c->d, c->KS, c->gamma[head], c->beta[head], c->eps, yf)
+  if (c->dtype == EH_BF16) EH_LN(DtBf16, 32);
+  else if (row_block(c, n_rows) == 32) EH_LN(DtF32, 32);
+  else EH_LN(DtF32, 16);
+#undef EH_LN
+}
+
+// Projection and partial statistics of the rows launch_ln has prepared.
+hipError_t project(const eh_ctx* c, int head, const int* n_rows_dev, int n_rows, bool argmax_only, const frag_t* yf,
+                   Stats* partials, int* n_parts, hipStream_t s) {
+  if (use_ksplit(c, n_rows))
+    return ksplit_launch(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, nullptr, 0, n_parts, s);
+  if (c->dtype == EH_BF16)
+    return gemm32_launch(c, head, n_rows_dev, n_rows, argmax_only, yf, partials, nullptr, n_parts, s);
+  return gemm_launch(c, head, n_rows_dev, n_rows, argmax_only, yf, partials, n_parts, s);
 }
 
 // LayerNorm + projection + statistics for one head; results to (H, lse, argmax).
@@ -127,37 +142,10 @@ eh_status run_head(eh_ctx* c, int head, const void* h, int64_t row_stride, const
                    hipStream_t s, frag_t* yf = nullptr, Stats* partials = nullptr) {
   if (!yf) yf = c->yf;
   if (!partials) partials = c->partials;
-  const bool bf = c->dtype == EH_BF16;
-  // heads without bias go to the batched kernels: bf16 in blocks of 32 rows
-  // (32x32x16 matrix instructions), f32 in blocks of 16
-  const bool batched = c->bias.empty() && c->use_gemm;
-  const int RB = (batched && bf) ? 32 : 16;
-  const int R_pad = (n_rows + RB - 1) / RB * RB;
-  {
-    dim3 g(R_pad), b(kLnThreads);
-    if (bf && RB == 32)
-      hipLaunchKernelGGL((ln_pack_kernel<DtBf16, 32>), g, b, 0, s, h, row_stride, row_idx, n_rows_dev,
-                         n_rows, R_pad, c->d, c->KS, c->gamma[head], c->beta[head], c->eps, yf);
-    else if (bf)
-      hipLaunchKernelGGL((ln_pack_kernel<DtBf16, 16>), g, b, 0, s, h, row_stride, row_idx, n_rows_dev,
-                         n_rows, R_pad, c->d, c->KS, c->gamma[head], c->beta[head], c->eps, yf);
-    else
-      hipLaunchKernelGGL((ln_pack_kernel<DtF32, 16>), g, b, 0, s, h, row_stride, row_idx, n_rows_dev,
-                         n_rows, R_pad, c->d, c->KS, c->gamma[head], c->beta[head], c->eps, yf);
-  }
-  int n_parts = kStreamGrid;
-  if (batched && bf) {
-    EH_HIP(c, gemm32_launch(c, head, n_rows_dev, n_rows, AO, yf, partials, nullptr, &n_parts, s));
-  } else if (batched) {
-    EH_HIP(c, gemm_launch(c, head, n_rows_dev, n_rows, AO, yf, partials, &n_parts, s));
-  } else {
-    const int NBtot = R_pad / 16;
-    for (int nb0 = 0; nb0 < NBtot; nb0 += kMaxNB) {
-      const int nbc = std::min(kMaxNB, NBtot - nb0);
-      if (bf) launch_stream<DtBf16, AO>(nbc, c, head, nb0, n_rows_dev, n_rows, R_pad, s, yf, partials);
-      else launch_stream<DtF32, AO>(nbc, c, head, nb0, n_rows_dev, n_rows, R_pad, s, yf, partials);
-    }
-  }
+  const int R_pad = round_up(n_rows, row_block(c, n_rows));
+  launch_ln(c, head, h, row_stride, row_idx, n_rows_dev, n_rows, R_pad, yf, s);
+  int n_parts = 0;
+  EH_HIP(c, project(c, head, n_rows_dev, n_rows, AO, yf, partials, &n_parts, s));
   hipLaunchKernelGGL(finalize_kernel, dim3(n_rows), dim3(64), 0, s, partials, n_parts, R_pad,
                      n_rows_dev, n_rows, AO ? nullptr : H, AO ? nullptr : lse, argmax, (int64_t)0, (int64_t)0);
   EH_HIP(c, hipGetLastError());
@@ -180,7 +168,7 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // The persistent kernel for up to 256 rows; at most 16 rows go to the decode kernel where the
 // context has one (hidden sizes up to 2048), and here otherwise.
 bool use_rows(const eh_ctx* c, int64_t n_rows) {
-  return c->rows_grid > 0 && c->use_gemm && (n_rows > 16 || c->decode_grid == 0) && n_rows >= 1 && n_rows <= kRowsMax &&
+  return c->rows_grid > 0 && (n_rows > 16 || c->decode_grid == 0) && n_rows >= 1 && n_rows <= kRowsMax &&
          n_rows <= c->max_rows;
 }
 
@@ -293,15 +281,13 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
         return bail(e, "copy bias");
     }
   }
-  // the kernels read whole groups of token blocks: up to kMaxNB (stream kernel) or 4 waves x 8
+  // the kernels read whole groups of token blocks: up to 4 waves x 8
   // blocks (batched kernel) starting inside the padded rows, so 32 zero blocks follow them
   const size_t y_frags = (size_t)(c->R_pad_max / 16 + 32) * c->KS * kWave;
   if ((e = dev_alloc(c, &c->yf, y_frags)) != hipSuccess) return bail(e, "hipMalloc(y)");
   if ((e = hipMemset(c->yf, 0, y_frags * sizeof(frag_t))) != hipSuccess) return bail(e, "memset y");
-  if ((e = dev_alloc(c, &c->partials, (size_t)kStreamGrid * c->R_pad_max)) != hipSuccess)
+  if ((e = dev_alloc(c, &c->partials, (size_t)kMaxParts * c->R_pad_max)) != hipSuccess)
     return bail(e, "hipMalloc(partials)");
-  if ((e = dev_alloc(c, &c->ws_H, (size_t)c->max_rows)) != hipSuccess) return bail(e, "hipMalloc(ws)");
-  if ((e = dev_alloc(c, &c->ws_lse, (size_t)c->max_rows)) != hipSuccess) return bail(e, "hipMalloc(ws)");
   if ((e = dev_alloc(c, &c->ws_argmax, (size_t)c->max_rows)) != hipSuccess) return bail(e, "hipMalloc(ws)");
   for (int i = 0; i < 2; ++i) {
     if ((e = dev_alloc(c, &c->active[i], (size_t)c->max_rows)) != hipSuccess) return bail(e, "hipMalloc(ws)");
@@ -345,10 +331,6 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
       hipDeviceProp_t prop;
       if ((e = hipGetDeviceProperties(&prop, c->device)) != hipSuccess) return bail(e, "device properties");
       c->num_cu = prop.multiProcessorCount;
-#ifdef EH_DIAGNOSTICS
-      const char* env = getenv("EH_DISABLE_GEMM");   // force the simple streaming kernel
-      c->use_gemm = !(env && env[0] == '1');
-#endif
     }
     // the status word both persistent kernels report a given-up wait in (read by eh_check)
     if ((e = dev_alloc(c, &c->dec_status, (size_t)4)) != hipSuccess) return bail(e, "hipMalloc(status)");
@@ -418,7 +400,7 @@ eh_status eh_eval_noalloc(eh_ctx* ctx, int32_t head, const void* h, int64_t h_ro
   const size_t R_pad = ((size_t)n_rows + 31) & ~(size_t)31;
   const size_t y_bytes = (R_pad / 16 + 32) * (size_t)ctx->KS * kWave * sizeof(frag_t);
   const size_t part_off = (y_bytes + 255) & ~(size_t)255;
-  const size_t need = part_off + (size_t)kStreamGrid * R_pad * sizeof(Stats);
+  const size_t need = part_off + (size_t)kMaxParts * R_pad * sizeof(Stats);
   if ((size_t)n_rows > ((size_t)1 << 20) || need > kNoAllocScratchBytes)
     return fail(ctx, EH_ERR_WORKSPACE,
                 "n_rows rows of d elements need " + std::to_string(need) + " bytes of workspace; the static one holds " +
@@ -440,7 +422,7 @@ namespace {
 eh_status ensure_mh(eh_ctx* ctx, int n_heads_needed) {
   if (ctx->mh_heads >= n_heads_needed) return EH_OK;
   const size_t y_stride = (size_t)(ctx->R_pad_max / 16 + 32) * ctx->KS * kWave;
-  const size_t part_stride = (size_t)kStreamGrid * ctx->R_pad_max;
+  const size_t part_stride = (size_t)kMaxParts * ctx->R_pad_max;
   EH_HIP(ctx, hipDeviceSynchronize());
   eh::frag_t* y = nullptr;
   eh::Stats* pt = nullptr;
@@ -473,7 +455,7 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
   if ((layer_stride * esz) % 16 != 0) return fail(ctx, EH_ERR_SHAPE, "hidden rows must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const bool batched =
-      ctx->dtype == EH_BF16 && ctx->bias.empty() && ((ctx->use_gemm && n_rows > 16) || metrics);
+      ctx->dtype == EH_BF16 && ctx->bias.empty() && (n_rows > 16 || metrics);
   if (!batched) {
     // shapes the many-heads kernels do not cover: one head after the other
     for (int l = 0; l < n_heads_eval; ++l) {
@@ -489,7 +471,7 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
   // per head: activations for max_rows rows (plus the zero blocks the kernel may read past
   // them), one set of partial statistics and one of second largest logits
   const size_t y_stride = (size_t)(ctx->R_pad_max / 16 + 32) * ctx->KS * kWave;
-  const size_t part_stride = (size_t)kStreamGrid * ctx->R_pad_max;
+  const size_t part_stride = (size_t)kMaxParts * ctx->R_pad_max;
   st = ensure_mh(ctx, n_heads_eval);
   if (st != EH_OK) return st;
   const int R_pad = (n_rows + 31) & ~31;
@@ -498,7 +480,11 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
                      (const float* const*)(ctx->d_gamma + head0), (const float* const*)(ctx->d_beta + head0),
                      ctx->eps, ctx->mh_yf, (int64_t)y_stride);
   int n_parts = 0;
-  EH_HIP(ctx, gemm32_launch_heads(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
+  if (use_ksplit(ctx, n_rows))
+    EH_HIP(ctx, ksplit_launch(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
+                              ctx->mh_partials, metrics ? ctx->mh_second : nullptr, (long long)part_stride, &n_parts, s));
+  else
+    EH_HIP(ctx, gemm32_launch_heads(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
                                   ctx->mh_partials, metrics ? ctx->mh_second : nullptr, (long long)part_stride,
                                   &n_parts, s));
   if (metrics)
@@ -584,61 +570,34 @@ eh_status eh_cascade(eh_ctx* ctx, const void* h_layers, int64_t layer_stride, in
     const int64_t n = (int64_t)ctx->n_heads * n_rows;
     hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, H_out, n, NAN);
   }
-  if (ctx->bias.empty() && ctx->use_gemm) {
-    // Two launches per head: the batched projection, then one kernel that merges the partial
-    // statistics, applies the exit rule, appends the rows that go on to the next head's list
-    // and writes their LayerNorm for the next head.  Three live-row counters rotate: head l
-    // reads counter l%3, fills (l+1)%3 and clears (l+2)%3.
-    const bool bf = ctx->dtype == EH_BF16;
-    const int RB = bf ? 32 : 16;
-    const int R_pad = (n_rows + RB - 1) / RB * RB;
-    int* cnt = ctx->n_active[0];
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, cnt, (int64_t)3, 0);
-    {
-      dim3 g(R_pad), b(kLnThreads);
-      if (bf)
-        hipLaunchKernelGGL((ln_pack_kernel<DtBf16, 32>), g, b, 0, s, h_layers, row_stride, (const int*)nullptr,
-                           (const int*)nullptr, n_rows, R_pad, ctx->d, ctx->KS, ctx->gamma[0], ctx->beta[0],
-                           ctx->eps, ctx->yf);
-      else
-        hipLaunchKernelGGL((ln_pack_kernel<DtF32, 16>), g, b, 0, s, h_layers, row_stride, (const int*)nullptr,
-                           (const int*)nullptr, n_rows, R_pad, ctx->d, ctx->KS, ctx->gamma[0], ctx->beta[0],
-                           ctx->eps, ctx->yf);
-    }
-    for (int l = 0; l < ctx->n_heads; ++l) {
-      const int last = l == ctx->n_heads - 1 ? 1 : 0;
-      const int* idx = l == 0 ? nullptr : ctx->active[l & 1];
-      const int* live = l == 0 ? nullptr : cnt + l % 3;
-      int n_parts = 0;
-      if (bf) EH_HIP(ctx, gemm32_launch(ctx, l, live, n_rows, false, ctx->yf, ctx->partials, nullptr, &n_parts, s));
-      else EH_HIP(ctx, gemm_launch(ctx, l, live, n_rows, false, ctx->yf, ctx->partials, &n_parts, s));
-      const void* hn = last ? nullptr : (const char*)h_layers + (int64_t)(l + 1) * layer_stride * esz;
-      const float* gn = last ? nullptr : ctx->gamma[l + 1];
-      const float* bn = last ? nullptr : ctx->beta[l + 1];
-      float* Hl = H_out ? H_out + (int64_t)l * n_rows : nullptr;
+  // Two launches per head: the batched projection, then one kernel that merges the partial
+  // statistics, applies the exit rule, appends the rows that go on to the next head's list
+  // and writes their LayerNorm for the next head.  Three live-row counters rotate: head l
+  // reads counter l%3, fills (l+1)%3 and clears (l+2)%3.
+  const int RB = row_block(ctx, n_rows);
+  const int R_pad = round_up(n_rows, RB);
+  int* cnt = ctx->n_active[0];
+  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, cnt, (int64_t)3, 0);
+  launch_ln(ctx, 0, h_layers, row_stride, nullptr, nullptr, n_rows, R_pad, ctx->yf, s);
+  for (int l = 0; l < ctx->n_heads; ++l) {
+    const int last = l == ctx->n_heads - 1 ? 1 : 0;
+    const int* idx = l == 0 ? nullptr : ctx->active[l & 1];
+    const int* live = l == 0 ? nullptr : cnt + l % 3;
+    int n_parts = 0;
+    EH_HIP(ctx, project(ctx, l, live, n_rows, false, ctx->yf, ctx->partials, &n_parts, s));
+    const void* hn = last ? nullptr : (const char*)h_layers + (int64_t)(l + 1) * layer_stride * esz;
+    const float* gn = last ? nullptr : ctx->gamma[l + 1];
+    const float* bn = last ? nullptr : ctx->beta[l + 1];
+    float* Hl = H_out ? H_out + (int64_t)l * n_rows : nullptr;
 #define EH_POST(DT, RBV)                                                                              \
   hipLaunchKernelGGL((cascade_post_kernel<DT, RBV>), dim3(n_rows), dim3(kLnThreads), 0, s, ctx->partials, n_parts, \
                      R_pad, idx, live, n_rows, ctx->tau[l], last, l, exit_layer, token, Hl,            \
                      (unsigned long long*)n_evals_out, ctx->active[(l + 1) & 1], cnt + (l + 1) % 3,    \
                      cnt + (l + 2) % 3, hn, row_stride, ctx->d, ctx->KS, gn, bn, ctx->eps, ctx->yf)
-      if (bf) EH_POST(DtBf16, 32);
-      else EH_POST(DtF32, 16);
+    if (ctx->dtype == EH_BF16) EH_POST(DtBf16, 32);
+    else if (RB == 32) EH_POST(DtF32, 32);
+    else EH_POST(DtF32, 16);
 #undef EH_POST
-    }
-    EH_HIP(ctx, hipGetLastError());
-    return EH_OK;
-  }
-  for (int l = 0; l < ctx->n_heads; ++l) {
-    const int* idx = l == 0 ? nullptr : ctx->active[(l - 1) & 1];
-    const int* cnt = l == 0 ? nullptr : ctx->n_active[(l - 1) & 1];
-    const void* hl = (const char*)h_layers + (int64_t)l * layer_stride * esz;
-    st = run_head<false>(ctx, l, hl, row_stride, idx, cnt, n_rows, ctx->ws_H, ctx->ws_lse,
-                         ctx->ws_argmax, s);
-    if (st != EH_OK) return st;
-    hipLaunchKernelGGL(decide_kernel, dim3(1), dim3(256), 0, s, ctx->ws_H, ctx->ws_argmax, idx, cnt,
-                       n_rows, ctx->tau[l], l == ctx->n_heads - 1 ? 1 : 0, l, exit_layer, token,
-                       ctx->active[l & 1], ctx->n_active[l & 1],
-                       H_out ? H_out + (int64_t)l * n_rows : nullptr, (unsigned long long*)n_evals_out);
   }
   EH_HIP(ctx, hipGetLastError());
   return EH_OK;
@@ -658,7 +617,6 @@ eh_status dssd_verify(eh_ctx* ctx, const void* f_final, const int32_t* draft, co
   if (st != EH_OK) return st;
   DeviceGuard guard(ctx->device);
   hipStream_t s = (hipStream_t)stream;
-  const bool bf = ctx->dtype == EH_BF16;
   if (use_rows(ctx, rows)) {
     // one persistent launch: LayerNorm, argmax-only projection, merge and prefix walk
     RowsParams p = rows_base(ctx, (int)rows);
@@ -676,24 +634,14 @@ eh_status dssd_verify(eh_ctx* ctx, const void* f_final, const int32_t* draft, co
     EH_HIP(ctx, rows_launch(ctx, p, s));
     return EH_OK;
   }
-  if (ctx->bias.empty() && ctx->use_gemm && rows > 16 && (size_t)(k + 1) * sizeof(int) <= 48 * 1024) {
+  if ((size_t)(k + 1) * sizeof(int) <= 48 * 1024) {
     // three launches: LayerNorm, argmax-only projection, then one kernel that merges the
     // partial argmaxes of a row's k+1 positions and walks the prefix
-    const int RB = bf ? 32 : 16;
-    const int R_pad = (int)((rows + RB - 1) / RB * RB);
+    const int R_pad = round_up((int)rows, row_block(ctx, (int)rows));
     const int fin = ctx->n_heads - 1;
-    dim3 g(R_pad), b(kLnThreads);
-    if (bf)
-      hipLaunchKernelGGL((ln_pack_kernel<DtBf16, 32>), g, b, 0, s, f_final, (int64_t)ctx->d, (const int*)nullptr,
-                         (const int*)nullptr, (int)rows, R_pad, ctx->d, ctx->KS, ctx->gamma[fin], ctx->beta[fin],
-                         ctx->eps, ctx->yf);
-    else
-      hipLaunchKernelGGL((ln_pack_kernel<DtF32, 16>), g, b, 0, s, f_final, (int64_t)ctx->d, (const int*)nullptr,
-                         (const int*)nullptr, (int)rows, R_pad, ctx->d, ctx->KS, ctx->gamma[fin], ctx->beta[fin],
-                         ctx->eps, ctx->yf);
+    launch_ln(ctx, fin, f_final, ctx->d, nullptr, nullptr, (int)rows, R_pad, ctx->yf, s);
     int n_parts = 0;
-    if (bf) EH_HIP(ctx, gemm32_launch(ctx, fin, nullptr, (int)rows, true, ctx->yf, ctx->partials, nullptr, &n_parts, s));
-    else EH_HIP(ctx, gemm_launch(ctx, fin, nullptr, (int)rows, true, ctx->yf, ctx->partials, &n_parts, s));
+    EH_HIP(ctx, project(ctx, fin, nullptr, (int)rows, true, ctx->yf, ctx->partials, &n_parts, s));
     hipLaunchKernelGGL(verify_post_kernel, dim3(B), dim3(256), (size_t)(k + 1) * sizeof(int), s, ctx->partials,
                        n_parts, R_pad, draft, draft_len, k, target, accepted, next_token);
     EH_HIP(ctx, hipGetLastError());
@@ -802,7 +750,7 @@ eh_status eh_head_losses(eh_ctx* ctx, int32_t head, const void* h_head, int64_t 
   st = ensure_mh(ctx, 2);
   if (st != EH_OK) return st;
   if (!ctx->kl_partials) {
-    EH_HIP(ctx, dev_alloc(ctx, &ctx->kl_partials, (size_t)kStreamGrid * ctx->R_pad_max));
+    EH_HIP(ctx, dev_alloc(ctx, &ctx->kl_partials, (size_t)kMaxParts * ctx->R_pad_max));
     EH_HIP(ctx, dev_alloc(ctx, &ctx->kl_rows, (size_t)2 * ctx->R_pad_max));
   }
   const size_t y_stride = (size_t)(ctx->R_pad_max / 16 + 32) * ctx->KS * kWave;

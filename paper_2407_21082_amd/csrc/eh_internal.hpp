@@ -21,7 +21,6 @@ struct eh_ctx {
   float eps = 1e-5f;
   int KS = 0, VT = 0, R_pad_max = 0;
   int num_cu = 0;
-  bool use_gemm = true;
   std::vector<eh::frag_t*> Wf;  // per head, fragment-major weights
   std::vector<float*> gamma, beta, bias;
   std::vector<float> tau;
@@ -44,9 +43,7 @@ struct eh_ctx {
   // [kStreamGrid][R_pad_max] and the per-token loss terms [2][R_pad_max]
   eh::KlStats* kl_partials = nullptr;
   float* kl_rows = nullptr;
-  float* ws_H = nullptr;        // [max_rows] internal outputs (cascade, verify)
-  float* ws_lse = nullptr;
-  int* ws_argmax = nullptr;
+  int* ws_argmax = nullptr;     // [max_rows] internal output (verify)
   int* active[2] = {nullptr, nullptr};
   int* n_active[2] = {nullptr, nullptr};
   // persistent decode kernel: control block and per-head partials
@@ -169,6 +166,12 @@ hipError_t gemm32_launch(const eh_ctx* ctx, int head, const int* n_rows_dev, int
 hipError_t gemm32_launch_heads(const eh_ctx* ctx, int head, int n_heads, const int* n_rows_dev, int n_rows,
                                bool argmax_only, const eh::frag_t* yf, long long y_stride, eh::Stats* partials,
                                float* second, long long part_stride, int* n_parts, hipStream_t s);
+// Projection + statistics of n_heads consecutive heads for a few rows (bf16 or fp32, with or without
+// bias vectors; groups of 64 rows): yf in the 32-row operand order, partials [*n_parts][n_rows rounded
+// up to 32] per head; `second` as below (bf16 only).
+hipError_t ksplit_launch(const eh_ctx* ctx, int head, int n_heads, const int* n_rows_dev, int n_rows,
+                         bool argmax_only, const eh::frag_t* yf, long long y_stride, eh::Stats* partials,
+                         float* second, long long part_stride, int* n_parts, hipStream_t s);
 // The fused projections of the training objectives (bf16, no bias vector): an exit head on
 // yf_head and the model's head on yf_model (both in the 32 x 16 operand order, same rows),
 // labels NULL or device [n_rows]; per-workgroup partial statistics go to

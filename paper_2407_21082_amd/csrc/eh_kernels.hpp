@@ -242,7 +242,7 @@ __device__ __forceinline__ void ln_write_row(const void* __restrict__ row, int d
                                              const float* __restrict__ gamma,
                                              const float* __restrict__ beta, float eps,
                                              frag_t* __restrict__ yf, int p, int tid, double* red) {
-  static_assert(RB == 16 || (RB == 32 && DT::EPL == 8), "row block");
+  static_assert(RB == 16 || RB == 32, "row block");
   const int n_chunks = KS * 4;
   auto put = [&](int c, const frag_t& v) { put_chunk<RB>(yf, KS, p, c, v); };
   if (n_chunks <= kLnCache * kWave)
@@ -297,94 +297,6 @@ __global__ __launch_bounds__(kLnThreads) void ln_pack_heads_kernel(const void* _
   __shared__ double red[2 * kLnWaves];
   ln_pack_row<DT, RB>(h, row_stride, nullptr, n_rows, R_pad, d, KS, gamma_tab[l], beta_tab[l], eps,
                       yf + (int64_t)l * y_stride, blockIdx.x, threadIdx.x, red);
-}
-
-// ---------------------------------------------------------------------------
-// Streaming projection with fused softmax statistics (general row counts).
-// Each wave owns whole vocabulary tiles (16 rows, all of k) and NB token
-// blocks; both operands come straight from global memory in fragment order.
-// The logits live only in the accumulators.  Per workgroup one Stats record
-// per token is written to `partials[blockIdx.x][R_pad]`.
-// ---------------------------------------------------------------------------
-template <typename DT, int NB, bool ARGMAX_ONLY>
-__global__ __launch_bounds__(256) void stream_kernel(const frag_t* __restrict__ Wf,
-                                                     const frag_t* __restrict__ yf,
-                                                     const float* __restrict__ bias, int VT, int KS,
-                                                     int V, int nb0, const int* __restrict__ n_rows_dev,
-                                                     int n_rows, int R_pad, Stats* __restrict__ partials) {
-  __shared__ Stats red[4][NB][16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int q = lane >> 4, n = lane & 15;
-  int n_live = n_rows;
-  if (n_rows_dev) n_live = min(max(*n_rows_dev, 0), n_rows);
-  const int nb_live = min(NB, (n_live - nb0 * 16 + 15) >> 4);
-  if (nb_live <= 0) return;  // uniform over the grid
-
-  Stats st[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) stats_init(st[b]);
-
-  const int gw = blockIdx.x * 4 + wave, tw = gridDim.x * 4;
-  const frag_t* yp = yf + (int64_t)nb0 * KS * kWave + lane;
-  for (int vt = gw; vt < VT; vt += tw) {
-    f32x4 acc[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const frag_t* wp = Wf + (int64_t)vt * KS * kWave + lane;
-    constexpr int U = (NB <= 1) ? 8 : (NB <= 2) ? 4 : 2;
-    int ks = 0;
-    for (; ks + U <= KS; ks += U) {
-      frag_t a[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) a[u] = __builtin_nontemporal_load(wp + (int64_t)(ks + u) * kWave);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          if (b < nb_live) {
-            const frag_t y = yp[((int64_t)b * KS + ks + u) * kWave];
-            acc[b] = DT::mma(a[u], y, acc[b]);
-          }
-        }
-      }
-    }
-    for (; ks < KS; ++ks) {
-      const frag_t a = __builtin_nontemporal_load(wp + (int64_t)ks * kWave);
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        if (b < nb_live) {
-          const frag_t y = yp[((int64_t)b * KS + ks) * kWave];
-          acc[b] = DT::mma(a, y, acc[b]);
-        }
-      }
-    }
-    const int row0 = vt * 16 + q * 4;
-    f32x4 bz = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (bias) bz = *(const f32x4*)(bias + row0);  // bias is padded to VT*16 entries
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      if (b < nb_live) stats_push4<ARGMAX_ONLY>(st[b], acc[b] + bz, row0, V);
-    }
-  }
-
-  // lanes n, n+16, n+32, n+48 hold the same token: fold the four row groups
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    st[b] = stats_merge(st[b], stats_shfl_xor(st[b], 16));
-    st[b] = stats_merge(st[b], stats_shfl_xor(st[b], 32));
-    if (q == 0) red[wave][b][n] = st[b];
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < NB * 16; i += blockDim.x) {
-    const int b = i >> 4, t = i & 15;
-    if (b < nb_live) {
-      Stats s = red[0][b][t];
-      s = stats_merge(s, red[1][b][t]);
-      s = stats_merge(s, red[2][b][t]);
-      s = stats_merge(s, red[3][b][t]);
-      partials[(int64_t)blockIdx.x * R_pad + (nb0 + b) * 16 + t] = s;
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,324 @@
+// Projection with fused softmax statistics for up to 64 rows at a time: the weight stream split
+// over k (arXiv 2407.21082, Sections 3.2 and 3.4.1).
+//
+// Up to 64 rows a head is a pure weight stream (at most 64 flop per byte in bf16), so what
+// counts is that the reads never stop.  A workgroup owns a slice of the vocabulary (at most 7
+// tiles of 32 rows per pass, one workgroup per CU); its four waves split the slice's k, not its
+// rows or tokens: wave w takes the k-steps w, w+4, ...  A wave then shares nothing with the
+// others while it streams: weights and activations go straight to registers in matrix-core
+// operand order, with no LDS, no barrier and no hand-counted wait in the loop, two k-steps
+// (36 KiB of weights and activations with 64 rows) always in flight per wave, 144 KiB per CU, and
+// the next pass's (or the next head's) first two k-steps are asked for before this one's are
+// finished, so that the stream runs on while the four waves add up their partial logits through
+// LDS and work out the statistics (about 3 us).  The activations of a step are read once per
+// workgroup, 4 KiB for 64 rows next to 14 KiB of weights; beyond 64 rows the accumulators no
+// longer fit and the kernels that share weights through LDS are the better ones.
+//
+// Measured (one MI355X, V = 50304, us before -> now; before: weights shared through LDS for bf16 and
+// fp32, both operands straight from memory without a pipeline for heads with a bias vector):
+//   8 heads x 64 rows, d = 2560, bf16    52.8 -> 45.3 per head (4.9 -> 5.7 TB/s of weights)
+//   8 heads x 32 rows, d = 1024, bf16    23.7 -> 18.4 per head (4.3 -> 5.6 TB/s)
+//   one call of 48 rows, d = 768, bf16 with a bias vector   56.5 -> 31.7 (LayerNorm and merge included)
+//   one call of 512 rows, d = 1024, bf16 with a bias vector  474 -> 112
+//   6 heads x 32 rows, d = 512, fp32 cascade                 273 -> 211
+//
+// Operands: v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32 on the same 16 bytes per
+// lane.  Weights stay in the one layout the library has (fragments of 16 rows); the lane
+// permutation that turns two of them into a 32-row operand is in the load addresses: lane l reads
+// lane (2h + l/32)*16 + l%16 of fragment (l%32)/16, whole 256-byte lines all the same.
+#pragma once
+#include "eh_internal.hpp"
+#include "eh_kernels.hpp"
+
+namespace eh {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int kKsWaves = 4;
+constexpr int kKsThreads = kKsWaves * kWave;
+constexpr int kKsMaxMT = 7;      // 32-row tiles per pass
+constexpr int kKsGroup = 64;     // rows per token group
+
+#define EH_KS_LDS __attribute__((address_space(3)))
+#define EH_KS_GLOBAL __attribute__((address_space(1)))
+
+template <typename DT>
+__device__ __forceinline__ f32x16 ks_mma(const frag_t& a, const frag_t& b, f32x16 c);
+template <>
+__device__ __forceinline__ f32x16 ks_mma<DtBf16>(const frag_t& a, const frag_t& b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ f32x16 ks_mma<DtF32>(const frag_t& a, const frag_t& b, f32x16 c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+  return c;
+}
+
+// LDS: partial logits handed between the waves ([destination][source][tile][lane] f32x4, one
+// token block at a time), then the waves' statistics ([word][wave][token], the sixth word the second largest logit).
+__host__ __device__ constexpr size_t ks_red_bytes() { return (size_t)kKsWaves * kKsWaves * kKsMaxMT * kWave * 16; }
+__host__ __device__ constexpr size_t ks_lds_bytes() { return ks_red_bytes() + (size_t)6 * kKsWaves * kKsGroup * 4; }
+
+// Waits for this wave's LDS traffic only: the weights in flight stay in flight.
+__device__ __forceinline__ void ks_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Loads go through buffer resources: scalar base and k offset, 32-bit lane offset, so a step's
+// addresses cost no vector registers.  Every offset is in range by construction (clamped tiles and
+// k-steps); the resource's size is not relied on.
+typedef __amdgpu_buffer_rsrc_t ks_buf_t;
+__device__ __forceinline__ ks_buf_t ks_buffer(const void* p) {
+  const uint64_t v = (uint64_t)p;  // wave-uniform, kept in scalar registers
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, 0xffffffffu, 0x00020000);
+}
+constexpr int kKsNt = 2;  // cache policy: non-temporal (a weight is read once)
+template <int AUX>
+__device__ __forceinline__ frag_t ks_load(ks_buf_t buf, uint32_t lane_off, uint32_t base) {
+  return __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)lane_off, (int)base, AUX));
+}
+
+// One wave's view of the slice of a workgroup: 16-row tiles [t0, t1) walked in `passes` passes of
+// MT 32-row tiles.
+struct KsSlice {
+  int t0, t1, passes, mt;
+  __device__ __forceinline__ KsSlice(int VT16, int part, int parts) {
+    t0 = (int)((long long)VT16 * part / parts);
+    t1 = (int)((long long)VT16 * (part + 1) / parts);
+    const int tiles = (t1 - t0 + 1) >> 1;
+    passes = (tiles + kKsMaxMT - 1) / kKsMaxMT;
+    mt = passes > 0 ? (tiles + passes - 1) / passes : 0;
+  }
+};
+
+// Byte offsets of this lane's operands of the pass's MT tiles from the pass's first fragment; a
+// half tile that is missing at the end of the slice repeats the slice's last one (masked later).
+template <int MT>
+__device__ __forceinline__ void ks_offsets(int tiles16, int KS, int lane, uint32_t (&voff)[MT]) {
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int t = min(2 * m + ((lane & 31) >> 4), tiles16 - 1);
+    voff[m] = ((uint32_t)t * (uint32_t)KS << 10) + (((lane >> 5) * 16 + (lane & 15)) << 4);
+  }
+}
+
+template <int MT>
+__device__ __forceinline__ void ks_load_a(frag_t (&a)[MT][2], ks_buf_t w, uint32_t at, const uint32_t (&voff)[MT]) {
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) a[m][h] = ks_load<kKsNt>(w, voff[m] + h * 512, at);
+}
+
+// byte offset of this wave's i-th k-step in the weights, clamped to the last one there is
+__device__ __forceinline__ uint32_t ks_at(int i, int wave, int KS) { return (uint32_t)min(wave + kKsWaves * i, KS - 1) << 10; }
+
+// The first two k-steps of a pass.
+template <int MT>
+__device__ __forceinline__ void ks_start(frag_t (&a)[2][MT][2], const void* w, int KS, int wave, const uint32_t (&voff)[MT]) {
+  const ks_buf_t wu = ks_buffer(w);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) ks_load_a<MT>(a[j], wu, ks_at(j, wave, KS), voff);
+}
+
+// One pass over this wave's share of k.  a holds the pass's first two k-steps on entry (asked
+// for, not waited for) and those of the pass at w_next (offsets voff_next) on return.  Activations:
+// fragment (block n, 2*ks + h) of 2*KS per block, in 32-row operand order.  A wave with an odd
+// number of k-steps runs one more on zeroed activations so that the two buffers keep their roles.
+template <typename DT, int MT, int NB>
+__device__ __forceinline__ void ks_pass(frag_t (&a)[2][MT][2], const void* w, const void* w_next, const frag_t* y, int KS,
+                                        int wave, int lane, const uint32_t (&voff)[MT], const uint32_t (&voff_next)[MT],
+                                        f32x16 (&acc)[MT][NB]) {
+  const int n = (KS - wave + kKsWaves - 1) / kKsWaves;
+  const int n2 = (n + 1) & ~1;
+  const ks_buf_t wu = ks_buffer(w), wx = ks_buffer(w_next), yu = ks_buffer(y);
+  const uint32_t lane16 = (uint32_t)lane << 4;
+  auto load_b = [&](frag_t (&b)[NB][2], int i) {
+    const uint32_t at = 2 * ks_at(i, wave, KS);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) b[nb][h] = ks_load<0>(yu, lane16 + h * 1024, at + (uint32_t)nb * 2 * KS * 1024);
+  };
+  frag_t b[2][NB][2];
+  load_b(b[0], 0);
+  load_b(b[1], 1);
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[m][nb][i] = 0.f;
+  auto step = [&](frag_t (&aj)[MT][2], frag_t (&bj)[NB][2]) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[m][nb] = ks_mma<DT>(aj[m][h], bj[nb][h], acc[m][nb]);
+  };
+  // refills are unconditional: a load under a branch makes the compiler wait for everything
+  int i = 0;
+  for (; i + 2 < n2; i += 2) {
+    step(a[0], b[0]);
+    ks_load_a<MT>(a[0], wu, ks_at(i + 2, wave, KS), voff);
+    load_b(b[0], i + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    step(a[1], b[1]);
+    ks_load_a<MT>(a[1], wu, ks_at(i + 3, wave, KS), voff);
+    load_b(b[1], i + 3);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (i < n2) {  // the last two steps refill with the next pass's first two
+    step(a[0], b[0]);
+    ks_load_a<MT>(a[0], wx, ks_at(0, wave, KS), voff_next);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t keep = i + 1 < n ? 0xffffffffu : 0u;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) b[1][nb][h] &= keep;
+    step(a[1], b[1]);
+    ks_load_a<MT>(a[1], wx, ks_at(1, wave, KS), voff_next);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The logits of a pass summed over the four waves and folded into running statistics.  Wave g ends
+// up with accumulator registers 4g..4g+3 of every tile, i.e. vocabulary rows row_base + 32m + 8g +
+// 4*(lane/32) + i of token lane%32.  bias: NULL or [rows padded to 16].  TOP2: second[nb] is the
+// largest logit besides st[nb].zb so far (with multiplicity).
+template <int MT, int NB, bool ARGMAX_ONLY, bool TOP2>
+__device__ __forceinline__ void ks_finish(const f32x16 (&acc)[MT][NB], EH_KS_LDS char* lds, int wave, int lane,
+                                          int row_base, int row_hi, const float* __restrict__ bias, Stats (&st)[NB],
+                                          float (&second)[NB]) {
+  EH_KS_LDS f32x4* red = (EH_KS_LDS f32x4*)lds;
+  const int r0 = row_base + 8 * wave + 4 * (lane >> 5);
+  const bool ragged = row_base + 32 * MT > row_hi;  // wave-uniform: only the slice's last pass can be
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    ks_lds_barrier();  // nobody still reads the previous block's (or pass's) partial logits
+#pragma unroll
+    for (int g = 0; g < kKsWaves; ++g)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        red[((g * kKsWaves + wave) * MT + m) * kWave + lane] =
+            f32x4{acc[m][nb][4 * g], acc[m][nb][4 * g + 1], acc[m][nb][4 * g + 2], acc[m][nb][4 * g + 3]};
+    ks_lds_barrier();
+    f32x4 z[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      EH_KS_LDS const f32x4* src = red + (wave * kKsWaves * MT + m) * kWave + lane;
+      z[m] = (src[0] + src[MT * kWave]) + (src[2 * MT * kWave] + src[3 * MT * kWave]);
+    }
+    if (bias) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        // (a half tile beyond the slice reads the bias of its last rows; masked below)
+        z[m] += *(const f32x4*)(bias + min(r0 + 32 * m, (row_hi - 1) & ~3));
+      }
+    }
+    if (ragged) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z[m][i] = r0 + 32 * m + i < row_hi ? z[m][i] : -INFINITY;
+    }
+    // one maximum over the lane's 4*MT logits (a NaN is ignored), then independent exponentials
+    float zmax = -INFINITY;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) zmax = fmaxf(zmax, fmaxf(fmaxf(z[m][0], z[m][1]), fmaxf(z[m][2], z[m][3])));
+    Stats& s = st[nb];
+    if constexpr (TOP2) {
+      float z1 = s.zb, z2 = second[nb];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          z2 = fmaxf(z2, fminf(z[m][i], z1));
+          z1 = fmaxf(z1, z[m][i]);
+        }
+      second[nb] = z2;
+    }
+    if (zmax > s.zb) {
+      int at = 0;
+#pragma unroll
+      for (int m = MT - 1; m >= 0; --m)
+#pragma unroll
+        for (int i = 3; i >= 0; --i) at = (z[m][i] == zmax) ? 32 * m + i : at;  // lowest index attaining the maximum
+      if (!ARGMAX_ONLY) {
+        const float mn = zmax * kLog2e;
+        const float dm = s.m - mn;
+        const float sc = fast_exp2(dm);
+        s.U = sc * (s.U + dm * s.S);
+        s.S = sc * s.S;
+        s.m = mn;
+      }
+      s.zb = zmax;
+      s.ib = r0 + at;
+    }
+    if (!ARGMAX_ONLY) {
+      float S4[4] = {0.f, 0.f, 0.f, 0.f}, U4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // a row beyond the slice (z = -inf, only where `ragged`) contributes 0 * (finite)
+          const float t = z[m][i] == -INFINITY ? -1.0e9f : z[m][i] * kLog2e - s.m;
+          const float e = fast_exp2(t);
+          S4[i] += e;
+          U4[i] += t * e;
+        }
+      s.S += (S4[0] + S4[1]) + (S4[2] + S4[3]);
+      s.U += (U4[0] + U4[1]) + (U4[2] + U4[3]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The workgroup's statistics of token t = threadIdx.x < 32*NB, merged over the lanes and waves that
+// hold its rows (every thread must call; the result is valid for those threads).
+template <int NB, bool TOP2>
+__device__ __forceinline__ Stats ks_merge(Stats (&st)[NB], float (&second)[NB], float& second_out, EH_KS_LDS char* lds,
+                                          int wave, int lane) {
+  EH_KS_LDS float* ws = (EH_KS_LDS float*)(lds + ks_red_bytes());
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    if constexpr (TOP2)  // second largest of a union
+      second[nb] = fmaxf(fminf(st[nb].zb, __shfl_xor(st[nb].zb, 32)), fmaxf(second[nb], __shfl_xor(second[nb], 32)));
+    st[nb] = stats_merge(st[nb], stats_shfl_xor(st[nb], 32));
+    if (lane < 32) {
+      const int at = wave * kKsGroup + nb * 32 + lane;
+      ws[0 * kKsWaves * kKsGroup + at] = st[nb].m;
+      ws[1 * kKsWaves * kKsGroup + at] = st[nb].S;
+      ws[2 * kKsWaves * kKsGroup + at] = st[nb].U;
+      ws[3 * kKsWaves * kKsGroup + at] = st[nb].zb;
+      ws[4 * kKsWaves * kKsGroup + at] = __int_as_float(st[nb].ib);
+      if constexpr (TOP2) ws[5 * kKsWaves * kKsGroup + at] = second[nb];
+    }
+  }
+  ks_lds_barrier();
+  Stats s;
+  stats_init(s);
+  second_out = -INFINITY;
+  if (threadIdx.x < 32 * NB) {
+#pragma unroll
+    for (int w = 0; w < kKsWaves; ++w) {
+      const int at = w * kKsGroup + (int)threadIdx.x;
+      Stats o;
+      o.m = ws[0 * kKsWaves * kKsGroup + at];
+      o.S = ws[1 * kKsWaves * kKsGroup + at];
+      o.U = ws[2 * kKsWaves * kKsGroup + at];
+      o.zb = ws[3 * kKsWaves * kKsGroup + at];
+      o.ib = __float_as_int(ws[4 * kKsWaves * kKsGroup + at]);
+      if constexpr (TOP2)
+        second_out = fmaxf(fminf(s.zb, o.zb), fmaxf(second_out, ws[5 * kKsWaves * kKsGroup + at]));
+      s = stats_merge(s, o);
+    }
+  }
+  return s;
+}
+
+}  // namespace eh

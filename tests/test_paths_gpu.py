@@ -45,3 +45,90 @@ def test_few_rows_cascade_is_row_by_row(B, dtype, rows):
         assert int(ex1) == int(ex[r]) and int(tok1) == int(tok[r])
         assert torch.equal(H1[:, 0].view(torch.int32), H[:, r].view(torch.int32))
     B.eh_destroy(ctx)
+
+
+def _eval(B, ctx, head, h, rows, **kw):
+    H, lse, am = torch.zeros(rows, device=DEV), torch.zeros(rows, device=DEV), _ints(rows)
+    B.eh_eval(ctx, head, h, rows, H, lse, am, **kw)
+    torch.cuda.synchronize()
+    return H, lse, am
+
+
+@pytest.mark.parametrize("dtype,bias,V,d,R", [
+    ("bf16", False, 5000, 96, 17), ("bf16", False, 4099, 160, 32), ("bf16", False, 4100, 1000, 33), ("bf16", False, 57000, 64, 64),
+    ("bf16", False, 33, 8, 40), ("bf16", True, 1, 64, 3), ("bf16", True, 777, 136, 1), ("bf16", True, 4099, 96, 65),
+    ("bf16", True, 60001, 32, 20), ("bf16", True, 1500, 264, 130), ("f32", False, 4099, 100, 17), ("f32", False, 777, 36, 32),
+    ("f32", False, 60001, 16, 18), ("f32", True, 4100, 1028, 5), ("f32", True, 50, 4, 64), ("f32", True, 1500, 132, 97)])
+def test_ksplit_projection(B, dtype, bias, V, d, R):
+    """The kernel that splits the weight stream over k: odd and missing k-steps of its four waves,
+    one and two blocks of 32 rows, ragged vocabulary slices, several passes per slice (V above
+    57344), several groups of 64 rows; gathered rows and a live count on the device."""
+    w = G.Workload("ks", d=d, V=V, n_heads=2, rows=R, dtype=dtype, seed=V + d + R)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    gen = torch.Generator(device=DEV).manual_seed(V + R)
+    bs = [torch.randn(V, generator=gen, device=DEV) for _ in range(2)] if bias else None
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0, 0.0], max_rows=R, bias=bs)
+    for l in range(2):
+        W = P.f64(heads.W[l])
+        orc = _oracle(hid.h[l], heads.gamma[l], heads.beta[l], W, bs[l] if bias else None, dtype == "bf16")
+        got = _eval(B, ctx, l, hid.h[l], R)
+        P.compare_head(f"ks{l}", *got, orc, [])
+        # half of the rows, gathered backwards, the count on the device: the same bits, the rest untouched
+        n = (R + 1) // 2
+        if n * 2 > R + 1 or R <= 16 and not bias:
+            continue
+        idx = torch.arange(R - 1, -1, -1, dtype=torch.int32, device=DEV)
+        sub = _eval(B, ctx, l, hid.h[l], R, row_idx=idx, n_rows_dev=torch.tensor([n], dtype=torch.int32, device=DEV))
+        for a, b, left in zip(sub, got, (0.0, 0.0, -7)):
+            assert torch.equal(a[:n], b.flip(0)[:n])
+            assert bool((a[n:] == left).all())
+    B.eh_destroy(ctx)
+
+
+def _oracle(h, gamma, beta, W, bias, bf16):
+    from oracle import eh_oracle as O
+    y = O.layernorm(P.f64(h), P.f64(gamma), P.f64(beta), 1e-5, bf16_out=bf16)
+    z = y @ W.T + (0.0 if bias is None else P.f64(bias))
+    m = z.max(axis=1, keepdims=True)
+    S = np.exp(z - m).sum(axis=1)
+    lse = m[:, 0] + np.log(S)
+    p = np.exp(z - lse[:, None])
+    top = np.sort(z, axis=1)
+    gap = top[:, -1] - top[:, -2] if z.shape[1] > 1 else np.full(z.shape[0], np.inf)
+    return lse - (p * z).sum(axis=1), lse, z.argmax(axis=1), gap
+
+
+@pytest.mark.parametrize("rows", [17, 40, 64])
+def test_many_heads_of_a_few_rows_in_one_stream(B, rows):
+    """eh_eval_heads up to 64 rows walks the heads in one launch whose weight stream runs on from
+    head to head: the same bits as a head at a time."""
+    w = G.Workload("ksheads", d=224, V=9001, n_heads=5, rows=rows, dtype="bf16", seed=rows)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0] * 5, max_rows=rows)
+    H, lse, am = torch.zeros((4, rows), device=DEV), torch.zeros((4, rows), device=DEV), _ints(4, rows)
+    B.eh_eval_heads(ctx, 1, 4, hid.h[1:], rows, H, lse, am)
+    for l in range(4):
+        for a, b in zip(_eval(B, ctx, 1 + l, hid.h[1 + l], rows), (H[l], lse[l], am[l])):
+            assert torch.equal(a, b)
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype,rows", [("bf16", 9), ("bf16", 90), ("f32", 20)])
+def test_cascade_of_heads_with_a_bias_vector(B, dtype, rows):
+    """Heads with a bias vector run the two-launches-per-head cascade at every row count."""
+    w = G.Workload("biascascade", d=128, V=3001, n_heads=5, rows=rows, dtype=dtype, seed=rows, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    bs = [0.3 * torch.randn(w.V, device=DEV) for _ in range(5)]
+    full = [_oracle(hid.h[l], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), bs[l], dtype == "bf16") for l in range(5)]
+    full = [np.stack([f[i] for f in full]) for i in range(4)]
+    tau = G.tau_for_schedule(full[0], 5)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows, bias=bs)
+    ex, tok, H, nev = _ints(rows), _ints(rows), torch.zeros((5, rows), device=DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
+    B.eh_cascade(ctx, hid.h, rows, ex, tok, H, nev)
+    torch.cuda.synchronize()
+    P.compare_cascade("biascascade", ex, tok, H, full[0], full[2], full[3], tau, [])
+    assert int(nev) == int((ex.long() + 1).sum())
+    B.eh_destroy(ctx)
