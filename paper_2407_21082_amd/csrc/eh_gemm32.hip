@@ -36,14 +36,13 @@
 // statistics.
 #include "eh_internal.hpp"
 #include "eh_kernels.hpp"
+#include "eh_ksplit.hpp"
 
 #include <type_traits>
 
 namespace eh {
 
 namespace {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kG32Waves = 4;
 constexpr int kG32Threads = kG32Waves * kWave;
@@ -756,21 +755,28 @@ __device__ __forceinline__ int rows_wait(const RowsParams& p, const RowsCtl& c, 
 }
 
 // Device-coherent accesses (no cache of another die keeps serving an older copy): 16-byte and
-// 4-byte stores, and loads that are only ISSUED here -- the caller waits (s_waitcnt vmcnt(0))
-// before it looks at the registers; the build checks that in the generated code.
+// 4-byte stores.
 __device__ __forceinline__ void store_coherent(frag_t* dst, const frag_t& v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(dst), "v"(v) : "memory");
+  // The data registers of a 16-byte store must not be overwritten in the next issue slot.  The
+  // compiler keeps that distance for its own stores but does not look into inline assembly.
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(dst), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_coherent(int* dst, int v) {
   asm volatile("global_store_dword %0, %1, off sc1" ::"v"(dst), "v"(v) : "memory");
 }
-__device__ __forceinline__ void issue_load_coherent(frag_t& dst, const frag_t* src) {
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(dst) : "v"(src) : "memory");
-}
-__device__ __forceinline__ void issue_load_coherent(int& dst, const int* src) {
-  asm volatile("global_load_dword %0, %1, off sc1" : "=v"(dst) : "v"(src) : "memory");
-}
-#define EH_LOADS_DONE() asm volatile("s_waitcnt vmcnt(0)" ::: "memory")
+// The partial statistics of one head's columns, read device-coherently.  The loads are builtins,
+// so the compiler counts them: a record may be spilled while others are still on their way.
+struct PartRecords {
+  ks_buf_t p4, pi;
+  int R_pad;
+  __device__ __forceinline__ PartRecords(const frag_t* part4, const int* parti, int r_pad)
+      : p4(ks_buffer(part4)), pi(ks_buffer(parti)), R_pad(r_pad) {}
+  __device__ __forceinline__ void load(int g, int col, frag_t& h, int& ib) const {
+    const uint32_t at = (uint32_t)(g * R_pad + col);
+    h = ks_load<kKsCoherent>(p4, at * 16, 0);
+    ib = (int)__builtin_amdgcn_raw_buffer_load_b32(pi, (int)(at * 4), 0, kKsCoherent);
+  }
+};
 // A partial statistics record travels as (m, S, U, zb) in one array and ib in another.
 __device__ __forceinline__ frag_t stats_head(const Stats& s) {
   return mk_frag(__float_as_uint(s.m), __float_as_uint(s.S), __float_as_uint(s.U), __float_as_uint(s.zb));
@@ -914,36 +920,26 @@ __device__ __forceinline__ void rows_layernorm(const RowsParams& p, int l, int r
 // Merge of the streaming workgroups' partial statistics of one column (one wave), in
 // finalize_kernel's order.  All records are requested before any is looked at: a device-coherent
 // load is a trip to memory, and one after the other they took 40 us per row.
-__device__ __forceinline__ Stats rows_merge(const frag_t* __restrict__ part4, const int* __restrict__ parti, int n_parts,
-                                            int R_pad, int col, int lane) {
-  constexpr int kPer = (1024 + kWave - 1) / kWave;  // records per lane at most (n_parts <= 1024)
+__device__ __forceinline__ Stats rows_merge(const PartRecords& parts, int n_parts, int col, int lane) {
   Stats s;
   stats_init(s);
   for (int g0 = 0; g0 < n_parts; g0 += 4 * kWave) {
     frag_t h[4];
     int ib[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int g = min(g0 + lane + i * kWave, n_parts - 1);
-      issue_load_coherent(h[i], part4 + (long long)g * R_pad + col);
-      issue_load_coherent(ib[i], parti + (long long)g * R_pad + col);
-    }
-    EH_LOADS_DONE();
+    for (int i = 0; i < 4; ++i) parts.load(min(g0 + lane + i * kWave, n_parts - 1), col, h[i], ib[i]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      asm volatile("" : "+v"(h[i]), "+v"(ib[i]));
+    for (int i = 0; i < 4; ++i)
       if (g0 + lane + i * kWave < n_parts) s = stats_merge(s, stats_from(h[i], ib[i]));
-    }
   }
-  (void)kPer;
 #pragma unroll
   for (int x = 32; x > 0; x >>= 1) s = stats_merge(s, stats_shfl_xor(s, x));
   return s;
 }
 
 // The same for two columns at once (one wait for the records of both).
-__device__ __forceinline__ void rows_merge2(const frag_t* __restrict__ part4, const int* __restrict__ parti, int n_parts,
-                                            int R_pad, int col0, int col1, int lane, Stats& s0, Stats& s1) {
+__device__ __forceinline__ void rows_merge2(const PartRecords& parts, int n_parts, int col0, int col1, int lane, Stats& s0,
+                                            Stats& s1) {
   stats_init(s0);
   stats_init(s1);
   for (int g0 = 0; g0 < n_parts; g0 += 4 * kWave) {
@@ -952,15 +948,11 @@ __device__ __forceinline__ void rows_merge2(const frag_t* __restrict__ part4, co
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int g = min(g0 + lane + i * kWave, n_parts - 1);
-      issue_load_coherent(h[0][i], part4 + (long long)g * R_pad + col0);
-      issue_load_coherent(ib[0][i], parti + (long long)g * R_pad + col0);
-      issue_load_coherent(h[1][i], part4 + (long long)g * R_pad + col1);
-      issue_load_coherent(ib[1][i], parti + (long long)g * R_pad + col1);
+      parts.load(g, col0, h[0][i], ib[0][i]);
+      parts.load(g, col1, h[1][i], ib[1][i]);
     }
-    EH_LOADS_DONE();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      asm volatile("" : "+v"(h[0][i]), "+v"(ib[0][i]), "+v"(h[1][i]), "+v"(ib[1][i]));
       if (g0 + lane + i * kWave < n_parts) {
         s0 = stats_merge(s0, stats_from(h[0][i], ib[0][i]));
         s1 = stats_merge(s1, stats_from(h[1][i], ib[1][i]));
@@ -972,6 +964,39 @@ __device__ __forceinline__ void rows_merge2(const frag_t* __restrict__ part4, co
     s0 = stats_merge(s0, stats_shfl_xor(s0, x));
     s1 = stats_merge(s1, stats_shfl_xor(s1, x));
   }
+}
+
+// LayerNorm of the first head's rows, spread over the streaming workgroups (four waves per row).
+__device__ __forceinline__ void rows_first_layernorm(const RowsParams& p, const RowsCtl& c, double* red) {
+  const int g = blockIdx.x, tid = threadIdx.x;
+  for (int r = g; r < p.n_rows; r += p.n_stream) {
+    const char* row = (const char*)p.h + ((long long)p.l0 * p.layer_stride + (long long)r * p.row_stride) * DtBf16::ESZ;
+    auto put = [&](int ch, const frag_t& v) { put_chunk32_coherent(p.y, p.KS, r, ch, v); };
+    if (p.KS * 4 <= kLnCache * kWave)
+      group_layernorm_cached<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, red, put);
+    else
+      group_layernorm<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, red, put);
+    __syncthreads();
+  }
+  EH_STORES_DONE();
+  __syncthreads();
+  if (tid == 0) ctl_add(c.ready(0), g, 1);
+  EH_ROWS_STAMP(1);
+}
+
+// The wait for all of it; leaves the counter in *flag.  False if the launch was aborted.
+__device__ __forceinline__ bool rows_first_wait(const RowsParams& p, const RowsCtl& c, int lane, int wave, int* flag) {
+  // the first head's activations are complete when every streaming workgroup has written its rows
+  if (wave == 0) {
+    const int v = rows_wait(p, c, c.ready(0), p.n_stream, lane);
+    if (lane == 0) *flag = v;
+  }
+  __syncthreads();
+  const int word = *flag;
+  __syncthreads();
+  if (word < 0) return false;
+  EH_AFTER_WAIT();
+  return true;
 }
 
 // Returns false if the launch was aborted (or every row has left).
@@ -1002,30 +1027,9 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
   };
   EH_ROWS_STAMP(0);
   warm(p.Wf[p.l0]);
-  // LayerNorm of the first head's rows, spread over the streaming workgroups (four waves per row)
-  for (int r = g; r < p.n_rows; r += p.n_stream) {
-    const char* row = (const char*)p.h + ((long long)p.l0 * p.layer_stride + (long long)r * p.row_stride) * DtBf16::ESZ;
-    auto put = [&](int ch, const frag_t& v) { put_chunk32_coherent(p.y, p.KS, r, ch, v); };
-    if (p.KS * 4 <= kLnCache * kWave)
-      group_layernorm_cached<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, red, put);
-    else
-      group_layernorm<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, red, put);
-    __syncthreads();
-  }
-  EH_STORES_DONE();
-  __syncthreads();
-  if (tid == 0) ctl_add(c.ready(0), g, 1);
-  EH_ROWS_STAMP(1);
-  // the first head's activations are complete when every streaming workgroup has written its rows
-  if (wave == 0) {
-    const int v = rows_wait(p, c, c.ready(0), p.n_stream, lane);
-    if (lane == 0) *flag = v;
-  }
-  __syncthreads();
-  int word = *flag;
-  __syncthreads();
-  if (word < 0) return false;
-  EH_AFTER_WAIT();
+  rows_first_layernorm(p, c, red);
+  if (!rows_first_wait(p, c, lane, wave, flag)) return false;
+  int word = 0;
   int ncols = p.n_rows;
   EH_ROWS_STAMP(2);
   for (int j = 0; j < nh; ++j) {
@@ -1097,6 +1101,100 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
       if (word < 0) return false;
       EH_AFTER_WAIT();
       ncols = j + 1 >= 2 ? (word >> 8) : p.n_rows;
+    }
+  }
+  return true;
+}
+
+// The same for up to 64 rows, on the k-split projection: nothing in a head's stream waits for another
+// wave, and the next head's first two k-steps (weights and, if they are there in time, activations)
+// are in flight while this head's statistics are added up and handed on.  One kernel per number of
+// blocks: with both in one the register allocator spilled 300 registers around the hand-over, and
+// every reload waited for the weights in flight (56 us per head).
+// Measured, us before (rows_stream) -> now: 64 rows x 32 heads of d = 2560 1586 -> 1484; 32 rows 1518 ->
+// 1312; 1 row x 16 heads 604 -> 534; 17 rows x 24 heads of d = 1024 552 -> 512; verification of 36
+// positions, d = 2560, 76 -> 67.
+template <int MT, int NB, bool ARGMAX_ONLY>
+__device__ __forceinline__ bool rows_stream_ks(const RowsParams& p, const RowsCtl& c, const KsSlice& sl, EH_KS_LDS char* lds,
+                                               int lane, int wave, double* red, int* flag) {
+  const int g = blockIdx.x, tid = threadIdx.x;
+  const int nh = p.l1 - p.l0;
+  const int nsw = ((int)gridDim.x - p.n_stream) * kG32Waves;  // service waves
+  const int row_hi = min(p.V, sl.t1 * 16);
+  const long long slice_at = (long long)sl.t0 * p.KS * kWave;
+  const long long pass_len = (long long)2 * MT * p.KS * kWave;
+  uint32_t voff[MT];
+  ks_offsets<MT>(sl.t1 - sl.t0, p.KS, lane, voff);
+  frag_t a[2][MT][2], b[2][2][2];
+  // (weights asked for in front of the LayerNorm would only hold up its own loads: a wave's loads
+  // return in order)
+  rows_first_layernorm(p, c, red);
+  ks_start<MT>(a, p.Wf[p.l0] + slice_at, p.KS, wave, voff);
+  if (!rows_first_wait(p, c, lane, wave, flag)) return false;  // leaves *flag >= 0
+  int ncols = p.n_rows;
+  ks_start_b<NB>(b, p.y, p.KS, wave, lane);
+  for (int j = 0; j < nh; ++j) {
+    if (ncols == 0) return false;  // every row has left: the same for all workgroups
+    const frag_t* W = p.Wf[p.l0 + j] + slice_at;
+    const frag_t* Wn = p.Wf[min(p.l0 + j + 1, p.l1 - 1)] + slice_at;
+    const frag_t* y = p.y + (long long)j * p.y_stride;
+    int word = 0, seen = 0;  // the next head's ready counter: this lane's word of it, and the sum once it is complete
+    Stats s;
+    float z2;
+    {
+      Stats st[NB];
+      float second[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) stats_init(st[nb]);
+      for (int q = 0; q < sl.passes; ++q) {
+        const bool last = q + 1 == sl.passes;
+        // towards the end of the head's last pass every wave looks whether the next head's activations
+        // are there (they have been for a while, as a rule); the answer is read two k-steps later
+        auto ask = [&]() {
+          if (lane < kSpread) word = ctl_load(c.ready(j + 1) + lane);  // (one counter more than heads: always there)
+        };
+        auto y_next = [&]() -> const frag_t* {
+          if (!last || j + 1 >= nh) return y;
+          int v = lane < kSpread ? word : 0;
+#pragma unroll
+          for (int x = kSpread / 2; x > 0; x >>= 1) v += __shfl_xor(v, x);
+          v = __builtin_amdgcn_readfirstlane(v);
+          if ((v & 0xff) < nsw) return y;  // not yet: nothing of it may be read (a cache would keep the old copy)
+          seen = v;
+          return y + p.y_stride;
+        };
+        f32x16 acc[MT][NB];
+        ks_pass<DtBf16, MT, NB>(a, b, W + q * pass_len, last ? Wn : W + (q + 1) * pass_len, y, p.KS, wave, lane, voff,
+                                sl.t1 - sl.t0 - (last ? 0 : 2 * MT * (q + 1)), acc, ask, y_next);
+        EH_AFTER_WAIT();
+        ks_finish<MT, NB, ARGMAX_ONLY, false>(acc, lds, wave, lane, (sl.t0 + 2 * MT * q) * 16, row_hi, nullptr, st, second);
+      }
+      s = ks_merge<NB, false>(st, second, z2, lds, wave, lane);
+    }
+    // A wave that saw the launch aborted has left *flag negative before it went (and before the
+    // barrier just passed): its share of the logits is missing, nothing may be handed on.
+    if (*flag < 0) return false;
+    if (wave == 0) {  // hand on the workgroup's records, one per column
+      const long long part_at = (long long)(j & 1) * p.n_stream * p.R_pad + (long long)g * p.R_pad;
+      if (tid < 32 * NB) {  // (columns beyond the live ones hold nothing anybody reads)
+        store_coherent(p.part4 + part_at + tid, stats_head(s));
+        store_coherent(p.parti + part_at + tid, s.ib);
+      }
+      EH_STORES_DONE();
+      if (tid == 0) ctl_add(c.done(j), g, 1);
+    }
+    if (j + 1 < nh) {
+      if (seen == 0) {
+        seen = rows_wait(p, c, c.ready(j + 1), nsw, lane, 0xff);
+        if (seen < 0) {
+          if (lane == 0) *flag = -1;
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          return false;
+        }
+        EH_AFTER_WAIT();
+        ks_start_b<NB>(b, y + p.y_stride, p.KS, wave, lane);
+      }
+      ncols = j + 1 >= 2 ? (seen >> 8) : p.n_rows;
     }
   }
   return true;
@@ -1221,6 +1319,7 @@ __device__ __forceinline__ void rows_serve_cascade(const RowsParams& p, const Ro
     EH_AFTER_WAIT();
     if (j == 2) EH_ROWS_STAMP(1);
     const long long part_at = (long long)(j & 1) * p.n_stream * p.R_pad;
+    const PartRecords parts(p.part4 + part_at, p.parti + part_at, p.R_pad);
     const float tau = p.tau[l];
     RowMask stay, mine;  // rows of mine that go on / that were decided this turn
     stay.set_all(0);
@@ -1229,12 +1328,12 @@ __device__ __forceinline__ void rows_serve_cascade(const RowsParams& p, const Ro
     Stats s01[2];
     const bool both = a0 && a1;  // the first two rows together: one trip to memory for both
     if (both)
-      rows_merge2(p.part4 + part_at, p.parti + part_at, p.n_stream, p.R_pad, cols.rank(r0), cols.rank(r1), lane, s01[0], s01[1]);
+      rows_merge2(parts, p.n_stream, cols.rank(r0), cols.rank(r1), lane, s01[0], s01[1]);
     for (int r = sw, k = 0; r < p.n_rows; r += nsw, ++k) {
       if (!alive.test(r)) continue;
       Stats s;
       if (both && k < 2) s = s01[k];
-      else s = rows_merge(p.part4 + part_at, p.parti + part_at, p.n_stream, p.R_pad, cols.rank(r), lane);
+      else s = rows_merge(parts, p.n_stream, cols.rank(r), lane);
       float H, lse;
       stats_finalize(s, H, lse);
       ++evals;
@@ -1330,6 +1429,7 @@ __device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const Rows
   if (!ok) return;
   EH_AFTER_WAIT();
   EH_ROWS_STAMP(20);
+  const PartRecords parts(p.part4, p.parti, p.R_pad);
   for (int pos = g; pos < p.n_rows; pos += p.n_stream) {
     float zb = -INFINITY;
     int ib = 0x7fffffff;
@@ -1337,15 +1437,9 @@ __device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const Rows
       frag_t h[4];
       int ri[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int q = min(q0 + tid + i * kG32Threads, p.n_stream - 1);
-        issue_load_coherent(h[i], p.part4 + (long long)q * p.R_pad + pos);
-        issue_load_coherent(ri[i], p.parti + (long long)q * p.R_pad + pos);
-      }
-      EH_LOADS_DONE();
+      for (int i = 0; i < 4; ++i) parts.load(min(q0 + tid + i * kG32Threads, p.n_stream - 1), pos, h[i], ri[i]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        asm volatile("" : "+v"(h[i]), "+v"(ri[i]));
         const float rz = __uint_as_float(h[i].w);
         if (q0 + tid + i * kG32Threads < p.n_stream && (rz > zb || (rz == zb && ri[i] < ib))) { zb = rz; ib = ri[i]; }
       }
@@ -1399,9 +1493,9 @@ __device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const Rows
   }
 }
 
-template <bool ARGMAX_ONLY>
-__global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel_rows(const RowsParams p) {
-  extern __shared__ __attribute__((aligned(16))) char g32_smem[];
+// KS_NB: 0 = rows_stream; 1 or 2 = rows_stream_ks with that many blocks of 32 rows.
+template <bool ARGMAX_ONLY, int KS_NB>
+__device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_smem) {
   __shared__ double red[2 * kLnWaves];
   __shared__ int flag;
   __shared__ float red_z[kG32Waves];
@@ -1427,12 +1521,40 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel_rows(const
   if (*(volatile int*)p.status != 0) return;
   RowsCtl c{p.ctl, p.l1 - p.l0 + 2};
   if ((int)blockIdx.x < p.n_stream) {
-    const bool ok = rows_stream<ARGMAX_ONLY>(p, c, lds, lane, wave, red, &flag);
+    bool ok = false;
+    if constexpr (KS_NB > 0) {
+      const KsSlice sl(p.VT16, blockIdx.x, p.n_stream);
+      switch (sl.mt) {
+        case 7: ok = rows_stream_ks<7, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        case 6: ok = rows_stream_ks<6, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        case 5: ok = rows_stream_ks<5, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        case 4: ok = rows_stream_ks<4, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        case 3: ok = rows_stream_ks<3, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        case 2: ok = rows_stream_ks<2, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        // (a workgroup without a tile of its own takes its turns like the others)
+        default: ok = rows_stream_ks<1, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+      }
+    } else {
+      ok = rows_stream<ARGMAX_ONLY>(p, c, lds, lane, wave, red, &flag);
+    }
     if (ok && p.mode == 1) rows_verify_tail(p, c, lane, wave, &flag, red_z, red_i);
     return;
   }
   const int sg = (int)blockIdx.x - p.n_stream, nsg = (int)gridDim.x - p.n_stream;
   if (p.mode == 0) rows_serve_cascade(p, c, lane, sg * kG32Waves + wave, nsg * kG32Waves);
+}
+
+template <bool ARGMAX_ONLY>
+__global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel_rows(const RowsParams p) {
+  extern __shared__ __attribute__((aligned(16))) char g32_smem[];
+  rows_kernel_body<ARGMAX_ONLY, 0>(p, g32_smem);
+}
+
+// Up to 32 * NB rows, NB = 1 or 2 (see rows_stream_ks).
+template <bool ARGMAX_ONLY, int NB>
+__global__ __launch_bounds__(kG32Threads, 1) void rows_ksplit_kernel(const RowsParams p) {
+  extern __shared__ __attribute__((aligned(16))) char g32_smem[];
+  rows_kernel_body<ARGMAX_ONLY, NB>(p, g32_smem);
 }
 
 // Presets of a cascade launch: the control block to zero, the outputs to "not decided".
@@ -1524,12 +1646,17 @@ hipError_t rows_prepare(eh_ctx* c) {
   if (e != hipSuccess) return e;
   const int cus = prop.multiProcessorCount;
   if (cus < 4 * kRowsServiceWgs) return hipSuccess;  // too small a device to set workgroups aside
-  const void* fns[2] = {(const void*)gemm32_stats_kernel_rows<false>, (const void*)gemm32_stats_kernel_rows<true>};
-  for (const void* fn : fns) {
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g32_lds_bytes());
+  const struct { const void* fn; size_t lds; } fns[6] = {{(const void*)gemm32_stats_kernel_rows<false>, g32_lds_bytes()},
+                                                       {(const void*)gemm32_stats_kernel_rows<true>, g32_lds_bytes()},
+                                                       {(const void*)rows_ksplit_kernel<false, 1>, ks_lds_bytes()},
+                                                       {(const void*)rows_ksplit_kernel<true, 1>, ks_lds_bytes()},
+                                                       {(const void*)rows_ksplit_kernel<false, 2>, ks_lds_bytes()},
+                                                       {(const void*)rows_ksplit_kernel<true, 2>, ks_lds_bytes()}};
+  for (const auto& [fn, lds] : fns) {
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) { (void)hipGetLastError(); return hipSuccess; }
     int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kG32Threads, g32_lds_bytes());
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kG32Threads, lds);
     if (e != hipSuccess || per_cu < 1) { (void)hipGetLastError(); return hipSuccess; }
   }
   // the kernel's workgroups wait for each other: all of them must be resident at once
@@ -1555,7 +1682,18 @@ hipError_t rows_launch(const eh_ctx* c, const RowsParams& p, hipStream_t s) {
     hipLaunchKernelGGL(rows_preset_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.ctl, n_ctl, p.exit_layer, p.token,
                        p.n_rows, p.H_out, n_H, p.live);
   }
-  if (p.argmax_only)
+  if (p.n_rows <= kKsGroup) {
+#define EH_ROWS_KS(AO_, NB_) \
+  hipLaunchKernelGGL((rows_ksplit_kernel<AO_, NB_>), dim3(c->rows_grid), dim3(kG32Threads), ks_lds_bytes(), s, p)
+    if (p.n_rows <= 32) {
+      if (p.argmax_only) EH_ROWS_KS(true, 1);
+      else EH_ROWS_KS(false, 1);
+    } else {
+      if (p.argmax_only) EH_ROWS_KS(true, 2);
+      else EH_ROWS_KS(false, 2);
+    }
+#undef EH_ROWS_KS
+  } else if (p.argmax_only)
     hipLaunchKernelGGL((gemm32_stats_kernel_rows<true>), dim3(c->rows_grid), dim3(kG32Threads), g32_lds_bytes(), s, p);
   else
     hipLaunchKernelGGL((gemm32_stats_kernel_rows<false>), dim3(c->rows_grid), dim3(kG32Threads), g32_lds_bytes(), s, p);

@@ -18,10 +18,11 @@ __device__ __forceinline__ void ks_heads(const KsSlice& sl, const frag_t* const*
   const long long slice_at = (long long)sl.t0 * KS * kWave;       // fragments (16 bytes per lane)
   const long long pass_len = (long long)2 * MT * KS * kWave;
   auto tiles_of = [&](int p) { return sl.t1 - sl.t0 - 2 * MT * p; };  // 16-row tiles from pass p on
-  uint32_t voff[MT], vnext[MT];
+  uint32_t voff[MT];
   ks_offsets<MT>(tiles_of(0), KS, lane, voff);
-  frag_t a[2][MT][2];
+  frag_t a[2][MT][2], b[2][2][2];
   ks_start<MT>(a, Wf[0] + slice_at, KS, wave, voff);
+  ks_start_b<NB>(b, yq, KS, wave, lane);
   for (int l = 0; l < n_heads; ++l) {
     Stats st[NB];
     float second[NB], z2;
@@ -34,13 +35,12 @@ __device__ __forceinline__ void ks_heads(const KsSlice& sl, const frag_t* const*
     const frag_t* Wn = Wf[min(l + 1, n_heads - 1)] + slice_at;
     for (int p = 0; p < sl.passes; ++p) {
       const bool last = p + 1 == sl.passes;
-      ks_offsets<MT>(tiles_of(last ? 0 : p + 1), KS, lane, vnext);
       f32x16 acc[MT][NB];
-      ks_pass<DT, MT, NB>(a, W + p * pass_len, last ? Wn : W + (p + 1) * pass_len, yq + l * y_stride, KS, wave, lane, voff,
-                          vnext, acc);
+      const frag_t* y = yq + l * y_stride;
+      ks_pass<DT, MT, NB>(a, b, W + p * pass_len, last ? Wn : W + (p + 1) * pass_len, y, KS, wave, lane, voff,
+                          tiles_of(last ? 0 : p + 1), acc, []() {},
+                          [&]() { return last && l + 1 < n_heads ? y + y_stride : y; });
       ks_finish<MT, NB, AO, TOP2>(acc, lds, wave, lane, (sl.t0 + 2 * MT * p) * 16, row_hi, bias ? bias[l] : nullptr, st, second);
-#pragma unroll
-      for (int m = 0; m < MT; ++m) voff[m] = vnext[m];
     }
     const Stats s = ks_merge<NB, TOP2>(st, second, z2, lds, wave, lane);
     const int t = blockIdx.y * kKsGroup + threadIdx.x;

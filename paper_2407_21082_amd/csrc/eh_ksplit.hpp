@@ -74,7 +74,8 @@ __device__ __forceinline__ ks_buf_t ks_buffer(const void* p) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, 0xffffffffu, 0x00020000);
 }
-constexpr int kKsNt = 2;  // cache policy: non-temporal (a weight is read once)
+constexpr int kKsNt = 2;         // cache policy: non-temporal (a weight is read once)
+constexpr int kKsCoherent = 16;  // cache policy: device-coherent (sc1)
 template <int AUX>
 __device__ __forceinline__ frag_t ks_load(ks_buf_t buf, uint32_t lane_off, uint32_t base) {
   return __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)lane_off, (int)base, AUX));
@@ -99,7 +100,7 @@ template <int MT>
 __device__ __forceinline__ void ks_offsets(int tiles16, int KS, int lane, uint32_t (&voff)[MT]) {
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
-    const int t = min(2 * m + ((lane & 31) >> 4), tiles16 - 1);
+    const int t = min(2 * m + ((lane & 31) >> 4), max(tiles16 - 1, 0));  // (an empty slice: its first tile, unused)
     voff[m] = ((uint32_t)t * (uint32_t)KS << 10) + (((lane >> 5) * 16 + (lane & 15)) << 4);
   }
 }
@@ -123,35 +124,43 @@ __device__ __forceinline__ void ks_start(frag_t (&a)[2][MT][2], const void* w, i
   for (int j = 0; j < 2; ++j) ks_load_a<MT>(a[j], wu, ks_at(j, wave, KS), voff);
 }
 
-// One pass over this wave's share of k.  a holds the pass's first two k-steps on entry (asked
-// for, not waited for) and those of the pass at w_next (offsets voff_next) on return.  Activations:
-// fragment (block n, 2*ks + h) of 2*KS per block, in 32-row operand order.  A wave with an odd
-// number of k-steps runs one more on zeroed activations so that the two buffers keep their roles.
-template <typename DT, int MT, int NB>
-__device__ __forceinline__ void ks_pass(frag_t (&a)[2][MT][2], const void* w, const void* w_next, const frag_t* y, int KS,
-                                        int wave, int lane, const uint32_t (&voff)[MT], const uint32_t (&voff_next)[MT],
-                                        f32x16 (&acc)[MT][NB]) {
+// Activations of this wave's i-th k-step: fragment (block nb, 2*ks + h) of 2*KS per block, in 32-row
+// operand order.
+template <int NB>
+__device__ __forceinline__ void ks_load_b(frag_t (&b)[2][2], ks_buf_t y, int i, int KS, int wave, int lane) {
+  const uint32_t at = 2 * ks_at(i, wave, KS), lane16 = (uint32_t)lane << 4;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) b[nb][h] = ks_load<0>(y, lane16 + h * 1024, at + (uint32_t)nb * 2 * KS * 1024);
+}
+template <int NB>
+__device__ __forceinline__ void ks_start_b(frag_t (&b)[2][2][2], const void* y, int KS, int wave, int lane) {
+  const ks_buf_t yu = ks_buffer(y);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) ks_load_b<NB>(b[j], yu, j, KS, wave, lane);
+}
+
+// One pass over this wave's share of k.  a and b hold the weights and activations of the pass's first
+// two k-steps on entry (asked for, not waited for) and those of the next pass on return: weights
+// at w_next (a slice of tiles16_next 16-row tiles, whose offsets replace voff), activations at
+// y_next(), which is called in front of the last two k-steps; ask() is called two k-steps earlier
+// (not at all if there are only two).  A wave with an odd number of k-steps runs one more on
+// zeroed activations so that the two buffers keep their roles.
+template <typename DT, int MT, int NB, typename AskFn, typename NextFn>
+__device__ __forceinline__ void ks_pass(frag_t (&a)[2][MT][2], frag_t (&b)[2][2][2], const void* w, const void* w_next,
+                                        const frag_t* y, int KS, int wave, int lane, uint32_t (&voff)[MT], int tiles16_next,
+                                        f32x16 (&acc)[MT][NB], AskFn ask, NextFn y_next) {
   const int n = (KS - wave + kKsWaves - 1) / kKsWaves;
   const int n2 = (n + 1) & ~1;
-  const ks_buf_t wu = ks_buffer(w), wx = ks_buffer(w_next), yu = ks_buffer(y);
-  const uint32_t lane16 = (uint32_t)lane << 4;
-  auto load_b = [&](frag_t (&b)[NB][2], int i) {
-    const uint32_t at = 2 * ks_at(i, wave, KS);
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) b[nb][h] = ks_load<0>(yu, lane16 + h * 1024, at + (uint32_t)nb * 2 * KS * 1024);
-  };
-  frag_t b[2][NB][2];
-  load_b(b[0], 0);
-  load_b(b[1], 1);
+  const ks_buf_t wu = ks_buffer(w), yu = ks_buffer(y);
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[m][nb][i] = 0.f;
-  auto step = [&](frag_t (&aj)[MT][2], frag_t (&bj)[NB][2]) {
+  auto step = [&](frag_t (&aj)[MT][2], frag_t (&bj)[2][2]) {
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -162,27 +171,32 @@ __device__ __forceinline__ void ks_pass(frag_t (&a)[2][MT][2], const void* w, co
   // refills are unconditional: a load under a branch makes the compiler wait for everything
   int i = 0;
   for (; i + 2 < n2; i += 2) {
-    step(a[0], b[0]);
-    ks_load_a<MT>(a[0], wu, ks_at(i + 2, wave, KS), voff);
-    load_b(b[0], i + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    step(a[1], b[1]);
-    ks_load_a<MT>(a[1], wu, ks_at(i + 3, wave, KS), voff);
-    load_b(b[1], i + 3);
-    __builtin_amdgcn_sched_barrier(0);
+    if (i + 4 >= n2) ask();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      step(a[j], b[j]);
+      ks_load_a<MT>(a[j], wu, ks_at(i + 2 + j, wave, KS), voff);
+      ks_load_b<NB>(b[j], yu, i + 2 + j, KS, wave, lane);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
+  const ks_buf_t wx = ks_buffer(w_next), yx = ks_buffer(y_next());
+  ks_offsets<MT>(tiles16_next, KS, lane, voff);
   if (i < n2) {  // the last two steps refill with the next pass's first two
-    step(a[0], b[0]);
-    ks_load_a<MT>(a[0], wx, ks_at(0, wave, KS), voff_next);
-    __builtin_amdgcn_sched_barrier(0);
-    const uint32_t keep = i + 1 < n ? 0xffffffffu : 0u;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int j = 0; j < 2; ++j) {
+      if (j == 1) {
+        const uint32_t keep = i + 1 < n ? 0xffffffffu : 0u;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) b[1][nb][h] &= keep;
-    step(a[1], b[1]);
-    ks_load_a<MT>(a[1], wx, ks_at(1, wave, KS), voff_next);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) b[1][nb][h] &= keep;
+      }
+      step(a[j], b[j]);
+      ks_load_a<MT>(a[j], wx, ks_at(j, wave, KS), voff);
+      ks_load_b<NB>(b[j], yx, j, KS, wave, lane);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 

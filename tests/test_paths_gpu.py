@@ -132,3 +132,37 @@ def test_cascade_of_heads_with_a_bias_vector(B, dtype, rows):
     P.compare_cascade("biascascade", ex, tok, H, full[0], full[2], full[3], tau, [])
     assert int(nev) == int((ex.long() + 1).sum())
     B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("rows,V,d", [(20, 3000, 256), (32, 1000, 96), (33, 9000, 8), (40, 60001, 64), (64, 5000, 1000), (64, 4200, 32)])
+def test_persistent_cascade_and_verification_up_to_64_rows(B, rows, V, d):
+    """The persistent kernel on the k-split stream: one and two blocks of 32 rows, workgroups without a
+    tile of their own (fewer than 244 tiles of 16), several passes per slice, as few as one k-step,
+    rows leaving on the way; then the verification of the same rows by the same kernel."""
+    w = G.Workload("rowsks", d=d, V=V, n_heads=5, rows=rows, dtype="bf16", seed=rows + V, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    full = P.oracle_all_heads(heads, hid.h, True)
+    tau = G.tau_for_schedule(full[0], 5)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows)
+    for _ in range(3):
+        ex, tok, H = _ints(rows), _ints(rows), torch.zeros((5, rows), device=DEV)
+        nev = torch.zeros(1, dtype=torch.int64, device=DEV)
+        B.eh_cascade(ctx, hid.h, rows, ex, tok, H, nev)
+        B.eh_check(ctx)
+        P.compare_cascade("rowsks", ex, tok, H, full[0], full[2], full[3], tau, [])
+        assert int(nev) == int((ex.long() + 1).sum())
+    if rows <= 16 or rows % 4:
+        return B.eh_destroy(ctx)
+    k, Bsz = 3, rows // 4
+    want = torch.tensor(full[2][4].reshape(Bsz, 4), dtype=torch.int32, device=DEV)
+    draft = want[:, :k].contiguous()
+    draft[1::2, 1] = (draft[1::2, 1] + 1) % V
+    acc, nxt, tgt = _ints(Bsz), _ints(Bsz), _ints(Bsz, 4)
+    B.dssd_verify(ctx, hid.h[4].reshape(Bsz, 4, d).contiguous(), draft, None, acc, nxt, tgt)
+    B.eh_check(ctx)
+    if (full[3][4] >= P.NEAR_TIE).all():
+        assert torch.equal(tgt, want)
+        assert acc[::2].eq(k).all() and acc[1::2].eq(1).all()
+        assert torch.equal(nxt, want.gather(1, acc[:, None].long())[:, 0])
+    B.eh_destroy(ctx)
