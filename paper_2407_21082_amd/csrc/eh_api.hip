@@ -125,12 +125,13 @@ void launch_ln(const eh_ctx* c, int head, const void* h, int64_t row_stride, con
 
 // Projection and partial statistics of the rows launch_ln has prepared.
 hipError_t project(const eh_ctx* c, int head, const int* n_rows_dev, int n_rows, bool argmax_only, const frag_t* yf,
-                   Stats* partials, int* n_parts, hipStream_t s) {
+                   Stats* partials, PartCount* parts, hipStream_t s) {
+  *parts = PartCount{0, 0, 0};
   if (use_ksplit(c, n_rows))
-    return ksplit_launch(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, nullptr, 0, n_parts, s);
+    return ksplit_launch(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, nullptr, 0, &parts->n, s);
   if (c->dtype == EH_BF16)
-    return gemm32_launch(c, head, n_rows_dev, n_rows, argmax_only, yf, partials, nullptr, n_parts, s);
-  return gemm_launch(c, head, n_rows_dev, n_rows, argmax_only, yf, partials, n_parts, s);
+    return gemm32_launch(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, nullptr, 0, parts, s);
+  return gemm_launch(c, head, n_rows_dev, n_rows, argmax_only, yf, partials, &parts->n, s);
 }
 
 // LayerNorm + projection + statistics for one head; results to (H, lse, argmax).
@@ -144,9 +145,9 @@ eh_status run_head(eh_ctx* c, int head, const void* h, int64_t row_stride, const
   if (!partials) partials = c->partials;
   const int R_pad = round_up(n_rows, row_block(c, n_rows));
   launch_ln(c, head, h, row_stride, row_idx, n_rows_dev, n_rows, R_pad, yf, s);
-  int n_parts = 0;
-  EH_HIP(c, project(c, head, n_rows_dev, n_rows, AO, yf, partials, &n_parts, s));
-  hipLaunchKernelGGL(finalize_kernel, dim3(n_rows), dim3(64), 0, s, partials, n_parts, R_pad,
+  PartCount parts;
+  EH_HIP(c, project(c, head, n_rows_dev, n_rows, AO, yf, partials, &parts, s));
+  hipLaunchKernelGGL(finalize_kernel, dim3(n_rows), dim3(64), 0, s, partials, parts, R_pad,
                      n_rows_dev, n_rows, AO ? nullptr : H, AO ? nullptr : lse, argmax, (int64_t)0, (int64_t)0);
   EH_HIP(c, hipGetLastError());
   return EH_OK;
@@ -479,20 +480,20 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
                      layer_stride, row_stride, n_rows, R_pad, ctx->d, ctx->KS,
                      (const float* const*)(ctx->d_gamma + head0), (const float* const*)(ctx->d_beta + head0),
                      ctx->eps, ctx->mh_yf, (int64_t)y_stride);
-  int n_parts = 0;
+  PartCount parts{0, 0, 0};
+  float* second = metrics ? ctx->mh_second : nullptr;
   if (use_ksplit(ctx, n_rows))
     EH_HIP(ctx, ksplit_launch(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
-                              ctx->mh_partials, metrics ? ctx->mh_second : nullptr, (long long)part_stride, &n_parts, s));
+                              ctx->mh_partials, second, (long long)part_stride, &parts.n, s));
   else
-    EH_HIP(ctx, gemm32_launch_heads(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
-                                  ctx->mh_partials, metrics ? ctx->mh_second : nullptr, (long long)part_stride,
-                                  &n_parts, s));
+    EH_HIP(ctx, gemm32_launch(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
+                              ctx->mh_partials, second, (long long)part_stride, &parts, s));
   if (metrics)
     hipLaunchKernelGGL(finalize_metrics_kernel, dim3(n_rows, n_heads_eval), dim3(64), 0, s, ctx->mh_partials,
-                       ctx->mh_second, n_parts, R_pad, n_rows, H, lse, argmax, max_prob, margin,
+                       ctx->mh_second, parts.n, R_pad, n_rows, H, lse, argmax, max_prob, margin,
                        (int64_t)part_stride, (int64_t)n_rows);
   else
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_rows, n_heads_eval), dim3(64), 0, s, ctx->mh_partials, n_parts,
+    hipLaunchKernelGGL(finalize_kernel, dim3(n_rows, n_heads_eval), dim3(64), 0, s, ctx->mh_partials, parts,
                        R_pad, (const int*)nullptr, n_rows, H, lse, argmax, (int64_t)part_stride,
                        (int64_t)n_rows);
   EH_HIP(ctx, hipGetLastError());
@@ -583,14 +584,14 @@ eh_status eh_cascade(eh_ctx* ctx, const void* h_layers, int64_t layer_stride, in
     const int last = l == ctx->n_heads - 1 ? 1 : 0;
     const int* idx = l == 0 ? nullptr : ctx->active[l & 1];
     const int* live = l == 0 ? nullptr : cnt + l % 3;
-    int n_parts = 0;
-    EH_HIP(ctx, project(ctx, l, live, n_rows, false, ctx->yf, ctx->partials, &n_parts, s));
+    PartCount parts;
+    EH_HIP(ctx, project(ctx, l, live, n_rows, false, ctx->yf, ctx->partials, &parts, s));
     const void* hn = last ? nullptr : (const char*)h_layers + (int64_t)(l + 1) * layer_stride * esz;
     const float* gn = last ? nullptr : ctx->gamma[l + 1];
     const float* bn = last ? nullptr : ctx->beta[l + 1];
     float* Hl = H_out ? H_out + (int64_t)l * n_rows : nullptr;
 #define EH_POST(DT, RBV)                                                                              \
-  hipLaunchKernelGGL((cascade_post_kernel<DT, RBV>), dim3(n_rows), dim3(kLnThreads), 0, s, ctx->partials, n_parts, \
+  hipLaunchKernelGGL((cascade_post_kernel<DT, RBV>), dim3(n_rows), dim3(kLnThreads), 0, s, ctx->partials, parts, \
                      R_pad, idx, live, n_rows, ctx->tau[l], last, l, exit_layer, token, Hl,            \
                      (unsigned long long*)n_evals_out, ctx->active[(l + 1) & 1], cnt + (l + 1) % 3,    \
                      cnt + (l + 2) % 3, hn, row_stride, ctx->d, ctx->KS, gn, bn, ctx->eps, ctx->yf)
@@ -640,10 +641,10 @@ eh_status dssd_verify(eh_ctx* ctx, const void* f_final, const int32_t* draft, co
     const int R_pad = round_up((int)rows, row_block(ctx, (int)rows));
     const int fin = ctx->n_heads - 1;
     launch_ln(ctx, fin, f_final, ctx->d, nullptr, nullptr, (int)rows, R_pad, ctx->yf, s);
-    int n_parts = 0;
-    EH_HIP(ctx, project(ctx, fin, nullptr, (int)rows, true, ctx->yf, ctx->partials, &n_parts, s));
+    PartCount parts;
+    EH_HIP(ctx, project(ctx, fin, nullptr, (int)rows, true, ctx->yf, ctx->partials, &parts, s));
     hipLaunchKernelGGL(verify_post_kernel, dim3(B), dim3(256), (size_t)(k + 1) * sizeof(int), s, ctx->partials,
-                       n_parts, R_pad, draft, draft_len, k, target, accepted, next_token);
+                       parts.n, R_pad, draft, draft_len, k, target, accepted, next_token);
     EH_HIP(ctx, hipGetLastError());
     return EH_OK;
   }

@@ -165,6 +165,20 @@ __device__ __forceinline__ Stats stats_shfl_xor(const Stats& s, int mask) {
   return o;
 }
 
+// How many partial statistics a row has.  The batched bf16 kernel shares its grid out between as many
+// groups of 256 rows as are live; where that is only known on the device, its readers work out the
+// same number.
+__host__ __device__ inline int gemm32_parts(int n_live, int grid, int max_parts) {
+  const int groups = (((n_live + 31) >> 5) + 7) / 8;
+  const int p = groups > 0 ? grid / groups : grid;
+  return p < 1 ? 1 : (p > max_parts ? max_parts : p);
+}
+struct PartCount {
+  int n;          // for the rows the host passed
+  int grid, max;  // grid > 0: the count follows the live rows
+  __device__ __forceinline__ int of(int n_live) const { return grid > 0 ? gemm32_parts(n_live, grid, max) : n; }
+};
+
 // Running statistics for the training objectives (Section 3.3) of one token: the head's
 // logits zs and the model's logits zt of the same vocabulary entries arrive together.
 // Base-2 domain as above: ms = max zs*log2e, Ss = sum 2^(ts - ms), mt/St the same for the

@@ -531,79 +531,190 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
 // 32-row tiles (no matrix instruction is spent on a half tile: the compute-bound shapes);
 // gran = 1 hands out 16-row tiles, which halves the imbalance between workgroups (the
 // bandwidth-bound shapes, where a workgroup's time is its bytes).
-__device__ __forceinline__ void vocab_slice(int VT16, int gran, int& t0, int& t1) {
+__device__ __forceinline__ void vocab_slice(int VT16, int gran, int part, int parts, int& t0, int& t1) {
   const int units = (VT16 + gran - 1) / gran;
-  t0 = gran * (int)((long long)units * blockIdx.x / gridDim.x);
-  t1 = min(VT16, gran * (int)((long long)units * (blockIdx.x + 1) / gridDim.x));
+  t0 = gran * (int)((long long)units * part / parts);
+  t1 = min(VT16, gran * (int)((long long)units * (part + 1) / parts));
+}
+// 32-row tiles per pass of what is left of a slice: passes of at most kMaxMT tiles of about equal size.
+__device__ __forceinline__ int pass_tiles(int tiles16) {
+  const int left = (tiles16 + 1) >> 1;
+  if (left <= 0) return 0;
+  const int passes = (left + kMaxMT - 1) / kMaxMT;
+  return (left + passes - 1) / passes;
 }
 
-// grid.x = workgroups over the vocabulary, grid.y = groups of 4*NB blocks of 32 tokens,
-// grid.z = heads (Wf_tab, if given, holds the weights of head blockIdx.z; activations and
-// outputs of consecutive heads lie y_stride fragments / part_stride records apart): the heads
-// of one launch are independent, so a workgroup of the next head starts wherever one of this
-// head has finished and the imbalance between workgroups does not idle the chip per head.
-template <int NB, bool ARGMAX_ONLY, bool TOP2>
+// A pass for a wave that owns no live token block: it still has to bring its share of the
+// weights into the ring and keep every barrier of pass32<MT, ...> (one when the pass opens, one
+// behind the prologue, one per k-step), but issues nothing else.  Its loads are the DMA pieces
+// only, in pass32's order: at the wait that opens step ks the pieces of steps ks+2 .. ks+D may
+// still be in flight.
+template <int MT, typename BT = NothingBetween>
+__device__ __forceinline__ void pass32_idle(const frag_t* __restrict__ Wf, int T16, int t16_end, int KS, int lane,
+                                            int wave, EH_LDS char* lds, BT between = BT()) {
+  constexpr int kDma = dma_per_wave(MT);
+  constexpr int NF = 2 * MT;
+  const int lastk = KS - 1;
+  const uint32_t lane16 = (uint32_t)lane << 4;
+  const EH_GLOBAL char* wbase = uniform_ptr(Wf);
+  long long wsrc[kDma];
+  int wdst[kDma];
+#pragma unroll
+  for (int i = 0; i < kDma; ++i) {
+    int f = wave + kG32Waves * i;
+    if (f >= NF) f = (wave < NF) ? wave + kG32Waves * ((NF - 1 - wave) / kG32Waves) : NF - 1;
+    const int t16 = min(T16 + f, t16_end - 1);
+    wsrc[i] = ((long long)t16 * KS) << 10;
+    wdst[i] = f * 1024;
+  }
+  auto dma = [&](int ks) {
+    const int k = min(ks, lastk);
+    EH_LDS char* slot = lds + (ks & (kSlots - 1)) * kSlotBytes;
+#pragma unroll
+    for (int i = 0; i < kDma; ++i)
+      __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + wsrc[i] + ((long long)k << 10) + lane16),
+                                       (EH_LDS void*)(slot + wdst[i]), 16, 0, 0);
+  };
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  dma(0);
+#pragma unroll
+  for (int j = 0; j < kDepth; ++j) dma(j + 1);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kDepth * kDma) : "memory");
+  for (int ks = 0; ks < KS; ++ks) {
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kDepth - 1) * kDma) : "memory");
+    dma(ks + kDepth + 1);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  between();
+}
+
+// The weights of the first kDepth + 1 k-steps of a pass, asked for ahead of time by this wave's DMA
+// share (the pass will fetch them again: what this buys is that they then come from the L2 and
+// not from HBM, and that the memory system has work while the waves compute).  They land in ring
+// slots, which nobody uses for them; the one slot that another wave of the workgroup may still
+// be reading when this is called right behind a k loop -- the operands of that loop's last step,
+// slot (KS - 1) mod 8 -- is left alone.  Waited for by the vmcnt(0) that opens the next pass at
+// the latest.
+__device__ __forceinline__ void ring_prefetch(const frag_t* __restrict__ Wf, int T16, int t16_end, int mt, int KS, int lane,
+                                              int wave, EH_LDS char* lds) {
+  constexpr int kAhead = kDepth + 1;  // k-steps asked for (seven were slower than four)
+  static_assert(kAhead <= kSlots, "one slot per k-step");
+  const int lastk = KS - 1;
+  const int busy = lastk & (kSlots - 1);
+  const uint32_t lane16 = (uint32_t)lane << 4;
+  const EH_GLOBAL char* wbase = uniform_ptr(Wf);
+#pragma unroll
+  for (int ks = 0; ks < kAhead; ++ks) {
+    if (ks == busy) continue;  // uniform
+    const int k = min(ks, lastk);
+    for (int f = wave; f < 2 * mt; f += kG32Waves) {
+      const int t16 = min(T16 + f, t16_end - 1);
+      __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + ((((long long)t16 * KS) + k) << 10) + lane16),
+                                       (EH_LDS void*)(lds + ks * kSlotBytes + f * 1024), 16, 0, 0);
+    }
+  }
+}
+
+// How the workgroups of a launch share n_live rows: groups of at most 8 blocks of 32 rows (two per
+// wave), as equal as they go, each with the same number of workgroups over the vocabulary.  The
+// live count may only be known on the device (a cascade), so the kernel works this out itself.
+struct G32Deal {
+  int groups, parts;      // token groups; workgroups over the vocabulary in each
+  int part, first, count; // this workgroup: its share of the vocabulary, its group's blocks
+  __device__ __forceinline__ G32Deal(int n_live, int grid, int max_parts, int wg) {
+    const int blocks = (n_live + 31) >> 5;
+    groups = (blocks + 2 * kG32Waves - 1) / (2 * kG32Waves);
+    parts = gemm32_parts(n_live, grid, max_parts);
+    const int y = groups > 0 ? wg / parts : 0;
+    part = wg - y * parts;
+    first = groups > 0 ? blocks * y / groups : 0;
+    count = y < groups ? blocks * (y + 1) / groups - first : 0;
+  }
+};
+
+// One launch covers n_heads consecutive heads (weights from the table; activations and outputs of
+// consecutive heads lie y_stride fragments / part_stride records apart): a workgroup walks its slice
+// of every head, and behind the last k loop of a pass, while the statistics are worked out, the next
+// pass's (or head's) first weights are asked for, so that the memory system does not idle.
+template <bool ARGMAX_ONLY, bool TOP2>
 __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
-    const frag_t* __restrict__ Wf, const frag_t* const* __restrict__ Wf_tab, const frag_t* __restrict__ yq,
-    long long y_stride, int VT16, int KS, int V, int gran, const int* __restrict__ n_rows_dev, int n_rows,
-    int R_pad, Stats* __restrict__ partials, float* __restrict__ second, long long part_stride) {
-  if (Wf_tab) Wf = Wf_tab[blockIdx.z];
-  yq += (long long)blockIdx.z * y_stride;
-  partials += (long long)blockIdx.z * part_stride;
-  if (TOP2) second += (long long)blockIdx.z * part_stride;
+    const frag_t* const* __restrict__ Wf_tab, int n_heads, const frag_t* __restrict__ yq, long long y_stride, int VT16, int KS,
+    int V, const int* __restrict__ n_rows_dev, int n_rows, int max_parts, int R_pad, Stats* __restrict__ partials,
+    float* __restrict__ second, long long part_stride) {
   extern __shared__ __attribute__((aligned(16))) char g32_smem[];
   EH_LDS char* lds = (EH_LDS char*)g32_smem;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int n_live = n_rows;
   if (n_rows_dev) n_live = min(max(*n_rows_dev, 0), n_rows);
-  const int live_blocks = (n_live + 31) >> 5;
-  // the whole workgroup leaves if its token group is empty (the waves share
-  // barriers, so a single wave must not leave on its own; waves beyond the live
-  // rows compute on zero or stale activation fragments and write nothing)
-  if (live_blocks - (int)(blockIdx.y * kG32Waves * NB) <= 0) return;
-  const int nb_first = (blockIdx.y * kG32Waves + wave) * NB;  // my first token block
-  const int nb_live = min(NB, live_blocks - nb_first);
-  int T0, T1;
-  vocab_slice(VT16, gran, T0, T1);
-  const int row_hi = min(V, T1 * 16);
-  Stats st[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) stats_init(st[n]);
+  const G32Deal deal(n_live, gridDim.x, max_parts, blockIdx.x);
+  // the whole workgroup leaves if there is nothing for it (the waves share barriers, so a single
+  // wave must not leave on its own; a wave without a block keeps the others company)
+  if (deal.count <= 0) return;
+  const int nb_live = deal.count / kG32Waves + (wave < deal.count % kG32Waves ? 1 : 0);
+  const int nb_first = deal.first + wave * (deal.count / kG32Waves) + min(wave, deal.count % kG32Waves);
+  // one token group of at most 5 blocks streams the weights once and is paced by that stream:
+  // balance the bytes (16-row tiles); otherwise balance the matrix instructions (32-row tiles).
+  // Slices differ by a tile (12 or 13 of 32 rows at 512 rows); from head to head they move on by
+  // one workgroup, so that none of them has the longer one every time.
+  const int gran = deal.groups == 1 && deal.count <= 5 ? 1 : 2;
+  auto slice_of = [&](int l) { return (deal.part + l) % deal.parts; };
   EH_LDS float* top2 = (EH_LDS float*)(lds + g32_ring_bytes()) + threadIdx.x * 4;
-  if constexpr (TOP2) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) top2[i] = -INFINITY;
-  }
-  const frag_t* ybase = yq + (long long)nb_first * 2 * KS * kWave;
-  for (int t = T0; t < T1;) {
-    const int left = (T1 - t + 1) >> 1;  // 32-row tiles, the last one possibly half
-    // split what is left into passes of at most kMaxMT tiles of about equal size
-    const int passes = (left + kMaxMT - 1) / kMaxMT;
-    const int mt = (left + passes - 1) / passes;
-    switch (mt) {
-      case 7: pass32<7, NB, ARGMAX_ONLY, TOP2>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st); break;
-      case 6: pass32<6, NB, ARGMAX_ONLY, TOP2>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st); break;
-      case 5: pass32<5, NB, ARGMAX_ONLY, TOP2>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st); break;
-      case 4: pass32<4, NB, ARGMAX_ONLY, TOP2>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st); break;
-      case 3: pass32<3, NB, ARGMAX_ONLY, TOP2>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st); break;
-      case 2: pass32<2, NB, ARGMAX_ONLY, TOP2>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st); break;
-      default: pass32<1, NB, ARGMAX_ONLY, TOP2>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st); break;
-    }
-    t += 2 * mt;
-  }
-  // lanes l and l+32 hold the same token: fold the two row groups
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));
+  for (int l = 0; l < n_heads; ++l) {
+    const frag_t* Wf = Wf_tab[l];
+    const frag_t* ybase = yq + l * y_stride + (long long)nb_first * 2 * KS * kWave;
+    int T0, T1;
+    vocab_slice(VT16, gran, slice_of(l), deal.parts, T0, T1);
+    const int row_hi = min(V, T1 * 16);
+    Stats st[2];
+    stats_init(st[0]);
+    stats_init(st[1]);
     if constexpr (TOP2) {
-      const float a1 = top2[2 * n], a2 = top2[2 * n + 1];
-      const float o1 = __shfl_xor(a1, 32), o2 = __shfl_xor(a2, 32);
-      const float u2 = fmaxf(fminf(a1, o1), fmaxf(a2, o2));  // second largest of the union
-      if (lane < 32 && n < nb_live) second[(long long)blockIdx.x * R_pad + (nb_first + n) * 32 + lane] = u2;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) top2[i] = -INFINITY;
     }
-    if (lane < 32 && n < nb_live)
-      partials[(long long)blockIdx.x * R_pad + (nb_first + n) * 32 + lane] = st[n];
+    for (int t = T0; t < T1;) {
+      const int mt = pass_tiles(T1 - t);
+      auto next = [&]() {
+        const int tn = t + 2 * mt;
+        if (tn < T1) {
+          ring_prefetch(Wf, tn, T1, pass_tiles(T1 - tn), KS, lane, wave, lds);
+        } else if (l + 1 < n_heads) {
+          int n0, n1;
+          vocab_slice(VT16, gran, slice_of(l + 1), deal.parts, n0, n1);
+          if (n0 < n1) ring_prefetch(Wf_tab[l + 1], n0, n1, pass_tiles(n1 - n0), KS, lane, wave, lds);
+        }
+      };
+#define EH_G32_PASS(MT_)                                                                                              \
+  if (nb_live <= 0) pass32_idle<MT_>(Wf, t, T1, KS, lane, wave, lds, next);                                           \
+  else if (nb_live == 1) pass32<MT_, 1, ARGMAX_ONLY, TOP2, false, Stats>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, \
+                                                        reinterpret_cast<Stats(&)[1]>(st[0]), 0, nullptr, next);        \
+  else pass32<MT_, 2, ARGMAX_ONLY, TOP2, false, Stats>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st, 0, nullptr, next)
+      switch (mt) {
+        case 7: EH_G32_PASS(7); break;
+        case 6: EH_G32_PASS(6); break;
+        case 5: EH_G32_PASS(5); break;
+        case 4: EH_G32_PASS(4); break;
+        case 3: EH_G32_PASS(3); break;
+        case 2: EH_G32_PASS(2); break;
+        default: EH_G32_PASS(1); break;
+      }
+#undef EH_G32_PASS
+      t += 2 * mt;
+    }
+    // lanes l and l+32 hold the same token: fold the two row groups
+    const long long at = l * part_stride + (long long)slice_of(l) * R_pad;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));
+      if constexpr (TOP2) {
+        const float a1 = top2[2 * n], a2 = top2[2 * n + 1];
+        const float o1 = __shfl_xor(a1, 32), o2 = __shfl_xor(a2, 32);
+        const float u2 = fmaxf(fminf(a1, o1), fmaxf(a2, o2));  // second largest of the union
+        if (lane < 32 && n < nb_live) second[at + (nb_first + n) * 32 + lane] = u2;
+      }
+      if (lane < 32 && n < nb_live) partials[at + (nb_first + n) * 32 + lane] = st[n];
+    }
   }
 }
 
@@ -624,7 +735,7 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_kl_kernel(
   const int nb_first = (blockIdx.y * kG32Waves + wave) * NBH;
   const int nb_live = min(NBH, live_blocks - nb_first);
   int T0, T1;
-  vocab_slice(VT16, 2, T0, T1);
+  vocab_slice(VT16, 2, blockIdx.x, gridDim.x, T0, T1);
   const int row_hi = min(V, T1 * 16);
   KlStats st[NBH];
 #pragma unroll
@@ -830,83 +941,6 @@ struct RowMask {
   }
 };
 
-// A pass for a wave that owns no live token block: it still has to bring its share of the
-// weights into the ring and keep every barrier of pass32<MT, ...> (one when the pass opens, one
-// behind the prologue, one per k-step), but issues nothing else.  Its loads are the DMA pieces
-// only, in pass32's order: at the wait that opens step ks the pieces of steps ks+2 .. ks+D may
-// still be in flight.
-template <int MT, typename BT = NothingBetween>
-__device__ __forceinline__ void pass32_idle(const frag_t* __restrict__ Wf, int T16, int t16_end, int KS, int lane,
-                                            int wave, EH_LDS char* lds, BT between = BT()) {
-  constexpr int kDma = dma_per_wave(MT);
-  constexpr int NF = 2 * MT;
-  const int lastk = KS - 1;
-  const uint32_t lane16 = (uint32_t)lane << 4;
-  const EH_GLOBAL char* wbase = uniform_ptr(Wf);
-  long long wsrc[kDma];
-  int wdst[kDma];
-#pragma unroll
-  for (int i = 0; i < kDma; ++i) {
-    int f = wave + kG32Waves * i;
-    if (f >= NF) f = (wave < NF) ? wave + kG32Waves * ((NF - 1 - wave) / kG32Waves) : NF - 1;
-    const int t16 = min(T16 + f, t16_end - 1);
-    wsrc[i] = ((long long)t16 * KS) << 10;
-    wdst[i] = f * 1024;
-  }
-  auto dma = [&](int ks) {
-    const int k = min(ks, lastk);
-    EH_LDS char* slot = lds + (ks & (kSlots - 1)) * kSlotBytes;
-#pragma unroll
-    for (int i = 0; i < kDma; ++i)
-      __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + wsrc[i] + ((long long)k << 10) + lane16),
-                                       (EH_LDS void*)(slot + wdst[i]), 16, 0, 0);
-  };
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  dma(0);
-#pragma unroll
-  for (int j = 0; j < kDepth; ++j) dma(j + 1);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kDepth * kDma) : "memory");
-  for (int ks = 0; ks < KS; ++ks) {
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kDepth - 1) * kDma) : "memory");
-    dma(ks + kDepth + 1);
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  between();
-}
-
-// The weights of the first kDepth + 1 k-steps of a pass, asked for ahead of time by this wave's DMA
-// share (the pass will fetch them again: what this buys is that they then come from the L2 and
-// not from HBM, and that the memory system has work while the waves compute).  They land in ring
-// slots, which nobody uses for them; the one slot that another wave of the workgroup may still
-// be reading when this is called right behind a k loop -- the operands of that loop's last step,
-// slot (KS - 1) mod 8 -- is left alone.  Waited for by the vmcnt(0) that opens the next pass at
-// the latest.
-template <int MT>
-__device__ __forceinline__ void ring_prefetch(const frag_t* __restrict__ Wf, int T16, int t16_end, int KS, int lane,
-                                              int wave, EH_LDS char* lds) {
-  constexpr int kDma = dma_per_wave(MT);
-  constexpr int NF = 2 * MT;
-  constexpr int kAhead = kDepth + 1;  // k-steps asked for (seven were slower than four)
-  static_assert(kAhead <= kSlots, "one slot per k-step");
-  const int lastk = KS - 1;
-  const int busy = lastk & (kSlots - 1);
-  const uint32_t lane16 = (uint32_t)lane << 4;
-  const EH_GLOBAL char* wbase = uniform_ptr(Wf);
-#pragma unroll
-  for (int ks = 0; ks < kAhead; ++ks) {
-    if (ks == busy) continue;  // uniform
-    const int k = min(ks, lastk);
-#pragma unroll
-    for (int i = 0; i < kDma; ++i) {
-      int f = wave + kG32Waves * i;
-      if (f >= NF) f = (wave < NF) ? wave + kG32Waves * ((NF - 1 - wave) / kG32Waves) : NF - 1;
-      const int t16 = min(T16 + f, t16_end - 1);
-      __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + ((((long long)t16 * KS) + k) << 10) + lane16),
-                                       (EH_LDS void*)(lds + ks * kSlotBytes + f * 1024), 16, 0, 0);
-    }
-  }
-}
-
 // LayerNorm of one row by one wave into column `pos` of an activation buffer (32-row operand order).
 __device__ __forceinline__ void rows_layernorm(const RowsParams& p, int l, int r, frag_t* __restrict__ yl, int pos, int lane) {
   const char* row = (const char*)p.h + ((long long)l * p.layer_stride + (long long)r * p.row_stride) * DtBf16::ESZ;
@@ -1010,20 +1044,11 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
   const int T0 = (int)((long long)p.VT16 * g / p.n_stream);
   const int T1 = (int)((long long)p.VT16 * (g + 1) / p.n_stream);
   const int row_hi = min(p.V, T1 * 16);
-  const int mt_first = T0 < T1 ? (((T1 - T0 + 1) >> 1) + (((T1 - T0 + 1) >> 1) + kMaxMT - 1) / kMaxMT - 1) / ((((T1 - T0 + 1) >> 1) + kMaxMT - 1) / kMaxMT) : 0;
-  // tiles per pass of a head's first pass; its first weights are brought towards the L2 while
-  // something else is going on (here: the LayerNorm of the first head)
+  const int mt_first = pass_tiles(T1 - T0);
+  // a head's first weights are brought towards the L2 while something else is going on (here: the
+  // LayerNorm of the first head)
   auto warm = [&](const frag_t* Wn) {
-    switch (mt_first) {
-      case 7: ring_prefetch<7>(Wn, T0, T1, p.KS, lane, wave, lds); break;
-      case 6: ring_prefetch<6>(Wn, T0, T1, p.KS, lane, wave, lds); break;
-      case 5: ring_prefetch<5>(Wn, T0, T1, p.KS, lane, wave, lds); break;
-      case 4: ring_prefetch<4>(Wn, T0, T1, p.KS, lane, wave, lds); break;
-      case 3: ring_prefetch<3>(Wn, T0, T1, p.KS, lane, wave, lds); break;
-      case 2: ring_prefetch<2>(Wn, T0, T1, p.KS, lane, wave, lds); break;
-      case 1: ring_prefetch<1>(Wn, T0, T1, p.KS, lane, wave, lds); break;
-      default: break;
-    }
+    if (T0 < T1) ring_prefetch(Wn, T0, T1, mt_first, p.KS, lane, wave, lds);
   };
   EH_ROWS_STAMP(0);
   warm(p.Wf[p.l0]);
@@ -1045,9 +1070,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
     const frag_t* Wf = p.Wf[l];
     const frag_t* ybase = p.y + (long long)j * p.y_stride + (long long)nb_first * 2 * p.KS * kWave;
     for (int t = T0; t < T1;) {
-      const int left = (T1 - t + 1) >> 1;
-      const int passes = (left + kMaxMT - 1) / kMaxMT;
-      const int mt = (left + passes - 1) / passes;
+      const int mt = pass_tiles(T1 - t);
       // behind the head's last k loop, while its statistics are worked out and handed on: the
       // start of the next head's weights is asked for (towards the L2; the next pass fetches it
       // again from there), so that this workgroup's share of the memory system does not idle
@@ -1580,62 +1603,43 @@ void launch_kl(dim3 g, hipStream_t s, const frag_t* Wf, long long wdelta, const 
                      KS, V, n_rows, R_pad, labels, partials);
 }
 
-template <int NB, bool AO, bool TOP2>
-void launch32(dim3 g, hipStream_t s, const frag_t* Wf, const frag_t* const* Wf_tab, const frag_t* yq,
-              long long y_stride, int VT16, int KS, int V, int gran, const int* n_rows_dev, int n_rows, int R_pad,
-              Stats* partials, float* second, long long part_stride) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)gemm32_stats_kernel<NB, AO, TOP2>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)g32_lds_bytes());
-    attr_set = true;
-  }
-  hipLaunchKernelGGL((gemm32_stats_kernel<NB, AO, TOP2>), g, dim3(kG32Threads), g32_lds_bytes(), s, Wf, Wf_tab, yq,
-                     y_stride, VT16, KS, V, gran, n_rows_dev, n_rows, R_pad, partials, second, part_stride);
+template <bool AO, bool TOP2>
+hipError_t launch32(int grid, hipStream_t s, const frag_t* const* Wf_tab, int n_heads, const frag_t* yq, long long y_stride,
+                    int VT16, int KS, int V, const int* n_rows_dev, int n_rows, int max_parts, int R_pad, Stats* partials,
+                    float* second, long long part_stride) {
+  static const hipError_t attr = hipFuncSetAttribute((const void*)gemm32_stats_kernel<AO, TOP2>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)g32_lds_bytes());
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((gemm32_stats_kernel<AO, TOP2>), dim3(grid), dim3(kG32Threads), g32_lds_bytes(), s, Wf_tab, n_heads, yq,
+                     y_stride, VT16, KS, V, n_rows_dev, n_rows, max_parts, R_pad, partials, second, part_stride);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-// n_heads > 1: heads head .. head+n_heads-1 in one launch (grid.z), their activations y_stride
+// n_heads > 1: heads head .. head+n_heads-1 in one launch, their activations y_stride
 // fragments and their partials (and second largest logits) part_stride records apart.
-hipError_t gemm32_launch_heads(const eh_ctx* c, int head, int n_heads, const int* n_rows_dev, int n_rows,
-                               bool argmax_only, const frag_t* yf, long long y_stride, Stats* partials,
-                               float* second, long long part_stride, int* n_parts, hipStream_t s) {
+hipError_t gemm32_launch(const eh_ctx* c, int head, int n_heads, const int* n_rows_dev, int n_rows, bool argmax_only,
+                         const frag_t* yf, long long y_stride, Stats* partials, float* second, long long part_stride,
+                         PartCount* parts, hipStream_t s) {
   const int R_pad = (n_rows + 31) & ~31;
-  const int blocks = R_pad / 32;
-  const int nb = blocks <= kG32Waves ? 1 : 2;
-  const int groups = (blocks + kG32Waves * nb - 1) / (kG32Waves * nb);
   const int cus = c->num_cu > 0 ? c->num_cu : 256;
-  const int VT32 = (c->VT + 1) / 2;
-  const int gx = std::max(1, std::min(VT32, cus / groups));
-  dim3 g(gx, groups, n_heads);
-  *n_parts = gx;
-  // one token group of at most 5 blocks streams the weights once and is paced by that stream:
-  // balance the bytes (16-row tiles); otherwise balance the matrix instructions (32-row tiles)
-  const int gran = (groups == 1 && blocks <= 5) ? 1 : 2;
-  const frag_t* Wf = c->Wf[head];
-  const frag_t* const* tab = n_heads > 1 ? (const frag_t* const*)(c->d_Wf + head) : nullptr;
-#define EH_L32(NB_, AO_, T2_)                                                                              \
-  launch32<NB_, AO_, T2_>(g, s, Wf, tab, yf, y_stride, c->VT, c->KS, c->V, gran, n_rows_dev, n_rows, R_pad, \
-                          partials, second, part_stride)
+  // one workgroup per compute unit, or one per group of 256 rows if that is more
+  const int grid = std::max(cus, (R_pad / 32 + 2 * kG32Waves - 1) / (2 * kG32Waves));
+  // (as many partial statistics as there is room for, and no slice without a tile of its own)
+  const int max_parts = std::max(1, std::min({cus, 512, (c->VT + 1) / 2}));
+  *parts = PartCount{gemm32_parts(n_rows, grid, max_parts), n_rows_dev ? grid : 0, max_parts};
+  const frag_t* const* tab = (const frag_t* const*)(c->d_Wf + head);
+#define EH_L32(AO_, T2_)                                                                                               \
+  return launch32<AO_, T2_>(grid, s, tab, n_heads, yf, y_stride, c->VT, c->KS, c->V, n_rows_dev, n_rows, max_parts, R_pad, \
+                            partials, second, part_stride)
   if (second) {  // entropy statistics plus the second largest logit
     if (argmax_only) return hipErrorInvalidValue;
-    if (nb == 1) EH_L32(1, false, true);
-    else EH_L32(2, false, true);
-  } else if (nb == 1) {
-    if (argmax_only) EH_L32(1, true, false);
-    else EH_L32(1, false, false);
-  } else {
-    if (argmax_only) EH_L32(2, true, false);
-    else EH_L32(2, false, false);
+    EH_L32(false, true);
   }
+  if (argmax_only) EH_L32(true, false);
+  EH_L32(false, false);
 #undef EH_L32
-  return hipGetLastError();
-}
-
-hipError_t gemm32_launch(const eh_ctx* c, int head, const int* n_rows_dev, int n_rows, bool argmax_only,
-                         const frag_t* yf, Stats* partials, float* second, int* n_parts, hipStream_t s) {
-  return gemm32_launch_heads(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, second, 0, n_parts, s);
 }
 
 hipError_t rows_prepare(eh_ctx* c) {

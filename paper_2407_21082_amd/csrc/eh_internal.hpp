@@ -153,19 +153,15 @@ hipError_t decode_prepare(eh_ctx* ctx);
 // partials[*n_parts][n_rows rounded up to 16].  Heads with a bias vector are not supported.
 hipError_t gemm_launch(const eh_ctx* ctx, int head, const int* n_rows_dev, int n_rows, bool argmax_only,
                        const eh::frag_t* yf, eh::Stats* partials, int* n_parts, hipStream_t s);
-// Same for bf16 with blocks of 32 rows: yf must hold the rows in the 32 x 16 operand
-// order (ln_pack_kernel<DtBf16, 32>), partials are [*n_parts][n_rows rounded up to 32].
-// `second`: NULL, or [*n_parts][rows rounded up to 32] floats that receive, per workgroup and
+// Same for bf16 with blocks of 32 rows, n_heads consecutive heads in one launch: yf must hold the rows
+// in the 32 x 16 operand order (ln_pack_kernel<DtBf16, 32>), partials are [*parts][n_rows rounded up
+// to 32]; the activations of head l lie l * y_stride fragments behind yf, its partials (and
+// second largest logits) l * part_stride records behind partials (second).
+// `second`: NULL, or [*parts][rows rounded up to 32] floats that receive, per workgroup and
 // row, the second largest logit (counting multiplicity) of the workgroup's vocabulary slice.
-hipError_t gemm32_launch(const eh_ctx* ctx, int head, const int* n_rows_dev, int n_rows, bool argmax_only,
-                         const eh::frag_t* yf, eh::Stats* partials, float* second, int* n_parts,
-                         hipStream_t s);
-// Several consecutive heads in one launch (independent heads: eh_eval_heads): the activations
-// of head l lie l * y_stride fragments behind yf, its partials (and second largest logits)
-// l * part_stride records behind partials (second).
-hipError_t gemm32_launch_heads(const eh_ctx* ctx, int head, int n_heads, const int* n_rows_dev, int n_rows,
-                               bool argmax_only, const eh::frag_t* yf, long long y_stride, eh::Stats* partials,
-                               float* second, long long part_stride, int* n_parts, hipStream_t s);
+hipError_t gemm32_launch(const eh_ctx* ctx, int head, int n_heads, const int* n_rows_dev, int n_rows,
+                         bool argmax_only, const eh::frag_t* yf, long long y_stride, eh::Stats* partials,
+                         float* second, long long part_stride, PartCount* parts, hipStream_t s);
 // Projection + statistics of n_heads consecutive heads for a few rows (bf16 or fp32, with or without
 // bias vectors; groups of 64 rows): yf in the 32-row operand order, partials [*n_parts][n_rows rounded
 // up to 32] per head; `second` as below (bf16 only).

@@ -313,7 +313,7 @@ __device__ __forceinline__ void stats_finalize(const Stats& s, float& H, float& 
 
 // blockIdx.y = head (relative): partials advance by part_stride records per head,
 // outputs by out_stride elements (both 0 for a single head).
-static __global__ __launch_bounds__(64) void finalize_kernel(const Stats* __restrict__ partials, int n_parts,
+static __global__ __launch_bounds__(64) void finalize_kernel(const Stats* __restrict__ partials, PartCount part_count,
                                                       int R_pad, const int* __restrict__ n_rows_dev,
                                                       int n_rows, float* __restrict__ H,
                                                       float* __restrict__ lse, int* __restrict__ argmax,
@@ -322,6 +322,7 @@ static __global__ __launch_bounds__(64) void finalize_kernel(const Stats* __rest
   int n_live = n_rows;
   if (n_rows_dev) n_live = min(max(*n_rows_dev, 0), n_rows);
   if (p >= n_live) return;
+  const int n_parts = part_count.of(n_live);
   partials += (int64_t)blockIdx.y * part_stride;
   const int64_t o = (int64_t)blockIdx.y * out_stride + p;
   Stats s;
@@ -391,7 +392,7 @@ static __global__ __launch_bounds__(64) void finalize_metrics_kernel(
 // ---------------------------------------------------------------------------
 template <typename DT, int RB>
 __global__ __launch_bounds__(kLnThreads) void cascade_post_kernel(
-    const Stats* __restrict__ partials, int n_parts, int R_pad, const int* __restrict__ row_idx,
+    const Stats* __restrict__ partials, PartCount part_count, int R_pad, const int* __restrict__ row_idx,
     const int* __restrict__ n_rows_dev, int n_rows, float tau, int is_last, int head,
     int* __restrict__ exit_layer,
     int* __restrict__ token, float* __restrict__ H_out, unsigned long long* __restrict__ n_evals,
@@ -408,6 +409,7 @@ __global__ __launch_bounds__(kLnThreads) void cascade_post_kernel(
   if (p >= n_live) return;
   const int r = row_idx ? row_idx[p] : p;
   if (tid < kWave) {  // the first wave merges and decides, exactly as finalize_kernel does
+    const int n_parts = part_count.of(n_live);
     Stats s;
     stats_init(s);
     for (int g = lane; g < n_parts; g += kWave) s = stats_merge(s, partials[(int64_t)g * R_pad + p]);
