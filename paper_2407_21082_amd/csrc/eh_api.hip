@@ -147,7 +147,7 @@ eh_status run_head(eh_ctx* c, int head, const void* h, int64_t row_stride, const
   launch_ln(c, head, h, row_stride, row_idx, n_rows_dev, n_rows, R_pad, yf, s);
   PartCount parts;
   EH_HIP(c, project(c, head, n_rows_dev, n_rows, AO, yf, partials, &parts, s));
-  hipLaunchKernelGGL(finalize_kernel, dim3(n_rows), dim3(64), 0, s, partials, parts, R_pad,
+  hipLaunchKernelGGL(finalize_kernel, dim3((n_rows + kFinRows - 1) / kFinRows), dim3(kFinThreads), 0, s, partials, parts, R_pad,
                      n_rows_dev, n_rows, AO ? nullptr : H, AO ? nullptr : lse, argmax, (int64_t)0, (int64_t)0);
   EH_HIP(c, hipGetLastError());
   return EH_OK;
@@ -489,11 +489,11 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
     EH_HIP(ctx, gemm32_launch(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
                               ctx->mh_partials, second, (long long)part_stride, &parts, s));
   if (metrics)
-    hipLaunchKernelGGL(finalize_metrics_kernel, dim3(n_rows, n_heads_eval), dim3(64), 0, s, ctx->mh_partials,
+    hipLaunchKernelGGL(finalize_metrics_kernel, dim3((n_rows + kFinRows - 1) / kFinRows, n_heads_eval), dim3(kFinThreads), 0, s, ctx->mh_partials,
                        ctx->mh_second, parts.n, R_pad, n_rows, H, lse, argmax, max_prob, margin,
                        (int64_t)part_stride, (int64_t)n_rows);
   else
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_rows, n_heads_eval), dim3(64), 0, s, ctx->mh_partials, parts,
+    hipLaunchKernelGGL(finalize_kernel, dim3((n_rows + kFinRows - 1) / kFinRows, n_heads_eval), dim3(kFinThreads), 0, s, ctx->mh_partials, parts,
                        R_pad, (const int*)nullptr, n_rows, H, lse, argmax, (int64_t)part_stride,
                        (int64_t)n_rows);
   EH_HIP(ctx, hipGetLastError());

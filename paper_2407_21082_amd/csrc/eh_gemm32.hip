@@ -53,10 +53,12 @@ constexpr int kSlotBytes = 2 * kMaxMT * 1024;
 #define EH_G32_DEPTH 3
 #endif
 constexpr int kDepth = EH_G32_DEPTH;  // activation register sets = k-steps a load may take (<= 6: ring of 8)
-// the weight ring, then 16 bytes per thread: the two largest logits of its (at most 2) token blocks
-// between passes (registers are too scarce to keep them live across the k loop)
+// the weight ring, then 16 bytes per thread: the second largest logit of its (at most 2) token blocks
+// between passes (registers are too scarce to keep it live across the k loop); then, per token
+// block, the 16 logits of the tile that holds the thread's largest one ([block][4][thread] f32x4)
 __host__ __device__ constexpr size_t g32_ring_bytes() { return (size_t)kSlots * kSlotBytes; }
-__host__ __device__ constexpr size_t g32_lds_bytes() { return g32_ring_bytes() + kG32Threads * 16; }
+__host__ __device__ constexpr size_t g32_park_at() { return g32_ring_bytes() + kG32Threads * 16; }
+__host__ __device__ constexpr size_t g32_lds_bytes() { return g32_park_at() + (size_t)2 * 4 * kG32Threads * 16; }
 
 #define EH_LDS __attribute__((address_space(3)))
 #define EH_GLOBAL __attribute__((address_space(1)))
@@ -84,39 +86,57 @@ __device__ __forceinline__ f32x16 mma32(const frag_t& a, const frag_t& b, f32x16
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// The 16 logits a lane holds of one 32-row tile (accumulator register j = 4g+i: vocabulary row
-// rowbase + 8g + i, increasing in j), all inside the vocabulary, pushed at once.  A single wave
-// per SIMD cannot hide the latency of a dependent chain, so the work is laid out as wide,
-// independent instruction groups: one maximum over the 16 (the running statistics are rescaled
-// at most once, in a branch that is rarely taken after the first tiles), then 16 independent
-// exponentials, then short sums.
 __device__ __forceinline__ float max3(float a, float b, float c) {
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
+__device__ __forceinline__ EH_LDS f32x4* park_of(EH_LDS char* lds, int n) {
+  return (EH_LDS f32x4*)(lds + g32_park_at()) + n * 4 * kG32Threads + threadIdx.x;
+}
 
+// The 16 logits a lane holds of one 32-row tile (accumulator register j = 4g+i: vocabulary row
+// rowbase + 8g + i, increasing in j), all inside the vocabulary, pushed at once.
+//
+// A single wave per SIMD cannot hide the latency of a dependent chain, so the work is laid out as
+// wide, independent instruction groups: one maximum over the 16, then 16 independent exponentials,
+// then short sums.  Some lane of the wave meets a new maximum in nearly every tile, so what a new
+// maximum costs is paid nearly every time.  It is kept small: the sums' reference point s.m follows
+// only when it falls 2^8 behind (the result does not depend on it; stats_resolve puts it on the
+// maximum in the end), and the maximum's index inside the tile is not looked for but the tile's
+// logits are parked in LDS for stats_resolve (s.ib holds the tile's first row until then).
+// With the search and the rescaling in every new maximum a logit took 64 clocks of the wave, which
+// was 17 % of the kernel at d = 2048 and 26 % at d = 1024.
 template <bool ARGMAX_ONLY>
-__device__ __forceinline__ void stats_push16(Stats& s, const f32x16& z, int rowbase) {
+__device__ __forceinline__ void stats_push16(Stats& s, const f32x16& acc, int rowbase, EH_LDS f32x4* park) {
+  // out of the accumulators once, in the quads that may be parked
+  f32x4 q[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    q[g] = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    asm volatile("" : "+v"(q[g]));
+  }
+  float z[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) z[j] = q[j >> 2][j & 3];
   // eight three-way maxima (a NaN operand is ignored, as by fmaxf)
   const float zmax = max3(max3(max3(z[0], z[1], z[2]), max3(z[3], z[4], z[5]), z[15]),
                           max3(z[6], z[7], z[8]), max3(max3(z[9], z[10], z[11]), max3(z[12], z[13], z[14]), z[15]));
   if (zmax > s.zb) {
-    int j = 15;
 #pragma unroll
-    for (int i = 14; i >= 0; --i) j = (z[i] == zmax) ? i : j;  // lowest index attaining the maximum
-    if (!ARGMAX_ONLY) {
-      const float mn = zmax * kLog2e;
+    for (int g = 0; g < 4; ++g) park[g * kG32Threads] = q[g];
+    s.zb = zmax;
+    s.ib = rowbase;
+  }
+  if (!ARGMAX_ONLY) {
+    const float mn = zmax * kLog2e;
+    if (mn > s.m + 8.f) {
       const float dm = s.m - mn;
       const float sc = fast_exp2(dm);
       s.U = sc * (s.U + dm * s.S);
       s.S = sc * s.S;
       s.m = mn;
     }
-    s.zb = zmax;
-    s.ib = rowbase + (j >> 2) * 8 + (j & 3);
-  }
-  if (!ARGMAX_ONLY) {
     float t[16], e[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) t[i] = z[i] * kLog2e - s.m;
@@ -133,6 +153,69 @@ __device__ __forceinline__ void stats_push16(Stats& s, const f32x16& z, int rowb
     }
     s.S += (S4[0] + S4[1]) + (S4[2] + S4[3]);
     s.U += (U4[0] + U4[1]) + (U4[2] + U4[3]);
+  }
+}
+
+// The same for the last tile of a slice, rows from row_hi on masked; four logits at a time (it is
+// one tile of a dozen, and the registers are wanted elsewhere).
+template <bool ARGMAX_ONLY>
+__device__ __forceinline__ void stats_push16_ragged(Stats& s, const f32x16& z, int rowbase, int row_hi, EH_LDS f32x4* park) {
+  auto masked = [&](int j) { return rowbase + (j >> 2) * 8 + (j & 3) < row_hi ? z[j] : -INFINITY; };
+  float zmax = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) zmax = fmaxf(zmax, masked(j));
+  if (zmax > s.zb) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) park[g * kG32Threads] = f32x4{masked(4 * g), masked(4 * g + 1), masked(4 * g + 2), masked(4 * g + 3)};
+    s.zb = zmax;
+    s.ib = rowbase;
+  }
+  if (!ARGMAX_ONLY) {
+    const float mn = zmax * kLog2e;
+    if (mn > s.m + 8.f) {
+      const float dm = s.m - mn;
+      const float sc = fast_exp2(dm);
+      s.U = sc * (s.U + dm * s.S);
+      s.S = sc * s.S;
+      s.m = mn;
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (rowbase + 8 * g + i < row_hi) {
+          const float t = z[4 * g + i] * kLog2e - s.m;
+          const float e = fast_exp2(t);
+          s.S += e;
+          s.U += t * e;
+        }
+      }
+    }
+  }
+}
+
+// Behind a head's last pass: the index of the lane's largest logit, and the sums moved to it as
+// their reference point.
+template <bool ARGMAX_ONLY>
+__device__ __forceinline__ void stats_resolve(Stats& s, const EH_LDS f32x4* park) {
+  if (s.ib != 0x7fffffff) {  // at least one logit
+    int at = 0;
+#pragma unroll
+    for (int g = 3; g >= 0; --g) {
+      const f32x4 z = park[g * kG32Threads];
+#pragma unroll
+      for (int i = 3; i >= 0; --i) at = z[i] == s.zb ? 8 * g + i : at;  // lowest index attaining the maximum
+    }
+    s.ib += at;
+    if (!ARGMAX_ONLY) {
+      const float mn = s.zb * kLog2e;
+      const float dm = s.m - mn;
+      const float sc = fast_exp2(dm);
+      s.U = sc * (s.U + dm * s.S);
+      s.S = sc * s.S;
+      s.m = mn;
+    }
   }
 }
 
@@ -324,7 +407,6 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
     fetch_a_half(a[0], mc, std::integral_constant<int, 0>{}, ks);
     fetch_a_half(a[1], mc, std::integral_constant<int, 1>{}, ks);
   };
-  constexpr int kLdsInFlight = 2 * (MT - 1);
 
   frag_t a[MT][2];
   frag_t b[kDepth][NB][2];
@@ -351,54 +433,68 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
       asm volatile("" : "+v"(b[n][0]));
       asm volatile("" : "+v"(b[n][1]));
     }
-    static_for<MT>([&](auto mc) {
-      constexpr int m = decltype(mc)::value;
-      asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a[m][0]), "+v"(a[m][1]) : "n"(kLdsInFlight));
-      // a wave issues one instruction per four cycles, and up to seven fit behind a matrix
-      // instruction: each k half is re-read right behind the matrix instructions that used it,
-      // instead of everything queueing up behind the tile's last one
+    // Tiles go two (the last ones three) at a time, first half of the k-step for all of them and then
+    // the second: the two matrix instructions on one accumulator then lie at least four instructions
+    // apart, and none waits for the result of the one before.
+    constexpr int NG = MT < 2 ? 1 : MT / 2;
+    static_for<NG>([&](auto gc) {
+      constexpr int g = decltype(gc)::value;
+      constexpr int m0 = 2 * g;
+      constexpr int GS = g == NG - 1 ? MT - m0 : 2;  // tiles of this group
+      static_for<GS>([&](auto ic) {  // their operands have landed (younger reads: those of all other groups)
+        constexpr int m = m0 + decltype(ic)::value;
+        frag_t(&am)[2] = a[m];
+        asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(am[0]), "+v"(am[1]) : "n"(2 * (MT - GS)));
+      });
       static_for<2>([&](auto hc) {
         constexpr int h = decltype(hc)::value;
-#pragma unroll
-        for (int n = 0; n < NB; ++n) {
-          if (!DUAL || ((n < NH) == (m < MH))) {
-            const int j = DUAL ? (n < NH ? n : n - NH) : n;
-            acc[m][j] = mma32(a[m][h], b[n][h], acc[m][j]);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (m == 0 && h == 1) asm volatile("s_barrier" ::: "memory");
-        if constexpr (m != 0) fetch_a_half(a[m][h], mc, hc, ks + 1);
-        if constexpr (m == MT - 1) {  // the last use of this k half of the activations: reload it for step ks+D
+        static_for<GS>([&](auto ic) {
+          constexpr int m = m0 + decltype(ic)::value;
+          constexpr std::integral_constant<int, m> mc{};
+          // a wave issues one instruction per four cycles, and up to seven fit behind a matrix
+          // instruction: each k half is re-read right behind the matrix instructions that used it,
+          // instead of everything queueing up behind the tile's last one
 #pragma unroll
           for (int n = 0; n < NB; ++n) {
-            if constexpr (kAhead) load_b_half_pre(b[n][h], n, nx_b10, hc);
-            else load_b_half(b[n][h], n, ks + kDepth, hc);
-          }
-        }
-        if constexpr (h == 0) {
-          // DMA piece i travels with tile min(i, MT-1), behind its first matrix instructions
-          // (the slot it fills was last read several steps ago: no need to be past the barrier)
-          static_for<kDma>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            if constexpr ((i < MT - 1 ? i : MT - 1) == m) {
-              if constexpr (kAhead) dma_part_pre(ic, nx_k10, nx_slot);
-              else dma_part(ic, ks + kDepth + 1);
+            if (!DUAL || ((n < NH) == (m < MH))) {
+              const int j = DUAL ? (n < NH ? n : n - NH) : n;
+              acc[m][j] = mma32(a[m][h], b[n][h], acc[m][j]);
             }
-          });
-          if constexpr (kAhead && m == kPre) {
-            nx_b10 = (long long)(2 * min(ks + kDepth, lastk)) << 10;
-            asm volatile("" : "+s"(nx_b10));
           }
           __builtin_amdgcn_sched_barrier(0);
-        } else if constexpr (kAhead && m == kPre) {
-          // this step's DMA pieces (tiles 0 .. kDma-1 <= kPre, first slot) are out: the next step's
-          nx_k10 = (long long)min(ks + kDepth + 2, lastk) << 10;
-          nx_slot = ((ks + kDepth + 2) & (kSlots - 1)) * kSlotBytes;
-          asm volatile("" : "+s"(nx_k10), "+s"(nx_slot));
-        }
+          if constexpr (g == 0 && h == 1 && m == m0) asm volatile("s_barrier" ::: "memory");
+          if constexpr (g != 0) fetch_a_half(a[m][h], mc, hc, ks + 1);
+          else if constexpr (h == 1) fetch_a(a[m], mc, ks + 1);  // slot ks+1 is complete only behind the barrier
+          if constexpr (m == MT - 1) {  // the last use of this k half of the activations: reload it for step ks+D
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+              if constexpr (kAhead) load_b_half_pre(b[n][h], n, nx_b10, hc);
+              else load_b_half(b[n][h], n, ks + kDepth, hc);
+            }
+          }
+          if constexpr (h == 0) {
+            // DMA piece i travels with tile min(i, MT-1), behind its first matrix instructions
+            // (the slot it fills was last read several steps ago: no need to be past the barrier)
+            static_for<kDma>([&](auto pc) {
+              constexpr int i = decltype(pc)::value;
+              if constexpr ((i < MT - 1 ? i : MT - 1) == m) {
+                if constexpr (kAhead) dma_part_pre(pc, nx_k10, nx_slot);
+                else dma_part(pc, ks + kDepth + 1);
+              }
+            });
+            if constexpr (kAhead && m == kPre) {
+              nx_b10 = (long long)(2 * min(ks + kDepth, lastk)) << 10;
+              asm volatile("" : "+s"(nx_b10));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          } else if constexpr (kAhead && m == kPre) {
+            // this step's DMA pieces (tiles 0 .. kDma-1 <= kPre, first slot) are out: the next step's
+            nx_k10 = (long long)min(ks + kDepth + 2, lastk) << 10;
+            nx_slot = ((ks + kDepth + 2) & (kSlots - 1)) * kSlotBytes;
+            asm volatile("" : "+s"(nx_k10), "+s"(nx_slot));
+          }
+        });
       });
-      if constexpr (m == 0) fetch_a(a[m], mc, ks + 1);  // slot ks+1 is complete only behind the barrier
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -474,55 +570,54 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
     }
     return;
   } else {
-  float z1[NB], z2[NB];
+  float z2[NB];
   EH_LDS float* top2 = (EH_LDS float*)(lds + g32_ring_bytes()) + threadIdx.x * 4;
   if constexpr (TOP2) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) { z1[n] = top2[2 * n]; z2[n] = top2[2 * n + 1]; }
+    for (int n = 0; n < NB; ++n) z2[n] = top2[n];
   }
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
-    // wave-uniform: only the vocabulary's last tile can be ragged
-    if (T16 * 16 + (m + 1) * 32 <= row_hi) {
+    const int row0 = T16 * 16 + m * 32;
+    // wave-uniform: only the slice's last tile can be ragged
+    if (row0 + 32 <= row_hi) {
 #pragma unroll
       for (int n = 0; n < NB; ++n) {
-        stats_push16<ARGMAX_ONLY>(st[n], acc[m][n], T16 * 16 + m * 32 + half * 4);
         if constexpr (TOP2) {
+          // the second largest of (largest so far >= second so far, another) is their median
+          float z1 = st[n].zb;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float zi = acc[m][n][i];
-            z2[n] = fmaxf(z2[n], fminf(zi, z1[n]));
-            z1[n] = fmaxf(z1[n], zi);
+          for (int j = 0; j < 16; ++j) {
+            z2[n] = __builtin_amdgcn_fmed3f(z1, z2[n], acc[m][n][j]);
+            z1 = fmaxf(z1, acc[m][n][j]);
           }
         }
+        stats_push16<ARGMAX_ONLY>(st[n], acc[m][n], row0 + half * 4, park_of(lds, n));
       }
       __builtin_amdgcn_sched_barrier(0);
       continue;
     }
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int row0 = T16 * 16 + m * 32 + g * 8 + half * 4;
+    for (int n = 0; n < NB; ++n) {
+      if constexpr (TOP2) {
+        float z1 = st[n].zb;
 #pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        const f32x4 z = {acc[m][n][4 * g], acc[m][n][4 * g + 1], acc[m][n][4 * g + 2], acc[m][n][4 * g + 3]};
-        stats_push4<ARGMAX_ONLY>(st[n], z, row0, row_hi);
-        if constexpr (TOP2) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float zi = (row0 + i < row_hi) ? z[i] : -INFINITY;
-            z2[n] = fmaxf(z2[n], fminf(zi, z1[n]));
-            z1[n] = fmaxf(z1[n], zi);
-          }
+        for (int j = 0; j < 16; ++j) {
+          const float zj = row0 + half * 4 + (j >> 2) * 8 + (j & 3) < row_hi ? acc[m][n][j] : -INFINITY;
+          z2[n] = __builtin_amdgcn_fmed3f(z1, z2[n], zj);
+          z1 = fmaxf(z1, zj);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      // keep the instruction scheduler from pulling all accumulators into
-      // vector registers at once (it would spill inside the k loop's tail)
+      stats_push16_ragged<ARGMAX_ONLY>(st[n], acc[m][n], row0 + half * 4, row_hi, park_of(lds, n));
+      // keep the instruction scheduler from pulling all accumulators into vector registers at once
+      // (it would spill inside the k loop's tail)
       __builtin_amdgcn_sched_barrier(0);
     }
   }
   if constexpr (TOP2) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) { top2[2 * n] = z1[n]; top2[2 * n + 1] = z2[n]; }
+    for (int n = 0; n < NB; ++n) top2[n] = z2[n];
   }
   }
 }
@@ -671,7 +766,7 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
     stats_init(st[1]);
     if constexpr (TOP2) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) top2[i] = -INFINITY;
+      for (int n = 0; n < 2; ++n) top2[n] = -INFINITY;
     }
     for (int t = T0; t < T1;) {
       const int mt = pass_tiles(T1 - t);
@@ -706,13 +801,14 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
     const long long at = l * part_stride + (long long)slice_of(l) * R_pad;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-      st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));
+      stats_resolve<ARGMAX_ONLY>(st[n], park_of(lds, n));
       if constexpr (TOP2) {
-        const float a1 = top2[2 * n], a2 = top2[2 * n + 1];
+        const float a1 = st[n].zb, a2 = top2[n];
         const float o1 = __shfl_xor(a1, 32), o2 = __shfl_xor(a2, 32);
         const float u2 = fmaxf(fminf(a1, o1), fmaxf(a2, o2));  // second largest of the union
         if (lane < 32 && n < nb_live) second[at + (nb_first + n) * 32 + lane] = u2;
       }
+      st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));
       if (lane < 32 && n < nb_live) partials[at + (nb_first + n) * 32 + lane] = st[n];
     }
   }
@@ -1099,6 +1195,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
     const long long part_at = (long long)(j & 1) * p.n_stream * p.R_pad + (long long)g * p.R_pad;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
+      stats_resolve<ARGMAX_ONLY>(st[n], park_of(lds, n));
       st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));  // lanes l and l+32 hold the same token
       if (lane < 32 && n < nb_live) {
         store_coherent(p.part4 + part_at + (nb_first + n) * 32 + lane, stats_head(st[n]));
