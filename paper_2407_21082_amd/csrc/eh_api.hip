@@ -134,6 +134,17 @@ hipError_t project(const eh_ctx* c, int head, const int* n_rows_dev, int n_rows,
   return gemm_launch(c, head, n_rows_dev, n_rows, argmax_only, yf, partials, &parts->n, s);
 }
 
+// Merge of the partial statistics of n_heads heads (part_stride records apart), outputs [n_heads][n_rows].
+void launch_finalize(const Stats* partials, PartCount parts, int R_pad, const int* n_rows_dev, int n_rows, int n_heads, float* H,
+                     float* lse, int* argmax, int64_t part_stride, hipStream_t s) {
+#define EH_FIN(FR)                                                                                                  \
+  hipLaunchKernelGGL((finalize_kernel<FR>), dim3((n_rows + FR - 1) / FR, n_heads), dim3(kFinThreads), 0, s, partials, \
+                     parts, R_pad, n_rows_dev, n_rows, H, lse, argmax, part_stride, (int64_t)n_rows)
+  if (fin_rows(n_rows) == 4) EH_FIN(4);
+  else EH_FIN(16);
+#undef EH_FIN
+}
+
 // LayerNorm + projection + statistics for one head; results to (H, lse, argmax).
 // yf / partials: the activation workspace and the per-workgroup partial statistics to use
 // (the context's own, or another buffer of at least the same layout for n_rows rows).
@@ -147,8 +158,7 @@ eh_status run_head(eh_ctx* c, int head, const void* h, int64_t row_stride, const
   launch_ln(c, head, h, row_stride, row_idx, n_rows_dev, n_rows, R_pad, yf, s);
   PartCount parts;
   EH_HIP(c, project(c, head, n_rows_dev, n_rows, AO, yf, partials, &parts, s));
-  hipLaunchKernelGGL(finalize_kernel, dim3((n_rows + kFinRows - 1) / kFinRows), dim3(kFinThreads), 0, s, partials, parts, R_pad,
-                     n_rows_dev, n_rows, AO ? nullptr : H, AO ? nullptr : lse, argmax, (int64_t)0, (int64_t)0);
+  launch_finalize(partials, parts, R_pad, n_rows_dev, n_rows, 1, AO ? nullptr : H, AO ? nullptr : lse, argmax, 0, s);
   EH_HIP(c, hipGetLastError());
   return EH_OK;
 }
@@ -488,14 +498,17 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
   else
     EH_HIP(ctx, gemm32_launch(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
                               ctx->mh_partials, second, (long long)part_stride, &parts, s));
-  if (metrics)
-    hipLaunchKernelGGL(finalize_metrics_kernel, dim3((n_rows + kFinRows - 1) / kFinRows, n_heads_eval), dim3(kFinThreads), 0, s, ctx->mh_partials,
-                       ctx->mh_second, parts.n, R_pad, n_rows, H, lse, argmax, max_prob, margin,
-                       (int64_t)part_stride, (int64_t)n_rows);
-  else
-    hipLaunchKernelGGL(finalize_kernel, dim3((n_rows + kFinRows - 1) / kFinRows, n_heads_eval), dim3(kFinThreads), 0, s, ctx->mh_partials, parts,
-                       R_pad, (const int*)nullptr, n_rows, H, lse, argmax, (int64_t)part_stride,
-                       (int64_t)n_rows);
+  if (metrics) {
+#define EH_FINM(FR)                                                                                                      \
+  hipLaunchKernelGGL((finalize_metrics_kernel<FR>), dim3((n_rows + FR - 1) / FR, n_heads_eval), dim3(kFinThreads), 0, s, \
+                     ctx->mh_partials, ctx->mh_second, parts.n, R_pad, n_rows, H, lse, argmax, max_prob, margin,         \
+                     (int64_t)part_stride, (int64_t)n_rows)
+    if (fin_rows(n_rows) == 4) EH_FINM(4);
+    else EH_FINM(16);
+#undef EH_FINM
+  } else {
+    launch_finalize(ctx->mh_partials, parts, R_pad, nullptr, n_rows, n_heads_eval, H, lse, argmax, (int64_t)part_stride, s);
+  }
   EH_HIP(ctx, hipGetLastError());
   return EH_OK;
 }

@@ -310,20 +310,21 @@ __device__ __forceinline__ void stats_finalize(const Stats& s, float& H, float& 
   lse = (float)(kLn2d * ((double)s.m + l2));
 }
 
-// A workgroup merges the partial statistics of 16 rows: thread (row t%16, lane t/16 of 16) takes the
-// records t/16, t/16 + 16, ... of its row, so that neighbouring threads read neighbouring records (one
-// wave per row read 20 bytes of every line it fetched: 62 us for 24 heads x 512 rows x 128
-// records).  TOP2: the second largest logit as well (with multiplicity; second of a union =
-// max(min(z1a, z1b), max(z2a, z2b))).  The result is valid for threads t < 16.
-constexpr int kFinRows = 16;
+// A workgroup merges the partial statistics of FR rows: thread t takes the records t/FR, t/FR + 256/FR,
+// ... of row t%FR, so that neighbouring threads read neighbouring records (one wave per row read
+// 20 bytes of every line it fetched: 62 us for 24 heads x 512 rows x 128 records).  16 rows; 4 for
+// launches of at most 64 rows, whose few workgroups would otherwise take 16 records a thread one
+// batch after the other (33.6 against 31.7 us for a whole call on 48 rows).  TOP2: the second largest logit as well (with multiplicity; second of a union =
+// max(min(z1a, z1b), max(z2a, z2b))).  The result is valid for threads t < FR.
 constexpr int kFinThreads = 256;
-template <bool TOP2>
+inline int fin_rows(int n_rows) { return n_rows <= 64 ? 4 : 16; }
+template <bool TOP2, int FR>
 __device__ __forceinline__ Stats merge_partials(const Stats* __restrict__ partials, const float* __restrict__ second, int n_parts,
                                                 int R_pad, int row, float& z2) {
-  __shared__ Stats red[kFinThreads / kWave][kFinRows];
-  __shared__ float red2[kFinThreads / kWave][kFinRows];
-  constexpr int Q = kFinThreads / kFinRows;
-  const int tid = threadIdx.x, q = tid / kFinRows;
+  __shared__ Stats red[kFinThreads / kWave][FR];
+  __shared__ float red2[kFinThreads / kWave][FR];
+  constexpr int Q = kFinThreads / FR;
+  const int tid = threadIdx.x, q = tid / FR;
   Stats s;
   stats_init(s);
   z2 = -INFINITY;
@@ -345,16 +346,16 @@ __device__ __forceinline__ Stats merge_partials(const Stats* __restrict__ partia
       if (g0 + i * Q < n_parts) add(o[i], o2[i]);
   }
 #pragma unroll
-  for (int x = kFinRows; x < kWave; x <<= 1) {
+  for (int x = FR; x < kWave; x <<= 1) {
     const float p2 = TOP2 ? __shfl_xor(z2, x) : 0.f;
     add(stats_shfl_xor(s, x), p2);
   }
-  if ((tid & (kWave - 1)) < kFinRows) {
-    red[tid / kWave][tid & (kFinRows - 1)] = s;
-    if (TOP2) red2[tid / kWave][tid & (kFinRows - 1)] = z2;
+  if ((tid & (kWave - 1)) < FR) {
+    red[tid / kWave][tid & (FR - 1)] = s;
+    if (TOP2) red2[tid / kWave][tid & (FR - 1)] = z2;
   }
   __syncthreads();
-  if (tid < kFinRows) {
+  if (tid < FR) {
     s = red[0][tid];
     z2 = TOP2 ? red2[0][tid] : -INFINITY;
 #pragma unroll
@@ -363,21 +364,22 @@ __device__ __forceinline__ Stats merge_partials(const Stats* __restrict__ partia
   return s;
 }
 
-// blockIdx.x = group of 16 rows, blockIdx.y = head (relative): partials advance by part_stride
+// blockIdx.x = group of FR rows, blockIdx.y = head (relative): partials advance by part_stride
 // records per head, outputs by out_stride elements (both 0 for a single head).
-static __global__ __launch_bounds__(kFinThreads) void finalize_kernel(const Stats* __restrict__ partials, PartCount part_count,
+template <int FR>
+__global__ __launch_bounds__(kFinThreads) void finalize_kernel(const Stats* __restrict__ partials, PartCount part_count,
                                                       int R_pad, const int* __restrict__ n_rows_dev,
                                                       int n_rows, float* __restrict__ H,
                                                       float* __restrict__ lse, int* __restrict__ argmax,
                                                       int64_t part_stride, int64_t out_stride) {
-  const int p = blockIdx.x * kFinRows + (threadIdx.x & (kFinRows - 1));
+  const int p = blockIdx.x * FR + (threadIdx.x & (FR - 1));
   int n_live = n_rows;
   if (n_rows_dev) n_live = min(max(*n_rows_dev, 0), n_rows);
-  if ((int)blockIdx.x * kFinRows >= n_live) return;
+  if ((int)blockIdx.x * FR >= n_live) return;
   float z2;
-  const Stats s = merge_partials<false>(partials + (int64_t)blockIdx.y * part_stride, nullptr, part_count.of(n_live), R_pad,
+  const Stats s = merge_partials<false, FR>(partials + (int64_t)blockIdx.y * part_stride, nullptr, part_count.of(n_live), R_pad,
                                         min(p, n_live - 1), z2);
-  if (threadIdx.x < kFinRows && p < n_live) {
+  if (threadIdx.x < FR && p < n_live) {
     const int64_t o = (int64_t)blockIdx.y * out_stride + p;
     float h, l;
     stats_finalize(s, h, l);
@@ -390,16 +392,17 @@ static __global__ __launch_bounds__(kFinThreads) void finalize_kernel(const Stat
 // Final merge with the other two confidence metrics of Section 3.4.1:
 //   max_prob = p(argmax) = 1 / S        (S sums 2^(t - m) with m the largest t: its own term is 1)
 //   margin   = p1 - p2 = (1 - e^(z2 - z1)) / S.
-static __global__ __launch_bounds__(kFinThreads) void finalize_metrics_kernel(
+template <int FR>
+__global__ __launch_bounds__(kFinThreads) void finalize_metrics_kernel(
     const Stats* __restrict__ partials, const float* __restrict__ second, int n_parts, int R_pad, int n_rows,
     float* __restrict__ H, float* __restrict__ lse, int* __restrict__ argmax, float* __restrict__ max_prob,
     float* __restrict__ margin, int64_t part_stride, int64_t out_stride) {
-  const int p = blockIdx.x * kFinRows + (threadIdx.x & (kFinRows - 1));
-  if ((int)blockIdx.x * kFinRows >= n_rows) return;
+  const int p = blockIdx.x * FR + (threadIdx.x & (FR - 1));
+  if ((int)blockIdx.x * FR >= n_rows) return;
   float z2;
-  const Stats s = merge_partials<true>(partials + (int64_t)blockIdx.y * part_stride, second + (int64_t)blockIdx.y * part_stride,
+  const Stats s = merge_partials<true, FR>(partials + (int64_t)blockIdx.y * part_stride, second + (int64_t)blockIdx.y * part_stride,
                                        n_parts, R_pad, min(p, n_rows - 1), z2);
-  if (threadIdx.x < kFinRows && p < n_rows) {
+  if (threadIdx.x < FR && p < n_rows) {
     const int64_t o = (int64_t)blockIdx.y * out_stride + p;
     float h, l;
     stats_finalize(s, h, l);
@@ -413,7 +416,7 @@ static __global__ __launch_bounds__(kFinThreads) void finalize_metrics_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Cascade step behind a head's projection (Sections 3.4.1, 3.4.2), one wave per
+// Cascade step behind a head's projection (Sections 3.4.1, 3.4.2), one workgroup per
 // position p of the head's active list: merge the partial statistics of the row,
 // apply the exit rule, and for a row that goes on append it to the next head's
 // active list and write its LayerNorm for the next head straight into the
@@ -434,6 +437,7 @@ __global__ __launch_bounds__(kLnThreads) void cascade_post_kernel(
     const float* __restrict__ gamma_next, const float* __restrict__ beta_next, float eps,
     frag_t* __restrict__ yf) {
   __shared__ double red[2 * kLnWaves];
+  __shared__ Stats wave_stats[kLnWaves];
   __shared__ int pos_s;
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
   if (p == 0 && tid == 0 && clear) *clear = 0;  // the counter of the head after next
@@ -441,34 +445,54 @@ __global__ __launch_bounds__(kLnThreads) void cascade_post_kernel(
   if (n_rows_dev) n_live = min(max(*n_rows_dev, 0), n_rows);
   if (p >= n_live) return;
   const int r = row_idx ? row_idx[p] : p;
-  if (tid < kWave) {  // the first wave merges and decides
-    const int n_parts = part_count.of(n_live);
-    Stats s;
-    stats_init(s);
-    for (int g = lane; g < n_parts; g += kWave) s = stats_merge(s, partials[(int64_t)g * R_pad + p]);
+  const int n_parts = part_count.of(n_live);
+  // Everything the workgroup needs from memory is asked for at once: a record per thread, and the
+  // row, whose LayerNorm does not depend on the decision (only whether and where it goes does).  One
+  // trip to memory after the other the step took 8 to 11 us a head.
+  Stats s;
+  stats_init(s);
+  if (tid < n_parts) s = partials[(int64_t)tid * R_pad + p];
+  constexpr int kKeep = kLnCache / kLnWaves;
+  frag_t keep[kKeep];
+  const void* row = (const char*)h_next + (int64_t)r * row_stride * DT::ESZ;
+  const bool ahead = !is_last && KS * 4 <= kLnCache * kWave;
+  if (ahead)
+    group_layernorm_cached<DT, kLnWaves>(row, d, KS * 4, gamma_next, beta_next, eps, tid, red,
+                                         [&](int c, const frag_t& v) { keep[(c - tid) / kLnThreads] = v; });
+  for (int g = tid + kLnThreads; g < n_parts; g += kLnThreads) s = stats_merge(s, partials[(int64_t)g * R_pad + p]);
 #pragma unroll
-    for (int x = 32; x > 0; x >>= 1) s = stats_merge(s, stats_shfl_xor(s, x));
-    if (lane == 0) {
-      int pos = -1;
-      float H, l;
-      stats_finalize(s, H, l);
-      if (H_out) H_out[r] = H;
-      if (n_evals) atomicAdd(n_evals, 1ull);
-      if (is_last || H < tau) {  // NaN never passes the test
-        exit_layer[r] = head;
-        token[r] = stats_token(s);
-      } else {
-        pos = atomicAdd(n_active_next, 1);
-        active_next[pos] = r;
-      }
-      pos_s = pos;
+  for (int x = 32; x > 0; x >>= 1) s = stats_merge(s, stats_shfl_xor(s, x));
+  if (lane == 0) wave_stats[tid >> 6] = s;
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int w = 1; w < kLnWaves; ++w) s = stats_merge(s, wave_stats[w]);
+    int pos = -1;
+    float H, l;
+    stats_finalize(s, H, l);
+    if (H_out) H_out[r] = H;
+    if (n_evals) atomicAdd(n_evals, 1ull);
+    if (is_last || H < tau) {  // NaN never passes the test
+      exit_layer[r] = head;
+      token[r] = stats_token(s);
+    } else {
+      pos = atomicAdd(n_active_next, 1);
+      active_next[pos] = r;
     }
+    pos_s = pos;
   }
   __syncthreads();
   const int pos = pos_s;
   if (pos < 0) return;
-  ln_write_row<DT, RB>((const char*)h_next + (int64_t)r * row_stride * DT::ESZ, d, KS, gamma_next, beta_next,
-                       eps, yf, pos, tid, red);
+  if (ahead) {
+#pragma unroll
+    for (int j = 0; j < kKeep; ++j) {
+      const int c = tid + j * kLnThreads;
+      if (c < KS * 4) put_chunk<RB>(yf, KS, pos, c, keep[j]);
+    }
+  } else {
+    ln_write_row<DT, RB>(row, d, KS, gamma_next, beta_next, eps, yf, pos, tid, red);
+  }
 }
 
 // ---------------------------------------------------------------------------
