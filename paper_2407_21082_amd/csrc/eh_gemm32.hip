@@ -30,10 +30,11 @@
 //  * at the end of a pass the accumulator tiles are folded into per-lane running
 //    statistics (one exponential per logit); logits are never stored.
 //
-// Measured on this shape the loop is bound by the rate the matrix cores sustain
-// on real (toggling) data, not by memory: removing all loads from the loop does
-// not shorten it, and the vendor GEMM library reaches the same rate without the
-// statistics.
+// Measured at 512 rows of d = 2048 (clock stamps of one workgroup): a k-step of 6 tiles takes 875 clocks
+// of which 768 are matrix instructions, at 1.6 to 1.8 GHz; with the weights read from one place
+// instead of streamed the same loop runs at 2.05 GHz, so what bounds it is the power the chip has
+// for matrix cores and memory together.  The statistics of a pass are next (12 k clocks of 72 k
+// before they parked new maxima).  24 heads: 2460 -> 2381 us.
 #include "eh_internal.hpp"
 #include "eh_kernels.hpp"
 #include "eh_ksplit.hpp"
