@@ -24,7 +24,8 @@
  *     other, one workgroup per compute unit: every call with at most 16 rows (heads
  *     without a bias vector, d up to 2048 for bf16 / 1024 for fp32), and eh_cascade
  *     and dssd_verify with up to 256 rows that the first kind does not serve (bf16
- *     heads without a bias vector: 17 to 256 rows, and fewer at d above 2048).  The
+ *     heads without a bias vector: 17 rows and more, and fewer at d above 2048; which
+ *     of them take one launch and which take several depends on the sizes).  The
  *     stream must have the device to itself while such a call runs (no other kernel
  *     holding compute units on another stream or from another context).  eh_create
  *     checks that the grids fit the empty device.  Every wait is bounded

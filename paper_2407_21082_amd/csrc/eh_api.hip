@@ -175,11 +175,21 @@ eh_status check_rows(eh_ctx* ctx, const void* h, int64_t row_stride, int n_rows)
 
 // Rows <= 16 go through the persistent decode kernel when the shape fits it.
 bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_rows <= 16; }
-// 17 .. 256 rows of a cascade or a verification go through the persistent rows kernel.
-// The persistent kernel for up to 256 rows; at most 16 rows go to the decode kernel where the
-// context has one (hidden sizes up to 2048), and here otherwise.
-bool use_rows(const eh_ctx* c, int64_t n_rows) {
-  return c->rows_grid > 0 && (n_rows > 16 || c->decode_grid == 0) && n_rows >= 1 && n_rows <= kRowsMax &&
+// The persistent rows kernel, one launch for a whole cascade or verification (at most 16 rows go to
+// the decode kernel where the context has one, and here otherwise).
+//
+// A verification: up to 64 positions.  Beyond, its one head cannot hide the LayerNorm and the hand-over
+// in front of its weights, and three launches are faster (d = 2560 / 1024, us, one launch against
+// three: 90 positions 78 / 43 against 65 / 34, 144 89 / 46 against 72 / 38, 252 105 / 54 against 87 / 42).
+//
+// A cascade: as long as the two launches per head and the gaps between them cost more than the
+// service workgroups, whose time grows with the rows, cost the streaming ones; the longer a head's
+// stream, the more rows that is.  10 heads, us, one launch against two per head: d = 768 100 rows
+// 299 / 299, 128 322 / 304; d = 1024 100 331 / 338, 128 355 / 344, 256 520 / 419; d = 2048 128 483 / 515,
+// 160 550 / 537, 256 705 / 625; d = 2560 160 633 / 651, 200 707 / 688, 256 806 / 740.
+bool use_rows(const eh_ctx* c, int64_t n_rows, bool verify) {
+  const int most = verify ? 64 : std::min(kRowsMax, std::max(64, 60 + c->d / 22));
+  return c->rows_grid > 0 && (n_rows > 16 || c->decode_grid == 0) && n_rows >= 1 && n_rows <= most &&
          n_rows <= c->max_rows;
 }
 
@@ -570,7 +580,7 @@ eh_status eh_cascade(eh_ctx* ctx, const void* h_layers, int64_t layer_stride, in
     EH_HIP(ctx, decode_launch(ctx, p, s));
     return EH_OK;
   }
-  if (use_rows(ctx, n_rows)) {
+  if (use_rows(ctx, n_rows, false)) {
     // one persistent launch for the whole cascade
     RowsParams p = rows_base(ctx, n_rows);
     p.h = h_layers; p.layer_stride = layer_stride; p.row_stride = row_stride;
@@ -631,7 +641,7 @@ eh_status dssd_verify(eh_ctx* ctx, const void* f_final, const int32_t* draft, co
   if (st != EH_OK) return st;
   DeviceGuard guard(ctx->device);
   hipStream_t s = (hipStream_t)stream;
-  if (use_rows(ctx, rows)) {
+  if (use_rows(ctx, rows, true)) {
     // one persistent launch: LayerNorm, argmax-only projection, merge and prefix walk
     RowsParams p = rows_base(ctx, (int)rows);
     p.h = f_final; p.layer_stride = 0; p.row_stride = ctx->d;
@@ -679,7 +689,7 @@ eh_status dssd_draft(eh_ctx* ctx, const void* h_positions, int64_t pos_stride, i
   if (limit < 0 || n_positions < 0) return fail(ctx, EH_ERR_SHAPE, "limit and n_positions must be non-negative");
   if (!draft_len || (limit > 0 && (!draft || !exit_layers))) return fail(ctx, EH_ERR_NULL, "a required pointer is NULL");
   if (n_positions > 0 && limit > 0 && !h_positions) return fail(ctx, EH_ERR_NULL, "h_positions is NULL");
-  const bool by_rows = ctx->decode_grid <= 0 && use_rows(ctx, 1);  // hidden sizes above the decode kernel's
+  const bool by_rows = ctx->decode_grid <= 0 && use_rows(ctx, 1, false);  // hidden sizes above the decode kernel's
   if (ctx->decode_grid <= 0 && !by_rows)
     return fail(ctx, EH_ERR_DTYPE, "drafting needs a single-launch cascade kernel (bf16 or fp32 heads without a bias "
                                    "vector; fp32 up to d = 1024)");

@@ -1131,7 +1131,6 @@ __device__ __forceinline__ bool rows_first_wait(const RowsParams& p, const RowsC
 }
 
 // Returns false if the launch was aborted (or every row has left).
-template <bool ARGMAX_ONLY>
 __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& c, EH_LDS char* lds, int lane, int wave,
                                             double* red, int* flag) {
   const int g = blockIdx.x, tid = threadIdx.x;
@@ -1177,9 +1176,9 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
       };
 #define EH_ROWS_PASS(MT_)                                                                                     \
   if (nb_live <= 0) pass32_idle<MT_>(Wf, t, T1, p.KS, lane, wave, lds, btw);                                     \
-  else if (nb_live == 1) pass32<MT_, 1, ARGMAX_ONLY, false, false, Stats>(Wf, ybase, t, T1, p.KS, row_hi, lane, wave, lds, \
+  else if (nb_live == 1) pass32<MT_, 1, false, false, false, Stats>(Wf, ybase, t, T1, p.KS, row_hi, lane, wave, lds, \
                                                         reinterpret_cast<Stats(&)[1]>(st[0]), 0, nullptr, btw);  \
-  else pass32<MT_, 2, ARGMAX_ONLY, false, false, Stats>(Wf, ybase, t, T1, p.KS, row_hi, lane, wave, lds, st, 0, nullptr, btw)
+  else pass32<MT_, 2, false, false, false, Stats>(Wf, ybase, t, T1, p.KS, row_hi, lane, wave, lds, st, 0, nullptr, btw)
       switch (mt) {
         case 7: EH_ROWS_PASS(7); break;
         case 6: EH_ROWS_PASS(6); break;
@@ -1196,7 +1195,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
     const long long part_at = (long long)(j & 1) * p.n_stream * p.R_pad + (long long)g * p.R_pad;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-      stats_resolve<ARGMAX_ONLY>(st[n], park_of(lds, n));
+      stats_resolve<false>(st[n], park_of(lds, n));
       st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));  // lanes l and l+32 hold the same token
       if (lane < 32 && n < nb_live) {
         store_coherent(p.part4 + part_at + (nb_first + n) * 32 + lane, stats_head(st[n]));
@@ -1656,7 +1655,7 @@ __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_
         default: ok = rows_stream_ks<1, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
       }
     } else {
-      ok = rows_stream<ARGMAX_ONLY>(p, c, lds, lane, wave, red, &flag);
+      ok = rows_stream(p, c, lds, lane, wave, red, &flag);
     }
     if (ok && p.mode == 1) rows_verify_tail(p, c, lane, wave, &flag, red_z, red_i);
     return;
@@ -1665,10 +1664,10 @@ __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_
   if (p.mode == 0) rows_serve_cascade(p, c, lane, sg * kG32Waves + wave, nsg * kG32Waves);
 }
 
-template <bool ARGMAX_ONLY>
+// More than 64 rows: cascades only (a verification of so many positions takes three launches).
 __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel_rows(const RowsParams p) {
   extern __shared__ __attribute__((aligned(16))) char g32_smem[];
-  rows_kernel_body<ARGMAX_ONLY, 0>(p, g32_smem);
+  rows_kernel_body<false, 0>(p, g32_smem);
 }
 
 // Up to 32 * NB rows, NB = 1 or 2 (see rows_stream_ks).
@@ -1748,8 +1747,7 @@ hipError_t rows_prepare(eh_ctx* c) {
   if (e != hipSuccess) return e;
   const int cus = prop.multiProcessorCount;
   if (cus < 4 * kRowsServiceWgs) return hipSuccess;  // too small a device to set workgroups aside
-  const struct { const void* fn; size_t lds; } fns[6] = {{(const void*)gemm32_stats_kernel_rows<false>, g32_lds_bytes()},
-                                                       {(const void*)gemm32_stats_kernel_rows<true>, g32_lds_bytes()},
+  const struct { const void* fn; size_t lds; } fns[5] = {{(const void*)gemm32_stats_kernel_rows, g32_lds_bytes()},
                                                        {(const void*)rows_ksplit_kernel<false, 1>, ks_lds_bytes()},
                                                        {(const void*)rows_ksplit_kernel<true, 1>, ks_lds_bytes()},
                                                        {(const void*)rows_ksplit_kernel<false, 2>, ks_lds_bytes()},
@@ -1795,10 +1793,10 @@ hipError_t rows_launch(const eh_ctx* c, const RowsParams& p, hipStream_t s) {
       else EH_ROWS_KS(false, 2);
     }
 #undef EH_ROWS_KS
-  } else if (p.argmax_only)
-    hipLaunchKernelGGL((gemm32_stats_kernel_rows<true>), dim3(c->rows_grid), dim3(kG32Threads), g32_lds_bytes(), s, p);
-  else
-    hipLaunchKernelGGL((gemm32_stats_kernel_rows<false>), dim3(c->rows_grid), dim3(kG32Threads), g32_lds_bytes(), s, p);
+  } else {
+    if (p.argmax_only || p.mode != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gemm32_stats_kernel_rows, dim3(c->rows_grid), dim3(kG32Threads), g32_lds_bytes(), s, p);
+  }
   return hipGetLastError();
 }
 
