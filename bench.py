@@ -542,7 +542,7 @@ def run_c2(args, torch, B, G, dev, steps, warmup, cpu_leg):
     roof = {"bound": "mfma", "achieved": flops_per_launch / avg_s / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": flops_per_launch / avg_s / 1e12 / MFMA_BF16_PEAK_TFLOPS,
             "traffic": TRAFFIC_BYTES_C2,
-            "kernel": "eh::gemm32_stats_kernel<2,false,false> (one head on 512 rows = 1/24 of the launch; the time "
+            "kernel": "eh::gemm32_stats_kernel<false,false> (one head on 512 rows = 1/24 of the launch; the time "
                       "per head includes its share of the LayerNorm and final-merge launches)",
             "avg_launch_us": avg_s * 1e6,
             "flops_per_launch": flops_per_launch, "launches": launches}
@@ -598,7 +598,7 @@ def run_c3(args, torch, B, G, dev, steps, warmup, cpu_leg, keep=None):
     avg_s = ev_s / launches
     roof = {"bound": "hbm", "achieved": bytes_per_launch / avg_s / 1e9, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS, "traffic": TRAFFIC_RATIO_C3 * bytes_per_launch,
-            "kernel": "eh::gemm32_stats_kernel_rows<false> (one launch = a whole cascade; one head on the live rows = "
+            "kernel": "eh::rows_ksplit_kernel<false,2> (one launch = a whole cascade; one head on the live rows = "
                       "cascade time / heads run)",
             "avg_launch_us": avg_s * 1e6, "bytes_per_launch": bytes_per_launch, "launches": launches}
     cfg = {"workload": "c3_dynexit: d=2560 V=50304 32 heads x 64 rows bf16, rows exit at first H<tau, "
@@ -655,8 +655,8 @@ def run_c4(args, torch, B, G, dev, steps, warmup, cpu_leg, heads=None):
     avg_s = ev_s / launches
     roof = {"bound": "hbm", "achieved": bytes_per_launch / avg_s / 1e9, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS, "traffic": TRAFFIC_RATIO_C4 * bytes_per_launch,
-            "kernel": "eh::gemm32_stats_kernel_rows<true> (one launch = one verification: LayerNorm, argmax-only "
-                      "projection of 144 positions, prefix comparison; the time also holds the preset launch)",
+            "kernel": "eh::gemm32_stats_kernel<true,false> (time of a whole verification, three launches: LayerNorm, argmax-only "
+                      "projection of 144 positions, prefix comparison)",
             "avg_launch_us": avg_s * 1e6, "bytes_per_launch": bytes_per_launch, "launches": launches}
     cfg = {"workload": "c4_verify: d=2560 V=50304 final head, 16 rows x (8 drafts + 1) bf16, "
                        f"{calls_per_step} verifications per bench step over {n_copies} weight copies",
