@@ -47,8 +47,6 @@ hipError_t scratch_address(int device, void** out) {
   return hipSuccess;
 }
 
-constexpr int kMaxParts = 512;       // partial statistics per row there is room for (one per workgroup over the vocabulary)
-
 struct DeviceGuard {
   int prev = -1;
   bool changed = false;
@@ -126,9 +124,9 @@ void launch_ln(const eh_ctx* c, int head, const void* h, int64_t row_stride, con
 // Projection and partial statistics of the rows launch_ln has prepared.
 hipError_t project(const eh_ctx* c, int head, const int* n_rows_dev, int n_rows, bool argmax_only, const frag_t* yf,
                    Stats* partials, PartCount* parts, hipStream_t s) {
-  *parts = PartCount{0, 0, 0};
+  *parts = PartCount{0, 0, 0, 0, 0};
   if (use_ksplit(c, n_rows))
-    return ksplit_launch(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, nullptr, 0, &parts->n, s);
+    return ksplit_launch(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, nullptr, 0, parts, s);
   if (c->dtype == EH_BF16)
     return gemm32_launch(c, head, 1, n_rows_dev, n_rows, argmax_only, yf, 0, partials, nullptr, 0, parts, s);
   return gemm_launch(c, head, n_rows_dev, n_rows, argmax_only, yf, partials, &parts->n, s);
@@ -500,11 +498,11 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
                      layer_stride, row_stride, n_rows, R_pad, ctx->d, ctx->KS,
                      (const float* const*)(ctx->d_gamma + head0), (const float* const*)(ctx->d_beta + head0),
                      ctx->eps, ctx->mh_yf, (int64_t)y_stride);
-  PartCount parts{0, 0, 0};
+  PartCount parts{0, 0, 0, 0, 0};
   float* second = metrics ? ctx->mh_second : nullptr;
   if (use_ksplit(ctx, n_rows))
     EH_HIP(ctx, ksplit_launch(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
-                              ctx->mh_partials, second, (long long)part_stride, &parts.n, s));
+                              ctx->mh_partials, second, (long long)part_stride, &parts, s));
   else
     EH_HIP(ctx, gemm32_launch(ctx, head0, n_heads_eval, nullptr, n_rows, false, ctx->mh_yf, (long long)y_stride,
                               ctx->mh_partials, second, (long long)part_stride, &parts, s));

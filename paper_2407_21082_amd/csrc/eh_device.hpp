@@ -165,18 +165,20 @@ __device__ __forceinline__ Stats stats_shfl_xor(const Stats& s, int mask) {
   return o;
 }
 
-// How many partial statistics a row has.  The batched bf16 kernel shares its grid out between as many
-// groups of 256 rows as are live; where that is only known on the device, its readers work out the
-// same number.
-__host__ __device__ inline int gemm32_parts(int n_live, int grid, int max_parts) {
-  const int groups = (((n_live + 31) >> 5) + 7) / 8;
+// How many partial statistics a row has.  A projection shares its grid out between as many groups of
+// `group` rows as are live; where that is only known on the device, its readers work out the same
+// number.  all > 0: the groups of the whole call share the grid as long as at least half of them are
+// live (see ksplit_kernel).
+__host__ __device__ inline int live_parts(int n_live, int group, int all, int grid, int max_parts) {
+  int groups = (n_live + group - 1) / group;
+  if (2 * groups >= all && all > groups) groups = all;
   const int p = groups > 0 ? grid / groups : grid;
   return p < 1 ? 1 : (p > max_parts ? max_parts : p);
 }
 struct PartCount {
-  int n;          // for the rows the host passed
-  int grid, max;  // grid > 0: the count follows the live rows
-  __device__ __forceinline__ int of(int n_live) const { return grid > 0 ? gemm32_parts(n_live, grid, max) : n; }
+  int n;                      // for the rows the host passed
+  int group, all, grid, max;  // grid > 0: the count follows the live rows
+  __device__ __forceinline__ int of(int n_live) const { return grid > 0 ? live_parts(n_live, group, all, grid, max) : n; }
 };
 
 // Running statistics for the training objectives (Section 3.3) of one token: the head's

@@ -47,6 +47,7 @@ namespace {
 
 constexpr int kG32Waves = 4;
 constexpr int kG32Threads = kG32Waves * kWave;
+constexpr int kG32Group = 2 * kG32Waves * 32;  // rows a workgroup takes at most: two blocks a wave
 constexpr int kMaxMT = 7;     // 32-row tiles per pass
 constexpr int kSlots = 8;     // LDS ring: k-steps of weight fragments (a slot is rewritten 7 steps after its last read)
 constexpr int kSlotBytes = 2 * kMaxMT * 1024;
@@ -720,7 +721,7 @@ struct G32Deal {
   __device__ __forceinline__ G32Deal(int n_live, int grid, int max_parts, int wg) {
     const int blocks = (n_live + 31) >> 5;
     groups = (blocks + 2 * kG32Waves - 1) / (2 * kG32Waves);
-    parts = gemm32_parts(n_live, grid, max_parts);
+    parts = live_parts(n_live, kG32Group, 0, grid, max_parts);
     const int y = groups > 0 ? wg / parts : 0;
     part = wg - y * parts;
     first = groups > 0 ? blocks * y / groups : 0;
@@ -1724,8 +1725,8 @@ hipError_t gemm32_launch(const eh_ctx* c, int head, int n_heads, const int* n_ro
   // one workgroup per compute unit, or one per group of 256 rows if that is more
   const int grid = std::max(cus, (R_pad / 32 + 2 * kG32Waves - 1) / (2 * kG32Waves));
   // (as many partial statistics as there is room for, and no slice without a tile of its own)
-  const int max_parts = std::max(1, std::min({cus, 512, (c->VT + 1) / 2}));
-  *parts = PartCount{gemm32_parts(n_rows, grid, max_parts), n_rows_dev ? grid : 0, max_parts};
+  const int max_parts = std::max(1, std::min({cus, kMaxParts, (c->VT + 1) / 2}));
+  *parts = PartCount{live_parts(n_rows, kG32Group, 0, grid, max_parts), kG32Group, 0, n_rows_dev ? grid : 0, max_parts};
   const frag_t* const* tab = (const frag_t* const*)(c->d_Wf + head);
 #define EH_L32(AO_, T2_)                                                                                               \
   return launch32<AO_, T2_>(grid, s, tab, n_heads, yf, y_stride, c->VT, c->KS, c->V, n_rows_dev, n_rows, max_parts, R_pad, \

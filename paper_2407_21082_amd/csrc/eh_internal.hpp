@@ -31,7 +31,7 @@ struct eh_ctx {
   float** d_bias = nullptr;
   float* d_tau = nullptr;
   eh::frag_t* yf = nullptr;     // [R_pad_max/16][KS][64] activations in fragment order
-  eh::Stats* partials = nullptr;  // [kStreamGrid][R_pad_max]
+  eh::Stats* partials = nullptr;  // [kMaxParts][R_pad_max]
   // workspace of eh_eval_heads, allocated by its first call: one activation buffer and one
   // set of partials per head
   eh::frag_t* mh_yf = nullptr;
@@ -40,7 +40,7 @@ struct eh_ctx {
   int mh_heads = 0;
   CalibScratch calib;  // eh_calibrate's scratch, grown on demand
   // workspace of eh_head_losses, allocated by its first call: partial statistics
-  // [kStreamGrid][R_pad_max] and the per-token loss terms [2][R_pad_max]
+  // [kMaxParts][R_pad_max] and the per-token loss terms [2][R_pad_max]
   eh::KlStats* kl_partials = nullptr;
   float* kl_rows = nullptr;
   int* ws_argmax = nullptr;     // [max_rows] internal output (verify)
@@ -72,6 +72,8 @@ struct eh_ctx {
 };
 
 namespace eh {
+
+constexpr int kMaxParts = 512;  // partial statistics per row there is room for (one per workgroup over the vocabulary)
 
 // Arguments of the persistent decode kernel (<= 16 rows, heads l0 .. l1-1).
 struct DecodeParams {
@@ -163,11 +165,11 @@ hipError_t gemm32_launch(const eh_ctx* ctx, int head, int n_heads, const int* n_
                          bool argmax_only, const eh::frag_t* yf, long long y_stride, eh::Stats* partials,
                          float* second, long long part_stride, PartCount* parts, hipStream_t s);
 // Projection + statistics of n_heads consecutive heads for a few rows (bf16 or fp32, with or without
-// bias vectors; groups of 64 rows): yf in the 32-row operand order, partials [*n_parts][n_rows rounded
-// up to 32] per head; `second` as below (bf16 only).
+// bias vectors; groups of 64 rows): yf in the 32-row operand order, partials [*parts][n_rows rounded
+// up to 32] per head; `second` as above (bf16 only).
 hipError_t ksplit_launch(const eh_ctx* ctx, int head, int n_heads, const int* n_rows_dev, int n_rows,
                          bool argmax_only, const eh::frag_t* yf, long long y_stride, eh::Stats* partials,
-                         float* second, long long part_stride, int* n_parts, hipStream_t s);
+                         float* second, long long part_stride, PartCount* parts, hipStream_t s);
 // The fused projections of the training objectives (bf16, no bias vector): an exit head on
 // yf_head and the model's head on yf_model (both in the 32 x 16 operand order, same rows),
 // labels NULL or device [n_rows]; per-workgroup partial statistics go to

@@ -5,14 +5,16 @@ namespace eh {
 
 namespace {
 
-// grid.x = workgroups over the vocabulary, grid.y = groups of 64 rows.  A workgroup walks its slice
-// of n_heads consecutive heads (weights and bias vectors from the tables; activations and partial
-// statistics of consecutive heads y_stride fragments / part_stride records apart) without its
-// weight stream stopping between them.
+__host__ __device__ inline int ks_groups(int n_rows) { return (n_rows + kKsGroup - 1) / kKsGroup; }
+
+// A workgroup walks its slice of the vocabulary (`part`) of n_heads consecutive heads (weights and bias
+// vectors from the tables; activations and partial statistics of consecutive heads y_stride fragments /
+// part_stride records apart) for the 64 rows from row0 on, without its weight stream stopping between
+// the heads.
 template <typename DT, int MT, int NB, bool AO, bool TOP2>
 __device__ __forceinline__ void ks_heads(const KsSlice& sl, const frag_t* const* __restrict__ Wf, const float* const* __restrict__ bias,
                                          int n_heads, const frag_t* __restrict__ yq, long long y_stride, int KS, int V,
-                                         int n_live, int R_pad, Stats* __restrict__ partials, float* __restrict__ second_out, long long part_stride,
+                                         int n_live, int row0, int part, int R_pad, Stats* __restrict__ partials, float* __restrict__ second_out, long long part_stride,
                                          EH_KS_LDS char* lds, int wave, int lane) {
   const int row_hi = min(V, sl.t1 * 16);
   const long long slice_at = (long long)sl.t0 * KS * kWave;       // fragments (16 bytes per lane)
@@ -43,18 +45,25 @@ __device__ __forceinline__ void ks_heads(const KsSlice& sl, const frag_t* const*
       ks_finish<MT, NB, AO, TOP2>(acc, lds, wave, lane, (sl.t0 + 2 * MT * p) * 16, row_hi, bias ? bias[l] : nullptr, st, second);
     }
     const Stats s = ks_merge<NB, TOP2>(st, second, z2, lds, wave, lane);
-    const int t = blockIdx.y * kKsGroup + threadIdx.x;
+    const int t = row0 + threadIdx.x;
     if (threadIdx.x < 32 * NB && t < n_live) {
-      partials[l * part_stride + (long long)blockIdx.x * R_pad + t] = s;
-      if constexpr (TOP2) second_out[l * part_stride + (long long)blockIdx.x * R_pad + t] = z2;
+      partials[l * part_stride + (long long)part * R_pad + t] = s;
+      if constexpr (TOP2) second_out[l * part_stride + (long long)part * R_pad + t] = z2;
     }
   }
 }
 
+// The groups of 64 rows share the grid: `parts` workgroups over the vocabulary each, those of one slice
+// side by side in time and, for a power of two of groups, on one die, whose L2 then fetches the slice
+// once (one workgroup taking the groups in turn: 169 us for 512 rows of d = 1024 with a bias vector,
+// against 122).  How many rows are live may only be known on the device.  While at least half of the
+// groups are, the slices stay as the host's rows give them, and so do a row's sums; below that the
+// grid is dealt out anew, or the few live groups would leave most compute units idle (40 live of 512
+// rows: 128 us with 32 workgroups, 37 with 256).
 template <typename DT, bool AO, bool TOP2>
 __global__ __launch_bounds__(kKsThreads, 1) void ksplit_kernel(
     const frag_t* const* __restrict__ Wf, const float* const* __restrict__ bias, int n_heads, const frag_t* __restrict__ yq,
-    long long y_stride, int VT16, int KS, int V, const int* __restrict__ n_rows_dev, int n_rows, int R_pad,
+    long long y_stride, int VT16, int KS, int V, const int* __restrict__ n_rows_dev, int n_rows, int max_parts, int R_pad,
     Stats* __restrict__ partials, float* __restrict__ second, long long part_stride) {
   extern __shared__ __attribute__((aligned(16))) char ks_smem[];
   EH_KS_LDS char* lds = (EH_KS_LDS char*)ks_smem;
@@ -62,14 +71,16 @@ __global__ __launch_bounds__(kKsThreads, 1) void ksplit_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int n_live = n_rows;
   if (n_rows_dev) n_live = min(max(*n_rows_dev, 0), n_rows);
-  const int mine = n_live - (int)blockIdx.y * kKsGroup;
+  const int parts = live_parts(n_live, kKsGroup, ks_groups(n_rows), gridDim.x, max_parts);
+  const int group = (int)blockIdx.x / parts, part = (int)blockIdx.x - group * parts, row0 = group * kKsGroup;
+  const int mine = n_live - row0;
   if (mine <= 0) return;
-  const KsSlice sl(VT16, blockIdx.x, gridDim.x);
-  yq += (long long)blockIdx.y * (kKsGroup / 32) * 2 * KS * kWave;
+  const KsSlice sl(VT16, part, parts);
+  yq += (long long)group * (kKsGroup / 32) * 2 * KS * kWave;
 #define EH_KS_CASE(MT_)                                                                                                    \
   case MT_:                                                                                                                \
-    if (mine <= 32) ks_heads<DT, MT_, 1, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, n_live, R_pad, partials, second, part_stride, lds, wave, lane); \
-    else ks_heads<DT, MT_, 2, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, n_live, R_pad, partials, second, part_stride, lds, wave, lane);           \
+    if (mine <= 32) ks_heads<DT, MT_, 1, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, n_live, row0, part, R_pad, partials, second, part_stride, lds, wave, lane); \
+    else ks_heads<DT, MT_, 2, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, n_live, row0, part, R_pad, partials, second, part_stride, lds, wave, lane);           \
     break
   switch (sl.mt) {
     EH_KS_CASE(7);
@@ -86,13 +97,13 @@ __global__ __launch_bounds__(kKsThreads, 1) void ksplit_kernel(
 
 template <typename DT, bool AO, bool TOP2>
 hipError_t launch_ksplit(dim3 g, hipStream_t s, const frag_t* const* Wf, const float* const* bias, int n_heads, const frag_t* yq,
-                         long long y_stride, int VT16, int KS, int V, const int* n_rows_dev, int n_rows, int R_pad,
+                         long long y_stride, int VT16, int KS, int V, const int* n_rows_dev, int n_rows, int max_parts, int R_pad,
                          Stats* partials, float* second, long long part_stride) {
   static const hipError_t attr = hipFuncSetAttribute((const void*)ksplit_kernel<DT, AO, TOP2>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_lds_bytes());
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((ksplit_kernel<DT, AO, TOP2>), g, dim3(kKsThreads), ks_lds_bytes(), s, Wf, bias, n_heads, yq, y_stride, VT16, KS,
-                     V, n_rows_dev, n_rows, R_pad, partials, second, part_stride);
+                     V, n_rows_dev, n_rows, max_parts, R_pad, partials, second, part_stride);
   return hipGetLastError();
 }
 
@@ -100,17 +111,19 @@ hipError_t launch_ksplit(dim3 g, hipStream_t s, const frag_t* const* Wf, const f
 
 hipError_t ksplit_launch(const eh_ctx* c, int head, int n_heads, const int* n_rows_dev, int n_rows, bool argmax_only,
                          const frag_t* yf, long long y_stride, Stats* partials, float* second, long long part_stride,
-                         int* n_parts, hipStream_t s) {
+                         PartCount* parts, hipStream_t s) {
   const int R_pad = (n_rows + 31) & ~31;
-  const int groups = (n_rows + kKsGroup - 1) / kKsGroup;
   const int cus = c->num_cu > 0 ? c->num_cu : 256;
-  const int gx = std::max(1, std::min(c->VT, cus / groups));
-  *n_parts = gx;
+  // one workgroup per compute unit, or one per group of rows if that is more; as many partial
+  // statistics as there is room for, and no slice without a tile of its own
+  const int groups = ks_groups(n_rows), grid = std::max(cus, groups);
+  const int max_parts = std::min({cus, kMaxParts, c->VT});
+  *parts = PartCount{live_parts(n_rows, kKsGroup, groups, grid, max_parts), kKsGroup, groups, n_rows_dev ? grid : 0, max_parts};
   const frag_t* const* W = (const frag_t* const*)(c->d_Wf + head);
   const float* const* bias = c->d_bias ? (const float* const*)(c->d_bias + head) : nullptr;
-  dim3 g(gx, groups);
+  const dim3 g(grid);
 #define EH_KS_GO(DT, AO_, T2_)                                                                                               \
-  return launch_ksplit<DT, AO_, T2_>(g, s, W, bias, n_heads, yf, y_stride, c->VT, c->KS, c->V, n_rows_dev, n_rows, R_pad, \
+  return launch_ksplit<DT, AO_, T2_>(g, s, W, bias, n_heads, yf, y_stride, c->VT, c->KS, c->V, n_rows_dev, n_rows, max_parts, R_pad, \
                                      partials, second, part_stride)
   if (second) {
     if (argmax_only || c->dtype != EH_BF16) return hipErrorInvalidValue;

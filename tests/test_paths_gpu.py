@@ -166,3 +166,70 @@ def test_persistent_cascade_and_verification_up_to_64_rows(B, rows, V, d):
         assert acc[::2].eq(k).all() and acc[1::2].eq(1).all()
         assert torch.equal(nxt, want.gather(1, acc[:, None].long())[:, 0])
     B.eh_destroy(ctx)
+
+
+def _bias_heads(d, V, n_heads, rows, dtype, seed, kappa=0.6):
+    w = G.Workload("biaslive", d=d, V=V, n_heads=n_heads, rows=rows, dtype=dtype, seed=seed, kappa=kappa)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    return w, heads, hid, [0.3 * torch.randn(V, generator=gen, device=DEV) for _ in range(n_heads)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_bias_heads_at_every_live_count(B, dtype):
+    """The k-split kernel deals its grid out anew when less than half of a call's groups of 64 rows are
+    live (here 7 groups: from 3 down); kernel and merge work the number of slices out on their own."""
+    R = 400
+    w, heads, hid, bs = _bias_heads(64, 9001, 1, R, dtype, 5)
+    orc = _oracle(hid.h[0], heads.gamma[0], heads.beta[0], P.f64(heads.W[0]), bs[0], dtype == "bf16")
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=R, bias=bs)
+    idx = torch.randperm(R, generator=torch.Generator().manual_seed(3)).to(torch.int32)
+    for n in (0, 1, 64, 65, 128, 192, 193, 256, 257, 400):
+        H, lse, am = _eval(B, ctx, 0, hid.h[0], R, row_idx=idx.to(DEV), n_rows_dev=torch.tensor([n], dtype=torch.int32, device=DEV))
+        if n:
+            P.compare_head(f"live{n}", H[:n], lse[:n], am[:n], tuple(x[idx[:n].numpy()] for x in orc), [])
+        assert bool((H[n:] == 0).all()) and bool((lse[n:] == 0).all()) and bool((am[n:] == -7).all())
+    B.eh_destroy(ctx)
+
+
+def test_bias_cascade_whose_live_rows_fall_below_half(B):
+    rows = 300
+    w, heads, hid, bs = _bias_heads(96, 8200, 6, rows, "bf16", 8)
+    full = [_oracle(hid.h[l], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), bs[l], True) for l in range(6)]
+    full = [np.stack([f[i] for f in full]) for i in range(4)]
+    tau = G.tau_for_schedule(full[0], 6)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows, bias=bs)
+    ex, tok, H, nev = _ints(rows), _ints(rows), torch.zeros((6, rows), device=DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
+    B.eh_cascade(ctx, hid.h, rows, ex, tok, H, nev)
+    torch.cuda.synchronize()
+    P.compare_cascade("biasbelowhalf", ex, tok, H, full[0], full[2], full[3], tau, [])
+    assert int(nev) == int((ex.long() + 1).sum())
+    live = [int((ex >= l).sum()) for l in range(6)]
+    assert live[0] > 256 and any(64 < n <= 128 for n in live) and live[-1] <= 128, live
+    B.eh_destroy(ctx)
+
+
+def test_few_live_rows_of_a_large_bias_call_have_the_whole_device(B):
+    """40 live rows cost about the same whether the call was made for 40 rows or for 512 (1.1 times as
+    much; 4 times when the grid followed the host's rows)."""
+    w, heads, hid, bs = _bias_heads(1024, 50304, 1, 512, "bf16", 2)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=512, bias=bs)
+    H, lse, am = torch.zeros(512, device=DEV), torch.zeros(512, device=DEV), _ints(512)
+    n_dev = torch.tensor([40], dtype=torch.int32, device=DEV)
+
+    def us(rows):
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                B.eh_eval(ctx, 0, hid.h[0], rows, H, lse, am, n_rows_dev=n_dev)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+
+    us(512)
+    assert us(512) < 2 * us(40)
+    B.eh_destroy(ctx)
