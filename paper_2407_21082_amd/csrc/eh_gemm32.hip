@@ -34,7 +34,7 @@
 // of which 768 are matrix instructions, at 1.6 to 1.8 GHz; with the weights read from one place
 // instead of streamed the same loop runs at 2.05 GHz, so what bounds it is the power the chip has
 // for matrix cores and memory together.  The statistics of a pass are next (12 k clocks of 72 k
-// before they parked new maxima).  24 heads: 2460 -> 2381 us.
+// before they parked new maxima).  24 heads: 2351 -> 2250 us.
 #include "eh_internal.hpp"
 #include "eh_kernels.hpp"
 #include "eh_ksplit.hpp"
@@ -731,8 +731,10 @@ struct G32Deal {
 
 // One launch covers n_heads consecutive heads (weights from the table; activations and outputs of
 // consecutive heads lie y_stride fragments / part_stride records apart): a workgroup walks its slice
-// of every head, and behind the last k loop of a pass, while the statistics are worked out, the next
-// pass's (or head's) first weights are asked for, so that the memory system does not idle.
+// of every head.  (Asking for the next pass's or head's first weights while the statistics are worked
+// out, as rows_stream does, costs more than it gives here: the next pass opens by waiting for them
+// and then fetches them again.  With it and without, us: 16 heads of d = 512 on 400 rows 547 and 513;
+// 6 heads of d = 1024 on 100 rows 150 and 142; 24 of d = 2048 on 512 rows 2277 and 2250.)
 template <bool ARGMAX_ONLY, bool TOP2>
 __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
     const frag_t* const* __restrict__ Wf_tab, int n_heads, const frag_t* __restrict__ yq, long long y_stride, int VT16, int KS,
@@ -772,21 +774,11 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
     }
     for (int t = T0; t < T1;) {
       const int mt = pass_tiles(T1 - t);
-      auto next = [&]() {
-        const int tn = t + 2 * mt;
-        if (tn < T1) {
-          ring_prefetch(Wf, tn, T1, pass_tiles(T1 - tn), KS, lane, wave, lds);
-        } else if (l + 1 < n_heads) {
-          int n0, n1;
-          vocab_slice(VT16, gran, slice_of(l + 1), deal.parts, n0, n1);
-          if (n0 < n1) ring_prefetch(Wf_tab[l + 1], n0, n1, pass_tiles(n1 - n0), KS, lane, wave, lds);
-        }
-      };
 #define EH_G32_PASS(MT_)                                                                                              \
-  if (nb_live <= 0) pass32_idle<MT_>(Wf, t, T1, KS, lane, wave, lds, next);                                           \
+  if (nb_live <= 0) pass32_idle<MT_>(Wf, t, T1, KS, lane, wave, lds);                                                 \
   else if (nb_live == 1) pass32<MT_, 1, ARGMAX_ONLY, TOP2, false, Stats>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, \
-                                                        reinterpret_cast<Stats(&)[1]>(st[0]), 0, nullptr, next);        \
-  else pass32<MT_, 2, ARGMAX_ONLY, TOP2, false, Stats>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st, 0, nullptr, next)
+                                                                  reinterpret_cast<Stats(&)[1]>(st[0]));              \
+  else pass32<MT_, 2, ARGMAX_ONLY, TOP2, false, Stats>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st)
       switch (mt) {
         case 7: EH_G32_PASS(7); break;
         case 6: EH_G32_PASS(6); break;
