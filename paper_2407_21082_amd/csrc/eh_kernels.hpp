@@ -312,12 +312,16 @@ __device__ __forceinline__ void stats_finalize(const Stats& s, float& H, float& 
 
 // A workgroup merges the partial statistics of FR rows: thread t takes the records t/FR, t/FR + 256/FR,
 // ... of row t%FR, so that neighbouring threads read neighbouring records (one wave per row read
-// 20 bytes of every line it fetched: 62 us for 24 heads x 512 rows x 128 records).  16 rows; 4 for
-// launches of at most 64 rows, whose few workgroups would otherwise take 16 records a thread one
-// batch after the other (33.6 against 31.7 us for a whole call on 48 rows).  TOP2: the second largest logit as well (with multiplicity; second of a union =
-// max(min(z1a, z1b), max(z2a, z2b))).  The result is valid for threads t < FR.
+// 20 bytes of every line it fetched: 62 us for 24 heads x 512 rows x 128 records).  FR = 16; 4 for
+// calls of at most 128 rows, whose few workgroups would otherwise take up to 16 records a thread one
+// batch after the other (a whole call, us, FR = 16 / 4: 48 rows 33.6 / 31.7, 100 rows 32.4 / 30.8,
+// 128 rows 33.3 / 31.0, 200 rows 40.9 / 40.6, 300 rows 55.5 / 55.6, 512 rows 64.2 / 65.0; 4 heads x
+// 100 rows 59.7 / 58.6, 16 x 100 218 / 222, 16 x 203 312 / 314).  The number of heads does not enter: the order of
+// the merge goes with FR, and many heads at once give the bits of one at a time.  TOP2: the second
+// largest logit as well (with multiplicity; second of a union = max(min(z1a, z1b), max(z2a, z2b))).
+// The result is valid for threads t < FR.
 constexpr int kFinThreads = 256;
-inline int fin_rows(int n_rows) { return n_rows <= 64 ? 4 : 16; }
+inline int fin_rows(int n_rows) { return n_rows <= 128 ? 4 : 16; }
 template <bool TOP2, int FR>
 __device__ __forceinline__ Stats merge_partials(const Stats* __restrict__ partials, const float* __restrict__ second, int n_parts,
                                                 int R_pad, int row, float& z2) {

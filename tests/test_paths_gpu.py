@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import eh_oracle as O
 from workloads import generators as G
 from tests import parity_util as P
 
@@ -87,7 +88,6 @@ def test_ksplit_projection(B, dtype, bias, V, d, R):
 
 
 def _oracle(h, gamma, beta, W, bias, bf16):
-    from oracle import eh_oracle as O
     y = O.layernorm(P.f64(h), P.f64(gamma), P.f64(beta), 1e-5, bf16_out=bf16)
     z = y @ W.T + (0.0 if bias is None else P.f64(bias))
     m = z.max(axis=1, keepdims=True)
@@ -232,4 +232,31 @@ def test_few_live_rows_of_a_large_bias_call_have_the_whole_device(B):
 
     us(512)
     assert us(512) < 2 * us(40)
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("rows", [67, 128, 129, 300])
+def test_merge_of_four_and_sixteen_rows_a_workgroup(B, rows):
+    """The merge of the partial statistics takes 4 rows a workgroup up to 128 rows and 16 beyond: both
+    sides of the line, rows that fill neither, with and without the extra metrics, and the bits of
+    one head at a time."""
+    n_heads = 5
+    w = G.Workload("merge", d=64, V=8203, n_heads=n_heads, rows=rows, dtype="bf16", seed=rows)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0] * n_heads, max_rows=rows)
+    H, lse, p1, margin = (torch.zeros((n_heads, rows), device=DEV) for _ in range(4))
+    am = _ints(n_heads, rows)
+    B.eh_eval_heads_metrics(ctx, 0, n_heads, hid.h, rows, H, lse, am, p1, margin)
+    for l in range(n_heads):
+        orc = _oracle(hid.h[l], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), None, True)
+        P.compare_head(f"merge{l}", H[l], lse[l], am[l], orc, [])
+        pm_o, mg_o = O.head_metrics(P.f64(hid.h[l]), P.f64(heads.gamma[l]), P.f64(heads.beta[l]), P.f64(heads.W[l]), 1e-5, True)
+        # exp of a difference of two logits of magnitude z: relative error that of their fp32 sums, 64 products deep
+        np.testing.assert_allclose(P.f64(p1[l]), pm_o, rtol=2e-5)
+        np.testing.assert_allclose(P.f64(margin[l]), mg_o, rtol=0, atol=2e-5)
+    B.eh_eval_heads(ctx, 0, n_heads, hid.h, rows, H, lse, am)
+    for l in range(n_heads):
+        for a, b in zip(_eval(B, ctx, l, hid.h[l], rows), (H[l], lse[l], am[l])):
+            assert torch.equal(a, b)
     B.eh_destroy(ctx)
