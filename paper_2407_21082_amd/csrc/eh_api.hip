@@ -97,12 +97,20 @@ void free_all(eh_ctx* ctx) {
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// The k-split kernel: heads with a bias vector, bf16 up to its 64 rows, fp32 up to 32 (beyond that
-// fp32 is bound by its matrix instructions, not by the weights, and gemm_launch's kernel, with
-// twice the rows per weight operand, is the better one: 432 against 472 us at 512 rows of d = 1024,
-// 47 against 48 at 64 of d = 512; at 32 rows 47 against 36).
+// The k-split kernel: heads with a bias vector; others up to 32 rows, bf16 up to its 64 unless a pass
+// has seven tiles.
+// fp32 beyond 32 rows is bound by its matrix instructions, not by the weights, and gemm_launch's
+// kernel, with twice the rows per weight operand, is the better one: 432 against 472 us at 512 rows
+// of d = 1024, 47 against 48 at 64 of d = 512; at 32 rows 47 against 36.
+// bf16 at 33 to 64 rows: with seven tiles a pass (V above 12 tiles of 16 a workgroup, 49152 on 256
+// compute units, up to 57344) two blocks of rows fill the register file, and the statistics behind a
+// pass spill; gemm32_launch's kernel is then the better one, up to six tiles this one is.  One head on
+// 48 rows, us, this kernel against that: V = 50304, d = 512 / 1024 / 2048 25.6 / 33.6 / 50.1 against 23.4 /
+// 30.4 / 45.1; V = 49152 21.9 / 30.1 / 45.6 against 22.4 / 29.1 / 45.6; 12 heads in one call, V = 50304 156 /
+// 238 / 422 against 154 / 240 / 419; V = 49152 132 / 214 / 390 against 150 / 235 / 409.
 bool use_ksplit(const eh_ctx* c, int n_rows) {
-  return !c->bias.empty() || n_rows <= (c->dtype == EH_BF16 ? 64 : 32);
+  if (!c->bias.empty() || n_rows <= 32) return true;
+  return c->dtype == EH_BF16 && n_rows <= 64 && ksplit_pass_tiles(c) < 7;
 }
 // Rows per block of the activations' operand order: 16 for gemm_launch's kernel, 32 for all others.
 int row_block(const eh_ctx* c, int n_rows) { return c->dtype == EH_BF16 || use_ksplit(c, n_rows) ? 32 : 16; }

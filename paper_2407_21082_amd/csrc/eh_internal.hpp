@@ -170,6 +170,8 @@ hipError_t gemm32_launch(const eh_ctx* ctx, int head, int n_heads, const int* n_
 hipError_t ksplit_launch(const eh_ctx* ctx, int head, int n_heads, const int* n_rows_dev, int n_rows,
                          bool argmax_only, const eh::frag_t* yf, long long y_stride, eh::Stats* partials,
                          float* second, long long part_stride, PartCount* parts, hipStream_t s);
+// 32-row tiles per pass of its largest slice for one group of rows.
+int ksplit_pass_tiles(const eh_ctx* ctx);
 // The fused projections of the training objectives (bf16, no bias vector): an exit head on
 // yf_head and the model's head on yf_model (both in the 32 x 16 operand order, same rows),
 // labels NULL or device [n_rows]; per-workgroup partial statistics go to

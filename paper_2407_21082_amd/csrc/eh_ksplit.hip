@@ -109,6 +109,11 @@ hipError_t launch_ksplit(dim3 g, hipStream_t s, const frag_t* const* Wf, const f
 
 }  // namespace
 
+int ksplit_pass_tiles(const eh_ctx* c) {
+  const int slices = std::min({c->num_cu > 0 ? c->num_cu : 256, kMaxParts, c->VT});
+  return ks_pass_tiles((c->VT + slices - 1) / slices);
+}
+
 hipError_t ksplit_launch(const eh_ctx* c, int head, int n_heads, const int* n_rows_dev, int n_rows, bool argmax_only,
                          const frag_t* yf, long long y_stride, Stats* partials, float* second, long long part_stride,
                          PartCount* parts, hipStream_t s) {
@@ -117,7 +122,7 @@ hipError_t ksplit_launch(const eh_ctx* c, int head, int n_heads, const int* n_ro
   // one workgroup per compute unit, or one per group of rows if that is more; as many partial
   // statistics as there is room for, and no slice without a tile of its own
   const int groups = ks_groups(n_rows), grid = std::max(cus, groups);
-  const int max_parts = std::min({cus, kMaxParts, c->VT});
+  const int max_parts = std::min({cus, kMaxParts, c->VT});  // (as in ksplit_pass_tiles)
   *parts = PartCount{live_parts(n_rows, kKsGroup, groups, grid, max_parts), kKsGroup, groups, n_rows_dev ? grid : 0, max_parts};
   const frag_t* const* W = (const frag_t* const*)(c->d_Wf + head);
   const float* const* bias = c->d_bias ? (const float* const*)(c->d_bias + head) : nullptr;

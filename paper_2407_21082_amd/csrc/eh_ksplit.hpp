@@ -81,6 +81,13 @@ __device__ __forceinline__ frag_t ks_load(ks_buf_t buf, uint32_t lane_off, uint3
   return __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)lane_off, (int)base, AUX));
 }
 
+// 32-row tiles per pass of a slice of tiles16 tiles of 16: passes of at most kKsMaxMT of about equal size.
+__host__ __device__ inline int ks_passes(int tiles16) { return ((tiles16 + 1) / 2 + kKsMaxMT - 1) / kKsMaxMT; }
+__host__ __device__ inline int ks_pass_tiles(int tiles16) {
+  const int passes = ks_passes(tiles16);
+  return passes > 0 ? ((tiles16 + 1) / 2 + passes - 1) / passes : 0;
+}
+
 // One wave's view of the slice of a workgroup: 16-row tiles [t0, t1) walked in `passes` passes of
 // MT 32-row tiles.
 struct KsSlice {
@@ -88,9 +95,8 @@ struct KsSlice {
   __device__ __forceinline__ KsSlice(int VT16, int part, int parts) {
     t0 = (int)((long long)VT16 * part / parts);
     t1 = (int)((long long)VT16 * (part + 1) / parts);
-    const int tiles = (t1 - t0 + 1) >> 1;
-    passes = (tiles + kKsMaxMT - 1) / kKsMaxMT;
-    mt = passes > 0 ? (tiles + passes - 1) / passes : 0;
+    passes = ks_passes(t1 - t0);
+    mt = ks_pass_tiles(t1 - t0);
   }
 };
 

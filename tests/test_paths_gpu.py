@@ -101,7 +101,7 @@ def _oracle(h, gamma, beta, W, bias, bf16):
 
 @pytest.mark.parametrize("rows", [17, 40, 64])
 def test_many_heads_of_a_few_rows_in_one_stream(B, rows):
-    """eh_eval_heads up to 64 rows walks the heads in one launch whose weight stream runs on from
+    """eh_eval_heads up to 64 rows (V up to 49152) walks the heads in one launch whose weight stream runs on from
     head to head: the same bits as a head at a time."""
     w = G.Workload("ksheads", d=224, V=9001, n_heads=5, rows=rows, dtype="bf16", seed=rows)
     heads = G.make_heads(w, DEV)
@@ -257,6 +257,25 @@ def test_merge_of_four_and_sixteen_rows_a_workgroup(B, rows):
         np.testing.assert_allclose(P.f64(margin[l]), mg_o, rtol=0, atol=2e-5)
     B.eh_eval_heads(ctx, 0, n_heads, hid.h, rows, H, lse, am)
     for l in range(n_heads):
+        for a, b in zip(_eval(B, ctx, l, hid.h[l], rows), (H[l], lse[l], am[l])):
+            assert torch.equal(a, b)
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("V", [49152, 49153, 57344, 57345])
+@pytest.mark.parametrize("rows", [32, 33, 64])
+def test_projection_of_33_to_64_rows_around_seven_tiles_a_pass(B, V, rows):
+    """33 to 64 rows leave the k-split kernel where its passes have seven tiles (12 tiles of 16 rows a
+    workgroup and more, up to 14): both sides of both lines."""
+    w = G.Workload("seven", d=40, V=V, n_heads=2, rows=rows, dtype="bf16", seed=V + rows)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0, 0.0], max_rows=rows)
+    H, lse, am = torch.zeros((2, rows), device=DEV), torch.zeros((2, rows), device=DEV), _ints(2, rows)
+    B.eh_eval_heads(ctx, 0, 2, hid.h, rows, H, lse, am)
+    for l in range(2):
+        orc = _oracle(hid.h[l], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), None, True)
+        P.compare_head(f"seven{l}", H[l], lse[l], am[l], orc, [])
         for a, b in zip(_eval(B, ctx, l, hid.h[l], rows), (H[l], lse[l], am[l])):
             assert torch.equal(a, b)
     B.eh_destroy(ctx)
