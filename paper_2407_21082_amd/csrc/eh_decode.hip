@@ -13,8 +13,8 @@
 //  * the matrix cores do the k-reduction (one 16x16 tile of logits per 1 KiB
 //    fragment pair); the streamers fold finished tiles into running softmax
 //    statistics, tiles split between two waves are summed by the service wave;
-//  * four more waves do everything that needs global round trips so that the
-//    streamers never drain their rings: three LayerNorm waves prepare the next
+//  * two or four more waves do everything that needs global round trips so that the
+//    streamers never drain their rings: one or three LayerNorm waves prepare the next
 //    head's rows in LDS (double buffered), and an exchange wave all-gathers
 //    the workgroups' partial statistics through tagged records, merges them
 //    and applies the threshold test (every workgroup reaches the same
@@ -37,13 +37,21 @@ namespace {
 
 constexpr int kStreamers = 8;
 // LayerNorm waves.  Every workgroup normalises every live row of every head for itself, about 5 us
-// a row of 2048 by one wave (a trip to memory, then three fp64 sweeps): one wave is enough for a
-// row or two but took 40 us for 8 rows, longer than the head's weights take to arrive (30 us).
-// Three keep the workgroup at three waves per SIMD (a fourth would cost the streamers registers:
-// 128 instead of 168, and spills).  With the exchange of four rows per sweep (Service::pass), 8 rows
-// through 24 heads of d = 2048: 1144 us before, 826 now; 1 row is unchanged.
-constexpr int kLnW = 3;
-constexpr int kThreads = (kStreamers + 1 + kLnW) * kWave;  // streamers + exchange wave + LayerNorm waves
+// a row of 2048 by one wave (a trip to memory, then three fp64 sweeps): one wave took 40 us for 8
+// rows, longer than the head's weights take to arrive (30 us).  Three keep the workgroup at three
+// waves per SIMD (a fourth would cost the streamers registers: 128 instead of 168, and spills).
+// With the exchange of four rows per sweep (Service::pass), 8 rows through 24 heads of d = 2048: 1144 us
+// before, 826 now; 2 rows through 12 of d = 1024: 200 and 181.
+// A call of one row has nothing for either to share out and pays for both, most of it at its end,
+// where nothing hides the exchange: it runs with one LayerNorm wave and one row per sweep.  1 row, us, as
+// for more rows and so: one head of d = 1024 28.8 and 27.5; 4 heads of d = 512 (V = 32000) 36.6 and 35.7,
+// of d = 256 in fp32 49.6 and 46.9; 12 heads of d = 2048 313.1 and 311.1.
+template <bool ONE_ROW>
+struct Few {
+  static constexpr int kLnW = ONE_ROW ? 1 : 3;
+  static constexpr int kSweepRows = ONE_ROW ? 1 : 4;  // rows of a head a sweep looks at
+  static constexpr int kThreads = (kStreamers + 1 + kLnW) * kWave;  // streamers + exchange wave + LayerNorm waves
+};
 constexpr int kRing = 4;              // fragments per ring buffer (two buffers per streamer wave)
 constexpr int kMaxLag = 3;            // heads the streamers may be ahead of the oldest open exchange
 constexpr int kSpinLimit = 1 << 22;   // polls of a flag of this workgroup (LDS) before giving up
@@ -98,7 +106,7 @@ struct Smem {
   __device__ __forceinline__ lds_vint_t* part_flag(int par) const { return (lds_vint_t*)(base + o2() + par * (kStreamers * 4)); }
   __device__ __forceinline__ unsigned o3() const { return o2() + 2 * (kStreamers * 4); }
   __device__ __forceinline__ lds_vint_t* abort_flag(int par) const { return (lds_vint_t*)(base + o3() + par * 4); }
-  // rows entering head l, left by the exchange wave for the LayerNorm wave (by parity of l)
+  // rows entering head l, left by the exchange wave for the LayerNorm waves (by parity of l)
   __device__ __forceinline__ lds_vint_t* live_word(int par) const { return (lds_vint_t*)(base + o3() + 8 + par * 4); }
   // number of streamer waves that have finished the head of this parity
   __device__ __forceinline__ lds_vint_t* arrived(int par) const { return (lds_vint_t*)(base + o3() + 16 + par * 4); }
@@ -436,10 +444,13 @@ __device__ __forceinline__ void streamer(const DecodeParams& p, const Smem& sm, 
 // same exit decision on their own.  Records of a speculated head that is dropped
 // are never written; a tag from an older launch never matches, so nothing has to
 // be reset between launches.
+template <bool ONE_ROW>
 struct Service {
   static constexpr int kRadix = 16;                   // workgroups of a group, and groups
   static constexpr int kWindow = 4;                   // heads in flight
-  static constexpr int kSweepRows = kWave / kRadix;   // rows of a head a sweep looks at
+  static constexpr int kSweepRows = Few<ONE_ROW>::kSweepRows;
+  static constexpr int kLnW = Few<ONE_ROW>::kLnW;
+  static_assert(kSweepRows <= kWave / kRadix, "a group of lanes per row");
   const DecodeParams& p;
   const Smem sm;
   int lane;
@@ -527,16 +538,18 @@ struct Service {
   }
 
   // The lowest kSweepRows set bits of `todo` (-1 where there are fewer).
-  static __device__ __forceinline__ void pick_rows(unsigned todo, int (&rows)[4]) {
+  static __device__ __forceinline__ void pick_rows(unsigned todo, int (&rows)[kSweepRows]) {
 #pragma unroll
     for (int g = 0; g < kSweepRows; ++g) {
       rows[g] = todo ? __ffs(todo) - 1 : -1;
       todo &= todo - 1u;  // 0 stays 0
     }
   }
-  __device__ __forceinline__ int my_row(const int (&rows)[4]) const {
-    const int g = lane >> 4;
-    return g == 0 ? rows[0] : g == 1 ? rows[1] : g == 2 ? rows[2] : rows[3];
+  __device__ __forceinline__ int my_row(const int (&rows)[kSweepRows]) const {
+    int r = -1;
+#pragma unroll
+    for (int g = 0; g < kSweepRows; ++g) r = (lane >> 4) == g ? rows[g] : r;
+    return r;
   }
 
   // A two-round all-gather with radix kRadix, then finalise and
@@ -670,7 +683,7 @@ struct Service {
   // once.  The streamers are told as soon as every row has exited.
   __device__ __forceinline__ void run_exchange() {
     live = initial_live();
-    if (lane == 0) *sm.live_word((p.l0 + 1) & 1) = (int)live;  // read by the LayerNorm wave in the first window
+    if (lane == 0) *sm.live_word((p.l0 + 1) & 1) = (int)live;  // read by the LayerNorm waves in the first window
     c = sent = p.l0;
     lds_barrier();  // B_{-1}
     for (int l = p.l0; l < p.l1; ++l) {
@@ -740,8 +753,9 @@ struct Service {
   }
 };
 
-template <typename DT>
-__global__ __launch_bounds__(kThreads, 1) void decode_kernel(const DecodeParams p) {
+template <typename DT, bool ONE_ROW>
+__global__ __launch_bounds__(Few<ONE_ROW>::kThreads, 1) void decode_kernel(const DecodeParams p) {
+  constexpr int kThreads = Few<ONE_ROW>::kThreads;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   Smem sm;
   sm.base = (EH_LDS char*)smem_raw;
@@ -786,11 +800,21 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(const DecodeParams 
   if (wave < kStreamers) {
     streamer<DT>(p, sm, wave, lane);
   } else {
-    Service sv{p, sm, lane, 0u};
+    Service<ONE_ROW> sv{p, sm, lane, 0u};
     if (wave == kStreamers) sv.run_exchange();
     else sv.template run_layernorm<DT>(wave - kStreamers - 1);
   }
 }
+
+struct DecodeLaunch {
+  void (*fn)(const DecodeParams);
+  int threads;
+};
+template <bool ONE_ROW>
+DecodeLaunch decode_for(const eh_ctx* c) {
+  return {c->dtype == EH_BF16 ? decode_kernel<DtBf16, ONE_ROW> : decode_kernel<DtF32, ONE_ROW>, Few<ONE_ROW>::kThreads};
+}
+DecodeLaunch decode_for(const eh_ctx* c, int n_rows) { return n_rows == 1 ? decode_for<true>(c) : decode_for<false>(c); }
 
 }  // namespace
 
@@ -804,12 +828,14 @@ hipError_t decode_prepare(eh_ctx* c) {
   hipError_t e = hipGetDeviceProperties(&prop, c->device);
   if (e != hipSuccess) return e;
   if (smem > (size_t)prop.sharedMemPerBlock && smem > (size_t)prop.maxSharedMemoryPerMultiProcessor) return hipSuccess;
-  const void* fn = c->dtype == EH_BF16 ? (const void*)decode_kernel<DtBf16> : (const void*)decode_kernel<DtF32>;
-  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (e != hipSuccess) { (void)hipGetLastError(); return hipSuccess; }
-  int per_cu = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kThreads, smem);
-  if (e != hipSuccess || per_cu < 1) { (void)hipGetLastError(); return hipSuccess; }
+  for (int n_rows : {1, 16}) {
+    const DecodeLaunch l = decode_for(c, n_rows);
+    e = hipFuncSetAttribute((const void*)l.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) { (void)hipGetLastError(); return hipSuccess; }
+    int per_cu = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)l.fn, l.threads, smem);
+    if (e != hipSuccess || per_cu < 1) { (void)hipGetLastError(); return hipSuccess; }
+  }
   // the kernel waits on other workgroups, so all of them must be resident at once
   c->num_cu = prop.multiProcessorCount;
   // (the exchange is two rounds of 16 records: at most 256 workgroups)
@@ -819,10 +845,8 @@ hipError_t decode_prepare(eh_ctx* c) {
 }
 
 hipError_t decode_launch(const eh_ctx* c, const DecodeParams& p, hipStream_t s) {
-  if (c->dtype == EH_BF16)
-    hipLaunchKernelGGL((decode_kernel<DtBf16>), dim3(c->decode_grid), dim3(kThreads), c->decode_smem, s, p);
-  else
-    hipLaunchKernelGGL((decode_kernel<DtF32>), dim3(c->decode_grid), dim3(kThreads), c->decode_smem, s, p);
+  const DecodeLaunch l = decode_for(c, p.n_rows);
+  hipLaunchKernelGGL(l.fn, dim3(c->decode_grid), dim3(l.threads), c->decode_smem, s, p);
   return hipGetLastError();
 }
 
