@@ -337,6 +337,9 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
     }
     if ((e = decode_prepare(c)) != hipSuccess) return bail(e, "decode_prepare");
     if ((e = rows_prepare(c)) != hipSuccess) return bail(e, "rows_prepare");
+    if ((e = gemm_prepare()) != hipSuccess) return bail(e, "gemm_prepare");
+    if ((e = gemm32_prepare()) != hipSuccess) return bail(e, "gemm32_prepare");
+    if ((e = ksplit_prepare()) != hipSuccess) return bail(e, "ksplit_prepare");
     if (c->rows_grid > 0 && (c->max_rows > 16 || c->decode_grid == 0)) {
       // workspace of the persistent kernel for 17 .. 256 rows: one activation buffer per head (plus
       // the blocks a wave may read past the last live one), two sets of partial statistics

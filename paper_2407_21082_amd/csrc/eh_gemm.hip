@@ -204,17 +204,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_stats_kernel(
 template <typename DT, bool AO>
 void launch_nb(int nb, dim3 g, hipStream_t s, const frag_t* Wf, const frag_t* yf, int VT, int KS, int V,
                const int* n_rows_dev, int n_rows, int R_pad, Stats* partials) {
-#define EH_G(NB)                                                                                     \
-  do {                                                                                               \
-    static bool attr_set = false;                                                                    \
-    if (!attr_set) {                                                                                 \
-      (void)hipFuncSetAttribute((const void*)gemm_stats_kernel<DT, NB, AO>,                          \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_lds_bytes()); \
-      attr_set = true;                                                                               \
-    }                                                                                                \
-    hipLaunchKernelGGL((gemm_stats_kernel<DT, NB, AO>), g, dim3(kGemmThreads), gemm_lds_bytes(), s, \
-                       Wf, yf, VT, KS, V, n_rows_dev, n_rows, R_pad, partials);                      \
-  } while (0)
+#define EH_G(NB)                                                                                   \
+  hipLaunchKernelGGL((gemm_stats_kernel<DT, NB, AO>), g, dim3(kGemmThreads), gemm_lds_bytes(), s, \
+                     Wf, yf, VT, KS, V, n_rows_dev, n_rows, R_pad, partials)
   switch (nb) {
     case 1: EH_G(1); break;
     case 2: EH_G(2); break;
@@ -234,6 +226,21 @@ static int pick_nb(int blocks) {
   if (per_wave <= 4) return per_wave;
   if (per_wave <= 6) return 6;
   return 8;
+}
+
+template <bool AO>
+static hipError_t set_lds() {
+  for (const void* fn : {(const void*)gemm_stats_kernel<DtF32, 1, AO>, (const void*)gemm_stats_kernel<DtF32, 2, AO>,
+                         (const void*)gemm_stats_kernel<DtF32, 3, AO>, (const void*)gemm_stats_kernel<DtF32, 4, AO>,
+                         (const void*)gemm_stats_kernel<DtF32, 6, AO>, (const void*)gemm_stats_kernel<DtF32, 8, AO>}) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_lds_bytes());
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+hipError_t gemm_prepare() {
+  const hipError_t e = set_lds<true>();
+  return e != hipSuccess ? e : set_lds<false>();
 }
 
 hipError_t gemm_launch(const eh_ctx* c, int head, const int* n_rows_dev, int n_rows, bool argmax_only,

@@ -1683,12 +1683,6 @@ __global__ void rows_preset_kernel(int* __restrict__ ctl, int n_ctl, int* __rest
 template <int NBH>
 void launch_kl(dim3 g, hipStream_t s, const frag_t* Wf, long long wdelta, const frag_t* yq, const frag_t* yq2,
                int VT16, int KS, int V, int n_rows, int R_pad, const int* labels, KlStats* partials) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)gemm32_kl_kernel<NBH>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)g32_lds_bytes());
-    attr_set = true;
-  }
   hipLaunchKernelGGL((gemm32_kl_kernel<NBH>), g, dim3(kG32Threads), g32_lds_bytes(), s, Wf, wdelta, yq, yq2, VT16,
                      KS, V, n_rows, R_pad, labels, partials);
 }
@@ -1697,15 +1691,22 @@ template <bool AO, bool TOP2>
 hipError_t launch32(int grid, hipStream_t s, const frag_t* const* Wf_tab, int n_heads, const frag_t* yq, long long y_stride,
                     int VT16, int KS, int V, const int* n_rows_dev, int n_rows, int max_parts, int R_pad, Stats* partials,
                     float* second, long long part_stride) {
-  static const hipError_t attr = hipFuncSetAttribute((const void*)gemm32_stats_kernel<AO, TOP2>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)g32_lds_bytes());
-  if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((gemm32_stats_kernel<AO, TOP2>), dim3(grid), dim3(kG32Threads), g32_lds_bytes(), s, Wf_tab, n_heads, yq,
                      y_stride, VT16, KS, V, n_rows_dev, n_rows, max_parts, R_pad, partials, second, part_stride);
   return hipGetLastError();
 }
 
 }  // namespace
+
+hipError_t gemm32_prepare() {
+  for (const void* fn : {(const void*)gemm32_stats_kernel<false, true>, (const void*)gemm32_stats_kernel<true, false>,
+                         (const void*)gemm32_stats_kernel<false, false>, (const void*)gemm32_kl_kernel<1>,
+                         (const void*)gemm32_kl_kernel<2>}) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g32_lds_bytes());
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 // n_heads > 1: heads head .. head+n_heads-1 in one launch, their activations y_stride
 // fragments and their partials (and second largest logits) part_stride records apart.

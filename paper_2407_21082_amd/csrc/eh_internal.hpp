@@ -150,6 +150,11 @@ int rows_service_workgroups(int n_rows);  // workgroups of a cascade's grid that
 // Sets up the decode kernel for this context (grid, LDS size, function
 // attributes).  Leaves ctx->decode_grid = 0 if the shape does not fit.
 hipError_t decode_prepare(eh_ctx* ctx);
+// LDS sizes of the projection kernels behind gemm_launch and its relatives below, on the current device
+// (a function attribute holds for one device: every context sets it for its own).
+hipError_t gemm_prepare();
+hipError_t gemm32_prepare();
+hipError_t ksplit_prepare();
 // Enqueues the batched projection + statistics kernel (fp32) for one head on the rows
 // laid out in yf (fragments of 16 rows); per-workgroup partial statistics go to
 // partials[*n_parts][n_rows rounded up to 16].  Heads with a bias vector are not supported.

@@ -99,15 +99,22 @@ template <typename DT, bool AO, bool TOP2>
 hipError_t launch_ksplit(dim3 g, hipStream_t s, const frag_t* const* Wf, const float* const* bias, int n_heads, const frag_t* yq,
                          long long y_stride, int VT16, int KS, int V, const int* n_rows_dev, int n_rows, int max_parts, int R_pad,
                          Stats* partials, float* second, long long part_stride) {
-  static const hipError_t attr = hipFuncSetAttribute((const void*)ksplit_kernel<DT, AO, TOP2>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_lds_bytes());
-  if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((ksplit_kernel<DT, AO, TOP2>), g, dim3(kKsThreads), ks_lds_bytes(), s, Wf, bias, n_heads, yq, y_stride, VT16, KS,
                      V, n_rows_dev, n_rows, max_parts, R_pad, partials, second, part_stride);
   return hipGetLastError();
 }
 
 }  // namespace
+
+hipError_t ksplit_prepare() {
+  for (const void* fn : {(const void*)ksplit_kernel<DtBf16, false, true>, (const void*)ksplit_kernel<DtBf16, true, false>,
+                         (const void*)ksplit_kernel<DtBf16, false, false>, (const void*)ksplit_kernel<DtF32, true, false>,
+                         (const void*)ksplit_kernel<DtF32, false, false>}) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_lds_bytes());
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 int ksplit_pass_tiles(const eh_ctx* c) {
   const int slices = std::min({c->num_cu > 0 ? c->num_cu : 256, kMaxParts, c->VT});
