@@ -4,9 +4,10 @@ on a threshold and beside it (strict H < tau, Sections 3.4.2 and 4.3.1), heads t
 no live row, rows with NaN / Inf hidden states, the persistent kernel's give-up path, and the
 calibration level met exactly (Section 3.4.1).
 
-Row counts pick the kernel: at most 16 rows run the persistent kernel, more the batched ones
-(bf16: 32-row blocks, one or two per wave; fp32: 16-row blocks); heads with a bias vector take
-the plain streaming kernel at any row count.
+Row counts pick the kernel: at most 16 rows run the decode kernel, more the batched ones (up to 64
+rows, and heads with a bias vector at any number, the k-split projection; beyond, bf16 in 32-row
+blocks, one or two per wave, fp32 in 16-row blocks).  Cascades of bf16 heads of 17 to 60 + d / 22 rows
+(at least 64) and verifications of up to 64 positions run in one persistent launch.
 """
 import math
 
@@ -423,7 +424,7 @@ def test_persistent_kernel_gives_up_cleanly_and_recovers(B):
 
 @pytest.mark.parametrize("mode", ["cascade", "verify"])
 def test_rows_kernel_gives_up_cleanly_and_recovers(B, mode):
-    """The same for the persistent kernel behind 17 .. 256 rows (cascade and verification)."""
+    """The same for the persistent kernel behind 17 .. 64 rows (cascade and verification)."""
     w = G.Workload("giveup", d=256, V=20000, n_heads=5, rows=48, dtype="bf16", seed=8, kappa=0.6)
     heads = G.make_heads(w, DEV)
     hid = G.make_hidden(w, heads, DEV)
@@ -495,7 +496,7 @@ def test_calibrate_level_at_the_boundary(B):
 def test_few_rows_of_a_wide_model_run_the_persistent_cascade(B, rows):
     """The single-launch kernel for at most 16 rows stops at hidden size 2048; beyond it (the 2.8B
     shape of the batched configurations has 2560) a cascade or a verification of few rows is served
-    by the kernel for up to 256 rows, in one launch as well.  Parity as for any cascade; that it is
+    by the persistent kernel for more rows, in one launch as well.  Parity as for any cascade; that it is
     that kernel which ran shows in its bounded wait giving up when told to poll zero times."""
     w = G.Workload("wide", d=2176, V=3000, n_heads=5, rows=rows, dtype="bf16", seed=40 + rows, kappa=0.6)
     heads = G.make_heads(w, DEV)
@@ -552,13 +553,14 @@ def test_few_rows_of_a_wide_model_run_the_persistent_cascade(B, rows):
     B.eh_destroy(ctx)
 
 
-# ------------------------------------------------------------------ every block layout of the rows kernel
+# ------------------------------------------------------------------ every block layout of a cascade
 @pytest.mark.parametrize("rows", [17, 33, 97, 129, 161, 193, 225, 256])
 def test_cascade_across_block_layouts(B, rows):
-    """1 to 8 blocks of 32 rows on the four waves of the kernel for 17 .. 256 rows (no block, one
-    or two per wave), shrinking from head to head as rows leave on the 10 / 40 / 70 % schedule, so
-    that the layout changes inside one launch; the oracle on every row, and the same launch
-    twice for a bitwise repeat (the list of live rows is built through atomics)."""
+    """1 to 8 blocks of 32 rows: one and two on the persistent k-split kernel (17 and 33 rows), more on
+    the four waves of the batched kernel behind a cascade of two launches per head (d = 160: from 68
+    rows), no block, one or two per wave, shrinking from head to head as rows leave on the
+    10 / 40 / 70 % schedule; the oracle on every row, and the same call twice for a bitwise repeat (the
+    list of live rows is built through atomics)."""
     w = G.Workload("blocks", d=160, V=2500, n_heads=7, rows=rows, dtype="bf16", seed=900 + rows, kappa=0.6)
     heads = G.make_heads(w, DEV)
     hid = G.make_hidden(w, heads, DEV)
@@ -582,4 +584,114 @@ def test_cascade_across_block_layouts(B, rows):
     assert len(set(ex.tolist())) >= 4
     assert torch.equal(ex, outs[1][0]) and torch.equal(tok, outs[1][1])
     assert torch.equal(Hout.view(torch.int32), outs[1][2].view(torch.int32))
+    B.eh_destroy(ctx)
+
+
+# ------------------------------------------------------------------ the persistent kernel above 64 rows
+@pytest.mark.parametrize("d,rows", [(1024, 106), (2560, 65), (2560, 97), (2560, 129), (2560, 161), (2560, 176)])
+def test_persistent_cascade_above_64_rows(B, d, rows):
+    """Wide models run cascades of 65 to 60 + d / 22 rows in one launch whose waves share weights
+    through LDS: 3 to 6 blocks of 32 rows on four waves, shrinking as rows leave; ties at the top, a NaN
+    row, a bitwise repeat, and the bounded wait giving up, which shows that it is that kernel."""
+    n, pair = 5, (100, 2900)
+    w = G.Workload("rows65", d=d, V=3000, n_heads=n, rows=rows, dtype="bf16", seed=60 + rows, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    full = P.oracle_all_heads(heads, hid.h, True)
+    tau = G.tau_for_schedule(full[0], n)
+
+    def cascade(ctx, want_H=True):
+        ex = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+        tok = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+        H = torch.zeros((n, rows), device=DEV) if want_H else None
+        nev = torch.zeros(1, dtype=torch.int64, device=DEV)
+        B.eh_cascade(ctx, hid.h, rows, ex, tok, H, nev)
+        torch.cuda.synchronize()
+        return ex, tok, H, nev
+
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows)
+    a = cascade(ctx)
+    B.eh_check(ctx)
+    b = cascade(ctx)
+    B.eh_check(ctx)
+    P.compare_cascade(f"rows{rows}", *a[:3], full[0], full[2], full[3], tau, [])
+    assert int(a[3]) == int((a[0].long() + 1).sum()) and len(set(a[0].tolist())) >= 4
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2].view(torch.int32), b[2].view(torch.int32))
+    # zero polls: only the persistent kernel can give up; finished rows are right, the others -1
+    B.eh_set_spin_limit(ctx, 0)
+    failures = 0
+    for _ in range(3):
+        ex, tok, _, _ = cascade(ctx, want_H=False)
+        try:
+            B.eh_check(ctx)
+        except B.EhError as e:
+            failures += 1
+            assert e.status == 5
+        done = ex >= 0
+        assert torch.equal(ex[done], a[0][done]) and torch.equal(tok[done], a[1][done])
+        assert (ex[~done] == -1).all() and (tok[~done] == -1).all()
+    assert failures >= 1, "zero polls never made a workgroup give up"
+    B.eh_set_spin_limit(ctx, 1 << 22)
+    again = cascade(ctx)
+    B.eh_check(ctx)
+    assert torch.equal(a[0], again[0]) and torch.equal(a[1], again[1])
+    B.eh_destroy(ctx)
+    # ties at the top of head 0, where every row with a finite entropy leaves; a NaN row goes to the end
+    wins = _plant_ties(w, heads, hid, [pair], True)[0]
+    bad = rows - 2
+    hid.h[:, bad, 7] = float("nan")
+    orc = P.oracle_head(hid.h[0], heads.gamma[0], heads.beta[0], heads.W[0], True)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [1e9] * (n - 1) + [float("inf")], max_rows=rows)
+    ex, tok, H, _ = cascade(ctx)
+    B.eh_check(ctx)
+    B.eh_destroy(ctx)
+    keep = [r for r in range(rows) if r != bad]
+    assert (ex[keep] == 0).all() and int(ex[bad]) == n - 1 and int(tok[bad]) == -1 and bool(torch.isnan(H[:, bad]).all())
+    P.compare_head("rows tie", H[0, keep], torch.from_numpy(orc[1][keep]), tok[keep], tuple(x[keep] for x in orc), [])
+    tied = [r for r in wins if r != bad and orc[3][r] == 0.0 and orc[2][r] == pair[0]]
+    assert len(tied) >= 1 and all(int(tok[r]) == pair[0] for r in tied)
+
+
+# ------------------------------------------------------------------ live rows across groups of 256
+@pytest.mark.parametrize("rows", [300, 400, 513])
+def test_cascade_whose_live_rows_cross_256(B, rows):
+    """The batched kernel shares its grid out between the groups of 256 rows that are live (here 2 or
+    3, then fewer as rows leave), and kernel and merge work the number of partial statistics out on
+    their own: V is large enough for the number to change with every group."""
+    n = 6
+    w = G.Workload("cross", d=64, V=9001, n_heads=n, rows=rows, dtype="bf16", seed=rows, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    full = P.oracle_all_heads(heads, hid.h, True)
+    tau = G.tau_for_schedule(full[0], n)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows)
+    ex = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+    tok = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+    for _ in range(2):                                        # the second call meets the first one's partials
+        H = torch.zeros((n, rows), device=DEV)
+        nev = torch.zeros(1, dtype=torch.int64, device=DEV)
+        B.eh_cascade(ctx, hid.h, rows, ex, tok, H, nev)
+        torch.cuda.synchronize()
+        P.compare_cascade(f"cross{rows}", ex, tok, H, full[0], full[2], full[3], tau, [])
+        assert int(nev) == int((ex.long() + 1).sum())
+    live = [int((ex >= l).sum()) for l in range(n)]
+    assert len({(x + 255) // 256 for x in live}) >= 2, live
+    B.eh_destroy(ctx)
+
+
+def test_eval_at_live_counts_around_256(B):
+    R = 400
+    w = G.Workload("live256", d=64, V=9001, n_heads=1, rows=R, dtype="bf16", seed=12)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    orc = P.oracle_head(hid.h[0], heads.gamma[0], heads.beta[0], heads.W[0], True)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=R)
+    idx = torch.randperm(R, generator=torch.Generator().manual_seed(4)).to(torch.int32)
+    for n in (0, 1, 255, 256, 257, 400):
+        H, lse, am = _outs(R)
+        B.eh_eval(ctx, 0, hid.h[0], R, H, lse, am, row_idx=idx.to(DEV), n_rows_dev=torch.tensor([n], dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        if n:
+            P.compare_head(f"live{n}", H[:n], lse[:n], am[:n], tuple(x[idx[:n].numpy()] for x in orc), [])
+        assert bool(torch.isnan(H[n:]).all()) and bool(torch.isnan(lse[n:]).all()) and bool((am[n:] == -7).all())
     B.eh_destroy(ctx)

@@ -77,7 +77,7 @@ def test_ksplit_projection(B, dtype, bias, V, d, R):
         P.compare_head(f"ks{l}", *got, orc, [])
         # half of the rows, gathered backwards, the count on the device: the same bits, the rest untouched
         n = (R + 1) // 2
-        if n * 2 > R + 1 or R <= 16 and not bias:
+        if R <= 16 and not bias:
             continue
         idx = torch.arange(R - 1, -1, -1, dtype=torch.int32, device=DEV)
         sub = _eval(B, ctx, l, hid.h[l], R, row_idx=idx, n_rows_dev=torch.tensor([n], dtype=torch.int32, device=DEV))
@@ -161,10 +161,13 @@ def test_persistent_cascade_and_verification_up_to_64_rows(B, rows, V, d):
     acc, nxt, tgt = _ints(Bsz), _ints(Bsz), _ints(Bsz, 4)
     B.dssd_verify(ctx, hid.h[4].reshape(Bsz, 4, d).contiguous(), draft, None, acc, nxt, tgt)
     B.eh_check(ctx)
-    if (full[3][4] >= P.NEAR_TIE).all():
-        assert torch.equal(tgt, want)
-        assert acc[::2].eq(k).all() and acc[1::2].eq(1).all()
-        assert torch.equal(nxt, want.gather(1, acc[:, None].long())[:, 0])
+    clear = torch.from_numpy((full[3][4] >= P.NEAR_TIE).reshape(Bsz, 4)).to(DEV)
+    assert torch.equal(tgt[clear], want[clear])
+    sure = clear.all(dim=1)                                   # a near tie at the top may go either way
+    assert int(sure.sum()) >= Bsz - 2
+    stop = torch.where(torch.arange(Bsz, device=DEV) % 2 == 0, k, 1)
+    assert torch.equal(acc[sure].long(), stop[sure])
+    assert torch.equal(nxt[sure], want.gather(1, stop[:, None])[:, 0][sure])
     B.eh_destroy(ctx)
 
 
