@@ -21,11 +21,13 @@
  *     and so leaves at the last head.  This is defined behaviour, not an error.
  *     Weights, gamma and beta must be finite.
  *   - Two kinds of call run a persistent kernel whose workgroups wait for each
- *     other, one workgroup per compute unit: every call with at most 16 rows (heads
- *     without a bias vector, d up to 2048 for bf16 / 1024 for fp32), and eh_cascade
- *     and dssd_verify with up to 256 rows that the first kind does not serve (bf16
- *     heads without a bias vector: 17 rows and more, and fewer at d above 2048; which
- *     of them take one launch and which take several depends on the sizes).  The
+ *     other, one workgroup per compute unit, both for heads without a bias vector:
+ *     eh_eval, eh_eval_heads, eh_cascade and dssd_draft with at most 16 rows (d up to
+ *     2048 for bf16 / 1024 for fp32; a context with V below 16 * compute units runs
+ *     it on fewer workgroups); and, bf16, what that leaves of eh_cascade with up to
+ *     R rows (and of dssd_draft at d above 2048) and of dssd_verify with up to 64
+ *     positions B * (k+1), of which up to 16 only at d above 2048.  R is
+ *     26 + V * (d + 620) / 10^6, rounded down, but at least 64 and at most 256.  The
  *     stream must have the device to itself while such a call runs (no other kernel
  *     holding compute units on another stream or from another context).  eh_create
  *     checks that the grids fit the empty device.  Every wait is bounded
@@ -34,8 +36,9 @@
  *     Such a launch also carries a tag (and, for dssd_verify, a choice of control
  *     block) that the host advances with every call, so these calls must be made
  *     anew each time: recording one into a HIP graph and replaying the graph is not
- *     supported.  eh_eval, eh_eval_heads, eh_eval_heads_metrics and eh_exit_decide
- *     with more than 16 rows, and eh_eval_noalloc with any number, carry no such state.
+ *     supported.  Calls that run none of the two (eh_eval and eh_eval_heads with more
+ *     than 16 rows, eh_eval_heads_metrics, eh_exit_decide and eh_eval_noalloc with any
+ *     number, eh_cascade and dssd_verify beyond the sizes above) carry no such state.
  */
 #ifndef EH_H_
 #define EH_H_
@@ -350,9 +353,9 @@ eh_status eh_calibrate(eh_ctx* ctx, const float* H, const int32_t* pred, const i
 
 /*
  * Waits for `stream` and reports failures that only the device can see: the
- * persistent kernels (calls with at most 16 rows; eh_cascade and dssd_verify with up
- * to 256 rows) wait for other workgroups with a bounded spin, and a call that gave
- * up sets a flag in the context.
+ * persistent kernels (see the general conventions for the calls that run one) wait
+ * for other workgroups with a bounded spin, and a call that gave up sets a flag in
+ * the context.
  * Returns EH_ERR_HIP if the flag is set (or if the synchronisation fails) and
  * clears it: outputs of rows the failed call did not finish hold -1 (exit_layer,
  * token, argmax) or NaN (H, lse), later calls run normally.
@@ -361,9 +364,9 @@ eh_status eh_check(eh_ctx* ctx, void* stream);
 
 /*
  * Bound of the persistent kernels' waits (the cascade of Section 3.4.2 and the
- * verification of Section 4.3.1 at up to 256 rows): the number of polls of another
- * workgroup's record or counter after which a workgroup gives up (each poll is followed by a short sleep; the default, 2^22, is several
- * seconds).  polls >= 0; 0 makes a workgroup give up at its first unanswered poll,
+ * verification of Section 4.3.1): the number of polls of another workgroup's record
+ * or counter after which a workgroup gives up (each poll is followed by a short
+ * sleep; the default, 2^22, is several seconds).  polls >= 0; 0 makes a workgroup give up at its first unanswered poll,
  * which is how the failure path is tested without hanging anything.
  */
 eh_status eh_set_spin_limit(eh_ctx* ctx, int32_t polls);

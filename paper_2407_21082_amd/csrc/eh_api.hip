@@ -185,16 +185,23 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // the decode kernel where the context has one, and here otherwise).
 //
 // A verification: up to 64 positions.  Beyond, its one head cannot hide the LayerNorm and the hand-over
-// in front of its weights, and three launches are faster (d = 2560 / 1024, us, one launch against
-// three: 90 positions 78 / 43 against 65 / 34, 144 89 / 46 against 72 / 38, 252 105 / 54 against 87 / 42).
+// in front of its weights, and three launches are faster (V = 50304, d = 2560 / 1024, us, one launch
+// against three: 90 positions 78 / 43 against 65 / 34, 144 89 / 46 against 72 / 38, 252 105 / 54 against
+// 87 / 42).
 //
 // A cascade: as long as the two launches per head and the gaps between them cost more than the
 // service workgroups, whose time grows with the rows, cost the streaming ones; the longer a head's
-// stream, the more rows that is.  10 heads, us, one launch against two per head: d = 768 100 rows
-// 299 / 299, 128 322 / 304; d = 1024 100 331 / 338, 128 355 / 344, 256 520 / 419; d = 2048 128 483 / 515,
-// 160 550 / 537, 256 705 / 625; d = 2560 160 633 / 651, 200 707 / 688, 256 806 / 740.
+// stream, the more rows that is.  Rows at which 10 heads take the same time either way (measured at
+// 68 to 200 rows), d = 512 / 1024 / 1536 / 2048 / 2560: V = 50304 88 / 104 / 143 / 161 / 198, V = 40001
+// 75 / 90 / 103 / 126 / 153, V = 32000 66 / 85 / 93 / 106 / 135; the line drawn is within 10 rows of
+// them, 3 % of a call's time.  To either side, one launch against two per head, us: V = 50304, d = 1024, 80
+// rows 297 / 328, 160 rows 391 / 353; d = 2560, 128 rows 553 / 630; V = 32000, d = 2048, 80 rows 334 / 381,
+// 160 rows 450 / 402.
+int rows_most(const eh_ctx* c) {
+  return (int)std::min<int64_t>(kRowsMax, std::max<int64_t>(64, 26 + (int64_t)c->V * (c->d + 620) / 1000000));
+}
 bool use_rows(const eh_ctx* c, int64_t n_rows, bool verify) {
-  const int most = verify ? 64 : std::min(kRowsMax, std::max(64, 60 + c->d / 22));
+  const int most = verify ? 64 : rows_most(c);
   return c->rows_grid > 0 && (n_rows > 16 || c->decode_grid == 0) && n_rows >= 1 && n_rows <= most &&
          n_rows <= c->max_rows;
 }
@@ -341,9 +348,9 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
     if ((e = gemm32_prepare()) != hipSuccess) return bail(e, "gemm32_prepare");
     if ((e = ksplit_prepare()) != hipSuccess) return bail(e, "ksplit_prepare");
     if (c->rows_grid > 0 && (c->max_rows > 16 || c->decode_grid == 0)) {
-      // workspace of the persistent kernel for 17 .. 256 rows: one activation buffer per head (plus
-      // the blocks a wave may read past the last live one), two sets of partial statistics
-      const int rmax = std::min(c->R_pad_max, kRowsMax);
+      // workspace of the persistent kernel for as many rows as it may get: one activation buffer per
+      // head (plus the blocks a wave may read past the last live one), two sets of partial statistics
+      const int rmax = std::min(c->R_pad_max, round_up(rows_most(c), 32));
       c->rows_y_stride = (long long)(rmax / 16 + 32) * c->KS * kWave;
       c->rows_ctl_ints = rows_control_ints(c->n_heads);
       if ((e = dev_alloc(c, &c->rows_y, (size_t)c->n_heads * c->rows_y_stride)) != hipSuccess) return bail(e, "hipMalloc(rows)");

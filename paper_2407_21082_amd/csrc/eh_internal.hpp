@@ -55,7 +55,7 @@ struct eh_ctx {
   int spin_limit = 1 << 22;                 // polls of another workgroup's record before giving up
   unsigned long long* dec_trace = nullptr;  // [n_heads][16] timestamps of workgroup 0 (diagnostics)
   int dec_trace_on = 0;
-  // persistent kernel for 17 .. 256 rows (bf16, no bias): 0 = shape not supported
+  // persistent kernel for cascades and verifications of few rows (bf16, no bias): 0 = shape not supported
   int rows_grid = 0;
   int* rows_ctl = nullptr;             // control block (counters, live-row masks), cleared before each launch
   int* rows_vctl = nullptr;            // two control blocks of a verification, used in turn: a launch clears the other one
@@ -64,8 +64,8 @@ struct eh_ctx {
   int rows_ctl_ints = 0;
   eh::frag_t* rows_y = nullptr;        // [n_heads][rows_y_stride] activations, one buffer per head
   long long rows_y_stride = 0;         // fragments
-  eh::frag_t* rows_part4 = nullptr;    // [2][rows_grid][256] partial statistics of two consecutive heads: (m, S, U, zb)
-  int* rows_parti = nullptr;           // [2][rows_grid][256]: ib
+  eh::frag_t* rows_part4 = nullptr;    // [2][rows_grid][rows] partial statistics of two consecutive heads: (m, S, U, zb)
+  int* rows_parti = nullptr;           // [2][rows_grid][rows]: ib
   void* static_scratch = nullptr;  // device address of the library's static workspace on this device
   std::vector<void*> allocs;
   std::string err = "";
@@ -104,8 +104,9 @@ struct DecodeParams {
   unsigned long long* trace;    // nullable: [n_heads][16] wall-clock stamps written by workgroup 0
 };
 
-// Arguments of the persistent kernel for 17 .. 256 rows (bf16 heads without a bias vector):
-// heads l0 .. l1-1 of a cascade (mode 0) or the model's head of a verification (mode 1).
+// Arguments of the persistent kernels for few rows (bf16 heads without a bias vector): heads
+// l0 .. l1-1 of a cascade (mode 0, at most kRowsMax rows) or the model's head of a verification (mode 1,
+// at most 64 positions).
 constexpr int kRowsMax = 256;
 struct RowsParams {
   const frag_t* const* Wf;

@@ -6,8 +6,9 @@ calibration level met exactly (Section 3.4.1).
 
 Row counts pick the kernel: at most 16 rows run the decode kernel, more the batched ones (up to 64
 rows, and heads with a bias vector at any number, the k-split projection; beyond, bf16 in 32-row
-blocks, one or two per wave, fp32 in 16-row blocks).  Cascades of bf16 heads of 17 to 60 + d / 22 rows
-(at least 64) and verifications of up to 64 positions run in one persistent launch.
+blocks, one or two per wave, fp32 in 16-row blocks).  Cascades of bf16 heads of 17 to
+26 + V (d + 620) / 10^6 rows (at least 64) and verifications of up to 64 positions run in one persistent
+launch.
 """
 import math
 
@@ -557,8 +558,7 @@ def test_few_rows_of_a_wide_model_run_the_persistent_cascade(B, rows):
 @pytest.mark.parametrize("rows", [17, 33, 97, 129, 161, 193, 225, 256])
 def test_cascade_across_block_layouts(B, rows):
     """1 to 8 blocks of 32 rows: one and two on the persistent k-split kernel (17 and 33 rows), more on
-    the four waves of the batched kernel behind a cascade of two launches per head (d = 160: from 68
-    rows), no block, one or two per wave, shrinking from head to head as rows leave on the
+    the four waves of the batched kernel behind a cascade of two launches per head, no block, one or two per wave, shrinking from head to head as rows leave on the
     10 / 40 / 70 % schedule; the oracle on every row, and the same call twice for a bitwise repeat (the
     list of live rows is built through atomics)."""
     w = G.Workload("blocks", d=160, V=2500, n_heads=7, rows=rows, dtype="bf16", seed=900 + rows, kappa=0.6)
@@ -588,13 +588,16 @@ def test_cascade_across_block_layouts(B, rows):
 
 
 # ------------------------------------------------------------------ the persistent kernel above 64 rows
-@pytest.mark.parametrize("d,rows", [(1024, 106), (2560, 65), (2560, 97), (2560, 129), (2560, 161), (2560, 176)])
-def test_persistent_cascade_above_64_rows(B, d, rows):
-    """Wide models run cascades of 65 to 60 + d / 22 rows in one launch whose waves share weights
-    through LDS: 3 to 6 blocks of 32 rows on four waves, shrinking as rows leave; ties at the top, a NaN
-    row, a bitwise repeat, and the bounded wait giving up, which shows that it is that kernel."""
+@pytest.mark.parametrize("d,V,rows", [(4096, 16384, 65), (4096, 16384, 97), (4096, 16384, 103), (6656, 20000, 129),
+                                      (6656, 20000, 171), (1024, 50304, 108)])
+def test_persistent_cascade_above_64_rows(B, d, V, rows):
+    """Where a head's stream is long, cascades of 65 to 26 + V (d + 620) / 10^6 rows run in one launch
+    whose waves share weights through LDS: 3 to 6 blocks of 32 rows on four waves (the largest of each
+    shape among them), shrinking as rows leave; LayerNorm in registers and (d above 4096) from memory;
+    ties at the top, a NaN row, a bitwise repeat, and the bounded wait giving up, which shows that it is
+    that kernel."""
     n, pair = 5, (100, 2900)
-    w = G.Workload("rows65", d=d, V=3000, n_heads=n, rows=rows, dtype="bf16", seed=60 + rows, kappa=0.6)
+    w = G.Workload("rows65", d=d, V=V, n_heads=n, rows=rows, dtype="bf16", seed=60 + rows, kappa=0.6)
     heads = G.make_heads(w, DEV)
     hid = G.make_hidden(w, heads, DEV)
     full = P.oracle_all_heads(heads, hid.h, True)
