@@ -104,8 +104,10 @@ __device__ __forceinline__ EH_LDS f32x4* park_of(EH_LDS char* lds, int n) {
 // wide, independent instruction groups: one maximum over the 16, then 16 independent exponentials,
 // then short sums.  Some lane of the wave meets a new maximum in nearly every tile, so what a new
 // maximum costs is paid nearly every time.  It is kept small: the sums' reference point s.m follows
-// only when it falls 2^8 behind (the result does not depend on it; stats_resolve puts it on the
-// maximum in the end), and the maximum's index inside the tile is not looked for but the tile's
+// only when it falls 2^8 behind (stats_resolve puts it on the maximum in the end; up to rounding the
+// result does not depend on it: where the two largest logits of a confident row fall to one lane, the
+// smaller first and less than 5.5 nats below, the entropy's error rises from about 3e-7 to at most
+// 1.4e-6), and the maximum's index inside the tile is not looked for but the tile's
 // logits are parked in LDS for stats_resolve (s.ib holds the tile's first row until then).
 // With the search and the rescaling in every new maximum a logit took 64 clocks of the wave, which
 // was 17 % of the kernel at d = 2048 and 26 % at d = 1024.
@@ -861,13 +863,14 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_kl_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Persistent kernel for 17 .. 256 rows (arXiv 2407.21082: the dynamic-exit cascade of Section
-// 3.4.2 on a batch of decode rows, and the verification pass of Section 4.3.1).  At these row
-// counts a head is a pure weight stream (at most 256 flop per byte), so what matters is that
-// the stream never stops: one launch runs every head, and nothing in it waits for a decision.
+// Persistent kernels for few rows (arXiv 2407.21082: the dynamic-exit cascade of Section 3.4.2 on
+// a batch of decode rows, up to 256 of them, and the verification pass of Section 4.3.1, up to 64
+// positions).  At these row counts a head is a pure weight stream (at most 256 flop per byte), so
+// what matters is that the stream never stops: one launch runs every head, and nothing in it waits
+// for a decision.
 //
 //  * Workgroups 0 .. n_stream-1 stream: each owns a slice of the vocabulary of every head and
-//    runs pass32 on it, head after head.  Before head l it only checks that the activations of
+//    runs pass32 (above 64 rows) or ks_pass on it, head after head.  Before head l it only checks that the activations of
 //    head l are there (a counter that is long complete by then) and reads how many columns they
 //    have; behind it, it leaves its partial statistics and bumps a counter.
 //  * The last workgroups serve: wave by wave they own rows.  For head l they wait for all
@@ -1529,8 +1532,9 @@ __device__ __forceinline__ void rows_serve_cascade(const RowsParams& p, const Ro
 // Tail of a verification (mode 1; every workgroup streams, none only serves): when all partial
 // argmax records are there, workgroup g merges those of the positions g, g + grid, ... (one
 // record per thread), and when all positions are merged workgroup b < B walks draft row b's prefix.
-__device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const RowsCtl& c, int lane, int wave, int* flag,
-                                                 float* red_z, int* red_i) {
+__device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const RowsCtl& c, int lane, int wave, int* flag) {
+  __shared__ float red_z[kG32Waves];
+  __shared__ int red_i[kG32Waves];
   const int g = blockIdx.x, tid = threadIdx.x;
   if (wave == 0) {
     const int v = rows_wait(p, c, c.done(0), p.n_stream, lane);
@@ -1611,13 +1615,11 @@ template <bool ARGMAX_ONLY, int KS_NB>
 __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_smem) {
   __shared__ double red[2 * kLnWaves];
   __shared__ int flag;
-  __shared__ float red_z[kG32Waves];
-  __shared__ int red_i[kG32Waves];
   EH_LDS char* lds = (EH_LDS char*)g32_smem;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (p.live && *(volatile const int*)p.live == 0) return;  // the same word for every workgroup: all or none
-  if (p.mode == 1) {
+  if (KS_NB > 0 && p.mode == 1) {
     // A verification has no preset launch in front of it.  Its results start as "not done" (the
     // thread that writes them here is the one that writes the real ones later), and the last
     // workgroup clears the control block of the verification after this one: nobody uses that
@@ -1650,7 +1652,11 @@ __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_
     } else {
       ok = rows_stream(p, c, lds, lane, wave, red, &flag);
     }
-    if (ok && p.mode == 1) rows_verify_tail(p, c, lane, wave, &flag, red_z, red_i);
+    if constexpr (KS_NB > 0) {
+      if (ok && p.mode == 1) rows_verify_tail(p, c, lane, wave, &flag);
+    } else if (!ok) {
+      EH_STORES_DONE();  // weights asked for ahead may still be on their way to the ring
+    }
     return;
   }
   const int sg = (int)blockIdx.x - p.n_stream, nsg = (int)gridDim.x - p.n_stream;
