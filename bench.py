@@ -44,12 +44,12 @@ HBM_PEAK_GBS = 8000.0
 # measured bytes per launch / algorithmic bytes per launch of the same launches
 # (profiles/c1_decode_persistent_kernel.md).  Reported as that ratio times this run's
 # algorithmic bytes per launch.
-TRAFFIC_RATIO_C1 = (1.9298e9 + 1.43e6) / 1.7635e9
-# The same for the batched projection kernel (profiles/c2_calib_gemm32_kernel.md,
-# profiles/c3_dynexit_c4_verify_kernels.md): measured HBM bytes per head.
-TRAFFIC_BYTES_C2 = 271.4e6 + 1.31e6        # 206 MB of weights, read 1.3 times by the two token groups
-TRAFFIC_RATIO_C3 = (264.9e6 + 0.70e6) / 257.75e6
-TRAFFIC_RATIO_C4 = (272.4e6 + 2.32e6) / 258.29e6
+TRAFFIC_RATIO_C1 = (1.9269e9 + 1.42e6) / 1.7635e9
+# The same for the batched configurations (profiles/c2_calib_gemm32_kernel.md,
+# profiles/c3_dynexit_c4_verify_kernels.md): measured HBM bytes per head, or per verification (all three launches).
+TRAFFIC_BYTES_C2 = 240.5e6 + 1.84e6        # 206 MB of weights, read 1.17 times by the two token groups
+TRAFFIC_RATIO_C3 = (262.3e6 + 1.04e6) / 257.75e6
+TRAFFIC_RATIO_C4 = (267.3e6 + 2.46e6) / 258.29e6
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 
@@ -264,7 +264,7 @@ def bench_draft(args, torch, B, G, dev):
     avg_s = ev_s / live
     roof = {"bound": "hbm", "achieved": bytes_per_launch / avg_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS, "traffic": TRAFFIC_RATIO_C1 * bytes_per_launch,
-            "kernel": "eh::decode_kernel<DtBf16> (one live launch = one drafted position's cascade)",
+            "kernel": "eh::decode_kernel<DtBf16,true> (one live launch = one drafted position's cascade)",
             "avg_launch_us": avg_s * 1e6, "bytes_per_launch": bytes_per_launch, "launches": live}
     cpu = None
     if not args.no_cpu_baseline:
@@ -461,7 +461,7 @@ def run_c1(args, torch, B, G, dev, steps, warmup, cpu_leg, ceiling):
     roof = {"bound": "hbm", "achieved": bytes_per_launch / avg_s / 1e9, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS,
             "traffic": TRAFFIC_RATIO_C1 * bytes_per_launch,
-            "kernel": "eh::decode_kernel<DtBf16> (one launch = one decode step's cascade)",
+            "kernel": "eh::decode_kernel<DtBf16,true> (one launch = one decode step's cascade)",
             "avg_launch_us": avg_s * 1e6, "bytes_per_launch": bytes_per_launch, "launches": launches}
     cfg = {"workload": "c1_decode: d=1024 V=50304 24 heads batch-1 bf16, "
                        f"{n_dec} decode steps per bench step, exit at first H<tau",
