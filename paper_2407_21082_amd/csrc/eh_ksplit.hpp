@@ -19,8 +19,10 @@
 //   8 heads x 64 rows, d = 2560, bf16    52.8 -> 45.3 per head (4.9 -> 5.7 TB/s of weights)
 //   8 heads x 32 rows, d = 1024, bf16    23.7 -> 18.4 per head (4.3 -> 5.6 TB/s)
 //   one call of 48 rows, d = 768, bf16 with a bias vector   56.5 -> 31.7 (LayerNorm and merge included)
-//   one call of 512 rows, d = 1024, bf16 with a bias vector  474 -> 112
+//   one call of 512 rows, d = 1024, bf16 with a bias vector  474 -> 122
 //   6 heads x 32 rows, d = 512, fp32 cascade                 273 -> 211
+// (single calls repeated on the same head, whose weights then stay in the 256 MB last-level cache; on
+// weights met for the first time the call on 48 rows gains 1.24 times, not 1.7)
 //
 // Operands: v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32 on the same 16 bytes per
 // lane.  Weights stay in the one layout the library has (fragments of 16 rows); the lane

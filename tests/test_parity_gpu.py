@@ -683,7 +683,7 @@ def _safe_tau(H, q, margin=5e-3):
 @pytest.mark.parametrize("dtype,d", [("bf16", 256), ("f32", 256), ("bf16", 2176)])
 def test_dssd_draft_matches_oracle(B, dtype, d):
     """d = 2176 is beyond the single-row kernel: the positions' cascades then run the persistent
-    kernel for up to 256 rows, with the same controller behind each."""
+    persistent kernel for more rows, with the same controller behind each."""
     # the planted direction's pull grows with sqrt(d): scaled back so that the entropies spread as at d = 256
     w, heads, hid, (H, _, am, gap) = _draft_case(dtype, seed=2024, d=d, kappa=0.25 * math.sqrt(256 / d))
     Ht, amt = H.T, am.T                                     # [position][head]
