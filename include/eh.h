@@ -343,7 +343,7 @@ eh_status eh_head_losses(eh_ctx* ctx, int32_t head, const void* h_head, int64_t 
  * bins were large enough.  They are unless the proportion stays within a hair of a
  * level over a wide range of thresholds (or M > 2^27); the call then sorts all tokens
  * instead.  The results are the same either way, and are complete in tau_out and
- * n_exit_out when the call returns.  Uses about 5.2 * M bytes + 8 MiB of scratch
+ * n_exit_out when the call returns.  Uses about 5.2 * M bytes + 10 MiB of scratch
  * memory (20 * M when it sorts) that the context keeps until eh_destroy; a call that
  * needs more than any before grows it, which synchronises the device.
  */

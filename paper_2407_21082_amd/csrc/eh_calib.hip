@@ -10,9 +10,9 @@
 //
 // R/C is not monotone in v, so there is nothing to bisect; but only the largest
 // qualifying v is wanted, and whole ranges of v can be ruled out from counts alone.
-// The entropies become order-preserving 32-bit keys, and the key range that the data
-// occupies is cut three times: into up to 8192 bins, each of those into up to 2048,
-// each of those into up to 256 single keys.  A bin whose tokens number cnt, cor of
+// The entropies become order-preserving 32-bit keys, which are cut three times: into 8192
+// bins over the range of a sample of the tokens and 8192 more outside it, each of those into
+// up to 2048, each of those into up to 512 single keys.  A bin whose tokens number cnt, cor of
 // them correct, on top of C0 tokens and R0 correct ones below it, holds
 //   - a top candidate (its largest key) with exactly C = C0 + cnt, R = R0 + cor, and
 //   - inner candidates whose proportion is at most (R0 + cor) / (C0 + cor)
@@ -26,15 +26,18 @@
 // proportion; rounding is monotone, so the bound survives it.
 //
 // Passes over the tokens: one that reads entropy, prediction and reference (12 bytes),
-// packs the correctness bits and finds the key range, two that read the entropies again
-// (4 bytes each; the second sets the tokens of kept bins aside), and one over the tokens set
-// aside.  The tables are small: 128 kept bins of the first level and 1024 of the second,
+// packs the correctness bits and counts, one that reads the entropies again (4 bytes) and
+// sets the tokens of kept bins aside, and one over the tokens set aside.  2^24 tokens, 11 levels: 141 us
+// with a pass of its own for the key range, 111 now; 2^20 96 and 81, 5000 80 and 69 (eight short
+// dependent launches and the wait of the host).  The tables are small: 128 kept bins of the first level and 1024 of the second,
 // over all epsilon together.  Data that keeps more (a
 // proportion that hovers at epsilon over a wide range of thresholds) sets a flag that
 // the host reads back, and the call is then served by the full sort below it: rocPRIM's
 // radix sort of (key, correctness) pairs, a running sum, and a search of every position.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
@@ -140,21 +143,24 @@ __global__ void calib_read_kernel(const uint32_t* __restrict__ keys, const unsig
 // ---------------------------------------------------------------------------------
 // The refinement: three levels of counts instead of a sort.
 
-constexpr int kBins1 = 8192;       // bins of level 1
+constexpr int kInner = 8192;       // bins of level 1 over the key range of a sample of the tokens
+constexpr int kOuterBits = 20;     // keys outside that range: bins of 2^20 keys
+constexpr int kOuter = 1 << (32 - kOuterBits);  // of which there are this many on either side
+constexpr int kBins1 = kInner + 2 * kOuter;     // ascending: below the sample's range, inside, above
 constexpr int kBins2 = 2048;       // bins of one kept level-1 bin
-constexpr int kBins3 = 256;        // single keys of one kept level-2 bin
+constexpr int kBins3 = 512;        // single keys of one kept level-2 bin
+constexpr int kSampleWgs = 64;     // workgroups that look at kSample tokens for their key range
+constexpr int kSample = 65536;
 constexpr int kCap1 = 128;         // kept bins of level 1, all epsilon together
 constexpr int kCap2 = 1024;        // kept bins of level 2
-constexpr int kChunk = 2048;       // tokens four waves take at a time: 4 x 8 x 64 (a workgroup of 1024: four times that)
-constexpr int kStageWave = 1024;    // tokens of kept bins a wave holds back before it appends them
 constexpr int kSegment = 32768;    // tokens behind one row of level-1 partial counts (16-bit counters)
 constexpr int64_t kRefineMax = (int64_t)1 << 27;  // larger sets go to the sort (4096 partial rows)
 
-// ascending key of a non-NaN entropy (the key of the sort above, not inverted)
+// Ascending key of an entropy (that of the sort above, not inverted): -0 and +0 have one, NaNs lie
+// above all others or below them.
 __device__ __forceinline__ uint32_t ascending_key(float h) {
-  if (h == 0.f) h = 0.f;
-  const uint32_t u = __float_as_uint(h);
-  return u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+  const uint32_t u = __float_as_uint(h + 0.f);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 __device__ __forceinline__ float ascending_entropy(uint32_t asc) {
   return __uint_as_float(asc ^ ((asc >> 31) ? 0x80000000u : 0xFFFFFFFFu));
@@ -163,41 +169,102 @@ __device__ __forceinline__ float ascending_entropy(uint32_t asc) {
 // Device memory of one call.  Counts are pairs in one 64-bit word: tokens in the low half,
 // correct tokens in the high half.
 struct CalibWork {
-  uint64_t* bits;     // [ceil(M / 64)] correctness of token i in bit i % 64 of word i / 64
-  uint32_t* part1;    // [ceil(M / kSegment)][kBins1] level-1 counts of a segment, 16 + 16 bits
-  uint32_t* kept;     // [M] tokens of kept level-1 bins: correct << 31 | row << 20 | key bits below s
+  uint64_t* bits;     // [ceil(M / 256)][4] correctness of token 256 b + 4 i + j in bit i of word [b][j]
+  uint32_t* part1;    // [ceil(M / kSegment)][kInner] level-1 counts of a segment, 16 + 16 bits
+  uint32_t* kept;     // [M] tokens of kept level-1 bins: correct << 31 | row << 20 | key inside the bin; a
+                      // wave's share of a segment has its own part
+  int* n_aside;       // [waves] tokens in each part
+  uint2* range;       // [kSampleWgs] smallest and largest key of a share of the sample
+  int* host_flag;     // host memory: 0 if a table has proved too small
   // preset to 0
-  uint32_t* key_max;  // [1] largest key (with key_min: the range the data occupies)
-  int* n_kept;        // [3] kept bins of level 1, of level 2; tokens in `kept`
+  int* n_kept;        // [2] kept bins of level 1, of level 2
   uint64_t* h1;       // [kBins1]
   uint64_t* sel1;     // [kBins1] which epsilon keep the bin
   uint64_t* h2;       // [kCap1][kBins2]
   uint64_t* sel2;     // [kCap1][kBins2]
   uint64_t* h3;       // [kCap2][kBins3]
   // preset to -1
-  uint32_t* key_min;  // [1]
   int* overflow;      // [1] -1, or 0 once a table has proved too small
-  int* slot1;         // [kBins1] row of a kept bin in h2
+  int* row_b3;        // [kCap1] Cut::b3 of a row's level-1 bin
+  signed char* slot1; // [kBins1] row of a kept bin in h2
   int* slot2;         // [kCap1][kBins2] row of a kept bin in h3
 };
 
-// How the occupied key range [lo, hi] is cut: level 1 takes the bits above s, level 2 the
-// next b2, level 3 the last b3.
+// Inclusive prefix sums over the lanes of a wave (of each row of 16 lanes), by cross-lane moves of the vector
+// unit (through LDS, as __shfl_up goes, a trip of 60 clocks a step).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t from_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t row_inclusive(uint32_t v) {
+  v += from_lane<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
+  v += from_lane<0x112, 0xf>(v);
+  v += from_lane<0x114, 0xf>(v);
+  v += from_lane<0x118, 0xf>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t v) {
+  v = row_inclusive(v);
+  v += from_lane<0x142, 0xa>(v);  // lane 15 of a row to the next (rows 1 and 3)
+  v += from_lane<0x143, 0xc>(v);  // lane 31 to rows 2 and 3
+  return v;
+}
+// The largest value of the wave.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t max_from_lane(uint32_t v) {
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max_from_lane<0x111, 0xf>(v);
+  v = max_from_lane<0x112, 0xf>(v);
+  v = max_from_lane<0x114, 0xf>(v);
+  v = max_from_lane<0x118, 0xf>(v);
+  v = max_from_lane<0x142, 0xa>(v);
+  v = max_from_lane<0x143, 0xc>(v);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// How the keys are cut.  The range [lo, hi] of the sample has kInner bins of level 1, which take the
+// bits above s of a key's distance from lo; the few keys outside it go to the bins of 2^20 keys
+// below and above.  Level 2 takes a bin's next (at most 11) bits, level 3 the rest (at most 9).
+// The range of all tokens would leave nothing outside, but is known only after a pass over all
+// entropies, which then had to be read once more to be counted (17 us of 141 for 2^24).
 struct Cut {
-  uint32_t base;
-  int s, b2, b3;
-  bool empty;
+  uint32_t lo, hi;
+  int s;
+  // the short way to an inner bin: the bits of an entropy less lo_bits, if that is below n_plain, are its
+  // key's distance from lo (everything else, -0 and NaN too, takes the long way)
+  uint32_t lo_bits, n_plain;
+  __device__ __forceinline__ int bin(uint32_t key) const {
+    return key < lo ? (int)(key >> kOuterBits)
+                    : key > hi ? kOuter + kInner + (int)(key >> kOuterBits) : kOuter + (int)((key - lo) >> s);
+  }
+  __device__ __forceinline__ uint32_t within(uint32_t key) const {  // a key's place inside its bin
+    return key < lo || key > hi ? key & ((1u << kOuterBits) - 1u) : (key - lo) & ((1u << s) - 1u);
+  }
+  __device__ __forceinline__ bool inner(int bin) const { return bin >= kOuter && bin < kOuter + kInner; }
+  __device__ __forceinline__ uint32_t start(int bin) const {  // the smallest key of a bin
+    return inner(bin) ? lo + ((uint32_t)(bin - kOuter) << s)
+                      : (uint32_t)(bin < kOuter ? bin : bin - kOuter - kInner) << kOuterBits;
+  }
+  __device__ __forceinline__ int bits(int bin) const { return inner(bin) ? s : kOuterBits; }
+  __device__ __forceinline__ int b2(int bin) const { return min(bits(bin), 11); }
+  __device__ __forceinline__ int b3(int bin) const { return bits(bin) - b2(bin); }
 };
+// Every lane of the wave must call.
 __device__ __forceinline__ Cut cut_of(const CalibWork& w) {
+  static_assert(kSampleWgs == 64, "a share per lane");
+  const uint2 r = w.range[threadIdx.x & 63];
   Cut c;
-  const uint32_t lo = *w.key_min, hi = *w.key_max;
-  c.empty = lo > hi;
-  c.base = lo;
-  const uint32_t span = c.empty ? 0u : hi - lo;
+  c.lo = ~wave_max(~r.x);
+  c.hi = wave_max(r.y);
+  if (c.lo > c.hi) c.lo = c.hi = 0;  // no token of the sample has an entropy: all keys are above the range
+  const uint32_t span = c.hi - c.lo;
   c.s = 0;
-  while ((span >> c.s) >= (uint32_t)kBins1) ++c.s;  // at most 19
-  c.b2 = c.s < 11 ? c.s : 11;
-  c.b3 = c.s - c.b2;                                // at most 8
+  while ((span >> c.s) >= (uint32_t)kInner) ++c.s;  // at most 19
+  const bool plain = c.lo >= 0x80000000u;  // no negative entropy in the range: keys and bits of a float differ by a constant
+  c.lo_bits = c.lo ^ 0x80000000u;
+  c.n_plain = plain ? span + 1u : 0u;
   return c;
 }
 
@@ -207,186 +274,160 @@ struct Pair {
 __device__ __forceinline__ Pair operator+(Pair a, Pair b) { return Pair{a.c + b.c, a.r + b.r}; }
 __device__ __forceinline__ Pair pair_of(uint64_t v) { return Pair{(uint32_t)v, (uint32_t)(v >> 32)}; }
 
-// Exclusive prefix of one Pair per thread over the 256 threads of a workgroup; *total_c
-// receives the sum of the first members.
-__device__ __forceinline__ Pair block_exclusive(Pair v, Pair* sh /* [4] */, int* total_c = nullptr) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  Pair inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t c = __shfl_up(inc.c, o), r = __shfl_up(inc.r, o);
-    if (lane >= o) inc = inc + Pair{c, r};
-  }
-  __syncthreads();  // sh may still be read from the call before
+// proportion r / c >= eps, by the correctly rounded quotient (c > 0).  The difference r - eps c in 32 bits
+// is off by less than 4e-7 c; only where that leaves the answer open is the division worked out.
+__device__ __forceinline__ bool reaches(uint32_t r, uint32_t c, double eps, float eps32) {
+  const float fc = (float)c;
+  const float diff = __builtin_fmaf(-eps32, fc, (float)r);
+  bool yes = diff > 0.f;
+  if (fabsf(diff) <= 1e-6f * fc) yes = (double)r / (double)c >= eps;
+  return yes;
+}
+
+// A workgroup barrier that orders LDS traffic only: loads, and counts sent to memory by atomics that
+// return nothing, are not waited for.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+constexpr int kWalkWaves = 16;  // waves of the workgroups that walk a table
+
+__device__ __forceinline__ Pair wave_inclusive(Pair v) { return Pair{wave_inclusive(v.c), wave_inclusive(v.r)}; }
+
+// Exclusive prefix of one Pair per thread over a workgroup of kWalkWaves waves; *total_c
+// receives the sum of the first members.  sh: kWalkWaves entries that no call before has used.
+__device__ __forceinline__ Pair block_exclusive(Pair v, Pair* sh, int* total_c = nullptr) {
+  static_assert(kWalkWaves == 16, "a row of lanes");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Pair inc = wave_inclusive(v);
   if (lane == 63) sh[wave] = inc;
-  __syncthreads();
+  lds_barrier();
+  const Pair own = sh[lane & 15];
+  const uint32_t c = row_inclusive(own.c), r = row_inclusive(own.r);
+  if (total_c) *total_c = __builtin_amdgcn_readlane((int)c, 15);
   Pair off{0, 0};
-  for (int k = 0; k < wave; ++k) off = off + sh[k];
-  if (total_c) *total_c = (int)(sh[0].c + sh[1].c + sh[2].c + sh[3].c);
+  if (wave > 0) off = Pair{(uint32_t)__builtin_amdgcn_readlane((int)c, wave - 1), (uint32_t)__builtin_amdgcn_readlane((int)r, wave - 1)};
   return Pair{off.c + inc.c - v.c, off.r + inc.r - v.r};
 }
-__device__ __forceinline__ int block_max(int v, int* sh /* [4] */) {
-#pragma unroll
-  for (int o = 32; o; o >>= 1) {
-    const int u = __shfl_xor(v, o);
-    v = u > v ? u : v;
-  }
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int m = sh[0];
-  for (int k = 1; k < 4; ++k) m = sh[k] > m ? sh[k] : m;
-  return m;
+// The last lane's value of those that are not negative (-1: none has one).
+__device__ __forceinline__ int last_of_wave(int v) {
+  const unsigned long long any = __ballot(v >= 0);
+  return any ? __builtin_amdgcn_readlane(v, 63 - __builtin_clzll(any)) : -1;
 }
 
-struct NodeShared {
-  Pair scan[4];
-  int red[4];
-  Pair at_top;  // counts up to and including the bin that node_scan names
+// What a walk decides on one bin of counts v on top of `run`: whether a candidate inside may
+// qualify, and whether its top candidate does (its proportion is at most the bound, and so is the quotient).
+struct Verdict {
+  bool may, top;
 };
-
-// One node: nb <= 256 * PER bins of counts in ascending key order, on top of `below`.
-// Thread t looks at bins [PER * t, PER * (t + 1)).  Gives back the bins' exclusive prefixes
-// (below included).  With JUDGE also the mask of the bins that may hold a qualifying
-// candidate and, as the return value, the highest bin whose top candidate qualifies (-1:
-// none); without it the return value is -1.
-template <int PER, bool JUDGE>
-__device__ __forceinline__ int node_scan(const uint64_t* __restrict__ t, int nb, Pair below, double eps,
-                                         Pair (&pre)[PER], unsigned& may, NodeShared& sh) {
-  const int b0 = threadIdx.x * PER;
-  Pair v[PER];
-  Pair sum{0, 0};
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    v[j] = b0 + j < nb ? pair_of(t[b0 + j]) : Pair{0, 0};
-    sum = sum + v[j];
-  }
-  Pair run = block_exclusive(sum, sh.scan) + below;
-  may = 0;
-  int top = -1;
-  Pair top_incl{0, 0};
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    pre[j] = run;
-    const Pair incl = run + v[j];
-    if (JUDGE && v[j].c) {
-      const double bound = v[j].r ? (double)incl.r / (double)(run.c + v[j].r) : (double)run.r / (double)(run.c + 1u);
-      if (bound >= eps) may |= 1u << j;
-      if ((double)incl.r / (double)incl.c >= eps) {
-        top = b0 + j;
-        top_incl = incl;
-      }
-    }
-    run = incl;
-  }
-  if (!JUDGE) return -1;
-  const int best = block_max(top, sh.red);
-  if (best >= 0 && best == top) sh.at_top = top_incl;
-  __syncthreads();
-  return best;
+__device__ __forceinline__ Verdict judge(Pair run, Pair v, double eps) {
+  Verdict d{false, false};
+  if (v.c == 0) return d;
+  const float e32 = (float)eps;
+  const Pair incl = run + v;
+  d.may = reaches(v.r ? incl.r : run.r, run.c + (v.r ? v.r : 1u), eps, e32);
+  if (d.may) d.top = reaches(incl.r, incl.c, eps, e32);
+  return d;
 }
 
-// Pass 0: correctness bits and the key range.  One workgroup of 1024 per segment of kSegment
-// tokens, a wave 8 x 64 consecutive tokens at a time.
-__global__ __launch_bounds__(1024) void calib_pack_kernel(const float* __restrict__ H, const int* __restrict__ pred,
-                                                          const int* __restrict__ ref, int64_t M, CalibWork w) {
-  __shared__ uint32_t sh_lo[16], sh_hi[16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t n_groups = (M + 63) >> 6;
-  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-  constexpr int U = 8;
-  for (int k = 0; k < kSegment / (16 * U * 64); ++k) {
-    const int64_t g0 = ((int64_t)blockIdx.x * (kSegment / (16 * U * 64)) + k) * (16 * U) + wave * U;
-    float h[U];
-    int a[U], b[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = ((g0 + u) << 6) + lane;
-      const bool in = i < M;
-      h[u] = in ? H[i] : NAN;
-      a[u] = in ? __builtin_nontemporal_load(pred + i) : 0;
-      b[u] = in ? __builtin_nontemporal_load(ref + i) : 1;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const unsigned long long ok = __ballot(a[u] == b[u]);
-      if (g0 + u < n_groups && lane == 0) w.bits[g0 + u] = ok;
-      if (h[u] == h[u]) {
-        const uint32_t key = ascending_key(h[u]);
-        lo = key < lo ? key : lo;
-        hi = key > hi ? key : hi;
-      }
-    }
-  }
-#pragma unroll
-  for (int o = 32; o; o >>= 1) {
-    const uint32_t l2 = __shfl_xor(lo, o), h2 = __shfl_xor(hi, o);
-    lo = l2 < lo ? l2 : lo;
-    hi = h2 > hi ? h2 : hi;
-  }
-  if (lane == 0) {
-    sh_lo[wave] = lo;
-    sh_hi[wave] = hi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < 16; ++k) {
-      lo = sh_lo[k] < lo ? sh_lo[k] : lo;
-      hi = sh_hi[k] > hi ? sh_hi[k] : hi;
-    }
-    if (lo <= hi) {
-      atomicMin(w.key_min, lo);
-      atomicMax(w.key_max, hi);
-    }
+// A wave takes blocks of 256 consecutive tokens, four to a lane.  The arrays are only known to be
+// aligned to their elements; the hardware loads 16 bytes from there all the same.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kBlock = 256;
+constexpr int kWaveBlocks = kSegment / 16 / kBlock;  // blocks that are a wave's share of a segment
+static_assert(kWaveBlocks * 4 <= 64, "a word of correctness bits per lane");
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unrolled<N, I + 1>(static_cast<F&&>(f));
   }
 }
 
-// The tokens a lane holds of one trip: 8, from 8 consecutive groups of 64 (a workgroup of 1024
-// takes 8192 consecutive tokens per trip).
-struct Trip {
-  float h[8];
-  unsigned long long ok[8];
-};
-__device__ __forceinline__ Trip load_trip(const float* __restrict__ H, int64_t M, const CalibWork& w, int64_t trip) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t n_groups = (M + 63) >> 6;
-  Trip t;
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int64_t g = trip * (blockDim.x / 64 * 8) + wave * 8 + u;
-    const int64_t i = (g << 6) + lane;
-    t.h[u] = i < M ? H[i] : NAN;
-    t.ok[u] = g < n_groups ? w.bits[g] : 0ull;
-  }
-  return t;
-}
-// f(u, valid, key offset from the range's base, correct) for the lane's 8 tokens; `valid` is
-// false for a NaN entropy or a token past the end.
-template <class F>
-__device__ __forceinline__ void for_trip(const Trip& t, uint32_t base, F&& f) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int u = 0; u < 8; ++u) f(u, t.h[u] == t.h[u], ascending_key(t.h[u]) - base, (unsigned)((t.ok[u] >> lane) & 1ull));
-}
-
-// Pass 1: one workgroup (of 1024) per segment of kSegment tokens counts into 16 + 16 bit bins
-// of its own in LDS (no bin can hold more than the segment) and writes them out.
-__global__ __launch_bounds__(1024) void calib_count1_kernel(const float* __restrict__ H, int64_t M, CalibWork w) {
+// Pass 1: correctness bits, and the level-1 counts.  One workgroup of 1024 per segment of kSegment
+// tokens; it counts into 16 + 16 bit bins of its own in LDS (no bin can hold more than the segment),
+// writes those inside the sample's range out and adds the others' few tokens to the table of all.
+// Bound by its 12 bytes per token (2^24: 35 us, 5.8 TB/s): a wave asks for block u + kAhead before it looks
+// at block u.
+__global__ __launch_bounds__(1024) void calib_count1_kernel(const float* __restrict__ H, const int* __restrict__ pred,
+                                                            const int* __restrict__ ref, int64_t M, CalibWork w) {
   __shared__ uint32_t bins[kBins1];
-  for (int b = threadIdx.x; b < kBins1; b += 1024) bins[b] = 0;
-  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kAhead = 2;
+  const int64_t g0 = (int64_t)blockIdx.x * 16 * kWaveBlocks + wave;  // its blocks: every 16th of the segment
+  f32x4_any h[kWaveBlocks];
+  i32x4_any a[kWaveBlocks], b[kWaveBlocks];
+  auto load = [&](int u) {
+    h[u] = *(const f32x4_any*)(H + (g0 + 16 * u) * kBlock + 4 * lane);
+    a[u] = __builtin_nontemporal_load((const i32x4_any*)(pred + (g0 + 16 * u) * kBlock + 4 * lane));
+    b[u] = __builtin_nontemporal_load((const i32x4_any*)(ref + (g0 + 16 * u) * kBlock + 4 * lane));
+  };
+  auto load_some = [&](int u) {
+    const int64_t i = (g0 + 16 * u) * kBlock + 4 * lane;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      h[u][j] = i + j < M ? H[i + j] : NAN;
+      a[u][j] = i + j < M ? pred[i + j] : 0;
+      b[u][j] = i + j < M ? ref[i + j] : 1;
+    }
+  };
+  const bool whole = (int64_t)(blockIdx.x + 1) * kSegment <= M;  // uniform
   const Cut c = cut_of(w);
-  if (!c.empty)
-    for (int k = 0; k < kSegment / (4 * kChunk); ++k)
-      for_trip(load_trip(H, M, w, (int64_t)blockIdx.x * (kSegment / (4 * kChunk)) + k), c.base,
-               [&](int, bool valid, uint32_t off, unsigned ok) {
-                 if (valid) atomicAdd(&bins[off >> c.s & (kBins1 - 1)], 1u + (ok << 16));
-               });
-  __syncthreads();
-  uint32_t* out = w.part1 + (size_t)blockIdx.x * kBins1;
-  for (int b = threadIdx.x; b < kBins1; b += 1024) out[b] = bins[b];
+  if (whole) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) load(u);
+  }
+  for (int i = threadIdx.x; i < kBins1; i += 1024) bins[i] = 0;
+  lds_barrier();
+  uint32_t bits_lo = 0, bits_hi = 0;  // word 4 u + j in lane 4 u + j
+  auto count = [&](auto uc) {
+    constexpr int u = decltype(uc)::value;
+    bool odd = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool right = a[u][j] == b[u][j];
+      const unsigned long long word = __ballot(right);
+      asm("v_writelane_b32 %0, %1, %2" : "+v"(bits_lo) : "s"((uint32_t)word), "n"(4 * u + j));
+      asm("v_writelane_b32 %0, %1, %2" : "+v"(bits_hi) : "s"((uint32_t)(word >> 32)), "n"(4 * u + j));
+      const uint32_t off = __float_as_uint(h[u][j]) - c.lo_bits;
+      const bool in = off < c.n_plain;
+      odd |= !in;
+      if (in) atomicAdd(&bins[kOuter + (off >> c.s)], right ? 0x10001u : 1u);
+    }
+    if (odd) {  // rare
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (__float_as_uint(h[u][j]) - c.lo_bits >= c.n_plain && h[u][j] == h[u][j])
+          atomicAdd(&bins[c.bin(ascending_key(h[u][j]))], a[u][j] == b[u][j] ? 0x10001u : 1u);
+    }
+  };
+  if (whole) {
+    unrolled<kWaveBlocks>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      if (u + kAhead < kWaveBlocks) load(u + kAhead);
+      __builtin_amdgcn_sched_barrier(0);
+      count(uc);
+    });
+  } else {
+    unrolled<kWaveBlocks>([&](auto uc) {
+      load_some(decltype(uc)::value);
+      count(uc);
+    });
+  }
+  const int64_t block = g0 + 16 * (lane >> 2);
+  if (lane < 4 * kWaveBlocks && block * kBlock < M) w.bits[block * 4 + (lane & 3)] = (unsigned long long)bits_hi << 32 | bits_lo;
+  lds_barrier();
+  uint32_t* out = w.part1 + (size_t)blockIdx.x * kInner;
+  for (int i = threadIdx.x; i < kInner; i += 1024) out[i] = bins[kOuter + i];
+  for (int i = threadIdx.x; i < 2 * kOuter; i += 1024) {
+    const int at = i < kOuter ? i : i + kInner;
+    const uint32_t v = bins[at];
+    if (v) atomicAdd((unsigned long long*)&w.h1[at], (unsigned long long)(v & 0xFFFFu) | ((unsigned long long)(v >> 16) << 32));
+  }
 }
-// grid (kBins1 / 256, 16): each thread adds up one bin over a sixteenth of the segments.
+
+// grid (kInner / 256, 16): each thread adds up one bin over a sixteenth of the segments.
 __global__ __launch_bounds__(256) void calib_sum1_kernel(CalibWork w, int n_parts) {
   const int b = blockIdx.x * 256 + threadIdx.x;
   const int per = (n_parts + gridDim.y - 1) / gridDim.y;
@@ -394,16 +435,12 @@ __global__ __launch_bounds__(256) void calib_sum1_kernel(CalibWork w, int n_part
   uint32_t cnt = 0, cor = 0;
 #pragma unroll 8
   for (int p = p0; p < p1; ++p) {
-    const uint32_t v = w.part1[(size_t)p * kBins1 + b];
+    const uint32_t v = w.part1[(size_t)p * kInner + b];
     cnt += v & 0xFFFFu;
     cor += v >> 16;
   }
-  if (cnt) atomicAdd((unsigned long long*)&w.h1[b], (unsigned long long)cnt | ((unsigned long long)cor << 32));
+  if (cnt) atomicAdd((unsigned long long*)&w.h1[kOuter + b], (unsigned long long)cnt | ((unsigned long long)cor << 32));
 }
-
-// A workgroup barrier that orders LDS traffic only: counts sent to memory by atomics that
-// return nothing are not waited for.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // table[idx] += (1, ok) for the lanes that are `on`; lanes of a wave that name the same word
 // (tokens of one entropy value sit together in the data as often as not) add once for all.
@@ -422,16 +459,15 @@ __device__ __forceinline__ void add_counted(uint64_t* __restrict__ table, uint32
   }
 }
 
-// Keeps a bin of a level for epsilon `e`; the first to keep it gives it a row in the next table.
-__device__ __forceinline__ void keep_bin(uint64_t* sel, int* slot, int* n_kept, int cap, int* overflow, int e) {
+// Keeps a bin of a level for epsilon `e`; the first to keep it gives it a row in the next table,
+// which is returned (-1: it has one already, or there is no room).
+__device__ __forceinline__ int keep_bin(uint64_t* sel, int* n_kept, int cap, int* overflow, int e) {
   const uint64_t old = atomicOr((unsigned long long*)sel, 1ull << e);
-  if (old == 0) {
-    const int row = atomicAdd(n_kept, 1);
-    if (row < cap)
-      *slot = row;
-    else
-      *overflow = 0;
-  }
+  if (old != 0) return -1;
+  const int row = atomicAdd(n_kept, 1);
+  if (row < cap) return row;
+  *overflow = 0;
+  return -1;
 }
 
 // What the levels hand on, per epsilon: the kept bins in the order in which the next level
@@ -443,116 +479,171 @@ struct EpsWalk {
   Pair below1[kCap1];
   int n2;                  // kept level-2 bins, descending: the order of the final walk
   uint32_t at2[kList2];    // index into sel2 / slot2: row of the level-1 bin * kBins2 + bin
-  uint32_t hi2[kList2];    // the key bits above level 3: level-1 bin << b2 | bin
+  uint32_t start2[kList2]; // smallest key of the bin
+  int b3[kList2];          // bits of its keys that level 3 takes
   Pair below2[kList2];
 };
 
-// Level 1, one workgroup per epsilon.
-__global__ __launch_bounds__(256) void calib_keep1_kernel(CalibWork w, EpsList eps, EpsWalk* __restrict__ walks) {
-  __shared__ NodeShared sh;
+// Level 1, one workgroup per epsilon; thread t looks at bins [PER * t, PER * (t + 1)).  Bound by what one CU
+// issues and its trips to memory: 9.6 us for twice the bins that took 12.4 with 256 threads and two
+// divisions a bin.
+__global__ __launch_bounds__(kWalkWaves * 64) void calib_keep1_kernel(CalibWork w, EpsList eps, EpsWalk* __restrict__ walks) {
+  __shared__ Pair scan[2][kWalkWaves];
+  __shared__ int top_w[kWalkWaves];
   __shared__ int bin[kCap1];
-  constexpr int PER = kBins1 / 256;
+  constexpr int PER = kBins1 / (kWalkWaves * 64);
+  static_assert(PER * kWalkWaves * 64 == kBins1 && PER <= 32, "bins per thread");
   const int e = blockIdx.x;
+  const double ep = eps.v[e];
   EpsWalk& walk = walks[e];
-  Pair pre[PER];
-  unsigned may;
-  const int top = node_scan<PER, true>(w.h1, kBins1, Pair{0, 0}, eps.v[e], pre, may, sh);
   const int b0 = threadIdx.x * PER;
+  Pair v[PER], sum{0, 0};
+#pragma unroll
+  for (int j = 0; j < PER; ++j) v[j] = pair_of(w.h1[b0 + j]);
+  const Cut c = cut_of(w);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) sum = sum + v[j];
+  const Pair below = block_exclusive(sum, scan[0]);
+  Pair run = below;
+  unsigned may = 0;
+  int top = -1;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const Verdict d = judge(run, v[j], ep);
+    may |= (unsigned)d.may << j;
+    if (d.top) top = b0 + j;
+    run = run + v[j];
+  }
+  top = last_of_wave(top);
+  if ((threadIdx.x & 63) == 0) top_w[threadIdx.x >> 6] = top;
+  lds_barrier();
+  top = last_of_wave(top_w[threadIdx.x & 15]);  // (every row of lanes sees the waves in order)
   unsigned mine = 0;
 #pragma unroll
   for (int j = 0; j < PER; ++j) mine |= (unsigned)((may >> j & 1u) && b0 + j >= top) << j;
   int total;
-  int k = (int)block_exclusive(Pair{(uint32_t)__popc(mine), 0u}, sh.scan, &total).c;
+  int k = (int)block_exclusive(Pair{(uint32_t)__popc(mine), 0u}, scan[1], &total).c;
+  run = below;
 #pragma unroll
-  for (int j = 0; j < PER; ++j)
+  for (int j = 0; j < PER; ++j) {
     if ((mine >> j & 1u) && k < kCap1) {
       bin[k] = b0 + j;
       walk.bin1[k] = b0 + j;
-      walk.below1[k] = pre[j];
+      walk.below1[k] = run;
       ++k;
     }
+    run = run + v[j];
+  }
   if (threadIdx.x == 0) {
     walk.n1 = total < kCap1 ? total : kCap1;
     if (total > kCap1) *w.overflow = 0;
   }
-  __syncthreads();
+  lds_barrier();
   // one bin per thread: the atomics of a workgroup are in flight together
   if ((int)threadIdx.x < total && threadIdx.x < kCap1) {
     const int b = bin[threadIdx.x];
-    keep_bin(&w.sel1[b], &w.slot1[b], &w.n_kept[0], kCap1, w.overflow, e);
+    const int row = keep_bin(&w.sel1[b], &w.n_kept[0], kCap1, w.overflow, e);
+    if (row >= 0) {
+      w.slot1[b] = (signed char)row;
+      w.row_b3[row] = c.b3(b);
+    }
   }
 }
 
 // Pass 2: tokens of kept level-1 bins are counted by their next b2 bits and set aside for
-// pass 3.  One workgroup of 1024 per segment, as in pass 1.
+// pass 3.  One workgroup of 1024 per segment, as in pass 1; a wave asks for all its entropies at once
+// and sets tokens aside in a part of `kept` of its own, so that nothing waits for another wave.  2^24 tokens are 256
+// groups of 64 for each SIMD of the card, and an instruction on each of them half a microsecond, so a
+// token costs little more than its look-up: one of a kept bin (1 in 100 as a rule, but one in every
+// other group) is only put into the wave's region of LDS, and what it takes to count it is done for
+// full waves of them.  2^24 tokens: 26 us worked out group by group, 23 with full waves, of which 4 were
+// the waves' reservation in one list, 20 now: 10 to bring the entropies, 5 to look at the last of them.
+constexpr int kStageWave = 512;    // tokens of kept bins a wave holds back
 __global__ __launch_bounds__(1024) void calib_count2_kernel(const float* __restrict__ H, int64_t M, CalibWork w) {
   __shared__ __align__(16) signed char slot[kBins1];  // rows are below kCap1 = 128
-  __shared__ uint32_t stage[16][kStageWave];  // a region per wave: no barrier while the tokens stream
-  __shared__ int n_wave[16], at;
-  // everything the kernel needs before the tokens is asked for at once: the latency is paid once
+  __shared__ uint32_t stage_key[16][kStageWave];  // a region per wave: no barrier while the tokens stream
+  __shared__ uint16_t stage_row[16][kStageWave];  // row << 6 | word of its correctness bit
+  __shared__ unsigned char stage_lane[16][kStageWave];  // the bit
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t wg_wave = (int64_t)blockIdx.x * 16 + wave, g0 = (int64_t)blockIdx.x * 16 * kWaveBlocks + wave;
+  static_assert(kBins1 == 1024 * 16, "16 bytes of the table per thread");
+  const int4 table = ((const int4*)w.slot1)[threadIdx.x];
   const int ov = *w.overflow;
   const Cut c = cut_of(w);
-  {
-    constexpr int N = kBins1 / 4 / 1024;
-    int4 v[N];
+  unsigned long long bits = 0;
+  if (lane < 4 * kWaveBlocks && (g0 + 16 * (lane >> 2)) * kBlock < M) bits = w.bits[(g0 + 16 * (lane >> 2)) * 4 + (lane & 3)];
+  f32x4_any h[kWaveBlocks];
+  if ((int64_t)(blockIdx.x + 1) * kSegment <= M) {  // uniform
 #pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = ((const int4*)w.slot1)[k * 1024 + threadIdx.x];
+    for (int u = 0; u < kWaveBlocks; ++u) h[u] = *(const f32x4_any*)(H + (g0 + 16 * u) * kBlock + 4 * lane);
+  } else {
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-      char4 c4;
-      c4.x = (signed char)v[k].x, c4.y = (signed char)v[k].y, c4.z = (signed char)v[k].z, c4.w = (signed char)v[k].w;
-      ((char4*)slot)[k * 1024 + threadIdx.x] = c4;
+    for (int u = 0; u < kWaveBlocks; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t i = (g0 + 16 * u) * kBlock + 4 * lane + j;
+        h[u][j] = i < M ? H[i] : NAN;
+      }
+  }
+  ((int4*)slot)[threadIdx.x] = table;
+  lds_barrier();
+  if (ov == 0) return;
+  uint32_t* keys = stage_key[wave];
+  uint16_t* rows = stage_row[wave];
+  unsigned char* lanes = stage_lane[wave];
+  uint32_t* kept = w.kept + wg_wave * kWaveBlocks * kBlock;
+  int n = 0, n_out = 0;  // held back; set aside (uniform over the wave)
+  auto count = [&]() {
+    for (int i0 = 0; i0 < n; i0 += 64) {
+      const bool on = i0 + lane < n;
+      const uint32_t key = on ? keys[i0 + lane] : 0u, rk = on ? rows[i0 + lane] : 0u, bit = on ? lanes[i0 + lane] : 0u;
+      const uint32_t row = rk >> 6, ok = (uint32_t)(__shfl(bits, rk & 63u) >> bit) & 1u, within = c.within(key);
+      add_counted(w.h2, row * kBins2 + (within >> c.b3(c.bin(key))), on, ok);
+      if (on) kept[n_out + i0 + lane] = (ok << 31) | (row << 20) | within;
+    }
+    n_out += n;
+    n = 0;
+  };
+#pragma unroll
+  for (int u = 0; u < kWaveBlocks; ++u) {
+    if (n + kBlock > kStageWave) count();
+    int row[4];
+    bool odd = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t off = __float_as_uint(h[u][j]) - c.lo_bits;
+      const bool in = off < c.n_plain;
+      odd |= !in;
+      row[j] = in ? slot[kOuter + (off >> c.s)] : -1;
+    }
+    if (odd) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (__float_as_uint(h[u][j]) - c.lo_bits >= c.n_plain && h[u][j] == h[u][j]) row[j] = slot[c.bin(ascending_key(h[u][j]))];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const unsigned long long on = __ballot(row[j] >= 0);
+      if (!on) continue;  // uniform over the wave
+      if (row[j] >= 0) {
+        const int at = n + __popcll(on & ((1ull << lane) - 1ull));
+        keys[at] = ascending_key(h[u][j]);
+        rows[at] = (uint16_t)((row[j] << 6) | (4 * u + j));
+        lanes[at] = (unsigned char)lane;
+      }
+      n += __popcll(on);
     }
   }
-  __syncthreads();
-  if (ov == 0 || c.empty) return;
-  const uint32_t ms = (1u << c.s) - 1u;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t* mine = stage[wave];
-  int n = 0;  // uniform over the wave
-  constexpr int kTrips = kSegment / (4 * kChunk);
-  for (int k = 0; k < kTrips; ++k) {
-    const Trip t = load_trip(H, M, w, (int64_t)blockIdx.x * kTrips + k);
-    int rows[8];  // all eight table look-ups of a trip in flight together
-    for_trip(t, c.base, [&](int u, bool valid, uint32_t off, unsigned) {
-      rows[u] = valid ? slot[off >> c.s & (kBins1 - 1)] : -1;
-    });
-    for_trip(t, c.base, [&](int u, bool, uint32_t off, unsigned ok) {
-      const int row = rows[u];
-      const unsigned long long on = __ballot(row >= 0);
-      if (!on) return;  // uniform over the wave
-      const uint32_t within = off & ms;
-      add_counted(w.h2, (uint32_t)row * kBins2 + (within >> c.b3), row >= 0, ok);
-      if (n + 64 > kStageWave) {  // a wave whose tokens are mostly kept: it appends what it holds by itself
-        int first = 0;
-        if (lane == 0) first = atomicAdd(&w.n_kept[2], n);
-        first = __shfl(first, 0);
-        for (int i = lane; i < n; i += 64) w.kept[first + i] = mine[i];
-        n = 0;
-      }
-      if (row >= 0) mine[n + __popcll(on & ((1ull << lane) - 1ull))] = (ok << 31) | ((uint32_t)row << 20) | within;
-      n += __popcll(on);
-    });
-  }
-  // the workgroup appends what its waves still hold with one reservation
-  if (lane == 0) n_wave[wave] = n;
-  lds_barrier();
-  if (threadIdx.x == 0) {
-    int total = 0;
-    for (int k = 0; k < 16; ++k) total += n_wave[k];
-    at = total ? atomicAdd(&w.n_kept[2], total) : 0;
-  }
-  lds_barrier();
-  int first = at;
-  for (int k = 0; k < wave; ++k) first += n_wave[k];
-  for (int i = lane; i < n; i += 64) w.kept[first + i] = mine[i];
+  count();
+  if (lane == 0) w.n_aside[wg_wave] = n_out;
 }
 
 // One node for one wave: nb <= 64 * PER bins, lane l looks at bins [PER * l, PER * (l + 1)).
-// As node_scan with JUDGE; the counts up to and including the bin returned come back in at_top.
+// Gives back the mask of the lane's bins that may hold a qualifying candidate and, as the return value, the highest
+// bin whose top candidate qualifies (-1: none), with the counts up to and including it in at_top.
 template <int PER>
 __device__ __forceinline__ int wave_node_scan(const uint64_t* __restrict__ t, int nb, Pair below, double eps,
-                                              Pair (&pre)[PER], unsigned& may, Pair& at_top) {
+                                              unsigned& may, Pair& at_top) {
   const int lane = threadIdx.x & 63;
   const int b0 = lane * PER;
   Pair v[PER];
@@ -562,164 +653,186 @@ __device__ __forceinline__ int wave_node_scan(const uint64_t* __restrict__ t, in
     v[j] = b0 + j < nb ? pair_of(t[b0 + j]) : Pair{0, 0};
     sum = sum + v[j];
   }
-  Pair inc = sum;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t c = __shfl_up(inc.c, o), r = __shfl_up(inc.r, o);
-    if (lane >= o) inc = inc + Pair{c, r};
-  }
+  const Pair inc = wave_inclusive(sum);
   Pair run{below.c + inc.c - sum.c, below.r + inc.r - sum.r};
   may = 0;
   int top = -1;
   Pair top_incl{0, 0};
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    pre[j] = run;
-    const Pair incl = run + v[j];
-    if (v[j].c) {
-      const double bound = v[j].r ? (double)incl.r / (double)(run.c + v[j].r) : (double)run.r / (double)(run.c + 1u);
-      if (bound >= eps) may |= 1u << j;
-      if ((double)incl.r / (double)incl.c >= eps) {
-        top = b0 + j;
-        top_incl = incl;
-      }
+    const Verdict d = judge(run, v[j], eps);
+    may |= (unsigned)d.may << j;
+    run = run + v[j];
+    if (d.top) {
+      top = b0 + j;
+      top_incl = run;
     }
-    run = incl;
   }
-  int best = top;
-#pragma unroll
-  for (int o = 32; o; o >>= 1) {
-    const int u = __shfl_xor(best, o);
-    best = u > best ? u : best;
-  }
+  const int best = last_of_wave(top);
   const int owner = best >= 0 ? best / PER : 0;
   at_top = Pair{(uint32_t)__shfl((int)top_incl.c, owner), (uint32_t)__shfl((int)top_incl.r, owner)};
   return best;
 }
 
-// Level 2, one workgroup per epsilon: down the kept level-1 bins, four at a time (a wave
+// Level 2, one workgroup per epsilon: down the kept level-1 bins, four at a time (four waves
 // each), until a top candidate qualifies.
-__global__ __launch_bounds__(256) void calib_keep2_kernel(CalibWork w, EpsList eps, EpsWalk* __restrict__ walks) {
-  __shared__ int top_w[4], cnt_w[4];
+__global__ __launch_bounds__(kWalkWaves * 64) void calib_keep2_kernel(CalibWork w, EpsList eps, EpsWalk* __restrict__ walks) {
+  constexpr int kNodes = 4, NW = kWalkWaves / kNodes;  // nodes at a time, waves on each
+  __shared__ Pair sum_w[kWalkWaves];
+  __shared__ int top_w[kWalkWaves], cnt_w[kWalkWaves];
   __shared__ uint32_t at2[kList2];
-  constexpr int PER = kBins2 / 64;
+  constexpr int PER = kBins2 / (NW * 64);
   const int ov = *w.overflow;
   const Cut c = cut_of(w);
   const int e = blockIdx.x;
+  const double ep = eps.v[e];
   EpsWalk& walk = walks[e];
   const int n1 = walk.n1;
   if (ov == 0) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int node = wave / NW, b0 = ((wave % NW) * 64 + lane) * PER;
   int n2 = 0;  // uniform over the workgroup
-  for (int r = 0; 4 * r < n1; ++r) {
-    const int i = n1 - 1 - (4 * r + wave);  // uniform over the wave
-    int top = -1, cnt = 0, before = 0, row = 0, bin1 = 0;
-    unsigned keep = 0;
-    Pair pre[PER];
+  for (int r = 0; kNodes * r < n1; ++r) {
+    const int i = n1 - 1 - (kNodes * r + node);  // uniform over the wave
+    int row = 0, bin1 = 0, nb = 0;
+    Pair below{0, 0};
+    Pair v[PER], sum{0, 0};
     if (i >= 0) {
       bin1 = walk.bin1[i];
+      below = walk.below1[i];
       row = w.slot1[bin1];
-      unsigned may;
-      Pair at_top;
-      top = wave_node_scan<PER>(w.h2 + (size_t)row * kBins2, 1 << c.b2, walk.below1[i], eps.v[e], pre, may, at_top);
+      nb = 1 << c.b2(bin1);
+    }
 #pragma unroll
-      for (int j = 0; j < PER; ++j) keep |= (unsigned)((may >> j & 1u) && lane * PER + j >= top) << j;
-      int inc = __popc(keep);
+    for (int j = 0; j < PER; ++j) {
+      v[j] = b0 + j < nb ? pair_of(w.h2[(size_t)row * kBins2 + b0 + j]) : Pair{0, 0};
+      sum = sum + v[j];
+    }
+    const Pair inc = wave_inclusive(sum);
+    if (lane == 63) sum_w[wave] = inc;
+    lds_barrier();
+    Pair run = below;
+    for (int k = node * NW; k < wave; ++k) run = run + sum_w[k];
+    run = Pair{run.c + inc.c - sum.c, run.r + inc.r - sum.r};
+    const Pair start = run;
+    unsigned may = 0;
+    int top = -1;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(inc, o);
-        if (lane >= o) inc += u;
+    for (int j = 0; j < PER; ++j) {
+      const Verdict d = judge(run, v[j], ep);
+      may |= (unsigned)d.may << j;
+      if (d.top) top = b0 + j;
+      run = run + v[j];
+    }
+    top = last_of_wave(top);
+    if (lane == 0) top_w[wave] = top;
+    lds_barrier();
+    for (int k = 0; k < NW; ++k) top = max(top, top_w[node * NW + k]);
+    unsigned keep = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) keep |= (unsigned)((may >> j & 1u) && b0 + j >= top) << j;
+    int before = (int)wave_inclusive((uint32_t)__popc(keep));
+    if (lane == 63) cnt_w[wave] = before;
+    before -= __popc(keep);
+    lds_barrier();
+    // the bins of the nodes down to the first one with a qualifying top candidate, each from its top
+    int stop = kNodes, first = n2, all = 0, cnt = 0;
+    for (int k = kWalkWaves - 1; k >= 0; --k)
+      if (top_w[k] >= 0) stop = k / NW;
+    for (int k = 0; k < kWalkWaves; ++k) {
+      const int q = k / NW, m = cnt_w[k];
+      if (q > stop) continue;
+      if (q < node) first += m;
+      if (q == node) {
+        cnt += m;
+        if (k < wave) before += m;
       }
-      before = inc - __popc(keep);
-      cnt = __shfl(inc, 63);
+      all += m;
     }
-    if (lane == 0) {
-      top_w[wave] = top;
-      cnt_w[wave] = cnt;
-    }
-    __syncthreads();
-    int stop = 4, first = n2, all = 0;
-    for (int k = 3; k >= 0; --k)
-      if (top_w[k] >= 0) stop = k;
-    for (int k = 0; k < 4 && k <= stop; ++k) {
-      if (k < wave) first += cnt_w[k];
-      all += cnt_w[k];
-    }
-    if (i >= 0 && wave <= stop) {  // the bins of this node, from the top
+    if (i >= 0 && node <= stop) {
       int at = first + cnt - 1 - before;
+      run = start;
 #pragma unroll
-      for (int j = 0; j < PER; ++j)
+      for (int j = 0; j < PER; ++j) {
         if (keep >> j & 1u) {
           if (at < kList2) {
-            at2[at] = (uint32_t)row * kBins2 + lane * PER + j;
-            walk.at2[at] = (uint32_t)row * kBins2 + lane * PER + j;
-            walk.hi2[at] = ((uint32_t)bin1 << c.b2) | (uint32_t)(lane * PER + j);
-            walk.below2[at] = pre[j];
+            at2[at] = (uint32_t)row * kBins2 + b0 + j;
+            walk.at2[at] = (uint32_t)row * kBins2 + b0 + j;
+            walk.start2[at] = c.start(bin1) + ((uint32_t)(b0 + j) << c.b3(bin1));
+            walk.b3[at] = c.b3(bin1);
+            walk.below2[at] = run;
           }
           --at;
         }
+        run = run + v[j];
+      }
     }
     n2 += all;
-    __syncthreads();  // top_w and cnt_w are rewritten in the next round
-    if (stop < 4) break;  // uniform: every smaller key is below one that qualifies
+    lds_barrier();  // the shared words are rewritten in the next round
+    if (stop < kNodes) break;  // uniform: every smaller key is below one that qualifies
   }
   if (threadIdx.x == 0) {
     walk.n2 = n2 < kList2 ? n2 : kList2;
     if (n2 > kList2) *w.overflow = 0;
   }
-  for (int k = threadIdx.x; k < n2 && k < kList2; k += 256)
-    keep_bin(&w.sel2[at2[k]], &w.slot2[at2[k]], &w.n_kept[1], kCap2, w.overflow, e);
+  for (int k = threadIdx.x; k < n2 && k < kList2; k += kWalkWaves * 64) {
+    const int row = keep_bin(&w.sel2[at2[k]], &w.n_kept[1], kCap2, w.overflow, e);
+    if (row >= 0) w.slot2[at2[k]] = row;
+  }
 }
 
 // Pass 3: the tokens set aside whose level-2 bin is kept are counted by their last b3 bits,
-// that is, by key.
-__global__ __launch_bounds__(256) void calib_count3_kernel(CalibWork w) {
+// that is, by key.  A wave takes the parts of `kept` in turn.
+__global__ __launch_bounds__(256) void calib_count3_kernel(CalibWork w, int n_parts) {
   if (*w.overflow == 0) return;
-  const Cut c = cut_of(w);
-  const int n = w.n_kept[2];
-  const uint32_t m3 = (1u << c.b3) - 1u;
-  for (int i0 = blockIdx.x * 256; i0 < n; i0 += gridDim.x * 256) {  // uniform over the workgroup
-    const int i = i0 + threadIdx.x;
-    const uint32_t v = i < n ? w.kept[i] : 0u;
-    const uint32_t within = v & 0xFFFFFu, row1 = (v >> 20) & 127u;
-    const int row = i < n ? w.slot2[(size_t)row1 * kBins2 + (within >> c.b3)] : -1;
-    add_counted(w.h3, (uint32_t)row * kBins3 + (within & m3), row >= 0, v >> 31);
+  const int lane = threadIdx.x & 63, n_waves = gridDim.x * 4;
+  for (int part = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); part < n_parts; part += n_waves) {
+    const int n = w.n_aside[part];
+    const uint32_t* kept = w.kept + (int64_t)part * kWaveBlocks * kBlock;
+    for (int i0 = 0; i0 < n; i0 += 64) {  // uniform over the wave
+      const bool in = i0 + lane < n;
+      const uint32_t v = in ? kept[i0 + lane] : 0u;
+      const uint32_t within = v & 0xFFFFFu, row1 = (v >> 20) & 127u;
+      const int b3 = in ? w.row_b3[row1] : 0;
+      const int row = in ? w.slot2[(size_t)row1 * kBins2 + (within >> b3)] : -1;
+      add_counted(w.h3, (uint32_t)row * kBins3 + (within & ((1u << b3) - 1u)), row >= 0, v >> 31);
+    }
   }
 }
 
 // Level 3, one workgroup per epsilon: the first single key, from the top, that qualifies.
-// Four kept level-2 bins at a time, a wave each.
-__global__ __launch_bounds__(256) void calib_pick_kernel(CalibWork w, EpsList eps, const EpsWalk* __restrict__ walks,
-                                                         float* __restrict__ tau, long long* __restrict__ n_exit) {
-  __shared__ int top_w[4];
-  __shared__ uint32_t cnt_w[4];
+// As many kept level-2 bins at a time as there are waves.  Also tells the host whether the tables were
+// large enough (a copy of that word behind the kernel took 4 us).
+__global__ __launch_bounds__(kWalkWaves * 64) void calib_pick_kernel(CalibWork w, EpsList eps, const EpsWalk* __restrict__ walks,
+                                                                     float* __restrict__ tau, long long* __restrict__ n_exit) {
+  __shared__ int top_w[kWalkWaves];
+  __shared__ uint32_t cnt_w[kWalkWaves];
   constexpr int PER = kBins3 / 64;
   const int ov = *w.overflow;
-  const Cut c = cut_of(w);
   const int e = blockIdx.x;
   const EpsWalk& walk = walks[e];
   const int n2 = walk.n2;
+  if (e == 0 && threadIdx.x == 0) __hip_atomic_store(w.host_flag, ov, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (ov == 0) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int r = 0; 4 * r < n2; ++r) {
-    const int q = 4 * r + wave;  // uniform over the wave
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int r = 0; kWalkWaves * r < n2; ++r) {
+    const int q = kWalkWaves * r + wave;  // uniform over the wave
     int top = -1;
     Pair at_top{0, 0};
     if (q < n2) {
       const int row = w.slot2[walk.at2[q]];
-      Pair pre[PER];
       unsigned may;
-      top = wave_node_scan<PER>(w.h3 + (size_t)row * kBins3, 1 << c.b3, walk.below2[q], eps.v[e], pre, may, at_top);
+      top = wave_node_scan<PER>(w.h3 + (size_t)row * kBins3, 1 << walk.b3[q], walk.below2[q], eps.v[e], may, at_top);
     }
     if (lane == 0) {
       top_w[wave] = top;
       cnt_w[wave] = at_top.c;
     }
     __syncthreads();
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < kWalkWaves; ++k)
       if (top_w[k] >= 0) {  // uniform
         if (threadIdx.x == 0) {
-          tau[e] = ascending_entropy(c.base + ((walk.hi2[4 * r + k] << c.b3) | (uint32_t)top_w[k]));
+          tau[e] = ascending_entropy(walk.start2[kWalkWaves * r + k] + (uint32_t)top_w[k]);
           if (n_exit) n_exit[e] = (long long)cnt_w[k];
         }
         return;
@@ -732,14 +845,45 @@ __global__ __launch_bounds__(256) void calib_pick_kernel(CalibWork w, EpsList ep
   }
 }
 
-// Presets the tables: n0 words of 0 from p0, n1 words of -1 from p1.
+// Presets the tables: n0 words of 0 from p0, n1 words of -1 from p1; and the first kSampleWgs workgroups
+// find the key range of kSample tokens spread evenly over the set (all of them if there are no more).
 __global__ __launch_bounds__(256) void calib_preset_kernel(int* __restrict__ p0, int64_t n0, int* __restrict__ p1,
-                                                           int64_t n1) {
+                                                           int64_t n1, const float* __restrict__ H, int64_t M,
+                                                           uint2* __restrict__ range) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n0)
     p0[i] = 0;
   else if (i - n0 < n1)
     p1[i - n0] = -1;
+  if (blockIdx.x >= kSampleWgs) return;
+  __shared__ uint32_t sh_lo[4], sh_hi[4];
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  constexpr int U = kSample / (kSampleWgs * 256);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t j = ((int64_t)blockIdx.x * U + u) * 256 + threadIdx.x;
+    const int64_t at = M <= kSample ? j : j * M / kSample;
+    const float h = at < M ? H[at] : NAN;
+    if (h == h) {
+      const uint32_t key = ascending_key(h);
+      lo = key < lo ? key : lo;
+      hi = key > hi ? key : hi;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o; o >>= 1) {
+    const uint32_t l2 = __shfl_xor(lo, o), h2 = __shfl_xor(hi, o);
+    lo = l2 < lo ? l2 : lo;
+    hi = h2 > hi ? h2 : hi;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sh_lo[threadIdx.x >> 6] = lo;
+    sh_hi[threadIdx.x >> 6] = hi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    range[blockIdx.x] = uint2{min(min(sh_lo[0], sh_lo[1]), min(sh_lo[2], sh_lo[3])),
+                              max(max(sh_hi[0], sh_hi[1]), max(sh_hi[2], sh_hi[3]))};
 }
 
 }  // namespace
@@ -804,24 +948,28 @@ hipError_t calibrate_refine(CalibScratch& sc, const float* H, const int* pred, c
     e = hipHostMalloc((void**)&sc.host_flag, sizeof(int), hipHostMallocDefault);
     if (e != hipSuccess) return e;
   }
-  const size_t n_groups = (size_t)((M + 63) >> 6);
+  const size_t n_groups = 4 * (size_t)((M + kBlock - 1) / kBlock);  // words of correctness bits
   const size_t n_segments = (size_t)((M + kSegment - 1) / kSegment);
-  const size_t kept_cap = (size_t)M;
+  const size_t kept_cap = n_segments * kSegment;
   const size_t zero_words = 4 + 2 * ((size_t)kBins1 + kBins1 + 2 * (size_t)kCap1 * kBins2 + (size_t)kCap2 * kBins3);
-  const size_t ones_words = 4 + (size_t)kBins1 + (size_t)kCap1 * kBins2;
-  e = calib_reserve(sc, (2 * n_groups + n_segments * kBins1 + kept_cap + 8 + zero_words + ones_words) * 4 + kMaxEps * sizeof(EpsWalk) + 256);
+  const size_t ones_words = 4 + (size_t)kCap1 + kBins1 / 4 + (size_t)kCap1 * kBins2;
+  e = calib_reserve(sc, (2 * n_groups + 4 + n_segments * (kInner + 16) + kept_cap + 8 + 2 * kSampleWgs + zero_words + ones_words) * 4 + kMaxEps * sizeof(EpsWalk) + 256);
   if (e != hipSuccess) return e;
   CalibWork w;
   uint32_t* p = (uint32_t*)sc.buf;
   w.bits = (uint64_t*)p;
   p += (2 * n_groups + 3) & ~(size_t)3;
   w.part1 = p;
-  p += n_segments * kBins1;
+  p += n_segments * kInner;
   w.kept = p;
-  p += (kept_cap + 3) & ~(size_t)3;
+  p += kept_cap;
+  w.n_aside = (int*)p;
+  p += n_segments * 16;
+  w.range = (uint2*)p;
+  p += 2 * kSampleWgs;
+  w.host_flag = sc.host_flag;
   uint32_t* zero0 = p;
-  w.key_max = p;
-  w.n_kept = (int*)(p + 1);
+  w.n_kept = (int*)p;
   p += 4;
   w.h1 = (uint64_t*)p;
   p += 2 * kBins1;
@@ -834,27 +982,25 @@ hipError_t calibrate_refine(CalibScratch& sc, const float* H, const int* pred, c
   w.h3 = (uint64_t*)p;
   p += 2 * (size_t)kCap2 * kBins3;
   uint32_t* ones0 = p;
-  w.key_min = p;
-  w.overflow = (int*)(p + 1);
+  w.overflow = (int*)p;
   p += 4;  // slot1 is read 16 bytes at a time
-  w.slot1 = (int*)p;
-  p += kBins1;
+  w.row_b3 = (int*)p;
+  p += kCap1;
+  w.slot1 = (signed char*)p;
+  p += kBins1 / 4;
   w.slot2 = (int*)p;
   p += (size_t)kCap1 * kBins2;
   EpsWalk* walks = (EpsWalk*)p;
   hipLaunchKernelGGL(calib_preset_kernel, dim3((unsigned)((zero_words + ones_words + 255) / 256)), dim3(256), 0, s,
-                     (int*)zero0, (int64_t)zero_words, (int*)ones0, (int64_t)ones_words);
-  hipLaunchKernelGGL(calib_pack_kernel, dim3((unsigned)n_segments), dim3(1024), 0, s, H, pred, ref, M, w);
-  hipLaunchKernelGGL(calib_count1_kernel, dim3((unsigned)n_segments), dim3(1024), 0, s, H, M, w);
-  hipLaunchKernelGGL(calib_sum1_kernel, dim3(kBins1 / 256, 16), dim3(256), 0, s, w, (int)n_segments);
-  hipLaunchKernelGGL(calib_keep1_kernel, dim3(el.n), dim3(256), 0, s, w, el, walks);
+                     (int*)zero0, (int64_t)zero_words, (int*)ones0, (int64_t)ones_words, H, M, w.range);
+  hipLaunchKernelGGL(calib_count1_kernel, dim3((unsigned)n_segments), dim3(1024), 0, s, H, pred, ref, M, w);
+  hipLaunchKernelGGL(calib_sum1_kernel, dim3(kInner / 256, 16), dim3(256), 0, s, w, (int)n_segments);
+  hipLaunchKernelGGL(calib_keep1_kernel, dim3(el.n), dim3(kWalkWaves * 64), 0, s, w, el, walks);
   hipLaunchKernelGGL(calib_count2_kernel, dim3((unsigned)n_segments), dim3(1024), 0, s, H, M, w);
-  hipLaunchKernelGGL(calib_keep2_kernel, dim3(el.n), dim3(256), 0, s, w, el, walks);
-  hipLaunchKernelGGL(calib_count3_kernel, dim3(256), dim3(256), 0, s, w);
-  hipLaunchKernelGGL(calib_pick_kernel, dim3(el.n), dim3(256), 0, s, w, el, walks, tau_out, n_exit_out);
+  hipLaunchKernelGGL(calib_keep2_kernel, dim3(el.n), dim3(kWalkWaves * 64), 0, s, w, el, walks);
+  hipLaunchKernelGGL(calib_count3_kernel, dim3((unsigned)std::min<size_t>(4 * n_segments, 2048)), dim3(256), 0, s, w, (int)(16 * n_segments));
+  hipLaunchKernelGGL(calib_pick_kernel, dim3(el.n), dim3(kWalkWaves * 64), 0, s, w, el, walks, tau_out, n_exit_out);
   e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = hipMemcpyAsync(sc.host_flag, w.overflow, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return e;
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;

@@ -502,6 +502,29 @@ def test_calibrate_hovering_proportion(B, small_ctx, spread):
             assert tau[i] == want_tau and n[i] == want_n, (spread, eps[i], tau[i], want_tau, n[i], want_n)
 
 
+@pytest.mark.parametrize("M", [32768, 65537, 300001, 1 << 20])
+@pytest.mark.parametrize("lift", [0.0, -2.0])
+def test_calibrate_outside_the_sample(B, small_ctx, M, lift):
+    """The bins of the first level are laid over the key range of a sample of the tokens (all of them up
+    to 65536); tokens outside it -- huge, tiny, negative and infinite entropies, both zeros -- go to the
+    bins on either side.  lift moves the entropies so that the range itself holds negative ones
+    (another way to the bin), and the arrays start one element behind a 16-byte boundary."""
+    H, pred, ref = G.make_calibration_case(M + 1, DEV, seed=M, V=50, ties=False, nan_every=997)
+    gen = torch.Generator(device=DEV).manual_seed(M)
+    H = H + lift
+    odd = torch.tensor([0.0, -0.0, 1e-30, 1e-42, -1e-9, -3.0, -1e20, 1e20, 900.0, float("inf"), float("-inf")], device=DEV)
+    at = torch.randperm(M, generator=gen, device=DEV)[:220] + 1
+    H[at] = odd.repeat(20)
+    H, pred, ref = H[1:], pred[1:], ref[1:]
+    eps = [0.0, 0.3, 0.5, 0.7, 0.8, 0.9, 0.95, 0.97, 0.99, 1.0]
+    before = B.eh_probe_calibrate_sorted(small_ctx)
+    tau, n = _calibrate(B, small_ctx, H, pred, ref, eps)
+    assert B.eh_probe_calibrate_sorted(small_ctx) == before
+    t = O.correctness(pred.cpu().numpy(), ref.cpu().numpy())
+    for i, (want_tau, want_n) in enumerate(_calibrate_by_counting(H.cpu().numpy().astype(np.float64), t, eps)):
+        assert tau[i] == want_tau and n[i] == want_n, (eps[i], tau[i], want_tau, n[i], want_n)
+
+
 def test_calibrate_degenerate_inputs(B, small_ctx):
     H = torch.tensor([0.5, 0.25, 2.0, 0.0, -0.0], device=DEV)
     same = torch.zeros(5, dtype=torch.int32, device=DEV)
