@@ -9,6 +9,13 @@ compile-time count of younger loads.  That is only sound if, in the generated co
     overwrite an address or an operand), and
   * no path reaches the end of the program with such a load still in flight.
 
+Weights travel to LDS by `global_load_lds_dwordx4` instructions that are inline asm too; for these the
+check is that no path from one reaches the end of the program without a `vmcnt(0)` (the
+workgroup's LDS is given to another one then), and that nothing but they uses m0.  The hardware wants
+five wait states between a vector instruction that writes a scalar register (v_readlane, v_readfirstlane) and a
+memory instruction that takes its address from it; the compiler keeps them for its own
+instructions only, so the check looks for them in front of every inline-asm load.
+
 This module proves both properties on the assembly text: for every `global_load_dwordx4`
 into VGPRs (and every `ds_read_b128`) that comes from an inline-asm statement it walks every path of the kernel's control-flow graph forward from the load,
 counting vector-memory loads issued after it (loads return in order, so
@@ -179,6 +186,64 @@ def check_kernel(lines, max_report=5, classes=(VM_LOADS, LDS_LOADS)):
     return findings, n_loads
 
 
+def _sregs(text: str) -> set:
+    regs = set()
+    for m in re.finditer(r"\bs(\d+)\b|\bs\[(\d+):(\d+)\]", text):
+        regs.update([int(m.group(1))] if m.group(1) else range(int(m.group(2)), int(m.group(3)) + 1))
+    return regs
+
+
+def check_scalar_addresses(lines, max_report=3):
+    """Inline-asm loads whose scalar address a vector instruction has written less than five wait states before
+    (straight-line code; a label in between counts as far enough: a branch takes longer)."""
+    prog = Program(lines)
+    findings = []
+    targets = set(prog.label_at.values())
+    for i, t in enumerate(prog.ins):
+        if not prog.by_hand[i] or not VMEM_RE.match(t):
+            continue
+        need, states, j = _sregs(t), 0, i
+        while need and states < 5 and j > 0 and j not in targets:
+            j -= 1
+            u = prog.ins[j]
+            op, _, args = u.partition(" ")
+            if op == "s_nop":
+                states += int(args, 0) + 1
+                continue
+            written = _sregs(args.split(",")[0]) & need
+            if written and op.startswith("v_"):
+                findings.append(f"`{t}` (#{i}): `{u}` {states} wait states before")
+                break
+            need -= written if op.startswith("s_") else set()
+            states += 1
+    return findings[:max_report]
+
+
+def check_lds_dma(lines, max_report=3):
+    """Findings on the hand-written loads to LDS (see above) and their number."""
+    prog = Program(lines)
+    ins = prog.ins
+    dma = [i for i, t in enumerate(ins) if prog.by_hand[i] and t.startswith("global_load_lds_dwordx4")]
+    if not dma:
+        return [], 0
+    findings = [f"`{t}` (#{i}) uses m0, which the hand-written loads to LDS overwrite"
+                for i, t in enumerate(ins) if not prog.by_hand[i] and re.search(r"\bm0\b", t)]
+    # instructions from which s_endpgm is reached without passing a wait for all loads
+    pred = [[] for _ in ins]
+    for i, succ in enumerate(prog.succ):
+        for s in succ:
+            pred[s].append(i)
+    todo = [i for i, t in enumerate(ins) if t.startswith("s_endpgm")]
+    undrained = set(todo)
+    while todo:
+        for q in pred[todo.pop()]:
+            if q not in undrained and not (ins[q].startswith("s_waitcnt") and "vmcnt(0)" in ins[q]):
+                undrained.add(q)
+                todo.append(q)
+    findings += [f"load to LDS #{i} may still be in flight at s_endpgm" for i in dma if i in undrained]
+    return findings[:max_report], len(dma)
+
+
 STEP_SYNC_RE = re.compile(r"^s_waitcnt vmcnt\((\d+)\)(?: lgkmcnt\(0\))?$")
 
 
@@ -188,13 +253,15 @@ def check_step_counts(name, lines, max_report=5):
     `; step-sync` (the compiler's own waits are not step syncs).  On every control-flow path from one step sync to the next, the loads
     issued (DMA + register loads) must divide the next sync's N -- by the same factor (the
     k-steps a load may stay in flight beyond the next one) everywhere in the kernel -- and
-    nothing else may use vector memory.  Paths end at a pass boundary (`vmcnt(0)`)."""
+    nothing else may use vector memory.  Paths end at a pass boundary (`vmcnt(0)`).  The last steps
+    of a pass follow steps that reload no activations; their waits (`; end-sync G`, G the loads of a full step)
+    count one full step less than the wait before them and the DMA loads since."""
     prog = Program(lines)
     ins = prog.ins
     sync_n = {}
     for i, t in enumerate(ins):
         m = STEP_SYNC_RE.match(t)
-        if m and int(m.group(1)) > 0 and "step-sync" in prog.note[i]:
+        if m and int(m.group(1)) > 0 and prog.note[i].split(" ")[0] in ("step-sync", "end-sync"):
             sync_n[i] = int(m.group(1))
     findings, depths, checked = [], set(), 0
     for start in sync_n:
@@ -209,6 +276,12 @@ def check_step_counts(name, lines, max_report=5):
             if pc in sync_n:
                 if dma + reg == 0:
                     pass                  # prologue: operands of step 0 come from LDS only
+                elif prog.note[pc] != "step-sync":
+                    group = int(prog.note[pc].split()[1], 0)
+                    if reg or sync_n[pc] != sync_n[start] - group + dma:
+                        findings.append(f"last steps: from sync #{start} (vmcnt({sync_n[start]})) to #{pc} {dma} DMA + {reg} "
+                                        f"register loads, wait vmcnt({sync_n[pc]}), full step {group}")
+                    continue
                 else:
                     checked += 1
                     n = sync_n[pc]
@@ -225,6 +298,8 @@ def check_step_counts(name, lines, max_report=5):
             elif UNTRACKED_RE.match(t):
                 reg += 1
             elif VMEM_RE.match(t):
+                if prog.note[start] != "step-sync":
+                    continue              # behind the last step: the statistics
                 findings.append(f"k-step after sync #{start}: other vector memory `{t}` (#{pc})")
                 continue
             for s in prog.succ[pc]:
@@ -243,6 +318,7 @@ def check_asm(asm: str):
     for name, body in kernels.items():
         f, n = check_kernel(body)
         g, _ = check_step_counts(name, body)
+        g += check_lds_dma(body)[0] + check_scalar_addresses(body)
         loads += n
         findings += [f"{name}: {x}" for x in f + g]
     return findings, len(kernels), loads

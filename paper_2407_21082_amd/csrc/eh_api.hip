@@ -110,6 +110,7 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // 238 / 422 against 154 / 240 / 419; V = 49152 132 / 214 / 390 against 150 / 235 / 409.
 bool use_ksplit(const eh_ctx* c, int n_rows) {
   if (!c->bias.empty() || n_rows <= 32) return true;
+  if (c->dtype == EH_BF16 && c->KS < kGemm32MinSteps) return true;  // d <= 64: there is no other
   return c->dtype == EH_BF16 && n_rows <= 64 && ksplit_pass_tiles(c) < 7;
 }
 // Rows per block of the activations' operand order: 16 for gemm_launch's kernel, 32 for all others.
@@ -198,6 +199,7 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // rows 297 / 328, 160 rows 391 / 353; d = 2560, 128 rows 553 / 630; V = 32000, d = 2048, 80 rows 334 / 381,
 // 160 rows 450 / 402.
 int rows_most(const eh_ctx* c) {
+  if (c->KS < kGemm32MinSteps) return 64;  // the kernel for more rows has no such narrow heads
   return (int)std::min<int64_t>(kRowsMax, std::max<int64_t>(64, 26 + (int64_t)c->V * (c->d + 620) / 1000000));
 }
 bool use_rows(const eh_ctx* c, int64_t n_rows, bool verify) {

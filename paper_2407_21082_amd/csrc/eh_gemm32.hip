@@ -45,22 +45,21 @@ namespace eh {
 
 namespace {
 
-constexpr int kG32Waves = 4;
+constexpr int kG32Waves = 8;
 constexpr int kG32Threads = kG32Waves * kWave;
-constexpr int kG32Group = 2 * kG32Waves * 32;  // rows a workgroup takes at most: two blocks a wave
+constexpr int kG32Group = kG32Waves * 32;  // rows a workgroup takes at most: a block a wave
 constexpr int kMaxMT = 7;     // 32-row tiles per pass
-constexpr int kSlots = 8;     // LDS ring: k-steps of weight fragments (a slot is rewritten 7 steps after its last read)
+constexpr int kSlots = 8;     // LDS ring: k-steps of weight fragments
 constexpr int kSlotBytes = 2 * kMaxMT * 1024;
-#ifndef EH_G32_DEPTH
-#define EH_G32_DEPTH 3
-#endif
-constexpr int kDepth = EH_G32_DEPTH;  // activation register sets = k-steps a load may take (<= 6: ring of 8)
+constexpr int kDepth = kGemm32MinSteps;  // activation register sets = k-steps a load may take
+constexpr int kRingAhead = 6;  // k-steps the weights are asked for ahead
+static_assert(kDepth < kRingAhead, "a step's weights are asked for before its activations");
 // the weight ring, then 16 bytes per thread: the second largest logit of its (at most 2) token blocks
 // between passes (registers are too scarce to keep it live across the k loop); then, per token
 // block, the 16 logits of the tile that holds the thread's largest one ([block][4][thread] f32x4)
 __host__ __device__ constexpr size_t g32_ring_bytes() { return (size_t)kSlots * kSlotBytes; }
-__host__ __device__ constexpr size_t g32_park_at() { return g32_ring_bytes() + kG32Threads * 16; }
-__host__ __device__ constexpr size_t g32_lds_bytes() { return g32_park_at() + (size_t)2 * 4 * kG32Threads * 16; }
+__host__ __device__ constexpr size_t g32_park_at() { return g32_ring_bytes() + kG32Threads * 4; }
+__host__ __device__ constexpr size_t g32_lds_bytes() { return g32_park_at() + (size_t)4 * kG32Threads * 16; }
 
 #define EH_LDS __attribute__((address_space(3)))
 #define EH_GLOBAL __attribute__((address_space(1)))
@@ -93,9 +92,7 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-__device__ __forceinline__ EH_LDS f32x4* park_of(EH_LDS char* lds, int n) {
-  return (EH_LDS f32x4*)(lds + g32_park_at()) + n * 4 * kG32Threads + threadIdx.x;
-}
+__device__ __forceinline__ EH_LDS f32x4* park_of(EH_LDS char* lds) { return (EH_LDS f32x4*)(lds + g32_park_at()) + threadIdx.x; }
 
 // The 16 logits a lane holds of one 32-row tile (accumulator register j = 4g+i: vocabulary row
 // rowbase + 8g + i, increasing in j), all inside the vocabulary, pushed at once.
@@ -269,6 +266,9 @@ __device__ __forceinline__ void kl_push16(KlStats& s, const f32x16& zs, const f3
   }
 }
 
+// Nothing of this wave may be on its way to LDS when the workgroup gives it up.
+#define EH_LOADS_DONE() asm volatile("s_waitcnt vmcnt(0)" ::: "memory")
+
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), in order
 template <int N, typename F, int I = 0>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -288,21 +288,28 @@ __host__ __device__ constexpr int dma_per_wave(int mt) { return (2 * mt + kG32Wa
 // wave's NB blocks of 32 tokens.
 //
 // k-step s (32 values of k) uses, per tile m, the operands a[m][0], a[m][1] (the
-// two 16-k halves, 32 rows each) and, per token block n, b[s % D][n][0..1], with
+// two 16-k halves, 32 rows each) and, per token block n, b[(s - KS) mod D][n][0..1], with
 // D = kDepth register sets.  Step s:
-//   wait until my loads up to B(s) and my share of DMA(s+1) have landed;
+//   wait until my loads up to B(s), and with them my share of DMA(s+1), have landed;
 //   tile 0's 2*NB matrix instructions; barrier (now every wave's share of DMA(s+1)
 //   is in LDS); then for each tile m: [its matrix instructions,] a[m] <- LDS slot of
-//   step s+1, and one piece of DMA(s+D+1); after the last tile's use of b[n] that
-//   register set is reloaded with B(s+D).  The ring slot DMA(s+D+1) goes to (8
-//   slots) was last read at least two steps ago and those reads have fed matrix
-//   instructions since, so nobody is reading it.
+//   step s+1, and one piece of DMA(s+6); after the last tile's use of b[n] that
+//   register set is reloaded with B(s+D).  The ring slot DMA(s+6) goes to (8
+//   slots) was last read in step s-3; those reads have fed matrix instructions of step s-2, which
+//   every wave has behind it once one of them has passed the barrier of step s-1: nobody is reading it.
 // Loads return in order and every wave issues them in the order
-//   DMA(0) | DMA(1) B(0) | DMA(2) B(1) | ... | DMA(s+D) B(s+D-1) | ...
+//   ... DMA(s+6) B(s+D) | DMA(s+7) B(s+D+1) | ...
 // (inside a step the pieces of its DMA and its B loads interleave, which does not
 // change the counts), so at the wait that opens step s the loads that may still be in
-// flight are exactly the last D-1 groups, DMA(s+2) B(s+1) ... DMA(s+D) B(s+D-1): a
-// wait on a compile-time count.
+// flight are exactly the last D-1 groups, and a wait on a compile-time count proves the rest.
+// The last D steps reload no activations; their waits count that.
+//
+// The ring does not stop at the end of a pass: the last 6 steps of a pass ask for the first 6 of the next one
+// (the rest of this head's slice, or the next head's), which travel while the statistics of this pass
+// are worked out.  A pass therefore starts with its first 6 steps in the ring, or on their way.
+// (When every pass filled the ring anew, a third of the time of a head of d = 1024 on 200 rows passed without
+// a byte of weights in flight.)  The DMA instructions are written by hand: one the compiler knows of
+// makes it wait, at the next access to LDS, until the data has arrived.
 // TOP2: also track the two largest logits of every token (z1 >= z2, with multiplicity) for the
 // "difference of the two largest probabilities" confidence metric (Section 3.4.1).
 //
@@ -313,17 +320,125 @@ __host__ __device__ constexpr int dma_per_wave(int mt) { return (2 * mt + kG32Wa
 // activations followed by the same NB/2 blocks of the model's (yq2), and a tile only meets
 // the blocks of its own side: accumulator [m][j] and [m + MT/2][j] then hold the two logits
 // of the same (vocabulary row, token) in the same register of the same lane.
-struct NothingBetween {
-  __device__ __forceinline__ void operator()() const {}
+// Where a pass takes its weights: mt tiles of 32 rows (both sides together) from 16-row tile t16 of W on, the
+// workgroup's tiles ending at t16_end.  mt = 0: there is no such pass.
+// zeros: a fragment of zeros, the weights of steps KS .. kDepth - 1 of a narrow dual pass (else NULL).
+struct G32Src {
+  const frag_t* W;
+  int t16, t16_end, mt;
+  const frag_t* zeros;
 };
-// `between` runs when the k loop is over and nobody reads the ring any more, before the
-// statistics of the pass are worked out: the place to ask for the next pass's first weights, so
-// that the memory system has something to do while this wave computes.
-template <int MT, int NB, bool ARGMAX_ONLY, bool TOP2, bool DUAL = false, typename ST = Stats, typename BT = NothingBetween>
-__device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag_t* __restrict__ yq,
-                                       int T16, int t16_end, int KS, int row_hi, int lane, int wave,
-                                       EH_LDS char* lds, ST (&st)[DUAL ? NB / 2 : NB], long long wdelta = 0,
-                                       const frag_t* __restrict__ yq2 = nullptr, BT between = BT()) {
+__device__ __forceinline__ const char* uniform_bytes(uint64_t v) {  // kept in scalar registers
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (const char*)(((uint64_t)hi << 32) | lo);
+}
+// Fragment f of the pass's k-step 0 (wave-uniform).  A missing odd half tile repeats the last one (masked later).
+template <bool DUAL>
+__device__ __forceinline__ const char* frag_src(const G32Src& p, int f, int KS, long long wdelta) {
+  const bool side2 = DUAL && f >= p.mt;
+  const int t16 = min(p.t16 + (side2 ? f - p.mt : f), p.t16_end - 1);
+  const uint64_t v = (uint64_t)p.W + (uint64_t)(((long long)t16 * KS) << 10) + (uint64_t)(side2 ? wdelta : 0);
+  return uniform_bytes(v);
+}
+// One fragment of a k-step into the ring, to LDS address slot + dst.  Not known to the compiler as a load:
+// waited for by hand.  (m0 holds the LDS address; nothing else in these kernels uses it, which the build checks.)
+__device__ __forceinline__ void ring_dma(const char* src, uint32_t lane_off, uint32_t slot, uint32_t dst) {
+  asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" ::"s"(slot), "s"(dst), "v"(lane_off), "s"(src) : "memory", "scc");
+}
+__device__ __forceinline__ uint32_t lds_offset(EH_LDS char* p) { return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)p); }
+
+// A wave's share of the first kRingAhead k-steps of a pass (fragments from `first_f` on), into the ring at slot rb.
+template <bool DUAL>
+__device__ __forceinline__ void ring_start(const G32Src& p, int KS, int rb, int lane, int wave, EH_LDS char* lds,
+                                           long long wdelta = 0, int first_f = 0) {
+  const uint32_t lane16 = (uint32_t)lane << 4, base = lds_offset(lds);
+#pragma unroll 1
+  for (int ks = 0; ks < kRingAhead; ++ks)
+#pragma unroll 1
+    for (int f = first_f + wave; f < 2 * p.mt; f += kG32Waves)
+      ring_dma(DUAL && ks >= KS && KS < kDepth ? uniform_bytes((uint64_t)p.zeros) : frag_src<DUAL>(p, f, KS, wdelta) + ((long long)min(ks, KS - 1) << 10),
+               lane16, __builtin_amdgcn_readfirstlane(base + ((rb + ks) & (kSlots - 1)) * kSlotBytes), __builtin_amdgcn_readfirstlane(f * 1024));
+}
+// Whether the ring runs on from pass to pass (it has to hold kRingAhead steps of the next one and none
+// of the one after).  Otherwise every pass is started by ring_begin.
+__device__ __forceinline__ bool ring_runs_on(int KS) { return KS >= kRingAhead; }
+template <bool DUAL>
+__device__ __forceinline__ void ring_begin(const G32Src& p, int KS, int rb, int lane, int wave, EH_LDS char* lds,
+                                           long long wdelta = 0) {
+  // nobody may still be reading the ring (previous pass) when it is refilled
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  ring_start<DUAL>(p, KS, rb, lane, wave, lds, wdelta);
+}
+
+// A wave's DMA pieces of a pass's k-steps from step kRingAhead on, those beyond the pass's end being the
+// next pass's first ones: the 2*MT fragments of a step are dealt round-robin to the waves.  A step has one scalar
+// base (a dual pass one for each piece, its sides being heads apart) and a lane offset per piece, so that moving on to
+// the next step costs a handful of scalar instructions: worked out per piece they took 110 clocks of a
+// step of 990.
+template <int MT, bool DUAL>
+struct RingFeed {
+  static constexpr int N = dma_per_wave(MT), NBASE = DUAL ? N : 1;
+  const char* base[NBASE];  // of the step the next pieces are for
+  uint32_t voff[N], dst[N]; // lane offsets; places inside a slot
+  uint32_t slot;            // LDS address of the step's slot
+  uint32_t ring, stride;
+  int left;                 // steps until the next pass's begin
+  const G32Src &cur, &next;
+  long long wdelta;
+  int KS, wave;
+  uint32_t lane16;
+  __device__ __forceinline__ RingFeed(const G32Src& cur_, const G32Src& next_, int ks_, int steps, int rb, int lane, int wave_, EH_LDS char* lds, long long wdelta_)
+      : ring(lds_offset(lds)), stride(1024), left(__builtin_amdgcn_readfirstlane(steps - kRingAhead)), cur(cur_), next(next_),
+        wdelta(wdelta_), KS(ks_), wave(wave_), lane16((uint32_t)lane << 4) {
+    slot = __builtin_amdgcn_readfirstlane(ring + ((rb + kRingAhead) & (kSlots - 1)) * kSlotBytes);
+#pragma unroll
+    for (int i = 0; i < N; ++i) dst[i] = __builtin_amdgcn_readfirstlane(min(wave + kG32Waves * i, 2 * kMaxMT - 1) * 1024);
+    if (left > 0) from(cur, 2 * MT, kRingAhead);
+    else turn();
+  }
+  __device__ __forceinline__ void from(const G32Src& p, int nf, int k) {
+    const char* b0 = frag_src<DUAL>(p, 0, KS, wdelta) + ((long long)k << 10);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      // a wave with fewer real fragments brings the last one once more, so that all waves count alike: to a
+      // place nobody reads, or where a slot is full to the place that has the same bytes
+      const int f = min(wave + kG32Waves * i, nf - 1);
+      if (DUAL) {
+        base[DUAL ? i : 0] = frag_src<DUAL>(p, f, KS, wdelta) + ((long long)k << 10);
+        voff[i] = lane16;
+      } else {
+        voff[i] = lane16 + ((uint32_t)(min(p.t16 + f, p.t16_end - 1) - min(p.t16, p.t16_end - 1)) * (uint32_t)KS << 10);
+      }
+    }
+    if (!DUAL) base[0] = b0;
+  }
+  __device__ __forceinline__ void turn() {
+    if (next.mt > 0) {
+      from(next, 2 * next.mt, 0);
+    } else {  // nothing follows: the last step again
+      from(cur, 2 * MT, KS - 1);
+      stride = 0;
+    }
+  }
+  template <int I>
+  __device__ __forceinline__ void piece() const { ring_dma(base[DUAL ? I : 0], voff[I], slot, dst[I]); }
+  __device__ __forceinline__ void advance() {
+    slot = slot + kSlotBytes == ring + kSlots * kSlotBytes ? ring : slot + kSlotBytes;
+#pragma unroll
+    for (int i = 0; i < NBASE; ++i) base[i] += stride;
+    if (--left == 0) turn();
+    asm volatile("" : "+s"(slot));
+#pragma unroll
+    for (int i = 0; i < NBASE; ++i) asm volatile("" : "+s"(base[i]));
+  }
+};
+
+template <int MT, int NB, bool ARGMAX_ONLY, bool TOP2, bool DUAL, typename ST>
+__device__ __forceinline__ void pass32(const G32Src& cur, const G32Src& next, int rb, const frag_t* __restrict__ yq, int KS,
+                                       int row_hi, int lane, int wave, EH_LDS char* lds, ST (&st)[DUAL ? NB / 2 : NB],
+                                       long long wdelta = 0, const frag_t* __restrict__ yq2 = nullptr) {
+  const int T16 = cur.t16;
+  const int steps = DUAL ? max(KS, kDepth) : KS;
   static_assert(!DUAL || (MT % 2 == 0 && NB % 2 == 0), "two equal sides");
   constexpr int NA = DUAL ? NB / 2 : NB;  // accumulator tiles per weight tile
   constexpr int MH = MT / 2, NH = NB / 2;
@@ -331,7 +446,6 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
   constexpr int kGroup = kDma + 2 * NB;            // loads a wave issues per k-step
   constexpr int kInFlight = (kDepth - 1) * kGroup;  // younger than what SYNC needs
   static_assert(kInFlight < 64, "vmcnt field");
-  constexpr int NF = 2 * MT;  // 16-row fragments per k-step
 
   f32x16 acc[MT][NA];
 #pragma unroll
@@ -343,36 +457,7 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
 
   const int lastk = KS - 1;
   const uint32_t lane16 = (uint32_t)lane << 4;  // byte offset of a lane inside a fragment
-  // DMA sources of this wave: fragment f = wave + 4*i of the step (or a repeat);
-  // wave-uniform byte offsets of (tile, k = 0) from the start of the weights
-  const EH_GLOBAL char* wbase = uniform_ptr(Wf);
-  long long wsrc[kDma];
-  int wdst[kDma];
-#pragma unroll
-  for (int i = 0; i < kDma; ++i) {
-    int f = wave + kG32Waves * i;
-    if (f >= NF) f = (wave < NF) ? wave + kG32Waves * ((NF - 1 - wave) / kG32Waves) : NF - 1;
-    // a missing odd half tile repeats the last one (masked later)
-    const bool side2 = DUAL && f >= 2 * MH;
-    const int t16 = min(T16 + (side2 ? f - 2 * MH : f), t16_end - 1);
-    wsrc[i] = (((long long)t16 * KS) << 10) + (side2 ? wdelta : 0);
-    wdst[i] = f * 1024;
-  }
-  // weight fragments of k-step ks into their ring slot: this wave's i-th fragment, or all of them
-  auto dma_part = [&](auto ic, int ks) {
-    constexpr int i = decltype(ic)::value;
-    const int k = min(ks, lastk);
-    EH_LDS char* slot = lds + (ks & (kSlots - 1)) * kSlotBytes;
-    __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + wsrc[i] + ((long long)k << 10) + lane16),
-                                     (EH_LDS void*)(slot + wdst[i]), 16, 0, 0);
-  };
-  auto dma = [&](int ks) { static_for<kDma>([&](auto ic) { dma_part(ic, ks); }); };
-  // the same with the step's scalars (k offset in bytes, ring slot offset) worked out beforehand
-  auto dma_part_pre = [&](auto ic, long long k10, int slotoff) {
-    constexpr int i = decltype(ic)::value;
-    __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + wsrc[i] + k10 + lane16),
-                                     (EH_LDS void*)(lds + slotoff + wdst[i]), 16, 0, 0);
-  };
+  RingFeed<MT, DUAL> feed(cur, next, KS, steps, rb, lane, wave, lds, wdelta);
   // activations: block n, k-step ks, half h -> fragment (n, 2*ks + h) of 2*KS per block
   const EH_GLOBAL char* ybase = uniform_ptr(yq);
   const EH_GLOBAL char* ybase2 = uniform_ptr(DUAL ? yq2 : yq);
@@ -404,7 +489,7 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
   auto fetch_a_half = [&](frag_t& ah, auto mc, auto hc, int ks) {
     constexpr int m = decltype(mc)::value;
     constexpr int h = decltype(hc)::value;
-    const uint32_t p = laneoff + (ks & (kSlots - 1)) * kSlotBytes;
+    const uint32_t p = laneoff + ((rb + ks) & (kSlots - 1)) * kSlotBytes;
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(ah) : "v"(p), "n"(m * 2048 + h * 512) : "memory");
   };
   auto fetch_a = [&](frag_t (&a)[2], auto mc, int ks) {
@@ -418,20 +503,22 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
   // loads up to B(ks) and its share of DMA(ks+1) have landed; tile 0 then runs at once
   // (its weights are in registers already), and the barrier that publishes DMA(ks+1)
   // to the other waves comes behind tile 0's matrix instructions, as do, spread over the
-  // tiles, the LDS reads for step ks+1 and the pieces of DMA(ks+D+1): a single wave issues
+  // tiles, the LDS reads for step ks+1 and the pieces of DMA(ks+6): a single wave issues
   // about one instruction per four cycles, so everything that is not a matrix instruction
   // has to sit between matrix instructions or the matrix core idles while it is issued.
   // Scalars of a step's loads are worked out a few tiles ahead, where the wave has issue slots
   // to spare (a wave issues one instruction per four clocks: anything left for the slot it is
   // needed in delays the next matrix instruction): at tile kPre the byte offset of the
-  // activations of step ks+D, and k offset and ring slot of the weights of the NEXT step's DMA.
+  // activations of step ks+D, and source and destination of the NEXT step's DMA.
+  // LEFT: the steps that follow this one where that is known to be less than D, else D: only steps with
+  // D others behind them reload activations, and the last one reads no weights for the next.
   constexpr bool kAhead = MT >= 4;
   constexpr int kPre = MT - 3;
-  long long nx_k10 = (long long)min(kDepth + 1, lastk) << 10;  // for step 0: DMA(D+1)
-  int nx_slot = ((kDepth + 1) & (kSlots - 1)) * kSlotBytes;
   long long nx_b10 = 0;
-  auto step = [&](frag_t (&b)[NB][2], int ks) {
-    asm volatile("s_waitcnt vmcnt(%0) ; step-sync" ::"n"(kInFlight) : "memory");
+  auto step = [&](frag_t (&b)[NB][2], int ks, auto left) {
+    constexpr int LEFT = decltype(left)::value;
+    if constexpr (LEFT >= kDepth - 1) asm volatile("s_waitcnt vmcnt(%0) ; step-sync" ::"n"(kInFlight) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0) ; end-sync %1" ::"n"((kDepth - 1 - LEFT) * kDma + LEFT * kGroup), "n"(kGroup) : "memory");
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
       asm volatile("" : "+v"(b[n][0]));
@@ -448,7 +535,7 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
       static_for<GS>([&](auto ic) {  // their operands have landed (younger reads: those of all other groups)
         constexpr int m = m0 + decltype(ic)::value;
         frag_t(&am)[2] = a[m];
-        asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(am[0]), "+v"(am[1]) : "n"(2 * (MT - GS)));
+        asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(am[0]), "+v"(am[1]) : "n"(LEFT > 0 ? 2 * (MT - GS) : 2 * (MT - m0 - GS)));
       });
       static_for<2>([&](auto hc) {
         constexpr int h = decltype(hc)::value;
@@ -467,9 +554,11 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
           }
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (g == 0 && h == 1 && m == m0) asm volatile("s_barrier" ::: "memory");
-          if constexpr (g != 0) fetch_a_half(a[m][h], mc, hc, ks + 1);
-          else if constexpr (h == 1) fetch_a(a[m], mc, ks + 1);  // slot ks+1 is complete only behind the barrier
-          if constexpr (m == MT - 1) {  // the last use of this k half of the activations: reload it for step ks+D
+          if constexpr (LEFT > 0) {
+            if constexpr (g != 0) fetch_a_half(a[m][h], mc, hc, ks + 1);
+            else if constexpr (h == 1) fetch_a(a[m], mc, ks + 1);  // slot ks+1 is complete only behind the barrier
+          }
+          if constexpr (LEFT >= kDepth && m == MT - 1) {  // the last use of this k half of the activations: reload it for step ks+D
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
               if constexpr (kAhead) load_b_half_pre(b[n][h], n, nx_b10, hc);
@@ -478,75 +567,67 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
           }
           if constexpr (h == 0) {
             // DMA piece i travels with tile min(i, MT-1), behind its first matrix instructions
-            // (the slot it fills was last read several steps ago: no need to be past the barrier)
             static_for<kDma>([&](auto pc) {
               constexpr int i = decltype(pc)::value;
-              if constexpr ((i < MT - 1 ? i : MT - 1) == m) {
-                if constexpr (kAhead) dma_part_pre(pc, nx_k10, nx_slot);
-                else dma_part(pc, ks + kDepth + 1);
-              }
+              if constexpr ((i < MT - 1 ? i : MT - 1) == m) feed.template piece<i>();
             });
-            if constexpr (kAhead && m == kPre) {
+            if constexpr (LEFT >= kDepth && kAhead && m == kPre) {
               nx_b10 = (long long)(2 * min(ks + kDepth, lastk)) << 10;
               asm volatile("" : "+s"(nx_b10));
             }
             __builtin_amdgcn_sched_barrier(0);
-          } else if constexpr (kAhead && m == kPre) {
+          } else if constexpr (LEFT > 0 && kAhead && m == kPre) {
             // this step's DMA pieces (tiles 0 .. kDma-1 <= kPre, first slot) are out: the next step's
-            nx_k10 = (long long)min(ks + kDepth + 2, lastk) << 10;
-            nx_slot = ((ks + kDepth + 2) & (kSlots - 1)) * kSlotBytes;
-            asm volatile("" : "+s"(nx_k10), "+s"(nx_slot));
+            feed.advance();
           }
         });
       });
       __builtin_amdgcn_sched_barrier(0);
     });
+    if constexpr (LEFT > 0 && !kAhead) feed.advance();
   };
 
-  // nobody may still be reading the ring (previous pass) when it is refilled
+  // The weights of the first kRingAhead steps are in the ring or on their way there; register set c
+  // is the one of step (c + KS) % D, so that the last steps always have the sets 0 .. D-1.
+  const int r = steps % kDepth;
+#pragma unroll
+  for (int c = 0; c < kDepth; ++c)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) load_b(b[c][n], n, (c + r) % kDepth);
+  // everything has landed everywhere
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  // Prologue.  Issue order: DMA(0) | DMA(1) B(0) | DMA(2) B(1) | ... | DMA(D) B(D-1)
-  dma(0);
 #pragma unroll
-  for (int j = 0; j < kDepth; ++j) {
-    dma(j + 1);
+  for (int c = 0; c < kDepth; ++c)
 #pragma unroll
-    for (int n = 0; n < NB; ++n) load_b(b[j][n], n, j);
-  }
-  // DMA(0) landed everywhere (younger: D whole groups), then a <- slot 0
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kDepth * kGroup) : "memory");
+    for (int n = 0; n < NB; ++n) {
+      asm volatile("" : "+v"(b[c][n][0]));
+      asm volatile("" : "+v"(b[c][n][1]));
+    }
   static_for<MT>([&](auto mc) { fetch_a(a[decltype(mc)::value], mc, 0); });
-  // From here the wait that opens step s sees, younger than B(s) and DMA(s+1), exactly
-  // the D-1 groups DMA(s+2) B(s+1) ... DMA(s+D) B(s+D-1).
+  constexpr std::integral_constant<int, kDepth> all{};
+  // nested so that no path through the code runs a step whose register set another one should have
+  // filled (the build walks them all)
   int ks = 0;
-  for (; ks + kDepth <= KS; ks += kDepth) {
-#pragma unroll
-    for (int j = 0; j < kDepth; ++j) step(b[j], ks + j);
-  }
-  // the last KS % D steps, nested so that step j+1 is only reachable through step j
-  auto tail = [&](auto self, auto jc) {
-    constexpr int j = decltype(jc)::value;
-    if constexpr (j < kDepth - 1) {
-      if (ks + j < KS) {
-        step(b[j], ks + j);
-        self(self, std::integral_constant<int, j + 1>{});
+  auto first = [&](auto self, auto cc) {  // steps % D of them, on the sets up to D - 1
+    constexpr int c = decltype(cc)::value;
+    if constexpr (c > 0) {
+      if (r >= kDepth - c) {
+        if constexpr (c > 1) self(self, std::integral_constant<int, c - 1>{});
+        step(b[c], ks++, all);
       }
     }
   };
-  tail(tail, std::integral_constant<int, 0>{});
-  // The loads issued past the end (clamped) still write their registers: wait for
-  // them, and keep every destination register reserved until here, or the
-  // compiler would hand it out again while a load is still on its way to it.
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  if (steps > kDepth) first(first, std::integral_constant<int, kDepth - 1>{});
+  for (; ks + kDepth < steps; ks += kDepth) {
 #pragma unroll
-  for (int n = 0; n < NB; ++n)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int j = 0; j < kDepth; ++j) asm volatile("" ::"v"(b[j][n][h]));
-#pragma unroll
-  for (int m = 0; m < MT; ++m) asm volatile("" ::"v"(a[m][0]), "v"(a[m][1]));
-  between();
+    for (int j = 0; j < kDepth; ++j) step(b[j], ks + j, all);
+  }
+  static_for<kDepth>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    step(b[j], ks + j, std::integral_constant<int, kDepth - 1 - j>{});
+  });
+  // what a step of this pass had too few pieces for
+  if (2 * next.mt > kG32Waves * kDma) ring_start<DUAL>(next, KS, rb + KS, lane, wave, lds, wdelta, kG32Waves * kDma);
 
   // accumulator register 4g+i of lane l: vocabulary row 32*tile + 8g + 4*(l/32) + i, token l%32
   const int half = lane >> 5;
@@ -575,7 +656,7 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
     return;
   } else {
   float z2[NB];
-  EH_LDS float* top2 = (EH_LDS float*)(lds + g32_ring_bytes()) + threadIdx.x * 4;
+  EH_LDS float* top2 = (EH_LDS float*)(lds + g32_ring_bytes()) + threadIdx.x;
   if constexpr (TOP2) {
 #pragma unroll
     for (int n = 0; n < NB; ++n) z2[n] = top2[n];
@@ -596,7 +677,7 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
             z1 = fmaxf(z1, acc[m][n][j]);
           }
         }
-        stats_push16<ARGMAX_ONLY>(st[n], acc[m][n], row0 + half * 4, park_of(lds, n));
+        stats_push16<ARGMAX_ONLY>(st[n], acc[m][n], row0 + half * 4, park_of(lds));
       }
       __builtin_amdgcn_sched_barrier(0);
       continue;
@@ -613,7 +694,7 @@ __device__ __forceinline__ void pass32(const frag_t* __restrict__ Wf, const frag
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      stats_push16_ragged<ARGMAX_ONLY>(st[n], acc[m][n], row0 + half * 4, row_hi, park_of(lds, n));
+      stats_push16_ragged<ARGMAX_ONLY>(st[n], acc[m][n], row0 + half * 4, row_hi, park_of(lds));
       // keep the instruction scheduler from pulling all accumulators into vector registers at once
       // (it would spill inside the k loop's tail)
       __builtin_amdgcn_sched_barrier(0);
@@ -644,74 +725,22 @@ __device__ __forceinline__ int pass_tiles(int tiles16) {
 }
 
 // A pass for a wave that owns no live token block: it still has to bring its share of the
-// weights into the ring and keep every barrier of pass32<MT, ...> (one when the pass opens, one
-// behind the prologue, one per k-step), but issues nothing else.  Its loads are the DMA pieces
-// only, in pass32's order: at the wait that opens step ks the pieces of steps ks+2 .. ks+D may
-// still be in flight.
-template <int MT, typename BT = NothingBetween>
-__device__ __forceinline__ void pass32_idle(const frag_t* __restrict__ Wf, int T16, int t16_end, int KS, int lane,
-                                            int wave, EH_LDS char* lds, BT between = BT()) {
+// weights into the ring and keep every barrier of pass32<MT, ...> (one when the pass opens, one per
+// k-step), but issues nothing else.  Its loads are the DMA pieces only, in pass32's order: at the wait
+// that opens step ks the pieces of steps ks+2 .. ks+5 may still be in flight.
+template <int MT, bool DUAL = false>
+__device__ __forceinline__ void pass32_idle(const G32Src& cur, const G32Src& next, int rb, int KS, int lane, int wave, EH_LDS char* lds,
+                                            long long wdelta = 0) {
   constexpr int kDma = dma_per_wave(MT);
-  constexpr int NF = 2 * MT;
-  const int lastk = KS - 1;
-  const uint32_t lane16 = (uint32_t)lane << 4;
-  const EH_GLOBAL char* wbase = uniform_ptr(Wf);
-  long long wsrc[kDma];
-  int wdst[kDma];
-#pragma unroll
-  for (int i = 0; i < kDma; ++i) {
-    int f = wave + kG32Waves * i;
-    if (f >= NF) f = (wave < NF) ? wave + kG32Waves * ((NF - 1 - wave) / kG32Waves) : NF - 1;
-    const int t16 = min(T16 + f, t16_end - 1);
-    wsrc[i] = ((long long)t16 * KS) << 10;
-    wdst[i] = f * 1024;
-  }
-  auto dma = [&](int ks) {
-    const int k = min(ks, lastk);
-    EH_LDS char* slot = lds + (ks & (kSlots - 1)) * kSlotBytes;
-#pragma unroll
-    for (int i = 0; i < kDma; ++i)
-      __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + wsrc[i] + ((long long)k << 10) + lane16),
-                                       (EH_LDS void*)(slot + wdst[i]), 16, 0, 0);
-  };
+  const int steps = DUAL ? max(KS, kDepth) : KS;
+  RingFeed<MT, DUAL> feed(cur, next, KS, steps, rb, lane, wave, lds, wdelta);
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  dma(0);
-#pragma unroll
-  for (int j = 0; j < kDepth; ++j) dma(j + 1);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kDepth * kDma) : "memory");
-  for (int ks = 0; ks < KS; ++ks) {
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kDepth - 1) * kDma) : "memory");
-    dma(ks + kDepth + 1);
+  for (int ks = 0; ks < steps; ++ks) {
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kRingAhead - 2) * kDma) : "memory");
+    static_for<kDma>([&](auto pc) { feed.template piece<decltype(pc)::value>(); });
+    feed.advance();
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  between();
-}
-
-// The weights of the first kDepth + 1 k-steps of a pass, asked for ahead of time by this wave's DMA
-// share (the pass will fetch them again: what this buys is that they then come from the L2 and
-// not from HBM, and that the memory system has work while the waves compute).  They land in ring
-// slots, which nobody uses for them; the one slot that another wave of the workgroup may still
-// be reading when this is called right behind a k loop -- the operands of that loop's last step,
-// slot (KS - 1) mod 8 -- is left alone.  Waited for by the vmcnt(0) that opens the next pass at
-// the latest.
-__device__ __forceinline__ void ring_prefetch(const frag_t* __restrict__ Wf, int T16, int t16_end, int mt, int KS, int lane,
-                                              int wave, EH_LDS char* lds) {
-  constexpr int kAhead = kDepth + 1;  // k-steps asked for (seven were slower than four)
-  static_assert(kAhead <= kSlots, "one slot per k-step");
-  const int lastk = KS - 1;
-  const int busy = lastk & (kSlots - 1);
-  const uint32_t lane16 = (uint32_t)lane << 4;
-  const EH_GLOBAL char* wbase = uniform_ptr(Wf);
-#pragma unroll
-  for (int ks = 0; ks < kAhead; ++ks) {
-    if (ks == busy) continue;  // uniform
-    const int k = min(ks, lastk);
-    for (int f = wave; f < 2 * mt; f += kG32Waves) {
-      const int t16 = min(T16 + f, t16_end - 1);
-      __builtin_amdgcn_global_load_lds((const EH_GLOBAL void*)(wbase + ((((long long)t16 * KS) + k) << 10) + lane16),
-                                       (EH_LDS void*)(lds + ks * kSlotBytes + f * 1024), 16, 0, 0);
-    }
-  }
+  if (2 * next.mt > kG32Waves * kDma) ring_start<DUAL>(next, KS, rb + KS, lane, wave, lds, wdelta, kG32Waves * kDma);
 }
 
 // How the workgroups of a launch share n_live rows: groups of at most 8 blocks of 32 rows (two per
@@ -722,7 +751,7 @@ struct G32Deal {
   int part, first, count; // this workgroup: its share of the vocabulary, its group's blocks
   __device__ __forceinline__ G32Deal(int n_live, int grid, int max_parts, int wg) {
     const int blocks = (n_live + 31) >> 5;
-    groups = (blocks + 2 * kG32Waves - 1) / (2 * kG32Waves);
+    groups = (blocks + kG32Waves - 1) / kG32Waves;
     parts = live_parts(n_live, kG32Group, 0, grid, max_parts);
     const int y = groups > 0 ? wg / parts : 0;
     part = wg - y * parts;
@@ -733,10 +762,7 @@ struct G32Deal {
 
 // One launch covers n_heads consecutive heads (weights from the table; activations and outputs of
 // consecutive heads lie y_stride fragments / part_stride records apart): a workgroup walks its slice
-// of every head.  (Asking for the next pass's or head's first weights while the statistics are worked
-// out, as rows_stream does, costs more than it gives here: the next pass opens by waiting for them
-// and then fetches them again.  With it and without, us: 16 heads of d = 512 on 400 rows 547 and 513;
-// 6 heads of d = 1024 on 100 rows 150 and 142; 24 of d = 2048 on 512 rows 2277 and 2250.)
+// of every head, and the weights run on through the ring from pass to pass and head to head.
 template <bool ARGMAX_ONLY, bool TOP2>
 __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
     const frag_t* const* __restrict__ Wf_tab, int n_heads, const frag_t* __restrict__ yq, long long y_stride, int VT16, int KS,
@@ -752,36 +778,48 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
   // the whole workgroup leaves if there is nothing for it (the waves share barriers, so a single
   // wave must not leave on its own; a wave without a block keeps the others company)
   if (deal.count <= 0) return;
-  const int nb_live = deal.count / kG32Waves + (wave < deal.count % kG32Waves ? 1 : 0);
-  const int nb_first = deal.first + wave * (deal.count / kG32Waves) + min(wave, deal.count % kG32Waves);
+  const bool live = wave < deal.count;
+  const int block = deal.first + wave;
   // one token group of at most 5 blocks streams the weights once and is paced by that stream:
   // balance the bytes (16-row tiles); otherwise balance the matrix instructions (32-row tiles).
   // Slices differ by a tile (12 or 13 of 32 rows at 512 rows); from head to head they move on by
   // one workgroup, so that none of them has the longer one every time.
   const int gran = deal.groups == 1 && deal.count <= 5 ? 1 : 2;
   auto slice_of = [&](int l) { return (deal.part + l) % deal.parts; };
-  EH_LDS float* top2 = (EH_LDS float*)(lds + g32_ring_bytes()) + threadIdx.x * 4;
+  EH_LDS float* top2 = (EH_LDS float*)(lds + g32_ring_bytes()) + threadIdx.x;
+  auto first_of = [&](int l) {
+    G32Src p;
+    vocab_slice(VT16, gran, slice_of(l), deal.parts, p.t16, p.t16_end);
+    p.W = Wf_tab[l];
+    p.zeros = nullptr;
+    p.mt = pass_tiles(p.t16_end - p.t16);
+    return p;
+  };
+  const bool run_on = ring_runs_on(KS);
+  int rb = 0;
+  G32Src cur = first_of(0);
+  if (run_on) ring_start<false>(cur, KS, rb, lane, wave, lds);
   for (int l = 0; l < n_heads; ++l) {
-    const frag_t* Wf = Wf_tab[l];
-    const frag_t* ybase = yq + l * y_stride + (long long)nb_first * 2 * KS * kWave;
-    int T0, T1;
-    vocab_slice(VT16, gran, slice_of(l), deal.parts, T0, T1);
-    const int row_hi = min(V, T1 * 16);
-    Stats st[2];
+    const frag_t* ybase = yq + l * y_stride + (long long)block * 2 * KS * kWave;
+    const int row_hi = min(V, cur.t16_end * 16);
+    Stats st[1];
     stats_init(st[0]);
-    stats_init(st[1]);
-    if constexpr (TOP2) {
-#pragma unroll
-      for (int n = 0; n < 2; ++n) top2[n] = -INFINITY;
-    }
-    for (int t = T0; t < T1;) {
-      const int mt = pass_tiles(T1 - t);
+    if constexpr (TOP2) top2[0] = -INFINITY;
+    for (bool more = true; more;) {
+      G32Src after = cur;  // what follows: the rest of the slice, or the next head's
+      after.t16 += 2 * cur.mt;
+      after.mt = pass_tiles(after.t16_end - after.t16);
+      more = after.mt > 0;
+      if (!more && l + 1 < n_heads) after = first_of(l + 1);
+      G32Src next = after;
+      if (!run_on) {
+        next.mt = 0;
+        ring_begin<false>(cur, KS, rb, lane, wave, lds);
+      }
 #define EH_G32_PASS(MT_)                                                                                              \
-  if (nb_live <= 0) pass32_idle<MT_>(Wf, t, T1, KS, lane, wave, lds);                                                 \
-  else if (nb_live == 1) pass32<MT_, 1, ARGMAX_ONLY, TOP2, false, Stats>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, \
-                                                                  reinterpret_cast<Stats(&)[1]>(st[0]));              \
-  else pass32<MT_, 2, ARGMAX_ONLY, TOP2, false, Stats>(Wf, ybase, t, T1, KS, row_hi, lane, wave, lds, st)
-      switch (mt) {
+  if (!live) pass32_idle<MT_>(cur, next, rb, KS, lane, wave, lds);                                                \
+  else pass32<MT_, 1, ARGMAX_ONLY, TOP2, false, Stats>(cur, next, rb, ybase, KS, row_hi, lane, wave, lds, st)
+      switch (cur.mt) {
         case 7: EH_G32_PASS(7); break;
         case 6: EH_G32_PASS(6); break;
         case 5: EH_G32_PASS(5); break;
@@ -791,75 +829,80 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
         default: EH_G32_PASS(1); break;
       }
 #undef EH_G32_PASS
-      t += 2 * mt;
+      cur = after;
+      rb = (rb + KS) & (kSlots - 1);
     }
     // lanes l and l+32 hold the same token: fold the two row groups
     const long long at = l * part_stride + (long long)slice_of(l) * R_pad;
-#pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      stats_resolve<ARGMAX_ONLY>(st[n], park_of(lds, n));
-      if constexpr (TOP2) {
-        const float a1 = st[n].zb, a2 = top2[n];
-        const float o1 = __shfl_xor(a1, 32), o2 = __shfl_xor(a2, 32);
-        const float u2 = fmaxf(fminf(a1, o1), fmaxf(a2, o2));  // second largest of the union
-        if (lane < 32 && n < nb_live) second[at + (nb_first + n) * 32 + lane] = u2;
-      }
-      st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));
-      if (lane < 32 && n < nb_live) partials[at + (nb_first + n) * 32 + lane] = st[n];
+    stats_resolve<ARGMAX_ONLY>(st[0], park_of(lds));
+    if constexpr (TOP2) {
+      const float a1 = st[0].zb, a2 = top2[0];
+      const float o1 = __shfl_xor(a1, 32), o2 = __shfl_xor(a2, 32);
+      const float u2 = fmaxf(fminf(a1, o1), fmaxf(a2, o2));  // second largest of the union
+      if (lane < 32 && live) second[at + block * 32 + lane] = u2;
     }
+    st[0] = stats_merge(st[0], stats_shfl_xor(st[0], 32));
+    if (lane < 32 && live) partials[at + block * 32 + lane] = st[0];
   }
+  EH_LOADS_DONE();
 }
 
 // The two projections of the training objectives (Section 3.3) fused: grid.x = workgroups over
-// the vocabulary, grid.y = groups of 4*NBH blocks of 32 tokens; a wave owns NBH token blocks,
+// the vocabulary, grid.y = groups of 8 blocks of 32 tokens; a wave owns a token block,
 // for which it holds the head's and the model's activations, and walks its slice of the
 // vocabulary in passes of at most 3 tiles of 32 rows of both weight matrices.
-template <int NBH>
 __global__ __launch_bounds__(kG32Threads, 1) void gemm32_kl_kernel(
     const frag_t* __restrict__ Wf, long long wdelta, const frag_t* __restrict__ yq, const frag_t* __restrict__ yq2,
-    int VT16, int KS, int V, int n_rows, int R_pad, const int* __restrict__ labels, KlStats* __restrict__ partials) {
+    const frag_t* __restrict__ zeros, int VT16, int KS, int V, int n_rows, int R_pad, const int* __restrict__ labels,
+    KlStats* __restrict__ partials) {
   extern __shared__ __attribute__((aligned(16))) char g32_smem[];
   EH_LDS char* lds = (EH_LDS char*)g32_smem;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int live_blocks = (n_rows + 31) >> 5;
-  if (live_blocks - (int)(blockIdx.y * kG32Waves * NBH) <= 0) return;
-  const int nb_first = (blockIdx.y * kG32Waves + wave) * NBH;
-  const int nb_live = min(NBH, live_blocks - nb_first);
+  if (live_blocks - (int)blockIdx.y * kG32Waves <= 0) return;
+  const int block = blockIdx.y * kG32Waves + wave;
+  const bool live = block < live_blocks;
   int T0, T1;
   vocab_slice(VT16, 2, blockIdx.x, gridDim.x, T0, T1);
   const int row_hi = min(V, T1 * 16);
-  KlStats st[NBH];
-#pragma unroll
-  for (int n = 0; n < NBH; ++n) {
-    const int token = (nb_first + n) * 32 + (lane & 31);
-    kl_init(st[n], (labels && token < n_rows) ? labels[token] : -1);
-  }
-  const frag_t* y1 = yq + (long long)nb_first * 2 * KS * kWave;
-  const frag_t* y2 = yq2 + (long long)nb_first * 2 * KS * kWave;
+  KlStats st[1];
+  const int token = block * 32 + (lane & 31);
+  kl_init(st[0], (labels && token < n_rows) ? labels[token] : -1);
+  const frag_t* y1 = yq + (long long)block * 2 * KS * kWave;
+  const frag_t* y2 = yq2 + (long long)block * 2 * KS * kWave;
   constexpr int kMaxMH = 3;
-  for (int t = T0; t < T1;) {
+  auto src_at = [&](int t) {  // the pass at 16-row tile t: passes of at most kMaxMH tiles a side of about equal size
     const int left = (T1 - t + 1) >> 1;
     const int passes = (left + kMaxMH - 1) / kMaxMH;
-    const int mh = (left + passes - 1) / passes;
-    switch (mh) {
-      case 3:
-        pass32<6, 2 * NBH, false, false, true, KlStats>(Wf, y1, t, T1, KS, row_hi, lane, wave, lds, st, wdelta, y2);
-        break;
-      case 2:
-        pass32<4, 2 * NBH, false, false, true, KlStats>(Wf, y1, t, T1, KS, row_hi, lane, wave, lds, st, wdelta, y2);
-        break;
-      default:
-        pass32<2, 2 * NBH, false, false, true, KlStats>(Wf, y1, t, T1, KS, row_hi, lane, wave, lds, st, wdelta, y2);
-        break;
+    return G32Src{Wf, t, T1, passes > 0 ? 2 * ((left + passes - 1) / passes) : 0, zeros};
+  };
+  const bool run_on = ring_runs_on(KS);
+  int rb = 0;
+  G32Src cur = src_at(T0);
+  if (run_on) ring_start<true>(cur, KS, rb, lane, wave, lds, wdelta);
+  while (cur.mt > 0) {
+    const G32Src after = src_at(cur.t16 + cur.mt);
+    G32Src next = after;
+    if (!run_on) {
+      next.mt = 0;
+      ring_begin<true>(cur, KS, rb, lane, wave, lds, wdelta);
     }
-    t += 2 * mh;
+#define EH_KL_PASS(MT_)                                                                       \
+  if (!live) pass32_idle<MT_, true>(cur, next, rb, KS, lane, wave, lds, wdelta);           \
+  else pass32<MT_, 2, false, false, true, KlStats>(cur, next, rb, y1, KS, row_hi, lane, wave, lds, st, wdelta, y2)
+    switch (cur.mt) {
+      case 6: EH_KL_PASS(6); break;
+      case 4: EH_KL_PASS(4); break;
+      default: EH_KL_PASS(2); break;
+    }
+#undef EH_KL_PASS
+    cur = after;
+    rb = (rb + KS) & (kSlots - 1);
   }
-#pragma unroll
-  for (int n = 0; n < NBH; ++n) {
-    st[n] = kl_merge(st[n], kl_shfl_xor(st[n], 32));  // lanes l and l+32 hold the same token
-    if (lane < 32 && n < nb_live) partials[(long long)blockIdx.x * R_pad + (nb_first + n) * 32 + lane] = st[n];
-  }
+  EH_LOADS_DONE();
+  st[0] = kl_merge(st[0], kl_shfl_xor(st[0], 32));  // lanes l and l+32 hold the same token
+  if (lane < 32 && live) partials[(long long)blockIdx.x * R_pad + block * 32 + lane] = st[0];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1093,21 +1136,29 @@ __device__ __forceinline__ void rows_merge2(const PartRecords& parts, int n_part
   }
 }
 
-// LayerNorm of the first head's rows, spread over the streaming workgroups (four waves per row).
+// LayerNorm of the first head's rows, spread over the streaming workgroups: four waves per row, in
+// workgroups of eight two rows at a time.
+template <int NW>
 __device__ __forceinline__ void rows_first_layernorm(const RowsParams& p, const RowsCtl& c, double* red) {
-  const int g = blockIdx.x, tid = threadIdx.x;
-  for (int r = g; r < p.n_rows; r += p.n_stream) {
+  constexpr int kTeams = NW / kLnWaves;
+  const int g = blockIdx.x, team = threadIdx.x / kLnThreads, tid = threadIdx.x % kLnThreads;
+  for (int r0 = g * kTeams; r0 < p.n_rows; r0 += p.n_stream * kTeams) {  // (the teams share the barriers)
+    const int r = min(r0 + team, p.n_rows - 1);
+    const bool mine = r0 + team < p.n_rows;
     const char* row = (const char*)p.h + ((long long)p.l0 * p.layer_stride + (long long)r * p.row_stride) * DtBf16::ESZ;
-    auto put = [&](int ch, const frag_t& v) { put_chunk32_coherent(p.y, p.KS, r, ch, v); };
+    auto put = [&](int ch, const frag_t& v) {
+      if (mine) put_chunk32_coherent(p.y, p.KS, r, ch, v);
+    };
+    double* own = red + team * 2 * kLnWaves;
     if (p.KS * 4 <= kLnCache * kWave)
-      group_layernorm_cached<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, red, put);
+      group_layernorm_cached<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, own, put);
     else
-      group_layernorm<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, red, put);
+      group_layernorm<DtBf16, kLnWaves>(row, p.d, p.KS * 4, p.gamma[p.l0], p.beta[p.l0], p.eps, tid, own, put);
     __syncthreads();
   }
   EH_STORES_DONE();
   __syncthreads();
-  if (tid == 0) ctl_add(c.ready(0), g, 1);
+  if (threadIdx.x == 0) ctl_add(c.ready(0), g, 1);
   EH_ROWS_STAMP(1);
 }
 
@@ -1119,7 +1170,7 @@ __device__ __forceinline__ bool rows_first_wait(const RowsParams& p, const RowsC
     if (lane == 0) *flag = v;
   }
   __syncthreads();
-  const int word = *flag;
+  const int word = __builtin_amdgcn_readfirstlane(*flag);  // (uniform for the compiler, too)
   __syncthreads();
   if (word < 0) return false;
   EH_AFTER_WAIT();
@@ -1136,15 +1187,14 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
   const int T0 = (int)((long long)p.VT16 * g / p.n_stream);
   const int T1 = (int)((long long)p.VT16 * (g + 1) / p.n_stream);
   const int row_hi = min(p.V, T1 * 16);
-  const int mt_first = pass_tiles(T1 - T0);
-  // a head's first weights are brought towards the L2 while something else is going on (here: the
-  // LayerNorm of the first head)
-  auto warm = [&](const frag_t* Wn) {
-    if (T0 < T1) ring_prefetch(Wn, T0, T1, mt_first, p.KS, lane, wave, lds);
-  };
+  const bool run_on = ring_runs_on(p.KS);
+  int rb = 0;
+  G32Src cur{p.Wf[p.l0], T0, T1, pass_tiles(T1 - T0), nullptr};
   EH_ROWS_STAMP(0);
-  warm(p.Wf[p.l0]);
-  rows_first_layernorm(p, c, red);
+  rows_first_layernorm<kG32Waves>(p, c, red);
+  // (weights asked for in front of the LayerNorm would only hold up its own loads: a wave's loads
+  // return in order)
+  if (run_on) ring_start<false>(cur, p.KS, rb, lane, wave, lds);
   if (!rows_first_wait(p, c, lane, wave, flag)) return false;
   int word = 0;
   int ncols = p.n_rows;
@@ -1152,30 +1202,25 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
   for (int j = 0; j < nh; ++j) {
     const int l = p.l0 + j;
     if (ncols == 0) return false;  // every row has left: the same for all workgroups
-    // token blocks of 32 columns, dealt to the four waves as evenly as they go (at most 2 each)
-    const int nblocks = (ncols + 31) >> 5;
-    const int nb_live = nblocks / kG32Waves + (wave < nblocks % kG32Waves ? 1 : 0);
-    const int nb_first = wave * (nblocks / kG32Waves) + min(wave, nblocks % kG32Waves);
-    Stats st[2];
+    const bool live = wave < (ncols + 31) >> 5;  // a block of 32 columns per wave
+    Stats st[1];
     stats_init(st[0]);
-    stats_init(st[1]);
-    const frag_t* Wf = p.Wf[l];
-    const frag_t* ybase = p.y + (long long)j * p.y_stride + (long long)nb_first * 2 * p.KS * kWave;
-    for (int t = T0; t < T1;) {
-      const int mt = pass_tiles(T1 - t);
-      // behind the head's last k loop, while its statistics are worked out and handed on: the
-      // start of the next head's weights is asked for (towards the L2; the next pass fetches it
-      // again from there), so that this workgroup's share of the memory system does not idle
-      const bool hand_on = t + 2 * mt >= T1 && j + 1 < nh;
-      auto btw = [&]() {
-        if (hand_on) warm(p.Wf[l + 1]);
-      };
+    const frag_t* ybase = p.y + (long long)j * p.y_stride + (long long)wave * 2 * p.KS * kWave;
+    for (bool more = cur.mt > 0; more;) {  // (a workgroup without a tile of its own has no pass)
+      G32Src after = cur;  // what follows: the rest of the slice, or the next head's
+      after.t16 += 2 * cur.mt;
+      after.mt = pass_tiles(after.t16_end - after.t16);
+      more = after.mt > 0;
+      if (!more && j + 1 < nh) after = G32Src{p.Wf[l + 1], T0, T1, pass_tiles(T1 - T0), nullptr};
+      G32Src next = after;
+      if (!run_on) {
+        next.mt = 0;
+        ring_begin<false>(cur, p.KS, rb, lane, wave, lds);
+      }
 #define EH_ROWS_PASS(MT_)                                                                                     \
-  if (nb_live <= 0) pass32_idle<MT_>(Wf, t, T1, p.KS, lane, wave, lds, btw);                                     \
-  else if (nb_live == 1) pass32<MT_, 1, false, false, false, Stats>(Wf, ybase, t, T1, p.KS, row_hi, lane, wave, lds, \
-                                                        reinterpret_cast<Stats(&)[1]>(st[0]), 0, nullptr, btw);  \
-  else pass32<MT_, 2, false, false, false, Stats>(Wf, ybase, t, T1, p.KS, row_hi, lane, wave, lds, st, 0, nullptr, btw)
-      switch (mt) {
+  if (!live) pass32_idle<MT_>(cur, next, rb, p.KS, lane, wave, lds);                                          \
+  else pass32<MT_, 1, false, false, false, Stats>(cur, next, rb, ybase, p.KS, row_hi, lane, wave, lds, st)
+      switch (cur.mt) {
         case 7: EH_ROWS_PASS(7); break;
         case 6: EH_ROWS_PASS(6); break;
         case 5: EH_ROWS_PASS(5); break;
@@ -1185,18 +1230,16 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
         default: EH_ROWS_PASS(1); break;
       }
 #undef EH_ROWS_PASS
-      t += 2 * mt;
+      cur = after;
+      rb = (rb + p.KS) & (kSlots - 1);
     }
     if (j < 8) EH_ROWS_STAMP(3 + 2 * j);
     const long long part_at = (long long)(j & 1) * p.n_stream * p.R_pad + (long long)g * p.R_pad;
-#pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      stats_resolve<false>(st[n], park_of(lds, n));
-      st[n] = stats_merge(st[n], stats_shfl_xor(st[n], 32));  // lanes l and l+32 hold the same token
-      if (lane < 32 && n < nb_live) {
-        store_coherent(p.part4 + part_at + (nb_first + n) * 32 + lane, stats_head(st[n]));
-        store_coherent(p.parti + part_at + (nb_first + n) * 32 + lane, st[n].ib);
-      }
+    stats_resolve<false>(st[0], park_of(lds));
+    st[0] = stats_merge(st[0], stats_shfl_xor(st[0], 32));  // lanes l and l+32 hold the same token
+    if (lane < 32 && live) {
+      store_coherent(p.part4 + part_at + wave * 32 + lane, stats_head(st[0]));
+      store_coherent(p.parti + part_at + wave * 32 + lane, st[0].ib);
     }
     if (j + 1 < nh) {
       // while those stores travel: look whether the next head's activations are there (they have
@@ -1212,7 +1255,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
     if (tid == 0) ctl_add(c.done(j), g, 1);
     if (j < 8) EH_ROWS_STAMP(4 + 2 * j);
     if (j + 1 < nh) {
-      word = *flag;
+      word = __builtin_amdgcn_readfirstlane(*flag);
       __syncthreads();  // the flag is rewritten at the end of the next head
       if (word < 0) return false;
       EH_AFTER_WAIT();
@@ -1235,7 +1278,7 @@ __device__ __forceinline__ bool rows_stream_ks(const RowsParams& p, const RowsCt
                                                int lane, int wave, double* red, int* flag) {
   const int g = blockIdx.x, tid = threadIdx.x;
   const int nh = p.l1 - p.l0;
-  const int nsw = ((int)gridDim.x - p.n_stream) * kG32Waves;  // service waves
+  const int nsw = ((int)gridDim.x - p.n_stream) * kKsWaves;  // service waves
   const int row_hi = min(p.V, sl.t1 * 16);
   const long long slice_at = (long long)sl.t0 * p.KS * kWave;
   const long long pass_len = (long long)2 * MT * p.KS * kWave;
@@ -1244,7 +1287,7 @@ __device__ __forceinline__ bool rows_stream_ks(const RowsParams& p, const RowsCt
   frag_t a[2][MT][2], b[2][2][2];
   // (weights asked for in front of the LayerNorm would only hold up its own loads: a wave's loads
   // return in order)
-  rows_first_layernorm(p, c, red);
+  rows_first_layernorm<kKsWaves>(p, c, red);
   ks_start<MT>(a, p.Wf[p.l0] + slice_at, p.KS, wave, voff);
   if (!rows_first_wait(p, c, lane, wave, flag)) return false;  // leaves *flag >= 0
   int ncols = p.n_rows;
@@ -1533,8 +1576,8 @@ __device__ __forceinline__ void rows_serve_cascade(const RowsParams& p, const Ro
 // argmax records are there, workgroup g merges those of the positions g, g + grid, ... (one
 // record per thread), and when all positions are merged workgroup b < B walks draft row b's prefix.
 __device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const RowsCtl& c, int lane, int wave, int* flag) {
-  __shared__ float red_z[kG32Waves];
-  __shared__ int red_i[kG32Waves];
+  __shared__ float red_z[kKsWaves];
+  __shared__ int red_i[kKsWaves];
   const int g = blockIdx.x, tid = threadIdx.x;
   if (wave == 0) {
     const int v = rows_wait(p, c, c.done(0), p.n_stream, lane);
@@ -1550,15 +1593,15 @@ __device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const Rows
   for (int pos = g; pos < p.n_rows; pos += p.n_stream) {
     float zb = -INFINITY;
     int ib = 0x7fffffff;
-    for (int q0 = 0; q0 < p.n_stream; q0 += 4 * kG32Threads) {  // all records requested before any is used
+    for (int q0 = 0; q0 < p.n_stream; q0 += 4 * kKsThreads) {  // all records requested before any is used
       frag_t h[4];
       int ri[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) parts.load(min(q0 + tid + i * kG32Threads, p.n_stream - 1), pos, h[i], ri[i]);
+      for (int i = 0; i < 4; ++i) parts.load(min(q0 + tid + i * kKsThreads, p.n_stream - 1), pos, h[i], ri[i]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float rz = __uint_as_float(h[i].w);
-        if (q0 + tid + i * kG32Threads < p.n_stream && (rz > zb || (rz == zb && ri[i] < ib))) { zb = rz; ib = ri[i]; }
+        if (q0 + tid + i * kKsThreads < p.n_stream && (rz > zb || (rz == zb && ri[i] < ib))) { zb = rz; ib = ri[i]; }
       }
     }
 #pragma unroll
@@ -1571,7 +1614,7 @@ __device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const Rows
     __syncthreads();
     if (tid == 0) {
 #pragma unroll
-      for (int w2 = 1; w2 < kG32Waves; ++w2)
+      for (int w2 = 1; w2 < kKsWaves; ++w2)
         if (red_z[w2] > zb || (red_z[w2] == zb && red_i[w2] < ib)) { zb = red_z[w2]; ib = red_i[w2]; }
       const int t = argmax_or_none(ib);
       __hip_atomic_store(c.target(pos), t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1613,7 +1656,8 @@ __device__ __forceinline__ void rows_verify_tail(const RowsParams& p, const Rows
 // KS_NB: 0 = rows_stream; 1 or 2 = rows_stream_ks with that many blocks of 32 rows.
 template <bool ARGMAX_ONLY, int KS_NB>
 __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_smem) {
-  __shared__ double red[2 * kLnWaves];
+  constexpr int NW = KS_NB > 0 ? kKsWaves : kG32Waves;
+  __shared__ double red[2 * NW];
   __shared__ int flag;
   EH_LDS char* lds = (EH_LDS char*)g32_smem;
   const int lane = threadIdx.x & 63;
@@ -1630,7 +1674,7 @@ __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_
       p.next_token[blockIdx.x] = -1;
     }
     if (blockIdx.x == gridDim.x - 1)
-      for (int i = threadIdx.x; i < p.n_ctl_next; i += kG32Threads) p.ctl_next[i] = 0;
+      for (int i = threadIdx.x; i < p.n_ctl_next; i += NW * kWave) p.ctl_next[i] = 0;
   }
   // a launch that gave up has not been acknowledged yet (eh_check clears the flag): do nothing
   if (*(volatile int*)p.status != 0) return;
@@ -1654,13 +1698,13 @@ __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_
     }
     if constexpr (KS_NB > 0) {
       if (ok && p.mode == 1) rows_verify_tail(p, c, lane, wave, &flag);
-    } else if (!ok) {
-      EH_STORES_DONE();  // weights asked for ahead may still be on their way to the ring
+    } else {
+      EH_LOADS_DONE();  // weights asked for ahead may still be on their way to the ring
     }
     return;
   }
   const int sg = (int)blockIdx.x - p.n_stream, nsg = (int)gridDim.x - p.n_stream;
-  if (p.mode == 0) rows_serve_cascade(p, c, lane, sg * kG32Waves + wave, nsg * kG32Waves);
+  if (p.mode == 0) rows_serve_cascade(p, c, lane, sg * NW + wave, nsg * NW);
 }
 
 // More than 64 rows: cascades only (a verification of so many positions takes three launches).
@@ -1671,7 +1715,7 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel_rows(const
 
 // Up to 32 * NB rows, NB = 1 or 2 (see rows_stream_ks).
 template <bool ARGMAX_ONLY, int NB>
-__global__ __launch_bounds__(kG32Threads, 1) void rows_ksplit_kernel(const RowsParams p) {
+__global__ __launch_bounds__(kKsThreads, 1) void rows_ksplit_kernel(const RowsParams p) {
   extern __shared__ __attribute__((aligned(16))) char g32_smem[];
   rows_kernel_body<ARGMAX_ONLY, NB>(p, g32_smem);
 }
@@ -1686,10 +1730,9 @@ __global__ void rows_preset_kernel(int* __restrict__ ctl, int n_ctl, int* __rest
   if (H_out && i < n_H) H_out[i] = NAN;
 }
 
-template <int NBH>
-void launch_kl(dim3 g, hipStream_t s, const frag_t* Wf, long long wdelta, const frag_t* yq, const frag_t* yq2,
+void launch_kl(dim3 g, hipStream_t s, const frag_t* Wf, long long wdelta, const frag_t* yq, const frag_t* yq2, const frag_t* zeros,
                int VT16, int KS, int V, int n_rows, int R_pad, const int* labels, KlStats* partials) {
-  hipLaunchKernelGGL((gemm32_kl_kernel<NBH>), g, dim3(kG32Threads), g32_lds_bytes(), s, Wf, wdelta, yq, yq2, VT16,
+  hipLaunchKernelGGL(gemm32_kl_kernel, g, dim3(kG32Threads), g32_lds_bytes(), s, Wf, wdelta, yq, yq2, zeros, VT16,
                      KS, V, n_rows, R_pad, labels, partials);
 }
 
@@ -1706,8 +1749,7 @@ hipError_t launch32(int grid, hipStream_t s, const frag_t* const* Wf_tab, int n_
 
 hipError_t gemm32_prepare() {
   for (const void* fn : {(const void*)gemm32_stats_kernel<false, true>, (const void*)gemm32_stats_kernel<true, false>,
-                         (const void*)gemm32_stats_kernel<false, false>, (const void*)gemm32_kl_kernel<1>,
-                         (const void*)gemm32_kl_kernel<2>}) {
+                         (const void*)gemm32_stats_kernel<false, false>, (const void*)gemm32_kl_kernel}) {
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g32_lds_bytes());
     if (e != hipSuccess) return e;
   }
@@ -1722,7 +1764,7 @@ hipError_t gemm32_launch(const eh_ctx* c, int head, int n_heads, const int* n_ro
   const int R_pad = (n_rows + 31) & ~31;
   const int cus = c->num_cu > 0 ? c->num_cu : 256;
   // one workgroup per compute unit, or one per group of 256 rows if that is more
-  const int grid = std::max(cus, (R_pad / 32 + 2 * kG32Waves - 1) / (2 * kG32Waves));
+  const int grid = std::max(cus, (R_pad / 32 + kG32Waves - 1) / kG32Waves);
   // (as many partial statistics as there is room for, and no slice without a tile of its own)
   const int max_parts = std::max(1, std::min({cus, kMaxParts, (c->VT + 1) / 2}));
   *parts = PartCount{live_parts(n_rows, kG32Group, 0, grid, max_parts), kG32Group, 0, n_rows_dev ? grid : 0, max_parts};
@@ -1747,16 +1789,17 @@ hipError_t rows_prepare(eh_ctx* c) {
   if (e != hipSuccess) return e;
   const int cus = prop.multiProcessorCount;
   if (cus < 4 * kRowsServiceWgs) return hipSuccess;  // too small a device to set workgroups aside
-  const struct { const void* fn; size_t lds; } fns[5] = {{(const void*)gemm32_stats_kernel_rows, g32_lds_bytes()},
-                                                       {(const void*)rows_ksplit_kernel<false, 1>, ks_lds_bytes()},
-                                                       {(const void*)rows_ksplit_kernel<true, 1>, ks_lds_bytes()},
-                                                       {(const void*)rows_ksplit_kernel<false, 2>, ks_lds_bytes()},
-                                                       {(const void*)rows_ksplit_kernel<true, 2>, ks_lds_bytes()}};
-  for (const auto& [fn, lds] : fns) {
+  const struct { const void* fn; size_t lds; int threads; } fns[5] = {
+      {(const void*)gemm32_stats_kernel_rows, g32_lds_bytes(), kG32Threads},
+      {(const void*)rows_ksplit_kernel<false, 1>, ks_lds_bytes(), kKsThreads},
+      {(const void*)rows_ksplit_kernel<true, 1>, ks_lds_bytes(), kKsThreads},
+      {(const void*)rows_ksplit_kernel<false, 2>, ks_lds_bytes(), kKsThreads},
+      {(const void*)rows_ksplit_kernel<true, 2>, ks_lds_bytes(), kKsThreads}};
+  for (const auto& [fn, lds, threads] : fns) {
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) { (void)hipGetLastError(); return hipSuccess; }
     int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kG32Threads, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds);
     if (e != hipSuccess || per_cu < 1) { (void)hipGetLastError(); return hipSuccess; }
   }
   // the kernel's workgroups wait for each other: all of them must be resident at once
@@ -1784,7 +1827,7 @@ hipError_t rows_launch(const eh_ctx* c, const RowsParams& p, hipStream_t s) {
   }
   if (p.n_rows <= kKsGroup) {
 #define EH_ROWS_KS(AO_, NB_) \
-  hipLaunchKernelGGL((rows_ksplit_kernel<AO_, NB_>), dim3(c->rows_grid), dim3(kG32Threads), ks_lds_bytes(), s, p)
+  hipLaunchKernelGGL((rows_ksplit_kernel<AO_, NB_>), dim3(c->rows_grid), dim3(kKsThreads), ks_lds_bytes(), s, p)
     if (p.n_rows <= 32) {
       if (p.argmax_only) EH_ROWS_KS(true, 1);
       else EH_ROWS_KS(false, 1);
@@ -1808,18 +1851,15 @@ hipError_t gemm32_kl_launch(const eh_ctx* c, int head, int model_head, int n_row
                             hipStream_t s) {
   const int R_pad = (n_rows + 31) & ~31;
   const int blocks = R_pad / 32;
-  const int nbh = blocks <= kG32Waves ? 1 : 2;
-  const int groups = (blocks + kG32Waves * nbh - 1) / (kG32Waves * nbh);
+  const int groups = (blocks + kG32Waves - 1) / kG32Waves;
   const int cus = c->num_cu > 0 ? c->num_cu : 256;
   const int VT32 = (c->VT + 1) / 2;
   const int gx = std::max(1, std::min(VT32, cus / groups));
   dim3 g(gx, groups);
   *n_parts = gx;
   const long long wdelta = (const char*)c->Wf[model_head] - (const char*)c->Wf[head];
-  if (nbh == 1)
-    launch_kl<1>(g, s, c->Wf[head], wdelta, yf_head, yf_model, c->VT, c->KS, c->V, n_rows, R_pad, labels, partials);
-  else
-    launch_kl<2>(g, s, c->Wf[head], wdelta, yf_head, yf_model, c->VT, c->KS, c->V, n_rows, R_pad, labels, partials);
+  const frag_t* zeros = yf_head + (long long)(c->R_pad_max / 16) * c->KS * kWave;  // behind the rows: never written
+  launch_kl(g, s, c->Wf[head], wdelta, yf_head, yf_model, zeros, c->VT, c->KS, c->V, n_rows, R_pad, labels, partials);
   return hipGetLastError();
 }
 

@@ -92,6 +92,38 @@ def test_only_inline_asm_loads_are_hand_counted():
     assert nl == 3 and any("touches its destination" in f for f in findings)
 
 
+def _dma(src="s[2:3]"):
+    return f"\t;;#ASMSTART\n\ts_add_u32 m0, s8, s9\n\ts_nop 0\n\tglobal_load_lds_dwordx4 v2, {src}\n\t;;#ASMEND\n"
+
+
+def test_hand_written_loads_to_lds():
+    """They have to be drained on every path to the end, own m0, and find their address in scalar registers
+    that no vector instruction has just written."""
+    step = STEP_OK.replace("\tglobal_load_lds_dwordx4 v[2:3], off\n", _dma())
+    assert C.check_asm(kernel(step))[0] == []
+    late = step.replace("\ts_endpgm", _dma() + "\ts_endpgm")
+    assert any("in flight at s_endpgm" in f for f in C.check_asm(kernel(late))[0])
+    m0 = step.replace("\ts_cbranch_scc1 .LBB0_1\n", "\ts_mov_b32 m0, s5\n\ts_cbranch_scc1 .LBB0_1\n")
+    assert any("uses m0" in f for f in C.check_asm(kernel(m0))[0])
+    near = step.replace("\ts_waitcnt vmcnt(0)\n\ts_endpgm", "\tv_readlane_b32 s3, v9, 1\n" + _dma() + "\ts_waitcnt vmcnt(0)\n\ts_endpgm")
+    assert any("wait states" in f for f in C.check_asm(kernel(near))[0])
+    far = near.replace("\tv_readlane_b32 s3, v9, 1\n", "\tv_readlane_b32 s3, v9, 1\n\ts_nop 4\n")
+    assert C.check_asm(kernel(far))[0] == []
+
+
+def test_last_steps_of_a_pass():
+    """Behind the last full step (2 DMA + 1 register load, one step in flight: 3) come steps without register
+    loads: every wait counts a full step less and the DMA loads in between."""
+    full = STEP_OK
+    dma2 = "\tglobal_load_lds_dwordx4 v[2:3], off\n\tglobal_load_lds_dwordx4 v[4:5], off\n"
+    tail = dma2 + "\ts_waitcnt vmcnt({}) ; end-sync 3\n" + dma2 + "\ts_waitcnt vmcnt({}) ; end-sync 3\n\ts_waitcnt vmcnt(0)\n\ts_endpgm"
+    ok = full.replace("\ts_waitcnt vmcnt(0)\n\ts_endpgm", tail.format(2, 1))
+    assert C.check_asm(kernel(ok))[0] == []
+    for a, b in ((3, 1), (2, 2)):
+        bad = full.replace("\ts_waitcnt vmcnt(0)\n\ts_endpgm", tail.format(a, b))
+        assert any("last steps" in f for f in C.check_asm(kernel(bad))[0]), (a, b)
+
+
 def test_built_library_was_checked():
     """The assembly the in-tree library was built from, if a build left it, is clean."""
     build_dir = os.path.join(os.path.dirname(C.__file__), "_build")

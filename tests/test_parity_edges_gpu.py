@@ -698,3 +698,54 @@ def test_eval_at_live_counts_around_256(B):
             P.compare_head(f"live{n}", H[:n], lse[:n], am[:n], tuple(x[idx[:n].numpy()] for x in orc), [])
         assert bool(torch.isnan(H[n:]).all()) and bool(torch.isnan(lse[n:]).all()) and bool((am[n:] == -7).all())
     B.eh_destroy(ctx)
+
+
+# ------------------------------------------------------------------ the weight ring across passes and heads
+@pytest.mark.parametrize("d,rows,V", [(64, 300, 9001), (96, 70, 50304), (128, 300, 50304), (160, 129, 3001), (192, 300, 50304),
+                                      (224, 256, 70001), (256, 65, 50257), (544, 520, 20000)])
+def test_weights_run_on_from_pass_to_pass(B, d, rows, V):
+    """Two heads on 65 to 520 rows.  The ring of weights runs on from pass to pass and head to head where
+    a pass has at least 6 k-steps of 32 (d > 160) and is filled anew below; three k-steps are the fewest the
+    kernel takes (d > 64), and their number modulo 3 decides which steps come first.  Slices of one to
+    three passes, of unequal lengths; one to three groups of rows, the last waves without a block."""
+    w = G.Workload("ring", d=d, V=V, n_heads=2, rows=rows, dtype="bf16", seed=d + rows)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0, 0.0], max_rows=rows)
+    out = [torch.zeros((2, rows), device=DEV) for _ in range(4)]
+    am = torch.full((2, rows), -7, dtype=torch.int32, device=DEV)
+    B.eh_eval_heads_metrics(ctx, 0, 2, hid.h, rows, out[0], out[1], am, out[2], out[3])
+    for l in range(2):
+        P.compare_head(f"ring{d}/{l}", out[0][l], out[1][l], am[l],
+                       P.oracle_head(hid.h[l], heads.gamma[l], heads.beta[l], heads.W[l], True), [])
+        one = _outs(rows)                             # the bits do not depend on what is evaluated around a head
+        B.eh_eval(ctx, l, hid.h[l], rows, *one)
+        assert torch.equal(one[0], out[0][l]) and torch.equal(one[1], out[1][l]) and torch.equal(one[2], am[l])
+    n = rows - rows // 3                              # fewer live rows than the host knows of
+    live = _outs(rows)
+    B.eh_eval(ctx, 1, hid.h[1], rows, *live, n_rows_dev=torch.tensor([n], dtype=torch.int32, device=DEV))
+    torch.cuda.synchronize()
+    P.compare_head(f"ring{d}/live", live[0][:n], live[1][:n], live[2][:n],
+                   P.oracle_head(hid.h[1][:n], heads.gamma[1], heads.beta[1], heads.W[1], True), [])
+    assert bool(torch.isnan(live[0][n:]).all())
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("d,rows,V", [(32, 70, 9001), (64, 300, 50304), (96, 33, 50304), (224, 520, 20000)])
+def test_losses_of_narrow_heads(B, d, rows, V):
+    """The dual pass has at least three k-steps: a head of d <= 64 runs the missing ones on zero weights."""
+    w = G.Workload("duo", d=d, V=V, n_heads=2, rows=rows, dtype="bf16", seed=d + rows)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    labels = torch.randint(0, V, (rows,), generator=torch.Generator().manual_seed(d), dtype=torch.int32)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0, 0.0], max_rows=rows)
+    kl, ce, loss = torch.zeros(rows, device=DEV), torch.zeros(rows, device=DEV), torch.zeros(3, device=DEV)
+    B.eh_head_losses(ctx, 0, hid.h[0], hid.h[1], labels.to(DEV), rows, 0.3, kl, ce, loss)
+    torch.cuda.synchronize()
+    f = P.f64
+    ref = O.head_losses(f(hid.h[0]), f(hid.h[1]), f(heads.gamma[0]), f(heads.beta[0]), f(heads.W[0]), f(heads.gamma[1]),
+                        f(heads.beta[1]), f(heads.W[1]), labels.numpy(), 0.3, bf16=True)
+    for got, key in ((kl, "kl"), (ce, "ce")):
+        want = np.asarray(ref[key])
+        assert np.all(np.abs(got.double().cpu().numpy() - want) <= 2e-3 + 1e-4 * np.abs(want)), key
+    B.eh_destroy(ctx)
