@@ -118,6 +118,12 @@ int row_block(const eh_ctx* c, int n_rows) { return c->dtype == EH_BF16 || use_k
 
 int round_up(int n, int to) { return (n + to - 1) / to * to; }
 
+// Rows of all heads together (padded) from which ln_pack_many_kernel's wave per row is the better LayerNorm: below,
+// the rows do not fill the chip and four waves have one done sooner.  One wave against four, us a call: 4 heads x
+// 20 rows of d = 1024 80.0 / 78.9, 4 x 64 86.7 / 85.0, 8 x 40 of d = 2048 278 / 277, 8 x 100 of d = 1024 169 / 170, 8 x 203 with
+// all metrics 226 / 230.
+constexpr int64_t kLnMany = 1024;
+
 // LayerNorm of a head's rows into yf, in the operand order of the kernel that n_rows rows go to.
 void launch_ln(const eh_ctx* c, int head, const void* h, int64_t row_stride, const int* row_idx, const int* n_rows_dev,
                int n_rows, int R_pad, frag_t* yf, hipStream_t s) {
@@ -514,10 +520,16 @@ eh_status eval_heads_impl(eh_ctx* ctx, int32_t head0, int32_t n_heads_eval, cons
   st = ensure_mh(ctx, n_heads_eval);
   if (st != EH_OK) return st;
   const int R_pad = (n_rows + 31) & ~31;
-  hipLaunchKernelGGL((ln_pack_heads_kernel<DtBf16, 32>), dim3(R_pad, n_heads_eval), dim3(kLnThreads), 0, s, h_layers,
-                     layer_stride, row_stride, n_rows, R_pad, ctx->d, ctx->KS,
-                     (const float* const*)(ctx->d_gamma + head0), (const float* const*)(ctx->d_beta + head0),
-                     ctx->eps, ctx->mh_yf, (int64_t)y_stride);
+  const float* const* gamma_tab = (const float* const*)(ctx->d_gamma + head0);
+  const float* const* beta_tab = (const float* const*)(ctx->d_beta + head0);
+  if (ctx->KS * 4 <= kLnCache * kWave && (int64_t)R_pad * n_heads_eval >= kLnMany)
+    hipLaunchKernelGGL((ln_pack_many_kernel<DtBf16>), dim3(R_pad / kLnTeam, n_heads_eval), dim3(kLnTeam * kWave),
+                       (size_t)ctx->KS * 4 * kLnTeam * sizeof(frag_t), s, h_layers, layer_stride, row_stride, n_rows, ctx->d,
+                       ctx->KS, gamma_tab, beta_tab, ctx->eps, ctx->mh_yf, (int64_t)y_stride);
+  else
+    hipLaunchKernelGGL((ln_pack_heads_kernel<DtBf16, 32>), dim3(R_pad, n_heads_eval), dim3(kLnThreads), 0, s, h_layers,
+                       layer_stride, row_stride, n_rows, R_pad, ctx->d, ctx->KS, gamma_tab, beta_tab, ctx->eps, ctx->mh_yf,
+                       (int64_t)y_stride);
   PartCount parts{0, 0, 0, 0, 0};
   float* second = metrics ? ctx->mh_second : nullptr;
   if (use_ksplit(ctx, n_rows))
@@ -608,10 +620,6 @@ eh_status eh_cascade(eh_ctx* ctx, const void* h_layers, int64_t layer_stride, in
     EH_HIP(ctx, rows_launch(ctx, p, s));
     return EH_OK;
   }
-  if (H_out) {
-    const int64_t n = (int64_t)ctx->n_heads * n_rows;
-    hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, H_out, n, NAN);
-  }
   // Two launches per head: the batched projection, then one kernel that merges the partial
   // statistics, applies the exit rule, appends the rows that go on to the next head's list
   // and writes their LayerNorm for the next head.  Three live-row counters rotate: head l
@@ -619,8 +627,14 @@ eh_status eh_cascade(eh_ctx* ctx, const void* h_layers, int64_t layer_stride, in
   const int RB = row_block(ctx, n_rows);
   const int R_pad = round_up(n_rows, RB);
   int* cnt = ctx->n_active[0];
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, cnt, (int64_t)3, 0);
-  launch_ln(ctx, 0, h_layers, row_stride, nullptr, nullptr, n_rows, R_pad, ctx->yf, s);
+#define EH_INIT(DT, RBV)                                                                                               \
+  hipLaunchKernelGGL((cascade_init_kernel<DT, RBV>), dim3(R_pad), dim3(kLnThreads), 0, s, h_layers, row_stride, n_rows, \
+                     R_pad, ctx->d, ctx->KS, ctx->gamma[0], ctx->beta[0], ctx->eps, ctx->yf, cnt, 3, H_out,             \
+                     (int64_t)ctx->n_heads * n_rows)
+  if (ctx->dtype == EH_BF16) EH_INIT(DtBf16, 32);
+  else if (RB == 32) EH_INIT(DtF32, 32);
+  else EH_INIT(DtF32, 16);
+#undef EH_INIT
   for (int l = 0; l < ctx->n_heads; ++l) {
     const int last = l == ctx->n_heads - 1 ? 1 : 0;
     const int* idx = l == 0 ? nullptr : ctx->active[l & 1];

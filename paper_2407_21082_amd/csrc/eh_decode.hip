@@ -151,7 +151,7 @@ __device__ __forceinline__ void stats_push4_any(Stats& s, f32x4 z, int row0, int
 
 // LayerNorm of one row held in registers (one global pass), fp64 arithmetic,
 // written to LDS in fragment order as token column n.
-template <typename DT>
+template <typename DT, bool ONE_ROW>
 __device__ __forceinline__ void ln_row_to_lds(const void* row, int d, int KS,
                                               const float* __restrict__ gamma,
                                               const float* __restrict__ beta, float eps, int lane, int n,
@@ -196,7 +196,7 @@ __device__ __forceinline__ void ln_row_to_lds(const void* row, int d, int KS,
           const int k = c * DT::EPL + e;
           y[e] = (double)gamma[k] * (((double)x[i][e] - mu) * rstd) + (double)beta[k];
         }
-        o = pack_elems<DT>(y);
+        o = pack_elems<DT, ONE_ROW>(y);
       }
       ybuf[(c >> 2) * kWave + (c & 3) * 16 + n] = o;
     }
@@ -665,7 +665,7 @@ struct Service {
       if (turn++ % kLnW != lnw) continue;
       const long long r = p.row_idx ? p.row_idx[n] : n;
       const char* row = (const char*)p.h + ((long long)l * p.layer_stride + r * p.row_stride) * esz;
-      ln_row_to_lds<DT>(row, p.d, p.KS, p.gamma[l], p.beta[l], p.eps, lane, n, ybuf);
+      ln_row_to_lds<DT, ONE_ROW>(row, p.d, p.KS, p.gamma[l], p.beta[l], p.eps, lane, n, ybuf);
     }
   }
 

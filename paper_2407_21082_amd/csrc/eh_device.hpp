@@ -82,6 +82,17 @@ __device__ __forceinline__ uint32_t f64_to_bf16_bits(double y) {
   }
   return f32_to_bf16_bits(f);
 }
+// The same where the result is a normal bf16 (`normal` is left false otherwise): the bits of the double
+// rounded as integers.  Its high word holds 20 bits of mantissa, of which 7 stay; whatever lies below only
+// matters as "not zero", which the lowest of the dropped bits takes on.
+__device__ __forceinline__ uint32_t f64_to_bf16_bits_normal(double y, bool& normal) {
+  const uint64_t v = __builtin_bit_cast(uint64_t, y);
+  const uint32_t hi = (uint32_t)(v >> 32), mag = hi & 0x7fffffffu;
+  normal &= mag - (897u << 20) < (253u << 20);  // exponents 1 .. 253 of a bf16 (254 may round up to infinity)
+  uint32_t t = (mag - (896u << 20)) | ((uint32_t)v != 0u ? 1u : 0u);
+  t += 0xfffu + ((t >> 13) & 1u);
+  return ((hi >> 16) & 0x8000u) | (t >> 13);
+}
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }

@@ -67,19 +67,34 @@ __device__ __forceinline__ void load_elems<DtF32>(const void* row, int k0, float
   decode_elems<DtF32>(*(const frag_t*)((const char*)row + (int64_t)k0 * 4), x);
 }
 
-template <typename DT>
-__device__ __forceinline__ frag_t pack_elems(const double (&y)[DT::EPL]);
-template <>
-__device__ __forceinline__ frag_t pack_elems<DtBf16>(const double (&y)[8]) {
-  uint32_t b[8];
+// EPL outputs -> 16 bytes.  LONG: every element by f64_to_bf16_bits (the decode kernel's call of one row, whose
+// timing wants it so: 313.5 us against 315.3; 8 rows 821.8 against 810.1 the other way).
+template <typename DT, bool LONG = false>
+struct Pack;
+template <bool LONG>
+struct Pack<DtBf16, LONG> {
+  static __device__ __forceinline__ frag_t elems(const double (&y)[8]) {
+    uint32_t b[8];
+    bool normal = !LONG;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) b[i] = f64_to_bf16_bits(y[i]);
-  return mk_frag(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
-}
-template <>
-__device__ __forceinline__ frag_t pack_elems<DtF32>(const double (&y)[4]) {
-  return mk_frag(__float_as_uint((float)y[0]), __float_as_uint((float)y[1]),
-                    __float_as_uint((float)y[2]), __float_as_uint((float)y[3]));
+    for (int i = 0; i < 8 && !LONG; ++i) b[i] = f64_to_bf16_bits_normal(y[i], normal);
+    if (!normal) {  // zeros, tiny and non-finite values: rare
+#pragma unroll
+      for (int i = 0; i < 8; ++i) b[i] = f64_to_bf16_bits(y[i]);
+    }
+    return mk_frag(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
+  }
+};
+template <bool LONG>
+struct Pack<DtF32, LONG> {
+  static __device__ __forceinline__ frag_t elems(const double (&y)[4]) {
+    return mk_frag(__float_as_uint((float)y[0]), __float_as_uint((float)y[1]), __float_as_uint((float)y[2]),
+                   __float_as_uint((float)y[3]));
+  }
+};
+template <typename DT, bool LONG = false>
+__device__ __forceinline__ frag_t pack_elems(const double (&y)[DT::EPL]) {
+  return Pack<DT, LONG>::elems(y);
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -279,6 +294,51 @@ __global__ __launch_bounds__(kLnThreads) void ln_pack_kernel(const void* __restr
   __shared__ double red[2 * kLnWaves];
   ln_pack_row<DT, RB>(h, row_stride, row_idx, n_live, R_pad, d, KS, gamma, beta, eps, yf, blockIdx.x,
                       threadIdx.x, red);
+}
+
+// The first launch of a cascade: LayerNorm of all rows for its first head, and the presets of the launches
+// behind it (three launches of 4 to 5 us each otherwise): n_clear counters to zero, n_H entropies to NaN.
+template <typename DT, int RB>
+__global__ __launch_bounds__(kLnThreads) void cascade_init_kernel(const void* __restrict__ h, int64_t row_stride, int n_rows,
+                                                          int R_pad, int d, int KS, const float* __restrict__ gamma,
+                                                          const float* __restrict__ beta, float eps,
+                                                          frag_t* __restrict__ yf, int* __restrict__ clear, int n_clear,
+                                                          float* __restrict__ H_out, int64_t n_H) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < n_clear) clear[threadIdx.x] = 0;
+  if (H_out)
+    for (int64_t i = (int64_t)blockIdx.x * kLnThreads + threadIdx.x; i < n_H; i += (int64_t)gridDim.x * kLnThreads) H_out[i] = NAN;
+  __shared__ double red[2 * kLnWaves];
+  ln_pack_row<DT, RB>(h, row_stride, nullptr, n_rows, R_pad, d, KS, gamma, beta, eps, yf, blockIdx.x, threadIdx.x, red);
+}
+
+// Several heads at once and many rows (bf16, blocks of 32 rows, rows of at most kLnCache * 64 chunks): a wave per row, eight rows
+// a workgroup, and the rows' chunks put next to each other in LDS before they go out, 128 bytes at a
+// time.  A row by four waves, whose chunks go out 16 bytes at a time, left the chip waiting at barriers
+// and wrote 64 lines with every store (8 heads x 203 rows of d = 1024 with all metrics 230 -> 226 us, 24 x 512 of
+// d = 2048 2296 -> 2278).  grid (R_pad / 8, heads).
+constexpr int kLnTeam = 8;
+template <typename DT>
+__global__ __launch_bounds__(kLnTeam* kWave) void ln_pack_many_kernel(const void* __restrict__ h_layers, int64_t layer_stride,
+                                                                      int64_t row_stride, int n_rows, int d, int KS,
+                                                                      const float* const* __restrict__ gamma_tab,
+                                                                      const float* const* __restrict__ beta_tab, float eps,
+                                                                      frag_t* __restrict__ yf, int64_t y_stride) {
+  extern __shared__ __attribute__((aligned(16))) char ln_smem[];
+  frag_t* tile = (frag_t*)ln_smem;  // [chunk][row], the rows of chunk c rotated by c against bank conflicts
+  const int l = blockIdx.y, p0 = blockIdx.x * kLnTeam, r = threadIdx.x >> 6, lane = threadIdx.x & 63, n_chunks = KS * 4;
+  auto put = [&](int c, const frag_t& v) { tile[c * kLnTeam + (r ^ (c & (kLnTeam - 1)))] = v; };
+  if (p0 + r < n_rows) {
+    const char* row = (const char*)h_layers + ((int64_t)l * layer_stride + (int64_t)(p0 + r) * row_stride) * DT::ESZ;
+    group_layernorm_cached<DT, 1>(row, d, n_chunks, gamma_tab[l], beta_tab[l], eps, lane, (double*)nullptr, put);
+  } else {
+    for (int c = lane; c < n_chunks; c += kWave) put(c, mk_frag(0, 0, 0, 0));
+  }
+  __syncthreads();
+  frag_t* dst = yf + (int64_t)l * y_stride + (int64_t)(p0 >> 5) * KS * kWave * 2 + (p0 & 31);
+  for (int i = threadIdx.x; i < n_chunks * kLnTeam; i += kLnTeam * kWave) {
+    const int c = i / kLnTeam, q = i % kLnTeam;
+    dst[(c >> 1) * kWave + (c & 1) * 32 + q] = tile[c * kLnTeam + (q ^ (c & (kLnTeam - 1)))];
+  }
 }
 
 // The same for several heads at once: blockIdx.y = head (relative to the first),

@@ -749,3 +749,30 @@ def test_losses_of_narrow_heads(B, d, rows, V):
         want = np.asarray(ref[key])
         assert np.all(np.abs(got.double().cpu().numpy() - want) <= 2e-3 + 1e-4 * np.abs(want)), key
     B.eh_destroy(ctx)
+
+
+# ------------------------------------------------------------------ LayerNorm of many rows at once
+@pytest.mark.parametrize("d,rows,heads", [(72, 130, 8), (520, 257, 4), (4096, 260, 4), (4104, 260, 4), (1000, 1000, 2), (96, 127, 8)])
+def test_layernorm_of_many_rows(B, d, rows, heads):
+    """From 1024 rows of all heads together a wave normalises a row and eight rows go out together
+    (hidden sizes up to 4096; the last case stays below).  Rows that do not fill the last eight, hidden sizes
+    that do not fill a lane's share, rows further apart than d, and rows of zeros and of tiny values, whose
+    outputs are no normal bf16 numbers before beta."""
+    w = G.Workload("many", d=d, V=300, n_heads=heads, rows=rows, dtype="bf16", seed=d + rows)
+    hs = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, hs, DEV)
+    for l in range(heads):
+        hs.beta[l][::3] = 0.0
+    h = torch.full((heads, rows, d + 8), 3.0, dtype=torch.bfloat16, device=DEV)
+    h[:, :, :d] = hid.h
+    h[:, 1, :d] = 0.0                                 # no variance: y is beta, zero at every third place
+    h[:, 2, :d] *= 1e-30
+    ctx = B.eh_create(hs.W, hs.gamma, hs.beta, [0.0] * heads, max_rows=rows)
+    H, lse = torch.zeros((heads, rows), device=DEV), torch.zeros((heads, rows), device=DEV)
+    am = torch.full((heads, rows), -7, dtype=torch.int32, device=DEV)
+    B.eh_eval_heads(ctx, 0, heads, h[:, :, :d], rows, H, lse, am)
+    torch.cuda.synchronize()
+    for l in range(heads):
+        P.compare_head(f"many{d}/{l}", H[l], lse[l], am[l],
+                       P.oracle_head(h[l, :, :d].contiguous(), hs.gamma[l], hs.beta[l], hs.W[l], True), [])
+    B.eh_destroy(ctx)
