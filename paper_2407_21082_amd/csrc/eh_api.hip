@@ -205,7 +205,11 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // rows 297 / 328, 160 rows 391 / 353; d = 2560, 128 rows 553 / 630; V = 32000, d = 2048, 80 rows 334 / 381,
 // 160 rows 450 / 402.
 int rows_most(const eh_ctx* c) {
-  if (c->KS < kGemm32MinSteps) return 64;  // the kernel for more rows has no such narrow heads
+  // Heads below 80 MB: a head's stream is over before the service workgroups have finished the one before
+  // (10 heads, one launch against two per head, us: V = 50304, d = 512, 70 rows 243 / 234; V = 32000,
+  // d = 1024, 70 rows 258 / 250, but d = 2048, 80 rows 326 / 369).  Nor has the kernel such narrow heads as
+  // have fewer than kGemm32MinSteps k-steps.
+  if (c->KS < kGemm32MinSteps || (int64_t)c->V * c->d < 40000000) return 64;
   return (int)std::min<int64_t>(kRowsMax, std::max<int64_t>(64, 26 + (int64_t)c->V * (c->d + 620) / 1000000));
 }
 bool use_rows(const eh_ctx* c, int64_t n_rows, bool verify) {
@@ -219,7 +223,7 @@ RowsParams rows_base(eh_ctx* c, int n_rows) {
   p.Wf = c->d_Wf; p.gamma = c->d_gamma; p.beta = c->d_beta; p.tau = c->d_tau;
   p.n_rows = n_rows; p.n_heads = c->n_heads;
   p.V = c->V; p.d = c->d; p.KS = c->KS; p.VT16 = c->VT; p.eps = c->eps;
-  p.n_stream = c->rows_grid - rows_service_workgroups(n_rows);
+  p.n_stream = c->rows_grid - rows_service_workgroups(n_rows, (long long)c->V * c->d);
   p.spin_limit = c->spin_limit;
   p.ctl = c->rows_ctl; p.y = c->rows_y; p.y_stride = c->rows_y_stride;
   p.part4 = c->rows_part4; p.parti = c->rows_parti; p.R_pad = (n_rows + 31) & ~31;
@@ -698,7 +702,7 @@ eh_status dssd_verify(eh_ctx* ctx, const void* f_final, const int32_t* draft, co
     launch_ln(ctx, fin, f_final, ctx->d, nullptr, nullptr, (int)rows, R_pad, ctx->yf, s);
     PartCount parts;
     EH_HIP(ctx, project(ctx, fin, nullptr, (int)rows, true, ctx->yf, ctx->partials, &parts, s));
-    hipLaunchKernelGGL(verify_post_kernel, dim3(B), dim3(256), (size_t)(k + 1) * sizeof(int), s, ctx->partials,
+    hipLaunchKernelGGL(verify_post_kernel, dim3(B), dim3(kWave * std::min(kVerifyWaves, k + 1)), (size_t)(k + 1) * sizeof(int), s, ctx->partials,
                        parts.n, R_pad, draft, draft_len, k, target, accepted, next_token);
     EH_HIP(ctx, hipGetLastError());
     return EH_OK;
@@ -812,12 +816,10 @@ eh_status eh_head_losses(eh_ctx* ctx, int32_t head, const void* h_head, int64_t 
   const size_t y_stride = (size_t)(ctx->R_pad_max / 16 + 32) * ctx->KS * kWave;
   const int R_pad = (n_rows + 31) & ~31;
   const int fin = ctx->n_heads - 1;
-  hipLaunchKernelGGL((ln_pack_kernel<DtBf16, 32>), dim3(R_pad), dim3(kLnThreads), 0, s, h_head, row_stride_head,
-                     (const int*)nullptr, (const int*)nullptr, n_rows, R_pad, ctx->d, ctx->KS, ctx->gamma[head],
-                     ctx->beta[head], ctx->eps, ctx->mh_yf);
-  hipLaunchKernelGGL((ln_pack_kernel<DtBf16, 32>), dim3(R_pad), dim3(kLnThreads), 0, s, h_model, row_stride_model,
-                     (const int*)nullptr, (const int*)nullptr, n_rows, R_pad, ctx->d, ctx->KS, ctx->gamma[fin],
-                     ctx->beta[fin], ctx->eps, ctx->mh_yf + y_stride);
+  const LnRows exit_rows{h_head, row_stride_head, ctx->gamma[head], ctx->beta[head]};
+  const LnRows model_rows{h_model, row_stride_model, ctx->gamma[fin], ctx->beta[fin]};
+  hipLaunchKernelGGL((ln_pack_pair_kernel<DtBf16, 32>), dim3(R_pad, 2), dim3(kLnThreads), 0, s, exit_rows, model_rows, n_rows, R_pad,
+                     ctx->d, ctx->KS, ctx->eps, ctx->mh_yf, (int64_t)y_stride);
   int n_parts = 0;
   EH_HIP(ctx, gemm32_kl_launch(ctx, head, fin, n_rows, ctx->mh_yf, ctx->mh_yf + y_stride, labels, ctx->kl_partials,
                                &n_parts, s));

@@ -1810,7 +1810,7 @@ hipError_t rows_prepare(eh_ctx* c) {
 hipError_t rows_launch(const eh_ctx* c, const RowsParams& p, hipStream_t s) {
   // every pointer the kernel dereferences unconditionally, and the sizes its indexing assumes
   if (!p.status || !p.ctl || !p.y || !p.part4 || !p.parti || !p.Wf || !p.gamma || !p.beta || !p.tau || !p.h) return hipErrorInvalidValue;
-  if (c->rows_grid <= kRowsServiceWgs || p.n_stream != (p.mode == 0 ? c->rows_grid - rows_service_workgroups(p.n_rows) : c->rows_grid)) return hipErrorInvalidValue;
+  if (c->rows_grid <= kRowsServiceWgs || p.n_stream != (p.mode == 0 ? c->rows_grid - rows_service_workgroups(p.n_rows, (long long)p.V * p.d) : c->rows_grid)) return hipErrorInvalidValue;
   if (p.n_rows < 1 || p.n_rows > kRowsMax || p.R_pad < p.n_rows || p.R_pad % 32 != 0) return hipErrorInvalidValue;
   if (p.l0 < 0 || p.l1 <= p.l0 || p.l1 > p.n_heads || rows_ctl_ints(p.l1 - p.l0) + 128 > c->rows_ctl_ints) return hipErrorInvalidValue;
   if ((long long)(p.R_pad / 16 + 32) * p.KS * kWave > p.y_stride) return hipErrorInvalidValue;  // one buffer per head
@@ -1844,7 +1844,21 @@ hipError_t rows_launch(const eh_ctx* c, const RowsParams& p, hipStream_t s) {
 }
 
 int rows_control_ints(int n_heads) { return rows_ctl_ints(n_heads) + 128; }  // + 128 words of time stamps (diagnostics build)
-int rows_service_workgroups(int) { return kRowsServiceWgs; }
+// A wave with one row more than the others doubles the service's time between two heads, which the streaming
+// workgroups see; each workgroup taken from them costs them 1/256 of their rate.  So: one row per service
+// wave, except where a head of 300 MB and more streams long enough to hide the second (above 128 rows) and
+// above 192 rows, where the waves' count has to stay below the 256 of its byte in c.ready.  At least
+// kRowsServiceWgs: fewer make no slice of the vocabulary a tile shorter.  10 heads, us, 12 workgroups / two
+// rows per wave / one: V = 50304, d = 2048, 120 rows 475 / - / 409, 150 rows - / 514 / 439; d = 2560, 175
+// rows - / 598 / 586; d = 4096 (412 MB), 185 rows - / 870 / 892, 210 rows 981 / 906 / -; V = 32000,
+// d = 2048, 101 rows 381 / - / 335.
+int rows_service_workgroups(int n_rows, long long head_elements) {
+  if (n_rows <= kKsGroup) return kRowsServiceWgs;  // the kernel of four waves a workgroup
+  const int rows_per_wave = n_rows <= 128 || (n_rows <= 192 && head_elements < 150000000ll) ? 1 : 2;
+  return std::max(kRowsServiceWgs, (n_rows + kG32Waves * rows_per_wave - 1) / (kG32Waves * rows_per_wave));
+}
+constexpr int kRowsServiceWgsMost = 192 / kG32Waves;
+static_assert(kRowsServiceWgsMost * kG32Waves < 256 && kRowsMax <= 2 * 8 * kRowsServiceWgsMost, "service waves in a byte");
 
 hipError_t gemm32_kl_launch(const eh_ctx* c, int head, int model_head, int n_rows, const frag_t* yf_head,
                             const frag_t* yf_model, const int* labels, KlStats* partials, int* n_parts,

@@ -150,7 +150,7 @@ hipError_t rows_prepare(eh_ctx* ctx);
 // Enqueues the preset of outputs and control block, then the kernel.
 hipError_t rows_launch(const eh_ctx* ctx, const RowsParams& p, hipStream_t s);
 int rows_control_ints(int n_heads);   // size of the control block for a launch over n_heads heads
-int rows_service_workgroups(int n_rows);  // workgroups of a cascade's grid that do not stream
+int rows_service_workgroups(int n_rows, long long head_elements);  // workgroups of a cascade's grid that do not stream
 
 // Sets up the decode kernel for this context (grid, LDS size, function
 // attributes).  Leaves ctx->decode_grid = 0 if the shape does not fit.

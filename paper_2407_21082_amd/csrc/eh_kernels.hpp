@@ -296,6 +296,22 @@ __global__ __launch_bounds__(kLnThreads) void ln_pack_kernel(const void* __restr
                       threadIdx.x, red);
 }
 
+// Two heads' rows in one launch (blockIdx.y = 0 or 1), each with its own hidden states: an exit head and the model's
+// for the training objectives (two launches took 14 us of 244).
+struct LnRows {
+  const void* h;
+  int64_t row_stride;
+  const float *gamma, *beta;
+};
+template <typename DT, int RB>
+__global__ __launch_bounds__(kLnThreads) void ln_pack_pair_kernel(LnRows a, LnRows b, int n_rows, int R_pad, int d, int KS,
+                                                          float eps, frag_t* __restrict__ yf, int64_t y_stride) {
+  const LnRows x = blockIdx.y ? b : a;
+  __shared__ double red[2 * kLnWaves];
+  ln_pack_row<DT, RB>(x.h, x.row_stride, nullptr, n_rows, R_pad, d, KS, x.gamma, x.beta, eps, yf + blockIdx.y * y_stride,
+                      blockIdx.x, threadIdx.x, red);
+}
+
 // The first launch of a cascade: LayerNorm of all rows for its first head, and the presets of the launches
 // behind it (three launches of 4 to 5 us each otherwise): n_clear counters to zero, n_H entropies to NaN.
 template <typename DT, int RB>
@@ -630,21 +646,32 @@ static __global__ void verify_compare_kernel(const int* __restrict__ draft, cons
 }
 
 // The same behind the batched projection in one launch: workgroup b merges the partial
-// argmax records of row b's k+1 positions (one wave per position, four at a time), then
+// argmax records of row b's k+1 positions (one wave per position, up to 16 at a time: with four, whose
+// records came one after the other, 9 positions took 8.5 us of a verification's 72), then
 // its first thread walks the prefix.  `target` (nullable) receives the merged argmaxes.
-static __global__ __launch_bounds__(256) void verify_post_kernel(
+constexpr int kVerifyWaves = 16;
+static __global__ __launch_bounds__(kVerifyWaves* kWave) void verify_post_kernel(
     const Stats* __restrict__ partials, int n_parts, int R_pad, const int* __restrict__ draft,
     const int* __restrict__ draft_len, int k, int* __restrict__ target, int* __restrict__ accepted,
     int* __restrict__ next_token) {
   extern __shared__ int verify_tgt[];  // k + 1 entries
   const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int j = wave; j <= k; j += 4) {
+  for (int j = wave; j <= k; j += (int)blockDim.x / kWave) {
     const int p = b * (k + 1) + j;
     float zb = -INFINITY;
     int ib = 0x7fffffff;
-    for (int g = lane; g < n_parts; g += kWave) {
-      const Stats q = partials[(int64_t)g * R_pad + p];
-      if (q.zb > zb || (q.zb == zb && q.ib < ib)) { zb = q.zb; ib = q.ib; }
+    for (int g0 = lane; g0 < n_parts; g0 += 4 * kWave) {  // four records asked for at a time
+      float z[4];
+      int i4[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const Stats& q = partials[(int64_t)min(g0 + i * kWave, n_parts - 1) * R_pad + p];
+        z[i] = q.zb;
+        i4[i] = q.ib;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)  // (the last record again where there are no more: no difference)
+        if (z[i] > zb || (z[i] == zb && i4[i] < ib)) { zb = z[i]; ib = i4[i]; }
     }
 #pragma unroll
     for (int x = 32; x > 0; x >>= 1) {

@@ -655,6 +655,15 @@ def test_persistent_cascade_above_64_rows(B, d, V, rows):
     assert len(tied) >= 1 and all(int(tok[r]) == pair[0] for r in tied)
 
 
+@pytest.mark.parametrize("d,V,rows", [(4096, 16384, 96), (6656, 20000, 104), (6656, 20000, 128), (6656, 20000, 161),
+                                      (4096, 50304, 129), (4096, 50304, 193)])
+def test_persistent_cascade_service_workgroups(B, d, V, rows):
+    """One row per service wave or two: 12 to 21 workgroups of eight such waves, at the last row that a
+    count takes and the first of the next, and the heads of 300 MB and more that keep two."""
+    test_persistent_cascade_above_64_rows(B, d, V, rows)
+
+
+
 # ------------------------------------------------------------------ live rows across groups of 256
 @pytest.mark.parametrize("rows", [300, 400, 513])
 def test_cascade_whose_live_rows_cross_256(B, rows):
