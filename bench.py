@@ -159,8 +159,8 @@ def bench_calibrate(args, torch, B, G, dev):
     avg_s = ev_s / args.steps
     roof = {"bound": "hbm", "achieved": bytes_per_launch / avg_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS, "traffic": None,
-            "kernel": "eh_calibrate (one pass that packs correctness and finds the key range, three passes "
-                      "that count entropies into bins, three small kernels that keep bins per level)",
+            "kernel": "eh_calibrate (a key range from a sample, one pass that packs correctness and "
+                      "counts entropies into bins, two more that count, small kernels that keep bins per level)",
             "avg_launch_us": avg_s * 1e6, "bytes_per_launch": bytes_per_launch, "launches": args.steps,
             "calls_served_by_full_sort": sorted_calls}
     cpu = None

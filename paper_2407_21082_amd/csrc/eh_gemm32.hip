@@ -10,17 +10,18 @@
 //  * v_mfma_f32_32x32x16_bf16: one wave per SIMD issues these back to back at the
 //    full rate of the matrix core (the 16x16x32 form needs two waves per SIMD for
 //    that, which would halve the accumulator tile a wave can hold);
-//  * one workgroup of 4 waves per CU.  The workgroup owns a contiguous slice of
-//    the vocabulary, walked in passes of at most 7 tiles of 32 rows, and a group
-//    of 4*NB blocks of 32 tokens; a wave owns NB token blocks and all tiles of
-//    the pass: up to 7*2 accumulator tiles = 224 registers;
+//  * one workgroup of 8 waves per CU, two per SIMD: while one wave folds a pass
+//    into its statistics the other has matrix instructions to issue.  The
+//    workgroup owns a contiguous slice of the vocabulary, walked in passes of at
+//    most 7 tiles of 32 rows, and a group of 8 blocks of 32 tokens; a wave owns
+//    one block and all tiles of the pass: up to 7 accumulator tiles;
 //  * the weights stay in the layout the decode kernel uses (fragments of 16 rows
-//    x 32 k).  They travel global -> LDS by DMA loads, once per workgroup, four
-//    k-steps ahead, and the LDS read applies the lane permutation that turns two
+//    x 32 k).  They travel global -> LDS by DMA loads, once per workgroup, six
+//    k-steps ahead and on across passes (the ring does not drain at a pass's end), and the LDS read applies the lane permutation that turns two
 //    16-row fragments into the two 32-row x 16-k operands of a k-step, so no
 //    second copy of the weights is needed.  A weight operand is re-read for the
 //    next k-step right after its last matrix instruction of this one, which
-//    spreads the LDS reads of the four waves evenly over the step;
+//    spreads the LDS reads of the waves evenly over the step;
 //  * the activations (L2 resident, private to a wave) are written by the
 //    LayerNorm kernel directly in 32x16 operand order and loaded straight into
 //    registers three k-steps ahead, into the registers just freed;
@@ -30,11 +31,11 @@
 //  * at the end of a pass the accumulator tiles are folded into per-lane running
 //    statistics (one exponential per logit); logits are never stored.
 //
-// Measured at 512 rows of d = 2048 (clock stamps of one workgroup): a k-step of 6 tiles takes 875 clocks
-// of which 768 are matrix instructions, at 1.6 to 1.8 GHz; with the weights read from one place
-// instead of streamed the same loop runs at 2.05 GHz, so what bounds it is the power the chip has
-// for matrix cores and memory together.  The statistics of a pass are next (12 k clocks of 72 k
-// before they parked new maxima).  24 heads: 2351 -> 2250 us.
+// Measured at 512 rows of d = 2048: the k loop runs at 1.6 to 1.8 GHz; with the weights read from one
+// place instead of streamed it runs at 2.05 GHz, so what bounds it is the power the chip has for matrix
+// cores and memory together: 24 heads 2242 us with four waves of two blocks, 2258 with eight of one (fewer
+// clocks at a lower rate).  Shapes that are not power bound gain: 400-row cascade of 12 heads, d = 512,
+// 607 -> 560 us; three metrics of 203 rows, d = 1024, 254 -> 230.
 #include "eh_internal.hpp"
 #include "eh_kernels.hpp"
 #include "eh_ksplit.hpp"
