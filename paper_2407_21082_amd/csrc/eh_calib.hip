@@ -675,20 +675,20 @@ __device__ __forceinline__ int wave_node_scan(const uint64_t* __restrict__ t, in
 }
 
 // Level 2, one workgroup per epsilon: down the kept level-1 bins, four at a time (four waves
-// each), until a top candidate qualifies.
+// each), until a top candidate qualifies.  It does not ask whether a table has proved too small already: the
+// workgroups beside it may be finding that out, and its waves, which share barriers, could see different
+// answers.  Behind an overflow of level 1 it walks bins without a row or with no counts, and keeps none.
 __global__ __launch_bounds__(kWalkWaves * 64) void calib_keep2_kernel(CalibWork w, EpsList eps, EpsWalk* __restrict__ walks) {
   constexpr int kNodes = 4, NW = kWalkWaves / kNodes;  // nodes at a time, waves on each
   __shared__ Pair sum_w[kWalkWaves];
   __shared__ int top_w[kWalkWaves], cnt_w[kWalkWaves];
   __shared__ uint32_t at2[kList2];
   constexpr int PER = kBins2 / (NW * 64);
-  const int ov = *w.overflow;
   const Cut c = cut_of(w);
   const int e = blockIdx.x;
   const double ep = eps.v[e];
   EpsWalk& walk = walks[e];
   const int n1 = walk.n1;
-  if (ov == 0) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int node = wave / NW, b0 = ((wave % NW) * 64 + lane) * PER;
   int n2 = 0;  // uniform over the workgroup
@@ -701,7 +701,7 @@ __global__ __launch_bounds__(kWalkWaves * 64) void calib_keep2_kernel(CalibWork 
       bin1 = walk.bin1[i];
       below = walk.below1[i];
       row = w.slot1[bin1];
-      nb = 1 << c.b2(bin1);
+      nb = row >= 0 ? 1 << c.b2(bin1) : 0;
     }
 #pragma unroll
     for (int j = 0; j < PER; ++j) {

@@ -1,6 +1,7 @@
 """The build's static checker for the batched kernel's hand-counted loads: it must accept a
 correctly waited load and flag the hazards it exists for (planted here, in text, on the CPU)."""
 import os
+import re
 
 from paper_2407_21082_amd import check_gemm_asm as C
 
@@ -122,6 +123,24 @@ def test_last_steps_of_a_pass():
     for a, b in ((3, 1), (2, 2)):
         bad = full.replace("\ts_waitcnt vmcnt(0)\n\ts_endpgm", tail.format(a, b))
         assert any("last steps" in f for f in C.check_asm(kernel(bad))[0]), (a, b)
+
+
+def test_calibration_kernels_do_not_ask_for_the_flag_they_raise():
+    """A calibration kernel that may find a table too small must not also branch on that finding: its waves
+    share barriers, and a store of another workgroup between two waves' reads would send some
+    of them home and leave the rest with words of LDS that nobody has written."""
+    with open(os.path.join(os.path.dirname(C.__file__), "csrc", "eh_calib.hip")) as f:
+        text = re.sub(r"//.*", "", f.read())
+    kernels = {re.search(r"(calib_\w+_kernel)", k).group(1): k for k in text.split("__global__")[1:]}
+    raising = set()
+    for name, body in kernels.items():
+        body = body.split("\n}\n")[0]
+        raises = re.search(r"\*w\.overflow\s*=[^=]|keep_bin\([^;]*w\.overflow", body)
+        asks = re.search(r"\*w\.overflow(?!\s*=[^=])", body)
+        if raises:
+            raising.add(name)
+        assert not (raises and asks), name
+    assert raising == {"calib_keep1_kernel", "calib_keep2_kernel"}, raising
 
 
 def test_built_library_was_checked():

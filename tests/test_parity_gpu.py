@@ -502,6 +502,32 @@ def test_calibrate_hovering_proportion(B, small_ctx, spread):
             assert tau[i] == want_tau and n[i] == want_n, (spread, eps[i], tau[i], want_tau, n[i], want_n)
 
 
+@pytest.mark.parametrize("n_other", [0, 31, 63])
+def test_calibrate_table_too_small_at_level_two(B, small_ctx, n_other):
+    """In ascending order the tokens are one correct, three wrong, then correct and wrong in turn: the
+    proportion stays just below 0.5 all the way up.  They lie in a few bins of the first level (2^18 keys
+    wide, the sample's range reaching from 1e-30 to 1e20), so that the first table is large enough and the
+    level 0.5 finds the second one too small, while the workgroups of other levels are walking theirs."""
+    M = 65536
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    H = 1.0 + torch.rand(M, generator=gen, device=DEV) / 32
+    H[0], H[1] = 1e-30, 1e20
+    rank = torch.empty(M, dtype=torch.int64, device=DEV)
+    rank[torch.argsort(H)] = torch.arange(M, device=DEV)
+    pred = ((rank > 3) & (rank % 2 == 0) | (rank == 0)).to(torch.int32)
+    H, pred = H.contiguous(), 1 - pred
+    ref = torch.zeros(M, dtype=torch.int32, device=DEV)
+    eps = [i / 64 for i in range(n_other) if i != 32] + [0.5]
+    t = O.correctness(pred.cpu().numpy(), ref.cpu().numpy())
+    want = _calibrate_by_counting(H.cpu().numpy().astype(np.float64), t, eps)
+    for turn in range(3):
+        before = B.eh_probe_calibrate_sorted(small_ctx)
+        tau, n = _calibrate(B, small_ctx, H, pred, ref, eps)
+        assert B.eh_probe_calibrate_sorted(small_ctx) == before + 1, turn
+        for i, (want_tau, want_n) in enumerate(want):
+            assert tau[i] == want_tau and n[i] == want_n, (turn, eps[i], tau[i], want_tau, n[i], want_n)
+
+
 @pytest.mark.parametrize("M", [32768, 65537, 300001, 1 << 20])
 @pytest.mark.parametrize("lift", [0.0, -2.0])
 def test_calibrate_outside_the_sample(B, small_ctx, M, lift):
