@@ -28,9 +28,9 @@
  *     R rows (and of dssd_draft at d above 2048) and of dssd_verify with up to 64
  *     positions B * (k+1), of which up to 16 only at d above 2048.  R is
  *     26 + V * (d + 620) / 10^6, rounded down, but at least 64 and at most 256 (64 at
- *     V * d below 4 * 10^7 and at d up to 64).  The
- *     stream must have the device to itself while such a call runs (no other kernel
- *     holding compute units on another stream or from another context).  eh_create
+ *     V * d below 4 * 10^7).  The stream must have the device to itself while such a
+ *     call runs (no other kernel holding compute units on another stream or from
+ *     another context).  eh_create
  *     checks that the grids fit the empty device.  Every wait is bounded
  *     (eh_set_spin_limit); a call that gives up sets a flag that eh_check reports
  *     and clears, rows it did not finish read -1 / NaN, and the context stays usable.

@@ -110,7 +110,6 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // 238 / 422 against 154 / 240 / 419; V = 49152 132 / 214 / 390 against 150 / 235 / 409.
 bool use_ksplit(const eh_ctx* c, int n_rows) {
   if (!c->bias.empty() || n_rows <= 32) return true;
-  if (c->dtype == EH_BF16 && c->KS < kGemm32MinSteps) return true;  // d <= 64: there is no other
   return c->dtype == EH_BF16 && n_rows <= 64 && ksplit_pass_tiles(c) < 7;
 }
 // Rows per block of the activations' operand order: 16 for gemm_launch's kernel, 32 for all others.
@@ -207,9 +206,8 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 int rows_most(const eh_ctx* c) {
   // Heads below 80 MB: a head's stream is over before the service workgroups have finished the one before
   // (10 heads, one launch against two per head, us: V = 50304, d = 512, 70 rows 243 / 234; V = 32000,
-  // d = 1024, 70 rows 258 / 250, but d = 2048, 80 rows 326 / 369).  Nor has the kernel such narrow heads as
-  // have fewer than kGemm32MinSteps k-steps.
-  if (c->KS < kGemm32MinSteps || (int64_t)c->V * c->d < 40000000) return 64;
+  // d = 1024, 70 rows 258 / 250, but d = 2048, 80 rows 326 / 369).
+  if ((int64_t)c->V * c->d < 40000000) return 64;
   return (int)std::min<int64_t>(kRowsMax, std::max<int64_t>(64, 26 + (int64_t)c->V * (c->d + 620) / 1000000));
 }
 bool use_rows(const eh_ctx* c, int64_t n_rows, bool verify) {

@@ -52,7 +52,7 @@ constexpr int kG32Group = kG32Waves * 32;  // rows a workgroup takes at most: a 
 constexpr int kMaxMT = 7;     // 32-row tiles per pass
 constexpr int kSlots = 8;     // LDS ring: k-steps of weight fragments
 constexpr int kSlotBytes = 2 * kMaxMT * 1024;
-constexpr int kDepth = kGemm32MinSteps;  // activation register sets = k-steps a load may take
+constexpr int kDepth = 3;      // activation register sets = k-steps a load may take
 constexpr int kRingAhead = 6;  // k-steps the weights are asked for ahead
 static_assert(kDepth < kRingAhead, "a step's weights are asked for before its activations");
 // the weight ring, then 16 bytes per thread: the second largest logit of its (at most 2) token blocks
@@ -323,11 +323,9 @@ __host__ __device__ constexpr int dma_per_wave(int mt) { return (2 * mt + kG32Wa
 // of the same (vocabulary row, token) in the same register of the same lane.
 // Where a pass takes its weights: mt tiles of 32 rows (both sides together) from 16-row tile t16 of W on, the
 // workgroup's tiles ending at t16_end.  mt = 0: there is no such pass.
-// zeros: a fragment of zeros, the weights of steps KS .. kDepth - 1 of a narrow dual pass (else NULL).
 struct G32Src {
   const frag_t* W;
   int t16, t16_end, mt;
-  const frag_t* zeros;
 };
 __device__ __forceinline__ const char* uniform_bytes(uint64_t v) {  // kept in scalar registers
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
@@ -348,16 +346,16 @@ __device__ __forceinline__ void ring_dma(const char* src, uint32_t lane_off, uin
 }
 __device__ __forceinline__ uint32_t lds_offset(EH_LDS char* p) { return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)p); }
 
-// A wave's share of the first kRingAhead k-steps of a pass (fragments from `first_f` on), into the ring at slot rb.
+// A wave's share of the first n_steps k-steps of a pass (fragments from `first_f` on), into the ring at slot rb.
 template <bool DUAL>
 __device__ __forceinline__ void ring_start(const G32Src& p, int KS, int rb, int lane, int wave, EH_LDS char* lds,
-                                           long long wdelta = 0, int first_f = 0) {
+                                           long long wdelta = 0, int first_f = 0, int n_steps = kRingAhead) {
   const uint32_t lane16 = (uint32_t)lane << 4, base = lds_offset(lds);
 #pragma unroll 1
-  for (int ks = 0; ks < kRingAhead; ++ks)
+  for (int ks = 0; ks < n_steps; ++ks)
 #pragma unroll 1
     for (int f = first_f + wave; f < 2 * p.mt; f += kG32Waves)
-      ring_dma(DUAL && ks >= KS && KS < kDepth ? uniform_bytes((uint64_t)p.zeros) : frag_src<DUAL>(p, f, KS, wdelta) + ((long long)min(ks, KS - 1) << 10),
+      ring_dma(frag_src<DUAL>(p, f, KS, wdelta) + ((long long)min(ks, KS - 1) << 10),
                lane16, __builtin_amdgcn_readfirstlane(base + ((rb + ks) & (kSlots - 1)) * kSlotBytes), __builtin_amdgcn_readfirstlane(f * 1024));
 }
 // Whether the ring runs on from pass to pass (it has to hold kRingAhead steps of the next one and none
@@ -368,7 +366,7 @@ __device__ __forceinline__ void ring_begin(const G32Src& p, int KS, int rb, int 
                                            long long wdelta = 0) {
   // nobody may still be reading the ring (previous pass) when it is refilled
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  ring_start<DUAL>(p, KS, rb, lane, wave, lds, wdelta);
+  ring_start<DUAL>(p, KS, rb, lane, wave, lds, wdelta, 0, min(kRingAhead, max(KS, kDepth)));
 }
 
 // A wave's DMA pieces of a pass's k-steps from step kRingAhead on, those beyond the pass's end being the
@@ -439,7 +437,7 @@ __device__ __forceinline__ void pass32(const G32Src& cur, const G32Src& next, in
                                        int row_hi, int lane, int wave, EH_LDS char* lds, ST (&st)[DUAL ? NB / 2 : NB],
                                        long long wdelta = 0, const frag_t* __restrict__ yq2 = nullptr) {
   const int T16 = cur.t16;
-  const int steps = DUAL ? max(KS, kDepth) : KS;
+  const int steps = max(KS, kDepth);
   static_assert(!DUAL || (MT % 2 == 0 && NB % 2 == 0), "two equal sides");
   constexpr int NA = DUAL ? NB / 2 : NB;  // accumulator tiles per weight tile
   constexpr int MH = MT / 2, NH = NB / 2;
@@ -604,6 +602,17 @@ __device__ __forceinline__ void pass32(const G32Src& cur, const G32Src& next, in
       asm volatile("" : "+v"(b[c][n][0]));
       asm volatile("" : "+v"(b[c][n][1]));
     }
+  // The steps a head of d <= 64 lacks: no activations, on its last weights once more.  (The k-split kernel, which
+  // streams the weights once for every 64 rows, instead, us: 8 heads of d = 32, 128 / 512 rows 123 / 403
+  // against 54 / 111 here.)
+  if (KS < kDepth) {
+#pragma unroll
+    for (int c = 1; c < kDepth; ++c)
+      if (c >= KS) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) b[c][n][0] = b[c][n][1] = mk_frag(0, 0, 0, 0);
+      }
+  }
   static_for<MT>([&](auto mc) { fetch_a(a[decltype(mc)::value], mc, 0); });
   constexpr std::integral_constant<int, kDepth> all{};
   // nested so that no path through the code runs a step whose register set another one should have
@@ -733,7 +742,7 @@ template <int MT, bool DUAL = false>
 __device__ __forceinline__ void pass32_idle(const G32Src& cur, const G32Src& next, int rb, int KS, int lane, int wave, EH_LDS char* lds,
                                             long long wdelta = 0) {
   constexpr int kDma = dma_per_wave(MT);
-  const int steps = DUAL ? max(KS, kDepth) : KS;
+  const int steps = max(KS, kDepth);
   RingFeed<MT, DUAL> feed(cur, next, KS, steps, rb, lane, wave, lds, wdelta);
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   for (int ks = 0; ks < steps; ++ks) {
@@ -792,7 +801,6 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
     G32Src p;
     vocab_slice(VT16, gran, slice_of(l), deal.parts, p.t16, p.t16_end);
     p.W = Wf_tab[l];
-    p.zeros = nullptr;
     p.mt = pass_tiles(p.t16_end - p.t16);
     return p;
   };
@@ -854,8 +862,7 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_stats_kernel(
 // vocabulary in passes of at most 3 tiles of 32 rows of both weight matrices.
 __global__ __launch_bounds__(kG32Threads, 1) void gemm32_kl_kernel(
     const frag_t* __restrict__ Wf, long long wdelta, const frag_t* __restrict__ yq, const frag_t* __restrict__ yq2,
-    const frag_t* __restrict__ zeros, int VT16, int KS, int V, int n_rows, int R_pad, const int* __restrict__ labels,
-    KlStats* __restrict__ partials) {
+    int VT16, int KS, int V, int n_rows, int R_pad, const int* __restrict__ labels, KlStats* __restrict__ partials) {
   extern __shared__ __attribute__((aligned(16))) char g32_smem[];
   EH_LDS char* lds = (EH_LDS char*)g32_smem;
   const int lane = threadIdx.x & 63;
@@ -876,7 +883,7 @@ __global__ __launch_bounds__(kG32Threads, 1) void gemm32_kl_kernel(
   auto src_at = [&](int t) {  // the pass at 16-row tile t: passes of at most kMaxMH tiles a side of about equal size
     const int left = (T1 - t + 1) >> 1;
     const int passes = (left + kMaxMH - 1) / kMaxMH;
-    return G32Src{Wf, t, T1, passes > 0 ? 2 * ((left + passes - 1) / passes) : 0, zeros};
+    return G32Src{Wf, t, T1, passes > 0 ? 2 * ((left + passes - 1) / passes) : 0};
   };
   const bool run_on = ring_runs_on(KS);
   int rb = 0;
@@ -1190,7 +1197,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
   const int row_hi = min(p.V, T1 * 16);
   const bool run_on = ring_runs_on(p.KS);
   int rb = 0;
-  G32Src cur{p.Wf[p.l0], T0, T1, pass_tiles(T1 - T0), nullptr};
+  G32Src cur{p.Wf[p.l0], T0, T1, pass_tiles(T1 - T0)};
   EH_ROWS_STAMP(0);
   rows_first_layernorm<kG32Waves>(p, c, red);
   // (weights asked for in front of the LayerNorm would only hold up its own loads: a wave's loads
@@ -1212,7 +1219,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
       after.t16 += 2 * cur.mt;
       after.mt = pass_tiles(after.t16_end - after.t16);
       more = after.mt > 0;
-      if (!more && j + 1 < nh) after = G32Src{p.Wf[l + 1], T0, T1, pass_tiles(T1 - T0), nullptr};
+      if (!more && j + 1 < nh) after = G32Src{p.Wf[l + 1], T0, T1, pass_tiles(T1 - T0)};
       G32Src next = after;
       if (!run_on) {
         next.mt = 0;
@@ -1731,9 +1738,9 @@ __global__ void rows_preset_kernel(int* __restrict__ ctl, int n_ctl, int* __rest
   if (H_out && i < n_H) H_out[i] = NAN;
 }
 
-void launch_kl(dim3 g, hipStream_t s, const frag_t* Wf, long long wdelta, const frag_t* yq, const frag_t* yq2, const frag_t* zeros,
+void launch_kl(dim3 g, hipStream_t s, const frag_t* Wf, long long wdelta, const frag_t* yq, const frag_t* yq2,
                int VT16, int KS, int V, int n_rows, int R_pad, const int* labels, KlStats* partials) {
-  hipLaunchKernelGGL(gemm32_kl_kernel, g, dim3(kG32Threads), g32_lds_bytes(), s, Wf, wdelta, yq, yq2, zeros, VT16,
+  hipLaunchKernelGGL(gemm32_kl_kernel, g, dim3(kG32Threads), g32_lds_bytes(), s, Wf, wdelta, yq, yq2, VT16,
                      KS, V, n_rows, R_pad, labels, partials);
 }
 
@@ -1873,8 +1880,7 @@ hipError_t gemm32_kl_launch(const eh_ctx* c, int head, int model_head, int n_row
   dim3 g(gx, groups);
   *n_parts = gx;
   const long long wdelta = (const char*)c->Wf[model_head] - (const char*)c->Wf[head];
-  const frag_t* zeros = yf_head + (long long)(c->R_pad_max / 16) * c->KS * kWave;  // behind the rows: never written
-  launch_kl(g, s, c->Wf[head], wdelta, yf_head, yf_model, zeros, c->VT, c->KS, c->V, n_rows, R_pad, labels, partials);
+  launch_kl(g, s, c->Wf[head], wdelta, yf_head, yf_model, c->VT, c->KS, c->V, n_rows, R_pad, labels, partials);
   return hipGetLastError();
 }
 

@@ -104,10 +104,6 @@ struct DecodeParams {
   unsigned long long* trace;    // nullable: [n_heads][16] wall-clock stamps written by workgroup 0
 };
 
-// k-steps of 32 below which gemm32_launch and the persistent kernel above 64 rows cannot run (their last
-// steps use every register set once).
-constexpr int kGemm32MinSteps = 3;
-
 // Arguments of the persistent kernels for few rows (bf16 heads without a bias vector): heads
 // l0 .. l1-1 of a cascade (mode 0, at most kRowsMax rows) or the model's head of a verification (mode 1,
 // at most 64 positions).

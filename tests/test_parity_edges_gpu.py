@@ -589,7 +589,7 @@ def test_cascade_across_block_layouts(B, rows):
 
 # ------------------------------------------------------------------ the persistent kernel above 64 rows
 @pytest.mark.parametrize("d,V,rows", [(4096, 16384, 65), (4096, 16384, 97), (4096, 16384, 103), (6656, 20000, 129),
-                                      (6656, 20000, 171), (1024, 50304, 108)])
+                                      (6656, 20000, 171), (1024, 50304, 108), (64, 630000, 66)])
 def test_persistent_cascade_above_64_rows(B, d, V, rows):
     """Where a head's stream is long, cascades of 65 to 26 + V (d + 620) / 10^6 rows run in one launch
     whose waves share weights through LDS: 3 to 6 blocks of 32 rows on four waves (the largest of each
@@ -710,12 +710,13 @@ def test_eval_at_live_counts_around_256(B):
 
 
 # ------------------------------------------------------------------ the weight ring across passes and heads
-@pytest.mark.parametrize("d,rows,V", [(64, 300, 9001), (96, 70, 50304), (128, 300, 50304), (160, 129, 3001), (192, 300, 50304),
+@pytest.mark.parametrize("d,rows,V", [(8, 90, 3001), (32, 520, 50304), (64, 40, 57000), (64, 300, 9001), (96, 70, 50304), (128, 300, 50304), (160, 129, 3001), (192, 300, 50304),
                                       (224, 256, 70001), (256, 65, 50257), (544, 520, 20000)])
 def test_weights_run_on_from_pass_to_pass(B, d, rows, V):
-    """Two heads on 65 to 520 rows.  The ring of weights runs on from pass to pass and head to head where
-    a pass has at least 6 k-steps of 32 (d > 160) and is filled anew below; three k-steps are the fewest the
-    kernel takes (d > 64), and their number modulo 3 decides which steps come first.  Slices of one to
+    """Two heads on 40 to 520 rows.  The ring of weights runs on from pass to pass and head to head where
+    a pass has at least 6 k-steps of 32 (d > 160) and is filled anew below; a pass has at least three k-steps
+    (narrower heads run the missing ones without activations), and their number modulo 3 decides which
+    steps come first.  Slices of one to
     three passes, of unequal lengths; one to three groups of rows, the last waves without a block."""
     w = G.Workload("ring", d=d, V=V, n_heads=2, rows=rows, dtype="bf16", seed=d + rows)
     heads = G.make_heads(w, DEV)
@@ -740,9 +741,35 @@ def test_weights_run_on_from_pass_to_pass(B, d, rows, V):
     B.eh_destroy(ctx)
 
 
+@pytest.mark.parametrize("rows", [128, 512])
+def test_narrow_heads_take_no_longer_than_wider_ones(B, rows):
+    """Heads of fewer k-steps than a pass has go the same way as those next to them: 8 heads of d = 32 and 64
+    took three times as long as of d = 96 where they went another."""
+    times = {}
+    for d in (32, 64, 96):
+        w = G.Workload("narrow", d=d, V=50304, n_heads=8, rows=rows, dtype="bf16", seed=d)
+        heads = G.make_heads(w, DEV)
+        ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0] * 8, max_rows=rows)
+        h = torch.randn((8, rows, d), device=DEV).to(torch.bfloat16)
+        H, lse = torch.zeros((8, rows), device=DEV), torch.zeros((8, rows), device=DEV)
+        am = torch.zeros((8, rows), dtype=torch.int32, device=DEV)
+        turns = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                B.eh_eval_heads(ctx, 0, 8, h, rows, H, lse, am)
+            b.record()
+            torch.cuda.synchronize()
+            turns.append(a.elapsed_time(b))
+        times[d] = sorted(turns)[2]
+        B.eh_destroy(ctx)
+    assert times[32] < 1.3 * times[96] and times[64] < 1.3 * times[96], times
+
+
 @pytest.mark.parametrize("d,rows,V", [(32, 70, 9001), (64, 300, 50304), (96, 33, 50304), (224, 520, 20000)])
 def test_losses_of_narrow_heads(B, d, rows, V):
-    """The dual pass has at least three k-steps: a head of d <= 64 runs the missing ones on zero weights."""
+    """The dual pass has at least three k-steps: a head of d <= 64 runs the missing ones without activations."""
     w = G.Workload("duo", d=d, V=V, n_heads=2, rows=rows, dtype="bf16", seed=d + rows)
     heads = G.make_heads(w, DEV)
     hid = G.make_hidden(w, heads, DEV)
