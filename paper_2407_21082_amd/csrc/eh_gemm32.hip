@@ -1474,6 +1474,12 @@ __device__ __forceinline__ void rows_serve_cascade(const RowsParams& p, const Ro
     const bool more = !last && j + 2 < nh;  // head j+2 exists: its LayerNorm is this turn's job
     const bool a0 = r0 < p.n_rows && alive.test(r0), a1 = r1 < p.n_rows && alive.test(r1);
     SvcRow row0, row1;
+    // The compiler has to take the lane for a new one in every turn.  What depends on it alone, some twenty
+    // addresses and masks, is otherwise worked out in front of the loop and kept in scratch: in the kernel of eight
+    // waves, with 256 registers each, 208 bytes of it, whose reloads are trips to the memory that the weights
+    // saturate, in the chain that the streaming workgroups wait for.  10 heads, us, with them and without: V = 70000,
+    // d = 512, 80 rows 268 / 236; V = 50304, d = 1024, 80 and 105 rows 300 / 280 and 313 / 285, d = 2048, 160 rows 443 / 432.
+    asm volatile("" : "+v"(lane));
     if (j == 2) EH_ROWS_STAMP(6);
     if (more && fits) {
       if (a0) svc_load_row(p, l + 2, r0, lane, row0);
@@ -1499,7 +1505,8 @@ __device__ __forceinline__ void rows_serve_cascade(const RowsParams& p, const Ro
     for (int r = sw, k = 0; r < p.n_rows; r += nsw, ++k) {
       if (!alive.test(r)) continue;
       Stats s;
-      if (both && k < 2) s = s01[k];
+      if (both && k == 0) s = s01[0];  // (an array indexed by k would lie in scratch)
+      else if (both && k == 1) s = s01[1];
       else s = rows_merge(parts, p.n_stream, cols.rank(r), lane);
       float H, lse;
       stats_finalize(s, H, lse);

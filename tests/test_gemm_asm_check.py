@@ -3,6 +3,8 @@ correctly waited load and flag the hazards it exists for (planted here, in text,
 import os
 import re
 
+import pytest
+
 from paper_2407_21082_amd import check_gemm_asm as C
 
 NAME = "_ZN2eh12_GLOBAL__N_117gemm_stats_kernelINS_6DtBf16ELi1ELb0EEEvPKDv4_jS5_iiiPKiiiPNS_5StatsE"
@@ -123,6 +125,24 @@ def test_last_steps_of_a_pass():
     for a, b in ((3, 1), (2, 2)):
         bad = full.replace("\ts_waitcnt vmcnt(0)\n\ts_endpgm", tail.format(a, b))
         assert any("last steps" in f for f in C.check_asm(kernel(bad))[0]), (a, b)
+
+
+def test_service_waves_keep_nothing_in_scratch_memory():
+    """In the persistent cascades the service waves are in the chain that everybody waits for: what the compiler
+    spills there comes back from a saturated memory (208 bytes of scratch above 64 rows cost 3 us of a
+    head's 25; 36 bytes are of the streaming waves)."""
+    path = os.path.join(os.path.dirname(C.__file__), "_build", "eh_gemm32.s")
+    if not os.path.exists(path):
+        pytest.skip("no build has left the assembly")
+    with open(path) as f:
+        text = f.read()
+    size = {}
+    for name, body in re.findall(r"\.amdhsa_kernel (\S+)(.*?)\.end_amdhsa_kernel", text, re.S):
+        size[name] = int(re.search(r"private_segment_fixed_size (\d+)", body).group(1))
+    above = [v for k, v in size.items() if "gemm32_stats_kernel_rows" in k]
+    upto64 = [v for k, v in size.items() if "rows_ksplit_kernel" in k]
+    assert len(above) == 1 and above[0] <= 48, size
+    assert len(upto64) == 4 and max(upto64) <= 64, size
 
 
 def test_calibration_kernels_do_not_ask_for_the_flag_they_raise():
