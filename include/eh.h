@@ -27,11 +27,11 @@
  *     it on fewer workgroups); and, bf16, what that leaves of eh_cascade with up to
  *     R rows (and of dssd_draft at d above 2048) and of dssd_verify with up to 64
  *     positions B * (k+1), of which up to 16 only at d above 2048.  R is
- *     26 + V * (d + 620) / 10^6, rounded down, but at least 64 and at most 256 (64 at
- *     V * d below 4 * 10^7).  The stream must have the device to itself while such a
- *     call runs (no other kernel holding compute units on another stream or from
- *     another context).  eh_create
- *     checks that the grids fit the empty device.  Every wait is bounded
+ *     26 + Q, at least 64 and at most 256, where Q is V * (d + 620) / 10^6, rounded down
+ *     (64 if V * d is below 3.5 * 10^7 and Q below 60).  The stream must have the device
+ *     to itself while such a call runs (no other kernel holding compute units on another
+ *     stream or from another context).  eh_create checks that the grids fit the empty
+ *     device.  Every wait is bounded
  *     (eh_set_spin_limit); a call that gives up sets a flag that eh_check reports
  *     and clears, rows it did not finish read -1 / NaN, and the context stays usable.
  *     Such a launch also carries a tag (and, for dssd_verify, a choice of control

@@ -198,17 +198,22 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // A cascade: as long as the two launches per head and the gaps between them cost more than the
 // service workgroups, whose time grows with the rows, cost the streaming ones; the longer a head's
 // stream, the more rows that is.  Rows at which 10 heads take the same time either way (measured at
-// 68 to 200 rows), d = 512 / 1024 / 1536 / 2048 / 2560: V = 50304 88 / 104 / 143 / 161 / 198, V = 40001
-// 75 / 90 / 103 / 126 / 153, V = 32000 66 / 85 / 93 / 106 / 135; the line drawn is within 10 rows of
-// them, 3 % of a call's time.  To either side, one launch against two per head, us: V = 50304, d = 1024, 80
-// rows 297 / 328, 160 rows 391 / 353; d = 2560, 128 rows 553 / 630; V = 32000, d = 2048, 80 rows 334 / 381,
-// 160 rows 450 / 402.
+// 65 to 256 rows): V = 50304, d = 512 / 640 / 768 / 1024 / 1536 none / 130 / 150 / 205 / above 256; V = 40001, d = 768
+// 88, d = 960 above 112; V = 32000, d = 1024 / 1536 / 2048 88 / 165 / 205; V = 38000, d = 1024 above 112; V = 64000,
+// d = 512 125.  One launch against two per head, us, 66 and 160 rows: V = 50304, d = 1024 279 / 314 and
+// 326 / 342, d = 2048 383 / 484 and 436 / 517; V = 32000, d = 2048 306 / 373 and 355 / 391.  The line lies below
+// those rows: it was drawn for an earlier form of the kernel, and the calls above it, which need not have
+// the device to themselves, have been left as they are.
 int rows_most(const eh_ctx* c) {
-  // Heads below 80 MB: a head's stream is over before the service workgroups have finished the one before
-  // (10 heads, one launch against two per head, us: V = 50304, d = 512, 70 rows 243 / 234; V = 32000,
-  // d = 1024, 70 rows 258 / 250, but d = 2048, 80 rows 326 / 369).
-  if ((int64_t)c->V * c->d < 40000000) return 64;
-  return (int)std::min<int64_t>(kRowsMax, std::max<int64_t>(64, 26 + (int64_t)c->V * (c->d + 620) / 1000000));
+  // Small heads: a head's stream is over before the service workgroups have finished the one before (10 heads, one
+  // launch against two per head, 65 / 80 rows, us: V = 50304, d = 512 238 / 239 against 233 / 234; V = 40001,
+  // d = 768 236 / 234 against 239 / 240; V = 32000, d = 1024 243 / 239 against 245 / 248; but d = 640 of V = 50304
+  // 242 / 238 against 255 / 259, d = 960 of V = 40001 248 / 256 against 276 / 275, and the more words, each of
+  // which costs the statistics behind a pass the same, the smaller: V = 64000, d = 512 245 / 246 against 257 / 259,
+  // V = 128256, d = 288 233 / 232 against 295 / 297).
+  const int64_t bulk = (int64_t)c->V * c->d, rows_by_bulk = (int64_t)c->V * (c->d + 620) / 1000000;
+  if (bulk < 35000000 && rows_by_bulk < 60) return 64;
+  return (int)std::min<int64_t>(kRowsMax, std::max<int64_t>(64, 26 + rows_by_bulk));
 }
 bool use_rows(const eh_ctx* c, int64_t n_rows, bool verify) {
   const int most = verify ? 64 : rows_most(c);

@@ -589,7 +589,8 @@ def test_cascade_across_block_layouts(B, rows):
 
 # ------------------------------------------------------------------ the persistent kernel above 64 rows
 @pytest.mark.parametrize("d,V,rows", [(4096, 16384, 65), (4096, 16384, 97), (4096, 16384, 103), (6656, 20000, 129),
-                                      (6656, 20000, 171), (1024, 50304, 108), (64, 630000, 66)])
+                                      (6656, 20000, 171), (1024, 50304, 108), (64, 630000, 66), (640, 50304, 89), (960, 40001, 89),
+                                      (288, 128256, 66)])
 def test_persistent_cascade_above_64_rows(B, d, V, rows):
     """Where a head's stream is long, cascades of 65 to 26 + V (d + 620) / 10^6 rows run in one launch
     whose waves share weights through LDS: 3 to 6 blocks of 32 rows on four waves (the largest of each
