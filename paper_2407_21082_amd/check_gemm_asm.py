@@ -14,7 +14,8 @@ check is that no path from one reaches the end of the program without a `vmcnt(0
 workgroup's LDS is given to another one then), and that nothing but they uses m0.  The hardware wants
 five wait states between a vector instruction that writes a scalar register (v_readlane, v_readfirstlane) and a
 memory instruction that takes its address from it; the compiler keeps them for its own
-instructions only, so the check looks for them in front of every inline-asm load.
+instructions only, so the check looks for them in front of every inline-asm load, on every path that leads
+there.
 
 This module proves both properties on the assembly text: for every `global_load_dwordx4`
 into VGPRs (and every `ds_read_b128`) that comes from an inline-asm statement it walks every path of the kernel's control-flow graph forward from the load,
@@ -193,29 +194,48 @@ def _sregs(text: str) -> set:
     return regs
 
 
+def _writers_before(prog, pred, i, need, reach):
+    """Instructions that last wrote one of the registers `need` less than `reach` wait states before instruction i,
+    on any path that leads there: (index, wait states in between, registers) -- `need` as {"s": set, "v": set}.
+    A branch counts as one state, like any instruction, taken or not."""
+    out, seen = [], set()
+    todo = [(q, 0, frozenset(need["s"]), frozenset(need["v"])) for q in pred[i]]
+    while todo:
+        j, states, ns, nv = todo.pop()
+        if (j, states, ns, nv) in seen or states >= reach or not (ns or nv):
+            continue
+        seen.add((j, states, ns, nv))
+        op, _, args = prog.ins[j].partition(" ")
+        dest = args.split(",")[0]
+        if op != "s_nop" and not op.startswith(("s_cmp", "s_waitcnt", "s_barrier", "s_cbranch", "s_branch", "ds_write", "global_store")):
+            ws, wv = _sregs(dest) & ns, _vregs(dest) & nv
+            if ws or wv:
+                out.append((j, states, ws, wv))
+                ns, nv = ns - ws, nv - wv
+        states += int(args, 0) + 1 if op == "s_nop" else 1
+        todo += [(q, states, ns, nv) for q in pred[j]]
+    return out
+
+
+def _predecessors(prog):
+    pred = [[] for _ in prog.ins]
+    for i, succ in enumerate(prog.succ):
+        for s in succ:
+            pred[s].append(i)
+    return pred
+
+
 def check_scalar_addresses(lines, max_report=3):
-    """Inline-asm loads whose scalar address a vector instruction has written less than five wait states before
-    (straight-line code; a label in between counts as far enough: a branch takes longer)."""
+    """Inline-asm loads whose scalar address a vector instruction has written less than five wait states before."""
     prog = Program(lines)
+    pred = _predecessors(prog)
     findings = []
-    targets = set(prog.label_at.values())
     for i, t in enumerate(prog.ins):
         if not prog.by_hand[i] or not VMEM_RE.match(t):
             continue
-        need, states, j = _sregs(t), 0, i
-        while need and states < 5 and j > 0 and j not in targets:
-            j -= 1
-            u = prog.ins[j]
-            op, _, args = u.partition(" ")
-            if op == "s_nop":
-                states += int(args, 0) + 1
-                continue
-            written = _sregs(args.split(",")[0]) & need
-            if written and op.startswith("v_"):
-                findings.append(f"`{t}` (#{i}): `{u}` {states} wait states before")
-                break
-            need -= written if op.startswith("s_") else set()
-            states += 1
+        for j, states, _, _ in _writers_before(prog, pred, i, {"s": _sregs(t), "v": set()}, 5):
+            if prog.ins[j].startswith("v_"):
+                findings.append(f"`{t}` (#{i}): `{prog.ins[j]}` {states} wait states before")
     return findings[:max_report]
 
 
@@ -229,10 +249,7 @@ def check_lds_dma(lines, max_report=3):
     findings = [f"`{t}` (#{i}) uses m0, which the hand-written loads to LDS overwrite"
                 for i, t in enumerate(ins) if not prog.by_hand[i] and re.search(r"\bm0\b", t)]
     # instructions from which s_endpgm is reached without passing a wait for all loads
-    pred = [[] for _ in ins]
-    for i, succ in enumerate(prog.succ):
-        for s in succ:
-            pred[s].append(i)
+    pred = _predecessors(prog)
     todo = [i for i, t in enumerate(ins) if t.startswith("s_endpgm")]
     undrained = set(todo)
     while todo:

@@ -112,6 +112,13 @@ def test_hand_written_loads_to_lds():
     assert any("wait states" in f for f in C.check_asm(kernel(near))[0])
     far = near.replace("\tv_readlane_b32 s3, v9, 1\n", "\tv_readlane_b32 s3, v9, 1\n\ts_nop 4\n")
     assert C.check_asm(kernel(far))[0] == []
+    # a label in between changes nothing for the path that falls through it
+    past = near.replace("\tv_readlane_b32 s3, v9, 1\n", "\tv_readlane_b32 s3, v9, 1\n.LBB0_9:\n")
+    assert any("wait states" in f for f in C.check_asm(kernel(past))[0])
+    # nor does the way round a loop: the instruction in front of the branch back comes before its first one
+    round_ = near.replace("\tv_readlane_b32 s3, v9, 1\n", ".LBB0_9:\n").replace(
+        "\ts_endpgm", "\tv_readlane_b32 s3, v9, 1\n\ts_cbranch_scc1 .LBB0_9\n\ts_waitcnt vmcnt(0)\n\ts_endpgm")
+    assert any("wait states" in f for f in C.check_asm(kernel(round_))[0])
 
 
 def test_last_steps_of_a_pass():
