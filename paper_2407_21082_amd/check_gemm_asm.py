@@ -15,7 +15,9 @@ workgroup's LDS is given to another one then), and that nothing but they uses m0
 five wait states between a vector instruction that writes a scalar register (v_readlane, v_readfirstlane) and a
 memory instruction that takes its address from it; the compiler keeps them for its own
 instructions only, so the check looks for them in front of every inline-asm load, on every path that leads
-there.
+there.  Likewise for vector instructions in inline asm: two wait states after a vector instruction that writes a
+scalar register they read, and as many as the matrix core takes after one whose result they read (12 for the
+32x32x16 form, 8 passes; 7 for the 16x16 forms).
 
 This module proves both properties on the assembly text: for every `global_load_dwordx4`
 into VGPRs (and every `ds_read_b128`) that comes from an inline-asm statement it walks every path of the kernel's control-flow graph forward from the load,
@@ -33,7 +35,7 @@ import re
 import sys
 from collections import deque
 
-KERNEL_RE = re.compile(r"^(_Z\w*gemm(?:32)?_(?:stats|kl)_kernel\w*):")
+KERNEL_RE = re.compile(r"^(_Z\w*(?:gemm(?:32)?_(?:stats|kl)_kernel|calib_count1_kernel)\w*):")
 LABEL_RE = re.compile(r"^(\.L\w+):")
 VREG_RE = re.compile(r"\bv(\d+)\b|\bv\[(\d+):(\d+)\]")
 UNTRACKED_RE = re.compile(r"^global_load_dwordx4\s+v\[(\d+):(\d+)\]\s*,")  # any addressing form
@@ -194,6 +196,10 @@ def _sregs(text: str) -> set:
     return regs
 
 
+# vector instructions whose second operand is a destination, too (a carry, or a scale's flag)
+TWO_DEST_RE = re.compile(r"^v_(add_co|sub_co|subrev_co|addc_co|subb_co|subbrev_co|mad_u64|mad_i64|div_scale)")
+
+
 def _writers_before(prog, pred, i, need, reach):
     """Instructions that last wrote one of the registers `need` less than `reach` wait states before instruction i,
     on any path that leads there: (index, wait states in between, registers) -- `need` as {"s": set, "v": set}.
@@ -206,7 +212,7 @@ def _writers_before(prog, pred, i, need, reach):
             continue
         seen.add((j, states, ns, nv))
         op, _, args = prog.ins[j].partition(" ")
-        dest = args.split(",")[0]
+        dest = ",".join(args.split(",")[:2 if TWO_DEST_RE.match(op) else 1])
         if op != "s_nop" and not op.startswith(("s_cmp", "s_waitcnt", "s_barrier", "s_cbranch", "s_branch", "ds_write", "global_store")):
             ws, wv = _sregs(dest) & ns, _vregs(dest) & nv
             if ws or wv:
@@ -236,6 +242,22 @@ def check_scalar_addresses(lines, max_report=3):
         for j, states, _, _ in _writers_before(prog, pred, i, {"s": _sregs(t), "v": set()}, 5):
             if prog.ins[j].startswith("v_"):
                 findings.append(f"`{t}` (#{i}): `{prog.ins[j]}` {states} wait states before")
+    return findings[:max_report]
+
+
+def check_vector_operands(lines, max_report=3):
+    """Inline-asm vector instructions too close behind the instruction that writes a source (see above)."""
+    prog = Program(lines)
+    pred = _predecessors(prog)
+    findings = []
+    for i, t in enumerate(prog.ins):
+        if not prog.by_hand[i] or not t.startswith("v_"):
+            continue
+        for j, states, ws, wv in _writers_before(prog, pred, i, {"s": _sregs(t), "v": _vregs(t)}, 12):
+            u = prog.ins[j]
+            if (ws and u.startswith("v_") and states < 2) or \
+                    (wv and u.startswith("v_mfma") and states < (12 if "32x32" in u else 7)):
+                findings.append(f"`{t}` (#{i}): `{u}` {states} wait states before")
     return findings[:max_report]
 
 
@@ -334,8 +356,8 @@ def check_asm(asm: str):
     findings, loads = [], 0
     for name, body in kernels.items():
         f, n = check_kernel(body)
-        g, _ = check_step_counts(name, body)
-        g += check_lds_dma(body)[0] + check_scalar_addresses(body)
+        g = check_step_counts(name, body)[0] if "gemm" in name else []
+        g += check_lds_dma(body)[0] + check_scalar_addresses(body) + check_vector_operands(body)
         loads += n
         findings += [f"{name}: {x}" for x in f + g]
     return findings, len(kernels), loads

@@ -388,8 +388,11 @@ __global__ __launch_bounds__(1024) void calib_count1_kernel(const float* __restr
     for (int j = 0; j < 4; ++j) {
       const bool right = a[u][j] == b[u][j];
       const unsigned long long word = __ballot(right);
-      asm("v_writelane_b32 %0, %1, %2" : "+v"(bits_lo) : "s"((uint32_t)word), "n"(4 * u + j));
-      asm("v_writelane_b32 %0, %1, %2" : "+v"(bits_hi) : "s"((uint32_t)(word >> 32)), "n"(4 * u + j));
+      // A vector instruction may read a scalar register only two wait states after another has written it (the
+      // ballot's compare has).  The compiler keeps that distance for its own instructions but does not look
+      // into inline assembly.
+      asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+          : "+v"(bits_lo), "+v"(bits_hi) : "s"((uint32_t)word), "s"((uint32_t)(word >> 32)), "n"(4 * u + j));
       const uint32_t off = __float_as_uint(h[u][j]) - c.lo_bits;
       const bool in = off < c.n_plain;
       odd |= !in;

@@ -121,6 +121,34 @@ def test_hand_written_loads_to_lds():
     assert any("wait states" in f for f in C.check_asm(kernel(round_))[0])
 
 
+@pytest.mark.parametrize("writer,asm,states", [
+    ("v_cmp_eq_u32_e64 s[4:5], v1, v2", "v_writelane_b32 v3, s5, 7", 2),
+    ("v_readlane_b32 s4, v1, 3", "v_writelane_b32 v3, s4, 7", 2),
+    ("v_add_co_u32_e64 v5, s[4:5], v1, v2", "v_writelane_b32 v3, s5, 7", 2),
+    ("v_mfma_f32_32x32x16_bf16 v[16:31], v[0:3], v[4:7], v[16:31]", "v_max3_f32 v9, v17, v30, v8", 12),
+    ("v_mfma_f32_16x16x32_bf16 v[16:19], v[0:3], v[4:7], v[16:19]", "v_max3_f32 v9, v17, v18, v8", 7)])
+def test_inline_asm_vector_instructions_keep_their_distance(writer, asm, states):
+    """The compiler does not count wait states in front of an instruction that it sees as text."""
+    def text(nops):
+        gap = f"\ts_nop {nops - 1}\n" if nops else ""
+        return f"_ZN2eh19calib_count1_kernelE:\n\t{writer}\n{gap}\t;;#ASMSTART\n\t{asm}\n\t;;#ASMEND\n\ts_endpgm\n.Lfunc_end0:\n"
+    assert C.check_asm(text(states)) == ([], 1, 0)
+    for nops in (0, states - 1):
+        assert any("wait states" in f for f in C.check_asm(text(nops))[0]), nops
+    # an instruction the compiler knows is the compiler's business
+    own = text(0).replace("\t;;#ASMSTART\n", "").replace("\t;;#ASMEND\n", "")
+    assert C.check_asm(own) == ([], 1, 0)
+
+
+def test_only_checked_sources_have_vector_instructions_in_inline_asm():
+    csrc = os.path.join(os.path.dirname(C.__file__), "csrc")
+    checked = {"eh_gemm.hip", "eh_gemm32.hip", "eh_calib.hip"}
+    for name in sorted(os.listdir(csrc)):
+        with open(os.path.join(csrc, name)) as f:
+            hit = re.search(r'asm(?: volatile)?\("[^;]*?\bv_\w+', f.read())
+        assert not hit or name in checked, (name, hit and hit.group(0))
+
+
 def test_last_steps_of_a_pass():
     """Behind the last full step (2 DMA + 1 register load, one step in flight: 3) come steps without register
     loads: every wait counts a full step less and the DMA loads in between."""
