@@ -849,7 +849,11 @@ __global__ __launch_bounds__(kWalkWaves * 64) void calib_pick_kernel(CalibWork w
 }
 
 // Presets the tables: n0 words of 0 from p0, n1 words of -1 from p1; and the first kSampleWgs workgroups
-// find the key range of kSample tokens spread evenly over the set (all of them if there are no more).
+// find the key range of kSample tokens, one from each of as many equal parts of the set (all tokens if there are
+// no more).  Which one of a part is left to a hash: at a fixed stride a set of equally long sequences would
+// be seen at the same few positions of each, whose entropies are a kind of their own; most tokens would then be
+// outside the range and take the long way (2^24 tokens in sequences of 256 with one entropy at their first
+// position: 552 us at a fixed stride, 104 now; the same tokens in no order 107 and 105).
 __global__ __launch_bounds__(256) void calib_preset_kernel(int* __restrict__ p0, int64_t n0, int* __restrict__ p1,
                                                            int64_t n1, const float* __restrict__ H, int64_t M,
                                                            uint2* __restrict__ range) {
@@ -862,10 +866,14 @@ __global__ __launch_bounds__(256) void calib_preset_kernel(int* __restrict__ p0,
   __shared__ uint32_t sh_lo[4], sh_hi[4];
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   constexpr int U = kSample / (kSampleWgs * 256);
+  const uint32_t part = (uint32_t)(M / kSample);  // tokens to choose from
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int64_t j = ((int64_t)blockIdx.x * U + u) * 256 + threadIdx.x;
-    const int64_t at = M <= kSample ? j : j * M / kSample;
+    uint32_t mix = (uint32_t)j * 0x9E3779B1u;
+    mix = (mix ^ (mix >> 15)) * 0x85EBCA77u;
+    mix ^= mix >> 13;
+    const int64_t at = M <= kSample ? j : j * M / kSample + __umulhi(mix, part);
     const float h = at < M ? H[at] : NAN;
     if (h == h) {
       const uint32_t key = ascending_key(h);

@@ -5,6 +5,7 @@ workload configurations then run at their real sizes, compared either in full
 or on a stated sample of rows/steps the oracle can afford.
 """
 import math
+import time
 
 import numpy as np
 import pytest
@@ -549,6 +550,38 @@ def test_calibrate_outside_the_sample(B, small_ctx, M, lift):
     t = O.correctness(pred.cpu().numpy(), ref.cpu().numpy())
     for i, (want_tau, want_n) in enumerate(_calibrate_by_counting(H.cpu().numpy().astype(np.float64), t, eps)):
         assert tau[i] == want_tau and n[i] == want_n, (eps[i], tau[i], want_tau, n[i], want_n)
+
+
+@pytest.mark.parametrize("M,length,first", [(1 << 20, 16, 9.5), (1 << 22, 64, 0.001), (3 << 20, 48, 9.5)])
+def test_calibrate_sequences_of_one_length(B, small_ctx, M, length, first):
+    """A set of sequences of one length, a divisor of the stride at which the key range could be sampled, whose first
+    positions all have one entropy: the exact answer, by counting, in about the time that the same tokens
+    take in no order (three to five times as long where the sample saw nothing but first positions)."""
+    gen = torch.Generator(device=DEV).manual_seed(M)
+    H = torch.empty(M, device=DEV).exponential_(generator=gen)
+    H = (0.9 * (H + torch.empty(M, device=DEV).exponential_(generator=gen))).clamp_(max=10.8)
+    pred = (torch.rand(M, generator=gen, device=DEV) > torch.exp(-0.9 * H)).to(torch.int32)
+    H[::length] = first
+    ref = torch.zeros(M, dtype=torch.int32, device=DEV)
+    eps = [0.5, 0.7, 0.8, 0.9, 0.95, 0.99]
+    perm = torch.randperm(M, generator=gen, device=DEV)
+    times = []
+    for h, p in ((H, pred), (H[perm].contiguous(), pred[perm].contiguous())):
+        before = B.eh_probe_calibrate_sorted(small_ctx)
+        tau, n = _calibrate(B, small_ctx, h, p, ref, eps)
+        assert B.eh_probe_calibrate_sorted(small_ctx) == before
+        t = O.correctness(p.cpu().numpy(), ref.cpu().numpy())
+        for i, (want_tau, want_n) in enumerate(_calibrate_by_counting(h.cpu().numpy().astype(np.float64), t, eps)):
+            assert tau[i] == want_tau and n[i] == want_n, (eps[i], tau[i], want_tau, n[i], want_n)
+        out = torch.zeros(len(eps), device=DEV), torch.zeros(len(eps), dtype=torch.int64, device=DEV)
+        turns = []
+        for _ in range(9):
+            t0 = time.perf_counter()
+            for _ in range(5):
+                B.eh_calibrate(small_ctx, h, p, ref, eps, *out)      # (waits for its stream)
+            turns.append(time.perf_counter() - t0)
+        times.append(min(turns))
+    assert times[0] < 1.5 * times[1], times
 
 
 def test_calibrate_degenerate_inputs(B, small_ctx):
