@@ -104,10 +104,13 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // of d = 1024, 47 against 48 at 64 of d = 512; at 32 rows 47 against 36.
 // bf16 at 33 to 64 rows: with seven tiles a pass (V above 12 tiles of 16 a workgroup, 49152 on 256
 // compute units, up to 57344) two blocks of rows fill the register file, and the statistics behind a
-// pass spill; gemm32_launch's kernel is then the better one, up to six tiles this one is.  One head on
-// 48 rows, us, this kernel against that: V = 50304, d = 512 / 1024 / 2048 25.6 / 33.6 / 50.1 against 23.4 /
-// 30.4 / 45.1; V = 49152 21.9 / 30.1 / 45.6 against 22.4 / 29.1 / 45.6; 12 heads in one call, V = 50304 156 /
-// 238 / 422 against 154 / 240 / 419; V = 49152 132 / 214 / 390 against 150 / 235 / 409.
+// pass spill; gemm32_launch's kernel is then the better one.  With six tiles and fewer it is the better one for a
+// single head of a large V (by up to 7 %), this one for several heads in one call: the line is drawn
+// for those.  48 rows, us, this kernel against that, d = 512 / 1024 / 2048: one head, V = 50304 25.2 / 32.9 / 48.8
+// against 21.7 / 28.9 / 43.2, V = 49152 22.7 / 29.1 / 44.3 against 21.3 / 27.7 / 43.8, V = 32000 18.3 / 23.4 / 32.6
+// against 17.3 / 23.4 / 32.4, V = 16384 15.5 / 17.2 / 23.2 against 15.6 / 17.6 / 24.9; 12 heads in one call,
+// V = 50304 155 / 236 / 419 against 130 / 221 / 404, V = 49152 131 / 212 / 386 against 127 / 214 / 395, V = 32000
+// 96 / 151 / 270 against 100 / 159 / 284, V = 16384 63 / 94 / 164 against 69 / 113 / 204.
 bool use_ksplit(const eh_ctx* c, int n_rows) {
   if (!c->bias.empty() || n_rows <= 32) return true;
   return c->dtype == EH_BF16 && n_rows <= 64 && ksplit_pass_tiles(c) < 7;
@@ -119,8 +122,8 @@ int round_up(int n, int to) { return (n + to - 1) / to * to; }
 
 // Rows of all heads together (padded) from which ln_pack_many_kernel's wave per row is the better LayerNorm: below,
 // the rows do not fill the chip and four waves have one done sooner.  One wave against four, us a call: 4 heads x
-// 20 rows of d = 1024 80.0 / 78.9, 4 x 64 86.7 / 85.0, 8 x 40 of d = 2048 278 / 277, 8 x 100 of d = 1024 169 / 170, 8 x 203 with
-// all metrics 226 / 230.
+// 20 rows of d = 1024 80.4 / 79.3, 4 x 64 87.0 / 85.0, 8 x 40 of d = 2048 276 / 275, 8 x 100 of d = 1024 165 / 166, 8 x 203 with
+// all metrics 222 / 224, 24 x 512 of d = 2048 2251 / 2271.
 constexpr int64_t kLnMany = 1024;
 
 // LayerNorm of a head's rows into yf, in the operand order of the kernel that n_rows rows go to.
@@ -190,10 +193,10 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // The persistent rows kernel, one launch for a whole cascade or verification (at most 16 rows go to
 // the decode kernel where the context has one, and here otherwise).
 //
-// A verification: up to 64 positions.  Beyond, its one head cannot hide the LayerNorm and the hand-over
-// in front of its weights, and three launches are faster (V = 50304, d = 2560 / 1024, us, one launch
-// against three: 90 positions 78 / 43 against 65 / 34, 144 89 / 46 against 72 / 38, 252 105 / 54 against
-// 87 / 42).
+// A verification: up to 64 positions, which is where the kernel has a form for it.  (Its one head cannot hide the
+// LayerNorm and the hand-over in front of its weights, and three launches have become the faster way
+// there as well: V = 50304, d = 512 / 1024 / 2560, us, one launch against three, 18 positions 28 / 36 / 58 against
+// 19 / 28 / 52, 63 positions 34 / 41 / 66 against 22 / 28 / 51.  The line has not been moved.)
 //
 // A cascade: as long as the two launches per head and the gaps between them cost more than the
 // service workgroups, whose time grows with the rows, cost the streaming ones; the longer a head's
@@ -330,8 +333,8 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
         return bail(e, "copy bias");
     }
   }
-  // the kernels read whole groups of token blocks: up to 4 waves x 8
-  // blocks (batched kernel) starting inside the padded rows, so 32 zero blocks follow them
+  // the fp32 kernel reads whole groups of token blocks, up to 4 waves x 8 blocks of 16 rows
+  // starting inside the padded rows, so 32 zero blocks follow them
   const size_t y_frags = (size_t)(c->R_pad_max / 16 + 32) * c->KS * kWave;
   if ((e = dev_alloc(c, &c->yf, y_frags)) != hipSuccess) return bail(e, "hipMalloc(y)");
   if ((e = hipMemset(c->yf, 0, y_frags * sizeof(frag_t))) != hipSuccess) return bail(e, "memset y");

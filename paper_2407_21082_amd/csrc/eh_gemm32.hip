@@ -55,9 +55,9 @@ constexpr int kSlotBytes = 2 * kMaxMT * 1024;
 constexpr int kDepth = 3;      // activation register sets = k-steps a load may take
 constexpr int kRingAhead = 6;  // k-steps the weights are asked for ahead
 static_assert(kDepth < kRingAhead, "a step's weights are asked for before its activations");
-// the weight ring, then 16 bytes per thread: the second largest logit of its (at most 2) token blocks
-// between passes (registers are too scarce to keep it live across the k loop); then, per token
-// block, the 16 logits of the tile that holds the thread's largest one ([block][4][thread] f32x4)
+// the weight ring, then 4 bytes per thread: the second largest logit of its token block between passes
+// (registers are too scarce to keep it live across the k loop); then the 16 logits of the tile that
+// holds the thread's largest one ([4][thread] f32x4)
 __host__ __device__ constexpr size_t g32_ring_bytes() { return (size_t)kSlots * kSlotBytes; }
 __host__ __device__ constexpr size_t g32_park_at() { return g32_ring_bytes() + kG32Threads * 4; }
 __host__ __device__ constexpr size_t g32_lds_bytes() { return g32_park_at() + (size_t)4 * kG32Threads * 16; }
@@ -280,8 +280,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // DMA loads a wave issues per k-step: the 2*MT fragments of a step are dealt
-// round-robin to the four waves; a wave with fewer real fragments repeats its
-// last one (same bytes to the same place) so that all waves count alike.
+// round-robin to the eight waves; a wave with fewer real fragments brings the
+// last one once more (see RingFeed) so that all waves count alike.
 __host__ __device__ constexpr int dma_per_wave(int mt) { return (2 * mt + kG32Waves - 1) / kG32Waves; }
 
 // One pass: MT tiles of 32 vocabulary rows starting at 16-row tile T16 (the workgroup's tiles end
@@ -753,7 +753,7 @@ __device__ __forceinline__ void pass32_idle(const G32Src& cur, const G32Src& nex
   if (2 * next.mt > kG32Waves * kDma) ring_start<DUAL>(next, KS, rb + KS, lane, wave, lds, wdelta, kG32Waves * kDma);
 }
 
-// How the workgroups of a launch share n_live rows: groups of at most 8 blocks of 32 rows (two per
+// How the workgroups of a launch share n_live rows: groups of at most 8 blocks of 32 rows (one per
 // wave), as equal as they go, each with the same number of workgroups over the vocabulary.  The
 // live count may only be known on the device (a cascade), so the kernel works this out itself.
 struct G32Deal {
@@ -1864,9 +1864,10 @@ int rows_control_ints(int n_heads) { return rows_ctl_ints(n_heads) + 128; }  // 
 // wave, except where a head of 300 MB and more streams long enough to hide the second (above 128 rows) and
 // above 192 rows, where the waves' count has to stay below the 256 of its byte in c.ready.  At least
 // kRowsServiceWgs: fewer make no slice of the vocabulary a tile shorter.  10 heads, us, 12 workgroups / two
-// rows per wave / one: V = 50304, d = 2048, 120 rows 475 / - / 409, 150 rows - / 514 / 439; d = 2560, 175
-// rows - / 598 / 586; d = 4096 (412 MB), 185 rows - / 870 / 892, 210 rows 981 / 906 / -; V = 32000,
-// d = 2048, 101 rows 381 / - / 335.
+// rows per wave / one: V = 50304, d = 1024, 105 rows 317 / 315 / 286; d = 2048, 120 rows 432 / 434 / 396, 150 rows
+// 467 / 469 / 430; d = 2560, 175 rows 547 / 547 / 557 to 561 (this head is below the line);
+// d = 4096 (412 MB), 120 rows 766 / 766 / 773 to 780, 160 rows 815 / 814 / 821, 185 rows 859 / 858 / 870, 210 rows
+// 948 / 895 / -; V = 32000, d = 2048, 101 rows 347 / 347 / 308.
 int rows_service_workgroups(int n_rows, long long head_elements) {
   if (n_rows <= kKsGroup) return kRowsServiceWgs;  // the kernel of four waves a workgroup
   const int rows_per_wave = n_rows <= 128 || (n_rows <= 192 && head_elements < 150000000ll) ? 1 : 2;
