@@ -782,15 +782,17 @@ __global__ __launch_bounds__(Few<ONE_ROW>::kThreads, 1) void decode_kernel(const
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // landed before this workgroup's barrier below
   }
-  // a launch that gave up has not been acknowledged yet (eh_check clears the flag): do nothing
-  if (*(volatile int*)p.status != 0) return;
   // zero both activation buffers (columns of rows that are not live stay zero)
   {
     lds_frag_t* y = sm.ybuf(0);
     const int total = 2 * p.KS * kWave;
     for (int i = threadIdx.x; i < total; i += kThreads) y[i] = mk_frag(0, 0, 0, 0);
     if (threadIdx.x < 2) {
-      *sm.abort_flag(threadIdx.x) = 0;
+      // A launch that gave up has not been acknowledged yet (eh_check clears the flag): do nothing.  One wave asks
+      // for its workgroup: another workgroup of this launch may give up at any moment, and the waves must not
+      // part over it.  Both abort flags set, every wave leaves behind the first head, before a record or a result is
+      // written.
+      *sm.abort_flag(threadIdx.x) = __builtin_amdgcn_readfirstlane(*(volatile int*)p.status);
       *sm.arrived(threadIdx.x) = 0;
     }
     if (threadIdx.x == 2) *sm.sent_word() = 0;

@@ -1170,11 +1170,11 @@ __device__ __forceinline__ void rows_first_layernorm(const RowsParams& p, const 
   EH_ROWS_STAMP(1);
 }
 
-// The wait for all of it; leaves the counter in *flag.  False if the launch was aborted.
-__device__ __forceinline__ bool rows_first_wait(const RowsParams& p, const RowsCtl& c, int lane, int wave, int* flag) {
+// The wait for all of it; leaves the counter in *flag.  False if the launch was aborted, or an earlier one gave up.
+__device__ __forceinline__ bool rows_first_wait(const RowsParams& p, const RowsCtl& c, int lane, int wave, int* flag, int gave_up) {
   // the first head's activations are complete when every streaming workgroup has written its rows
   if (wave == 0) {
-    const int v = rows_wait(p, c, c.ready(0), p.n_stream, lane);
+    const int v = gave_up != 0 ? -1 : rows_wait(p, c, c.ready(0), p.n_stream, lane);
     if (lane == 0) *flag = v;
   }
   __syncthreads();
@@ -1187,7 +1187,7 @@ __device__ __forceinline__ bool rows_first_wait(const RowsParams& p, const RowsC
 
 // Returns false if the launch was aborted (or every row has left).
 __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& c, EH_LDS char* lds, int lane, int wave,
-                                            double* red, int* flag) {
+                                            double* red, int* flag, int gave_up) {
   const int g = blockIdx.x, tid = threadIdx.x;
   const int nh = p.l1 - p.l0;
   const int nsw = ((int)gridDim.x - p.n_stream) * kG32Waves;  // service waves
@@ -1203,7 +1203,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
   // (weights asked for in front of the LayerNorm would only hold up its own loads: a wave's loads
   // return in order)
   if (run_on) ring_start<false>(cur, p.KS, rb, lane, wave, lds);
-  if (!rows_first_wait(p, c, lane, wave, flag)) return false;
+  if (!rows_first_wait(p, c, lane, wave, flag, gave_up)) return false;
   int word = 0;
   int ncols = p.n_rows;
   EH_ROWS_STAMP(2);
@@ -1283,7 +1283,7 @@ __device__ __forceinline__ bool rows_stream(const RowsParams& p, const RowsCtl& 
 // positions, d = 2560, 76 -> 67.
 template <int MT, int NB, bool ARGMAX_ONLY>
 __device__ __forceinline__ bool rows_stream_ks(const RowsParams& p, const RowsCtl& c, const KsSlice& sl, EH_KS_LDS char* lds,
-                                               int lane, int wave, double* red, int* flag) {
+                                               int lane, int wave, double* red, int* flag, int gave_up) {
   const int g = blockIdx.x, tid = threadIdx.x;
   const int nh = p.l1 - p.l0;
   const int nsw = ((int)gridDim.x - p.n_stream) * kKsWaves;  // service waves
@@ -1297,7 +1297,7 @@ __device__ __forceinline__ bool rows_stream_ks(const RowsParams& p, const RowsCt
   // return in order)
   rows_first_layernorm<kKsWaves>(p, c, red);
   ks_start<MT>(a, p.Wf[p.l0] + slice_at, p.KS, wave, voff);
-  if (!rows_first_wait(p, c, lane, wave, flag)) return false;  // leaves *flag >= 0
+  if (!rows_first_wait(p, c, lane, wave, flag, gave_up)) return false;  // leaves *flag >= 0
   int ncols = p.n_rows;
   ks_start_b<NB>(b, p.y, p.KS, wave, lane);
   for (int j = 0; j < nh; ++j) {
@@ -1691,25 +1691,28 @@ __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_
     if (blockIdx.x == gridDim.x - 1)
       for (int i = threadIdx.x; i < p.n_ctl_next; i += NW * kWave) p.ctl_next[i] = 0;
   }
-  // a launch that gave up has not been acknowledged yet (eh_check clears the flag): do nothing
-  if (*(volatile int*)p.status != 0) return;
+  // Not 0: a launch that gave up has not been acknowledged yet (eh_check clears the flag), and this one does nothing.
+  // Another workgroup of this launch may give up at any moment, and the waves of a streaming workgroup must not part
+  // over it: the first one's answer, looked at behind the first LayerNorm, counts for all.  Service waves
+  // share nothing within their workgroup.
+  const int gave_up = __builtin_amdgcn_readfirstlane(*(volatile int*)p.status);
   RowsCtl c{p.ctl, p.l1 - p.l0 + 2};
   if ((int)blockIdx.x < p.n_stream) {
     bool ok = false;
     if constexpr (KS_NB > 0) {
       const KsSlice sl(p.VT16, blockIdx.x, p.n_stream);
       switch (sl.mt) {
-        case 7: ok = rows_stream_ks<7, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
-        case 6: ok = rows_stream_ks<6, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
-        case 5: ok = rows_stream_ks<5, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
-        case 4: ok = rows_stream_ks<4, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
-        case 3: ok = rows_stream_ks<3, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
-        case 2: ok = rows_stream_ks<2, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        case 7: ok = rows_stream_ks<7, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag, gave_up); break;
+        case 6: ok = rows_stream_ks<6, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag, gave_up); break;
+        case 5: ok = rows_stream_ks<5, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag, gave_up); break;
+        case 4: ok = rows_stream_ks<4, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag, gave_up); break;
+        case 3: ok = rows_stream_ks<3, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag, gave_up); break;
+        case 2: ok = rows_stream_ks<2, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag, gave_up); break;
         // (a workgroup without a tile of its own takes its turns like the others)
-        default: ok = rows_stream_ks<1, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag); break;
+        default: ok = rows_stream_ks<1, KS_NB, ARGMAX_ONLY>(p, c, sl, lds, lane, wave, red, &flag, gave_up); break;
       }
     } else {
-      ok = rows_stream(p, c, lds, lane, wave, red, &flag);
+      ok = rows_stream(p, c, lds, lane, wave, red, &flag, gave_up);
     }
     if constexpr (KS_NB > 0) {
       if (ok && p.mode == 1) rows_verify_tail(p, c, lane, wave, &flag);
@@ -1719,6 +1722,7 @@ __device__ __forceinline__ void rows_kernel_body(const RowsParams& p, char* g32_
     return;
   }
   const int sg = (int)blockIdx.x - p.n_stream, nsg = (int)gridDim.x - p.n_stream;
+  if (gave_up != 0) return;
   if (p.mode == 0) rows_serve_cascade(p, c, lane, sg * NW + wave, nsg * NW);
 }
 

@@ -198,6 +198,24 @@ def test_calibration_kernels_do_not_ask_for_the_flag_they_raise():
     assert raising == {"calib_keep1_kernel", "calib_keep2_kernel"}, raising
 
 
+def test_waves_of_a_workgroup_do_not_part_over_the_status_word():
+    """Any workgroup of a launch may raise the status word of the persistent kernels; waves of another one that each
+    looked for themselves could part over it, some leaving before the barriers and the LayerNorm they
+    share.  Decode kernel: one wave's answer, in LDS.  Rows kernel: read once, and asked about by the wave that speaks
+    for a streaming workgroup and by the service waves, each for itself."""
+    text = {}
+    for source in ("eh_decode.hip", "eh_gemm32.hip"):
+        with open(os.path.join(os.path.dirname(C.__file__), "csrc", source)) as f:
+            text[source] = re.sub(r"//.*", "", f.read())
+        assert len(re.findall(r"volatile[^;]*p\.status", text[source])) == 1
+        assert not re.search(r"if \(\*\(volatile", text[source].replace("*(volatile const int*)p.live", ""))
+    assert re.search(r"if \(threadIdx\.x < 2\) \{\s+\*sm\.abort_flag\(threadIdx\.x\) = __builtin_amdgcn_readfirstlane\(\*\(volatile", text["eh_decode.hip"])
+    uses = re.findall(r"[^\n]*gave_up != 0[^\n]*", text["eh_gemm32.hip"])
+    assert len(uses) == 2 and "? -1 : rows_wait" in uses[0] and uses[1].strip().endswith("return;"), uses
+    before_first = text["eh_gemm32.hip"].split(uses[0])[0]
+    assert before_first.rstrip().endswith("if (wave == 0) {")
+
+
 def test_built_library_was_checked():
     """The assembly the in-tree library was built from, if a build left it, is clean."""
     build_dir = os.path.join(os.path.dirname(C.__file__), "_build")
