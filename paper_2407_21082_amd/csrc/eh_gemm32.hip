@@ -605,7 +605,7 @@ __device__ __forceinline__ void pass32(const G32Src& cur, const G32Src& next, in
   // The steps a head of d <= 64 lacks: no activations, on its last weights once more.  (The k-split kernel, which
   // streams the weights once for every 64 rows, instead, us: 8 heads of d = 32, 128 / 512 rows 123 / 403
   // against 54 / 111 here.)
-  if (KS < kDepth) {
+  if (__builtin_expect(KS < kDepth, 0)) {
 #pragma unroll
     for (int c = 1; c < kDepth; ++c)
       if (c >= KS) {
