@@ -77,7 +77,9 @@ typedef enum { EH_F32 = 0, EH_BF16 = 1 } eh_dtype;
  * gamma[l], beta[l]   device, [d] float.  Copied at creation.
  * bias      NULL, or n_heads device pointers [V] float added to the logits.  Copied.
  *           Entries 10^6 and more below the largest one, -infinity among them, mask a word
- *           and count as 10^6 below it.
+ *           and count as 10^6 below it.  Where the largest one is above 2^24 in magnitude,
+ *           those that lie below it by 2^-20 of it (and 10^6) count as -infinity; above
+ *           10^9 the argmax is right, but the entropy and log-sum-exp are not defined.
  * tau       host, [n_heads] float, thresholds in nats (Section 3.4.1); the last
  *           entry is ignored.  Copied.
  * w_dtype must equal h_dtype.  In EH_BF16 mode the LayerNorm output is rounded

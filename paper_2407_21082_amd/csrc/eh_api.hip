@@ -119,9 +119,10 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // against 17.3 / 23.4 / 32.4, V = 16384 15.5 / 17.2 / 23.2 against 15.6 / 17.6 / 24.9; 12 heads in one call,
 // V = 50304 155 / 236 / 419 against 130 / 221 / 404, V = 49152 131 / 212 / 386 against 127 / 214 / 395, V = 32000
 // 96 / 151 / 270 against 100 / 159 / 284, V = 16384 63 / 94 / 164 against 69 / 113 / 204.
+// Contexts of `wide` values (eh_internal.hpp) with a bias vector go there at any number of rows: its statistics test every logit.
 constexpr int kF32Split = 256;
 bool use_ksplit(const eh_ctx* c, int n_rows) {
-  if (n_rows <= 32) return true;
+  if (n_rows <= 32 || (c->wide && !c->bias.empty())) return true;
   if (c->dtype == EH_F32) return !c->bias.empty() || c->d >= kF32Split;
   return n_rows <= 64 && ksplit_pass_tiles(c) < 7;
 }
@@ -323,6 +324,9 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
   const int Vp = c->VT * 16;
   c->Wf.resize(c->n_heads); c->gamma.resize(c->n_heads); c->beta.resize(c->n_heads);
   if (cfg->bias) c->bias.resize(c->n_heads);
+  int* wide = nullptr;
+  if ((e = dev_alloc(c, &wide, (size_t)1)) != hipSuccess) return bail(e, "hipMalloc(wide)");
+  if ((e = hipMemset(wide, 0, sizeof(int))) != hipSuccess) return bail(e, "memset wide");
   for (int l = 0; l < c->n_heads; ++l) {
     if ((e = dev_alloc(c, &c->Wf[l], wf_frags)) != hipSuccess) return bail(e, "hipMalloc(W)");
     if ((e = dev_alloc(c, &c->gamma[l], (size_t)c->d)) != hipSuccess) return bail(e, "hipMalloc(gamma)");
@@ -342,10 +346,13 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
     if (cfg->bias) {
       if ((e = dev_alloc(c, &c->bias[l], (size_t)Vp)) != hipSuccess) return bail(e, "hipMalloc(bias)");
       if ((e = hipMemset(c->bias[l], 0, sizeof(float) * Vp)) != hipSuccess) return bail(e, "memset bias");
-      hipLaunchKernelGGL(copy_bias_kernel, dim3(1), dim3(kBiasThreads), 0, 0, cfg->bias[l], c->V, c->bias[l]);
+      hipLaunchKernelGGL(copy_bias_kernel, dim3(1), dim3(kBiasThreads), 0, 0, cfg->bias[l], c->V, c->bias[l], wide);
       if ((e = hipGetLastError()) != hipSuccess) return bail(e, "bias launch");
     }
   }
+  int is_wide = 0;
+  if ((e = hipMemcpy(&is_wide, wide, sizeof(int), hipMemcpyDeviceToHost)) != hipSuccess) return bail(e, "copy wide");
+  c->wide = is_wide != 0;
   // the fp32 kernel reads whole groups of token blocks, up to 4 waves x 8 blocks of 16 rows
   // starting inside the padded rows, so 32 zero blocks follow them
   const size_t y_frags = (size_t)(c->R_pad_max / 16 + 32) * c->KS * kWave;

@@ -21,6 +21,9 @@ struct eh_ctx {
   float eps = 1e-5f;
   int KS = 0, VT = 0, R_pad_max = 0;
   int num_cu = 0;
+  // a bias vector's largest entry is not finite or above 2^24 in magnitude: logits may be infinite, or rounded at
+  // the size of their products, and the kernels that take neither are not used
+  bool wide = false;
   std::vector<eh::frag_t*> Wf;  // per head, fragment-major weights
   std::vector<float*> gamma, beta, bias;
   std::vector<float> tau;

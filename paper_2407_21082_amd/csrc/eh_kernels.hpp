@@ -11,11 +11,16 @@ namespace eh {
 // A context's copy of a bias vector, by one workgroup.  Entries that mask a word (-infinity, the lowest float) are raised to
 // kBiasSpan below the largest entry: a logit there has probability 0 all the same, and the statistics need no test per
 // logit: its share t * 2^t of an entropy's sum is 0 where -infinity * 0 would be NaN, and where a lane holds nothing
-// but masked words, t = z log2 e - m stays below 1 (at 10^20 the product's rounding alone is 10^13).  NaN stays, and so does
-// a vector without a finite largest entry.
+// but masked words, t = z log2 e - m stays below 1 (at 10^20 the product's rounding alone is 10^13).  NaN stays.
+// Where the largest entry is further from 0 than kBiasTop (a word forced by 10^30, say), a float kBiasSpan below it may
+// round back to it: there *wide is set, which selects the kernels that test every logit for -infinity, and that is what
+// entries become that lie below the largest by kBiasSpan and by 2^-20 of it.  A vector without a finite largest entry is
+// copied as it is.
 constexpr float kBiasSpan = 1e6f;
+constexpr float kBiasTop = 16777216.f;  // 2^24: a float there is exact to 1
 constexpr int kBiasThreads = 1024;
-static __global__ __launch_bounds__(kBiasThreads) void copy_bias_kernel(const float* __restrict__ bias, int V, float* __restrict__ out) {
+static __global__ __launch_bounds__(kBiasThreads) void copy_bias_kernel(const float* __restrict__ bias, int V, float* __restrict__ out,
+                                                                        int* __restrict__ wide) {
   __shared__ float top[kBiasThreads];
   float m = -INFINITY;
   for (int i = threadIdx.x; i < V; i += kBiasThreads) m = fmaxf(m, bias[i]);
@@ -25,8 +30,10 @@ static __global__ __launch_bounds__(kBiasThreads) void copy_bias_kernel(const fl
     if ((int)threadIdx.x < n) top[threadIdx.x] = fmaxf(top[threadIdx.x], top[threadIdx.x + n]);
     __syncthreads();
   }
-  const float lowest = top[0] < INFINITY ? top[0] - kBiasSpan : -INFINITY;
-  for (int i = threadIdx.x; i < V; i += kBiasThreads) out[i] = bias[i] < lowest ? lowest : bias[i];
+  const bool raise = fabsf(top[0]) <= kBiasTop;
+  if (!raise && threadIdx.x == 0) *wide = 1;
+  const float span = fmaxf(kBiasSpan, fabsf(top[0]) * 0x1p-20f), lowest = fabsf(top[0]) < INFINITY ? top[0] - span : -INFINITY;
+  for (int i = threadIdx.x; i < V; i += kBiasThreads) out[i] = bias[i] < lowest ? (raise ? lowest : -INFINITY) : bias[i];
 }
 
 // ---------------------------------------------------------------------------

@@ -13,7 +13,7 @@ __host__ __device__ inline int ks_groups(int n_rows) { return (n_rows + kKsGroup
 // the heads.
 template <typename DT, int MT, int NB, bool AO, bool TOP2>
 __device__ __forceinline__ void ks_heads(const KsSlice& sl, const frag_t* const* __restrict__ Wf, const float* const* __restrict__ bias,
-                                         int n_heads, const frag_t* __restrict__ yq, long long y_stride, int KS, int V,
+                                         int n_heads, const frag_t* __restrict__ yq, long long y_stride, int KS, int V, bool wide,
                                          int n_live, int row0, int part, int R_pad, Stats* __restrict__ partials, float* __restrict__ second_out, long long part_stride,
                                          EH_KS_LDS char* lds, int wave, int lane) {
   const int row_hi = min(V, sl.t1 * 16);
@@ -42,7 +42,7 @@ __device__ __forceinline__ void ks_heads(const KsSlice& sl, const frag_t* const*
       ks_pass<DT, MT, NB>(a, b, W + p * pass_len, last ? Wn : W + (p + 1) * pass_len, y, KS, wave, lane, voff,
                           tiles_of(last ? 0 : p + 1), acc, []() {},
                           [&]() { return last && l + 1 < n_heads ? y + y_stride : y; });
-      ks_finish<MT, NB, AO, TOP2>(acc, lds, wave, lane, (sl.t0 + 2 * MT * p) * 16, row_hi, bias ? bias[l] : nullptr, st, second);
+      ks_finish<MT, NB, AO, TOP2>(acc, lds, wave, lane, (sl.t0 + 2 * MT * p) * 16, row_hi, bias ? bias[l] : nullptr, st, second, wide);
     }
     const Stats s = ks_merge<NB, TOP2>(st, second, z2, lds, wave, lane);
     const int t = row0 + threadIdx.x;
@@ -63,7 +63,7 @@ __device__ __forceinline__ void ks_heads(const KsSlice& sl, const frag_t* const*
 template <typename DT, bool AO, bool TOP2>
 __global__ __launch_bounds__(kKsThreads, 1) void ksplit_kernel(
     const frag_t* const* __restrict__ Wf, const float* const* __restrict__ bias, int n_heads, const frag_t* __restrict__ yq,
-    long long y_stride, int VT16, int KS, int V, const int* __restrict__ n_rows_dev, int n_rows, int max_parts, int R_pad,
+    long long y_stride, int VT16, int KS, int V, int wide, const int* __restrict__ n_rows_dev, int n_rows, int max_parts, int R_pad,
     Stats* __restrict__ partials, float* __restrict__ second, long long part_stride) {
   extern __shared__ __attribute__((aligned(16))) char ks_smem[];
   EH_KS_LDS char* lds = (EH_KS_LDS char*)ks_smem;
@@ -79,8 +79,8 @@ __global__ __launch_bounds__(kKsThreads, 1) void ksplit_kernel(
   yq += (long long)group * (kKsGroup / 32) * 2 * KS * kWave;
 #define EH_KS_CASE(MT_)                                                                                                    \
   case MT_:                                                                                                                \
-    if (mine <= 32) ks_heads<DT, MT_, 1, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, n_live, row0, part, R_pad, partials, second, part_stride, lds, wave, lane); \
-    else ks_heads<DT, MT_, 2, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, n_live, row0, part, R_pad, partials, second, part_stride, lds, wave, lane);           \
+    if (mine <= 32) ks_heads<DT, MT_, 1, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, wide != 0, n_live, row0, part, R_pad, partials, second, part_stride, lds, wave, lane); \
+    else ks_heads<DT, MT_, 2, AO, TOP2>(sl, Wf, bias, n_heads, yq, y_stride, KS, V, wide != 0, n_live, row0, part, R_pad, partials, second, part_stride, lds, wave, lane);           \
     break
   switch (sl.mt) {
     EH_KS_CASE(7);
@@ -97,10 +97,10 @@ __global__ __launch_bounds__(kKsThreads, 1) void ksplit_kernel(
 
 template <typename DT, bool AO, bool TOP2>
 hipError_t launch_ksplit(dim3 g, hipStream_t s, const frag_t* const* Wf, const float* const* bias, int n_heads, const frag_t* yq,
-                         long long y_stride, int VT16, int KS, int V, const int* n_rows_dev, int n_rows, int max_parts, int R_pad,
+                         long long y_stride, int VT16, int KS, int V, int wide, const int* n_rows_dev, int n_rows, int max_parts, int R_pad,
                          Stats* partials, float* second, long long part_stride) {
   hipLaunchKernelGGL((ksplit_kernel<DT, AO, TOP2>), g, dim3(kKsThreads), ks_lds_bytes(), s, Wf, bias, n_heads, yq, y_stride, VT16, KS,
-                     V, n_rows_dev, n_rows, max_parts, R_pad, partials, second, part_stride);
+                     V, wide, n_rows_dev, n_rows, max_parts, R_pad, partials, second, part_stride);
   return hipGetLastError();
 }
 
@@ -135,7 +135,7 @@ hipError_t ksplit_launch(const eh_ctx* c, int head, int n_heads, const int* n_ro
   const float* const* bias = c->d_bias ? (const float* const*)(c->d_bias + head) : nullptr;
   const dim3 g(grid);
 #define EH_KS_GO(DT, AO_, T2_)                                                                                               \
-  return launch_ksplit<DT, AO_, T2_>(g, s, W, bias, n_heads, yf, y_stride, c->VT, c->KS, c->V, n_rows_dev, n_rows, max_parts, R_pad, \
+  return launch_ksplit<DT, AO_, T2_>(g, s, W, bias, n_heads, yf, y_stride, c->VT, c->KS, c->V, c->wide, n_rows_dev, n_rows, max_parts, R_pad, \
                                      partials, second, part_stride)
   if (second) {
     if (argmax_only || c->dtype != EH_BF16) return hipErrorInvalidValue;

@@ -251,14 +251,14 @@ __device__ __forceinline__ void ks_pass(frag_t (&a)[2][MT][2], frag_t (&b)[2][2]
 // The logits of a pass summed over the four waves and folded into running statistics.  Wave g ends
 // up with accumulator registers 4g..4g+3 of every tile, i.e. vocabulary rows row_base + 32m + 8g +
 // 4*(lane/32) + i of token lane%32.  bias: NULL or [rows padded to 16].  TOP2: second[nb] is the
-// largest logit besides st[nb].zb so far (with multiplicity).  n_cols: columns that anybody reads; a second block
+// largest logit besides st[nb].zb so far (with multiplicity).  wide: a logit may be -infinity.  n_cols: columns that anybody reads; a second block
 // beyond them is left out.  (Between two heads of a persistent cascade of 64 rows this takes 8 us, more than the loads in
 // flight last.  16 heads, us, without the second block where nobody reads it: 33 rows of d = 2048 598 -> 581, 40 of d = 1024
 // 401 -> 392, 64 of d = 2560 731 -> 725.)
 template <int MT, int NB, bool ARGMAX_ONLY, bool TOP2>
 __device__ __forceinline__ void ks_finish(const f32x16 (&acc)[MT][NB], EH_KS_LDS char* lds, int wave, int lane,
                                           int row_base, int row_hi, const float* __restrict__ bias, Stats (&st)[NB],
-                                          float (&second)[NB], int n_cols = 32 * NB) {
+                                          float (&second)[NB], bool wide, int n_cols = 32 * NB) {
   EH_KS_LDS f32x4* red = (EH_KS_LDS f32x4*)lds;
   const int r0 = row_base + 8 * wave + 4 * (lane >> 5);
   const bool ragged = row_base + 32 * MT > row_hi;  // wave-uniform: only the slice's last pass can be
@@ -332,7 +332,7 @@ __device__ __forceinline__ void ks_finish(const f32x16 (&acc)[MT][NB], EH_KS_LDS
         for (int m = 0; m < MT; ++m)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            // a row beyond the slice (z = -inf, only where `ragged`) contributes 0 * (finite)
+            // a row beyond the slice, or a masked word (z = -inf), contributes 0 * (finite)
             const float t = masked && z[m][i] == -INFINITY ? -1.0e9f : z[m][i] * kLog2e - s.m;
             const float e = fast_exp2(t);
             S4[i] += e;
@@ -341,7 +341,7 @@ __device__ __forceinline__ void ks_finish(const f32x16 (&acc)[MT][NB], EH_KS_LDS
       };
       // without the test where nothing is masked: 16 heads of d = 1024 on 64 rows 419 -> 405 us (with one block of
       // rows the second copy costs more than it saves: 8 heads of d = 2048 on 32 rows 263 -> 266)
-      if (NB > 1 && !ragged) add(false);
+      if (NB > 1 && !ragged && !wide) add(false);
       else add(true);
       s.S += (S4[0] + S4[1]) + (S4[2] + S4[3]);
       s.U += (U4[0] + U4[1]) + (U4[2] + U4[3]);

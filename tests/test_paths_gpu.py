@@ -442,3 +442,31 @@ def test_bias_vectors_that_mask_words(B, dtype, d, V, rows, mask):
     ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=rows, bias=bs)
     P.compare_head("masked", *_eval(B, ctx, 0, hid.h[0], rows), orc, [])
     B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype,d,V,rows", [
+    ("bf16", 136, 9001, 9), ("bf16", 136, 9001, 33), ("bf16", 136, 9001, 64), ("bf16", 136, 50257, 64), ("bf16", 136, 9001, 65),
+    ("bf16", 136, 20011, 160), ("f32", 136, 9001, 40), ("f32", 256, 9001, 40)])
+@pytest.mark.parametrize("top,rest", [(1.6e7, 0.0), (1e9, 0.0), (1e14, 0.0), (1e30, 0.0), (3.4028234663852886e38, 0.0), (-1e30, -2e30)])
+def test_bias_vectors_that_force_a_word(B, dtype, d, V, rows, top, rest):
+    """A bias far above all others forces a word, however far: the argmax, a verification's targets and a cascade's
+    tokens.  Up to 10^9 the entropy (0) and the log-sum-exp as well; beyond, a product z log2 e is rounded by more than an
+    exponent holds."""
+    w, heads, hid, bs = _bias_heads(d, V, 2, rows, dtype, V + rows)
+    word = V // 3
+    for b in bs:
+        b += rest
+        b[word] = top
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0, 0.0], max_rows=rows, bias=bs)
+    for l in range(2):
+        H, lse, am = _eval(B, ctx, l, hid.h[l], rows)
+        assert bool((am == word).all())
+        if abs(top) <= 1e9:
+            assert float(H.abs().max()) <= P.TOL_H and float((lse / top - 1.0).abs().max()) <= P.TOL_LSE_REL
+    ex, tok, H = _ints(rows), _ints(rows), torch.zeros((2, rows), device=DEV)
+    B.eh_cascade(ctx, hid.h, rows, ex, tok, H, None)
+    assert bool((tok == word).all())
+    acc, nxt, tgt = _ints(1), _ints(1), _ints(1, rows)
+    B.dssd_verify(ctx, hid.h[1].reshape(1, rows, w.d).contiguous(), torch.full((1, rows - 1), word, dtype=torch.int32, device=DEV), None, acc, nxt, tgt)
+    assert bool((tgt == word).all()) and (int(acc), int(nxt)) == (rows - 1, word)
+    B.eh_destroy(ctx)
