@@ -119,11 +119,12 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // against 17.3 / 23.4 / 32.4, V = 16384 15.5 / 17.2 / 23.2 against 15.6 / 17.6 / 24.9; 12 heads in one call,
 // V = 50304 155 / 236 / 419 against 130 / 221 / 404, V = 49152 131 / 212 / 386 against 127 / 214 / 395, V = 32000
 // 96 / 151 / 270 against 100 / 159 / 284, V = 16384 63 / 94 / 164 against 69 / 113 / 204.
-// Contexts of `wide` values (eh_internal.hpp) with a bias vector go there at any number of rows: its statistics test every logit.
+// Contexts of `wide` values (eh_internal.hpp) with a bias vector go there at any number of rows: its statistics test every
+// logit.  fp32 ones take its form on fp32 matrix instructions, and gemm_launch's kernel beyond 32 rows without one.
 constexpr int kF32Split = 256;
 bool use_ksplit(const eh_ctx* c, int n_rows) {
   if (n_rows <= 32 || (c->wide && !c->bias.empty())) return true;
-  if (c->dtype == EH_F32) return !c->bias.empty() || c->d >= kF32Split;
+  if (c->dtype == EH_F32) return !c->bias.empty() || (c->d >= kF32Split && !c->wide);
   return n_rows <= 64 && ksplit_pass_tiles(c) < 7;
 }
 // Rows per block of the activations' operand order: 16 for gemm_launch's kernel, 32 for all others.
@@ -242,7 +243,7 @@ RowsParams rows_base(eh_ctx* c, int n_rows) {
   RowsParams p{};
   p.Wf = c->d_Wf; p.gamma = c->d_gamma; p.beta = c->d_beta; p.tau = c->d_tau;
   p.n_rows = n_rows; p.n_heads = c->n_heads;
-  p.V = c->V; p.d = c->d; p.KS = c->KS; p.VT16 = c->VT; p.eps = c->eps;
+  p.V = c->V; p.d = c->d; p.KS = c->KS; p.VT16 = c->VT; p.eps = c->eps; p.wide = c->wide;
   p.n_stream = c->rows_grid - rows_service_workgroups(n_rows, (long long)c->V * c->d);
   p.spin_limit = c->spin_limit;
   p.ctl = c->rows_ctl; p.y = c->rows_y; p.y_stride = c->rows_y_stride;
@@ -334,15 +335,17 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
     const unsigned blocks = (unsigned)((wf_frags + 255) / 256);
     if (c->dtype == EH_BF16)
       hipLaunchKernelGGL((repack_w_kernel<DtBf16>), dim3(blocks), dim3(256), 0, 0, cfg->W[l], c->V,
-                         c->d, c->VT, c->KS, c->Wf[l]);
+                         c->d, c->VT, c->KS, c->Wf[l], wide);
     else
       hipLaunchKernelGGL((repack_w_kernel<DtF32>), dim3(blocks), dim3(256), 0, 0, cfg->W[l], c->V,
-                         c->d, c->VT, c->KS, c->Wf[l]);
+                         c->d, c->VT, c->KS, c->Wf[l], wide);
     if ((e = hipGetLastError()) != hipSuccess) return bail(e, "repack launch");
     if ((e = hipMemcpy(c->gamma[l], cfg->gamma[l], sizeof(float) * c->d, hipMemcpyDeviceToDevice)) != hipSuccess)
       return bail(e, "copy gamma");
     if ((e = hipMemcpy(c->beta[l], cfg->beta[l], sizeof(float) * c->d, hipMemcpyDeviceToDevice)) != hipSuccess)
       return bail(e, "copy beta");
+    hipLaunchKernelGGL(check_wide_kernel, dim3(1), dim3(256), 0, 0, c->gamma[l], c->beta[l], c->d, wide);
+    if ((e = hipGetLastError()) != hipSuccess) return bail(e, "check launch");
     if (cfg->bias) {
       if ((e = dev_alloc(c, &c->bias[l], (size_t)Vp)) != hipSuccess) return bail(e, "hipMalloc(bias)");
       if ((e = hipMemset(c->bias[l], 0, sizeof(float) * Vp)) != hipSuccess) return bail(e, "memset bias");

@@ -21,8 +21,8 @@ struct eh_ctx {
   float eps = 1e-5f;
   int KS = 0, VT = 0, R_pad_max = 0;
   int num_cu = 0;
-  // a bias vector's largest entry is not finite or above 2^24 in magnitude: logits may be infinite, or rounded at
-  // the size of their products, and the kernels that take neither are not used
+  // a bias vector's largest entry is not finite or above 2^24 in magnitude, or a weight, gamma or beta is not finite or above
+  // 2^30: logits may be infinite, or rounded at the size of their products, and the kernels that take neither are not used
   bool wide = false;
   std::vector<eh::frag_t*> Wf;  // per head, fragment-major weights
   std::vector<float*> gamma, beta, bias;
@@ -121,6 +121,7 @@ struct RowsParams {
   int n_rows, n_heads, l0, l1, mode, argmax_only;
   int V, d, KS, VT16;
   float eps;
+  bool wide;                    // of the context
   int n_stream;                 // workgroups that stream weights; the rest of the grid serves
   int spin_limit;
   int* ctl;                     // control block, all zero at launch

@@ -38,11 +38,17 @@ static __global__ __launch_bounds__(kBiasThreads) void copy_bias_kernel(const fl
 
 // ---------------------------------------------------------------------------
 // Row-major W [V, d] -> fragment-major copy (done once, at context creation).
-// One thread per 16-byte chunk of the destination.
+// One thread per 16-byte chunk of the destination.  *wide is set if a value is not within 2^30.
 // ---------------------------------------------------------------------------
+constexpr uint32_t kWideBits = 0x4e800000u;  // 2^30
+__device__ __forceinline__ bool f32_is_wide(uint32_t bits) { return (bits & 0x7fffffffu) > kWideBits; }
+static __global__ void check_wide_kernel(const float* __restrict__ x, const float* __restrict__ y, int n, int* __restrict__ wide) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    if (f32_is_wide(__float_as_uint(x[i])) || f32_is_wide(__float_as_uint(y[i]))) *wide = 1;
+}
 template <typename DT>
 __global__ __launch_bounds__(256) void repack_w_kernel(const void* __restrict__ W, int V, int d,
-                                                       int VT, int KS, frag_t* __restrict__ Wf) {
+                                                       int VT, int KS, frag_t* __restrict__ Wf, int* __restrict__ wide) {
   const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t total = (int64_t)VT * KS * kWave;
   if (o >= total) return;
@@ -57,6 +63,10 @@ __global__ __launch_bounds__(256) void repack_w_kernel(const void* __restrict__ 
   if (row < V && k0 < d) {
     const char* src = (const char*)W + ((int64_t)row * d + k0) * DT::ESZ;
     v = *(const frag_t*)src;  // d % EPL == 0 and a 16-byte aligned base are checked by the host
+    bool out = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out |= f32_is_wide(v[i]) || (DT::EPL == 8 && f32_is_wide(v[i] << 16));
+    if (out) *wide = 1;
   }
   Wf[o] = v;
 }

@@ -109,7 +109,8 @@ hipError_t launch_ksplit(dim3 g, hipStream_t s, const frag_t* const* Wf, const f
 hipError_t ksplit_prepare() {
   for (const void* fn : {(const void*)ksplit_kernel<DtBf16, false, true>, (const void*)ksplit_kernel<DtBf16, true, false>,
                          (const void*)ksplit_kernel<DtBf16, false, false>, (const void*)ksplit_kernel<DtF32, true, false>,
-                         (const void*)ksplit_kernel<DtF32, false, false>}) {
+                         (const void*)ksplit_kernel<DtF32, false, false>, (const void*)ksplit_kernel<DtF32Whole, true, false>,
+                         (const void*)ksplit_kernel<DtF32Whole, false, false>}) {
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_lds_bytes());
     if (e != hipSuccess) return e;
   }
@@ -144,6 +145,10 @@ hipError_t ksplit_launch(const eh_ctx* c, int head, int n_heads, const int* n_ro
   if (c->dtype == EH_BF16) {
     if (argmax_only) EH_KS_GO(DtBf16, true, false);
     EH_KS_GO(DtBf16, false, false);
+  }
+  if (c->wide) {
+    if (argmax_only) EH_KS_GO(DtF32Whole, true, false);
+    EH_KS_GO(DtF32Whole, false, false);
   }
   if (argmax_only) EH_KS_GO(DtF32, true, false);
   EH_KS_GO(DtF32, false, false);

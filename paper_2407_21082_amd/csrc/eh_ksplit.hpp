@@ -68,19 +68,28 @@ __device__ __forceinline__ KsSplit ks_split(const frag_t& x0, const frag_t& x1) 
   return s;
 }
 
+// fp32 on fp32 matrix instructions, for contexts of `wide` values: infinity does not split into parts.
+struct DtF32Whole {};
+__device__ __forceinline__ f32x16 ks_mma_f32(const frag_t& a, const frag_t& b, f32x16 c) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i]), __uint_as_float(b[i]), c, 0, 0, 0);
+  return c;
+}
+
 // One k-step of all tiles and blocks.  fp32 products as six of bf16 parts, the smallest first (hi*lo, mid*mid, hi*mid,
 // hi*hi; what is left out, mid*lo and lo*lo, is below 2^-23 of a product and of either sign): 192 clocks of the
 // matrix core for a 32 x 32 x 16 tile instead of 512.  Cascade of 6 heads, us, 512 / 192: 32 rows of d = 512 204 / 190, 24 of
 // d = 1024 293 / 275; one head on 128 rows of d = 1024 with a bias vector 135 / 92.
 template <typename DT, int MT, int NB>
 __device__ __forceinline__ void ks_step(const frag_t (&a)[MT][2], const frag_t (&b)[2][2], f32x16 (&acc)[MT][NB]) {
-  if constexpr (std::is_same<DT, DtBf16>::value) {
+  if constexpr (!std::is_same<DT, DtF32>::value) {
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[m][nb] = ks_mma(a[m][h], b[nb][h], acc[m][nb]);
+        for (int nb = 0; nb < NB; ++nb)
+          acc[m][nb] = std::is_same<DT, DtBf16>::value ? ks_mma(a[m][h], b[nb][h], acc[m][nb]) : ks_mma_f32(a[m][h], b[nb][h], acc[m][nb]);
   } else {
     KsSplit y[NB];
 #pragma unroll

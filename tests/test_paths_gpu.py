@@ -470,3 +470,60 @@ def test_bias_vectors_that_force_a_word(B, dtype, d, V, rows, top, rest):
     B.dssd_verify(ctx, hid.h[1].reshape(1, rows, w.d).contiguous(), torch.full((1, rows - 1), word, dtype=torch.int32, device=DEV), None, acc, nxt, tgt)
     assert bool((tgt == word).all()) and (int(acc), int(nxt)) == (rows - 1, word)
     B.eh_destroy(ctx)
+
+
+def _heads_with_a_switch(d, V, n_heads, rows, dtype, seed):
+    """Heads whose LayerNorm output is 1 at the last place in every row, where all words have weight 0."""
+    w = G.Workload("switch", d=d, V=V, n_heads=n_heads, rows=rows, dtype=dtype, seed=seed, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    for W, g, b in zip(heads.W, heads.gamma, heads.beta):
+        W[:, -1] = 0.0
+        g[-1] = 0.0
+        b[-1] = 1.0
+    return heads, hid
+
+
+@pytest.mark.parametrize("dtype,d,V,rows,bias", [
+    ("bf16", 256, 9001, 20, False), ("bf16", 256, 9001, 33, False), ("bf16", 256, 9001, 64, False), ("bf16", 256, 9001, 64, True),
+    ("bf16", 256, 9001, 65, True), ("bf16", 256, 20011, 160, True), ("f32", 128, 9001, 20, False), ("f32", 256, 9001, 32, False),
+    ("f32", 256, 9001, 40, True), ("f32", 128, 9001, 130, True)])
+def test_weights_of_infinity_that_mask_words(B, dtype, d, V, rows, bias):
+    """A weight of -infinity on a place of the LayerNorm output that is 1 in every row takes its word out: the
+    statistics are those of the words that are left, also where whole tiles are masked; in a cascade as well.  (d such that
+    the four waves of the k-split kernel have an even number of k-steps each: none runs one on activations of 0.)"""
+    heads, hid = _heads_with_a_switch(d, V, 2, rows, dtype, V + rows)
+    gen = torch.Generator(device=DEV).manual_seed(rows)
+    bs = [0.3 * torch.randn(V, generator=gen, device=DEV) for _ in range(2)] if bias else None
+    out = torch.zeros(V, dtype=torch.bool, device=DEV)
+    out[::3] = True
+    out[256:1024] = True
+    out[-40:] = True
+    low = torch.where(out, -1e6, 0.0)  # a probability of 0 in 64 bits as well
+    orc = [_oracle(hid.h[l], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), low + bs[l] if bias else low, dtype == "bf16") for l in range(2)]
+    for W in heads.W:
+        W[out, -1] = -np.inf
+    tau = [float(np.median(orc[0][0])), float("inf")]
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows, bias=bs)
+    for l in range(2):
+        P.compare_head(f"switch{l}", *_eval(B, ctx, l, hid.h[l], rows), orc[l], [])
+    ex, tok, H = _ints(rows), _ints(rows), torch.zeros((2, rows), device=DEV)
+    B.eh_cascade(ctx, hid.h, rows, ex, tok, H, None)
+    torch.cuda.synchronize()
+    full = [np.stack([o[i] for o in orc]) for i in range(4)]
+    P.compare_cascade("switch", ex, tok, H, full[0], full[2], full[3], tau, [])
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("d,rows,bias", [(128, 20, False), (256, 32, False), (256, 40, False), (128, 40, True), (256, 130, True)])
+def test_fp32_weights_of_infinity_that_force_a_word(B, d, rows, bias):
+    """A weight of infinity does not split into bf16 parts: its word has the largest logit all the same."""
+    heads, hid = _heads_with_a_switch(d, 9001, 1, rows, "f32", rows)
+    heads.W[0][4321, -1] = np.inf
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=rows, bias=[torch.zeros(9001, device=DEV)] if bias else None)
+    H, lse, am = _eval(B, ctx, 0, hid.h[0], rows)
+    assert bool((am == 4321).all())
+    acc, nxt, tgt = _ints(1), _ints(1), _ints(1, rows)
+    B.dssd_verify(ctx, hid.h[0].reshape(1, rows, d).contiguous(), torch.full((1, rows - 1), 4321, dtype=torch.int32, device=DEV), None, acc, nxt, tgt)
+    assert bool((tgt == 4321).all()) and (int(acc), int(nxt)) == (rows - 1, 4321)
+    B.eh_destroy(ctx)
