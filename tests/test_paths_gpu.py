@@ -527,3 +527,47 @@ def test_fp32_weights_of_infinity_that_force_a_word(B, d, rows, bias):
     B.dssd_verify(ctx, hid.h[0].reshape(1, rows, d).contiguous(), torch.full((1, rows - 1), 4321, dtype=torch.int32, device=DEV), None, acc, nxt, tgt)
     assert bool((tgt == 4321).all()) and (int(acc), int(nxt)) == (rows - 1, 4321)
     B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("R,counts", [(192, (129, 150, 170, 192)), (400, (288, 300, 340, 384))])
+def test_rows_do_not_depend_on_their_place_in_the_list(B, R, counts):
+    """A live count on the device comes with a list of rows whose order is that of their arrival: the bits of a row are
+    the same at every place, with five or six blocks of 32 in a group and several tiles a slice, too."""
+    w = G.Workload("place", d=160, V=40001, n_heads=1, rows=R, dtype="bf16", seed=R)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=R)
+    gen = torch.Generator().manual_seed(R)
+    for n in counts:
+        live = torch.tensor([n], dtype=torch.int32, device=DEV)
+        one = _eval(B, ctx, 0, hid.h[0], R, n_rows_dev=live)
+        for _ in range(2):
+            p = torch.randperm(n, generator=gen)
+            other = _eval(B, ctx, 0, hid.h[0], R, row_idx=torch.cat([p, torch.arange(n, R)]).to(torch.int32).to(DEV), n_rows_dev=live)
+            for a, b in zip(other, one):
+                assert torch.equal(a[:n], b[:n][p.to(DEV)])
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("rows", [192, 230, 400])
+def test_cascades_of_two_launches_repeat_to_the_bit(B, rows):
+    """V and the live counts are such that groups of five and six blocks of rows with several tiles a slice come up."""
+    n = 8
+    w = G.Workload("again", d=160, V=40001, n_heads=n, rows=rows, dtype="bf16", seed=rows, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    full = P.oracle_all_heads(heads, hid.h, True, rows=slice(0, 32))
+    tau = G.tau_for_schedule(full[0], n)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows)
+    first = None
+    for _ in range(8):
+        ex, tok, H = _ints(rows), _ints(rows), torch.zeros((n, rows), device=DEV)
+        B.eh_cascade(ctx, hid.h, rows, ex, tok, H, None)
+        torch.cuda.synchronize()
+        got = [ex, tok, H.view(torch.int32)]
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(got, first))
+    live = [int((ex >= l).sum()) for l in range(1, n)]
+    assert any(128 < x <= 192 or 256 < x <= 384 for x in live), live
+    P.compare_cascade("again", ex[:32], tok[:32], H[:, :32], full[0], full[2], full[3], tau, [])
+    B.eh_destroy(ctx)
