@@ -99,9 +99,9 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // The k-split kernel: up to 32 rows; fp32 heads with a bias vector or of d = 256 and more at any number of rows, bf16 heads
 // up to its 64 unless a pass has seven tiles.  (bf16 heads with a bias vector went there at any number of rows before the
-// batched kernel took one, us, V = 50257, there / here: d = 768, 48 rows 30.3 / 25.9, 100 rows 41.3 / 27.1, 200 rows 65.2 / 33.0;
-// d = 1024, 300 rows 117 / 50, 512 rows 121 / 61.  Relative error against 64 bits, d = 768, 48 rows: 1.1e-7 / 2.4e-7, one chain of
-// fp32 sums over k instead of four: that of heads without one.)
+// batched kernel took one, us, V = 50257, there / here: d = 768, 48 rows 30.3 / 27.3, 100 rows 41.4 / 28.3, 200 rows 65.1 / 37.1;
+// d = 1024, 300 rows 117 / 59, 512 rows 121 / 70.  Relative error of the entropies against 64 bits, mean of 12 sets: d = 768, 48 rows
+// 9.5e-8 / 9.5e-8, d = 2048, 200 rows 1.10e-7 / 1.14e-7.)
 // fp32 beyond 32 rows goes where its products cost least: this kernel makes them of bf16 parts (ks_step), gemm_launch's
 // of fp32 matrix instructions, but with less to do at the end of a pass, of which a narrow head has many.  One
 // head of V = 50304, us, this kernel against that, 64 / 300 / 1000 rows: d = 64 22.5 / 60 / 141 against 16.9 / 46 / 114,

@@ -508,8 +508,8 @@ __global__ __launch_bounds__(kFinThreads) void finalize_kernel(const Stats* __re
 }
 
 // Final merge with the other two confidence metrics of Section 3.4.1:
-//   max_prob = p(argmax) = 1 / S        (S sums 2^(t - m) with m the largest t: its own term is 1)
-//   margin   = p1 - p2 = (1 - e^(z2 - z1)) / S.
+//   max_prob = p1 = 2^(z1 log2 e - m) / S   (S sums such terms; m is the rounded product, so this one is not quite 1)
+//   margin   = p1 - p2 = p1 (1 - e^(z2 - z1)).
 template <int FR>
 __global__ __launch_bounds__(kFinThreads) void finalize_metrics_kernel(
     const Stats* __restrict__ partials, const float* __restrict__ second, int n_parts, int R_pad, int n_rows,
@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kFinThreads) void finalize_metrics_kernel(
     if (H) H[o] = h;
     if (lse) lse[o] = l;
     if (argmax) argmax[o] = stats_token(s);
-    const float p1 = 1.0f / s.S;  // NaN statistics give NaN metrics
+    const float p1 = fast_exp2(fmaf(s.zb, kLog2e, -s.m)) / s.S;  // NaN statistics give NaN metrics
     if (max_prob) max_prob[o] = p1;
     if (margin) margin[o] = p1 * (1.0f - fast_exp2((z2 - s.zb) * kLog2e));
   }

@@ -424,6 +424,40 @@ def test_batched_kernel_with_a_bias_vector(B, V, rows):
 
 
 @pytest.mark.parametrize("dtype,d,V,rows", [
+    ("bf16", 1536, 9001, 9), ("bf16", 1536, 9001, 20), ("bf16", 1536, 9001, 64), ("bf16", 1536, 9001, 65), ("bf16", 1536, 50257, 64),
+    ("bf16", 1536, 20011, 300), ("f32", 1024, 9001, 40), ("f32", 1024, 9001, 130)])
+def test_bias_vectors_with_an_offset(B, dtype, d, V, rows):
+    """A bias vector may have any common offset: it is added to finished sums.  At 10^4 a logit is then rounded to 2^-11,
+    once, and the entropy follows with the mean of |log p + H|, of size 1 (H + 2^-11 and 2^-10); a sum that starts from the bias
+    is rounded d / 16 times."""
+    w, heads, hid, bs = _bias_heads(d, V, 1, rows, dtype, V + rows, kappa=0.2)
+    bs[0] += 1e4
+    orc = _oracle(hid.h[0], heads.gamma[0], heads.beta[0], P.f64(heads.W[0]), bs[0], dtype == "bf16")
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=rows, bias=bs)
+    H, lse, am = _eval(B, ctx, 0, hid.h[0], rows)
+    B.eh_destroy(ctx)
+    print("entropies off by", float((H.double().cpu() - torch.from_numpy(orc[0])).abs().max()))
+    P.compare_head("offset", H, lse, am, orc, [])
+
+
+@pytest.mark.parametrize("d", [512, 776, 2048])
+def test_bias_heads_keep_their_precision_beyond_the_few_rows(B, d):
+    """The sums of a head with a bias vector are made of quarters of k on both sides of the line between the kernels: the rows 32
+    at a time (the k-split kernel) and all at once (the batched one) are equally far from 64 bits.  (Norms of 320 errors, by
+    chance within 1.25 of each other; one chain over k has log-sum-exps more than twice as far.)"""
+    rows = 320
+    w, heads, hid, bs = _bias_heads(d, 20011, 1, rows, "bf16", d, kappa=1.0)
+    orc = _oracle(hid.h[0], heads.gamma[0], heads.beta[0], P.f64(heads.W[0]), bs[0], True)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=rows, bias=bs)
+    few = [_eval(B, ctx, 0, hid.h[0][i:i + 32].contiguous(), 32) for i in range(0, rows, 32)]
+    off = [[float(np.linalg.norm(x.double().cpu().numpy() - o)) for x, o in zip(got, orc)] for got in
+           ([torch.cat([f[i] for f in few]) for i in range(2)], _eval(B, ctx, 0, hid.h[0], rows)[:2])]
+    print("errors of entropies and log-sum-exps, 32 rows at a time and all at once:", off)
+    assert off[1][0] <= 1.5 * off[0][0] and off[1][1] <= 1.5 * off[0][1]
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype,d,V,rows", [
     ("bf16", 136, 9001, 9), ("bf16", 136, 9001, 33), ("bf16", 136, 9001, 64), ("bf16", 136, 50257, 64), ("bf16", 136, 9001, 65),
     ("bf16", 136, 20011, 160), ("f32", 136, 9001, 40), ("f32", 256, 9001, 40), ("f32", 256, 9001, 70)])
 @pytest.mark.parametrize("mask", [-np.inf, -3.4028234663852886e38, -1e30])
