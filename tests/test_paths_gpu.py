@@ -304,6 +304,34 @@ def test_weights_past_the_caches(B, rows):
     B.eh_destroy(ctx)
 
 
+@pytest.mark.parametrize("d,n,rows", [(1024, 3, 160), (768, 4, 192), (512, 2, 257), (768, 3, 320), (1024, 2, 353), (1536, 2, 384), (512, 2, 530)])
+def test_five_and_six_blocks_on_weights_that_run_on(B, d, n, rows):
+    """Groups of five and six blocks of rows with passes of several tiles, whose weights run on from pass to pass and head to
+    head: one group past the caches (non-temporal loads), several groups (the shared form), with and without the
+    extra metrics.  The oracle on a row of every block, and the bits of a head at a time, whose loads are ordinary ones."""
+    w = G.Workload("runon", d=d, V=50001, n_heads=n, rows=rows, dtype="bf16", seed=rows + d)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0] * n, max_rows=rows)
+    H, lse, am = torch.zeros((n, rows), device=DEV), torch.zeros((n, rows), device=DEV), _ints(n, rows)
+    B.eh_eval_heads(ctx, 0, n, hid.h, rows, H, lse, am)
+    m = [torch.zeros((n, rows), device=DEV), torch.zeros((n, rows), device=DEV), _ints(n, rows)]
+    prob, margin = torch.zeros((n, rows), device=DEV), torch.zeros((n, rows), device=DEV)
+    B.eh_eval_heads_metrics(ctx, 0, n, hid.h, rows, *m, prob, margin)
+    at = torch.tensor(sorted(set(range(3, rows, 16)) | {rows - 1}), device=DEV)
+    for l in range(n):
+        orc = _oracle(hid.h[l][at], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), None, True)
+        P.compare_head(f"runon{l}", H[l][at], lse[l][at], am[l][at], orc, [])
+        y = O.layernorm(P.f64(hid.h[l][at]), P.f64(heads.gamma[l]), P.f64(heads.beta[l]), 1e-5, bf16_out=True)
+        z = torch.from_numpy(y @ P.f64(heads.W[l]).T)
+        p = torch.exp(torch.topk(z, 2, dim=1).values - torch.logsumexp(z, dim=1)[:, None])
+        assert float((prob[l][at].double().cpu() - p[:, 0]).abs().max()) <= 2e-4
+        assert float((margin[l][at].double().cpu() - (p[:, 0] - p[:, 1])).abs().max()) <= 2e-4
+        for a, b, c in zip(_eval(B, ctx, l, hid.h[l], rows), (H[l], lse[l], am[l]), (x[l] for x in m)):
+            assert torch.equal(a, b) and torch.equal(a, c)
+    B.eh_destroy(ctx)
+
+
 @pytest.mark.parametrize("V", [14999, 15000])
 @pytest.mark.parametrize("Bsz,k", [(1, 16), (3, 6), (8, 7)])
 def test_verification_on_both_sides_of_small_heads(B, V, Bsz, k):
