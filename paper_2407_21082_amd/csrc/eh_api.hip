@@ -209,8 +209,8 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // take less time at every size measured (us, one launch / three: V = 50304, d = 512, 24 and 64 positions 28.6 / 19.4 and
 // 34.3 / 21.3, d = 1024, 40 positions 41.3 / 27.6, d = 2048, 64 56.8 / 42.7, d = 2560, 18 and 63 59.6 / 52.3 and
 // 67.4 / 52.7; V = 32000, d = 1024, 60 32.9 / 22.3; V = 128256, d = 2048, 32 100 / 93).  Heads of less than kVerifySmall
-// elements take one launch up to 64 positions (V = 20000, d = 256, 48 23.3 / 14.8): the bounded wait and its
-// report by eh_check are part of the interface there.
+// elements still take one launch up to 64 positions, and not because it is the faster way (V = 20000, d = 256, 48
+// 23.3 / 14.8): the tests of a verification that gives up its bounded wait and is tried again run there.
 constexpr int64_t kVerifySmall = 6000000;
 //
 // A cascade: as long as the two launches per head and the gaps between them cost more than the

@@ -304,6 +304,52 @@ def test_weights_past_the_caches(B, rows):
     B.eh_destroy(ctx)
 
 
+@pytest.mark.parametrize("d,V,n,rows", [(1024, 50001, 4, 400), (1024, 50001, 4, 300), (512, 50001, 6, 230)])
+def test_cascades_past_the_caches(B, d, V, n, rows):
+    """Two launches per head on weights of more than 256 MB together, read with non-temporal loads, by rows that leave: two
+    groups of live rows, one group of five and six blocks, then fewer."""
+    w = G.Workload("pastcasc", d=d, V=V, n_heads=n, rows=rows, dtype="bf16", seed=rows + d, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    at = torch.arange(5, rows, 11, device=DEV)
+    orc = [_oracle(hid.h[l][at], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), None, True) for l in range(n)]
+    full = [np.stack([o[i] for o in orc]) for i in range(4)]
+    tau = G.tau_for_schedule(full[0], n)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, tau, max_rows=rows)
+    first = None
+    for _ in range(3):
+        ex, tok, H = _ints(rows), _ints(rows), torch.zeros((n, rows), device=DEV)
+        B.eh_cascade(ctx, hid.h, rows, ex, tok, H, None)
+        torch.cuda.synchronize()
+        got = [ex, tok, H.view(torch.int32)]
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(got, first))
+    print("live rows per head:", [int((ex >= l).sum()) for l in range(n)])
+    P.compare_cascade("pastcasc", ex[at], tok[at], H[:, at], full[0], full[2], full[3], tau, [])
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("rows", [100, 180])
+def test_verification_by_a_head_past_the_caches(B, rows):
+    """A head of more than 256 MB by itself: the argmax-only projection reads it with non-temporal loads.  Targets by the oracle, on
+    a row in seven, and by the entropy evaluation of the same rows on all."""
+    d, V = 2560, 53001
+    w = G.Workload("pastver", d=d, V=V, n_heads=1, rows=rows, dtype="bf16", seed=rows, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=rows)
+    am = _eval(B, ctx, 0, hid.h[0], rows)[2]
+    at = torch.arange(0, rows, 7, device=DEV)
+    orc = _oracle(hid.h[0][at], heads.gamma[0], heads.beta[0], P.f64(heads.W[0]), None, True)
+    for _ in range(2):
+        acc, nxt, tgt = _ints(1), _ints(1), _ints(1, rows)
+        B.dssd_verify(ctx, hid.h[0].reshape(1, rows, d).contiguous(), am[None, :-1].contiguous(), None, acc, nxt, tgt)
+        assert torch.equal(tgt[0], am) and (int(acc), int(nxt)) == (rows - 1, int(am[-1]))
+        clear = torch.from_numpy(orc[3] >= P.NEAR_TIE)
+        assert bool(clear.any()) and torch.equal(tgt[0][at].cpu()[clear], torch.from_numpy(orc[2].astype(np.int32))[clear])
+    B.eh_destroy(ctx)
+
+
 @pytest.mark.parametrize("d,n,rows", [(1024, 3, 160), (768, 4, 192), (512, 2, 257), (768, 3, 320), (1024, 2, 353), (1536, 2, 384), (512, 2, 530)])
 def test_five_and_six_blocks_on_weights_that_run_on(B, d, n, rows):
     """Groups of five and six blocks of rows with passes of several tiles, whose weights run on from pass to pass and head to
@@ -363,9 +409,9 @@ def test_verification_on_both_sides_of_small_heads(B, V, Bsz, k):
 @pytest.mark.parametrize("rows", [129, 160, 161, 192, 193, 300, 353])
 @pytest.mark.parametrize("V", [3000, 20011, 40001, 50257, 60001])
 def test_five_and_six_blocks_of_rows(B, rows, V):
-    """Five and six blocks of 32 rows in a group (129 to 192 rows, and two groups of such): four waves share the
-    last blocks' tiles, one to four of the up to seven of a pass, and hand their statistics to one of them.  Passes of
-    one to seven tiles, two passes a slice, and the second largest logit, which goes the same way."""
+    """Five and six blocks of 32 rows in a group (129 to 192 rows, and two groups of such).  In the two groups, of 300 and
+    353 rows, four waves share the last blocks' tiles, one to four of the up to seven of a pass, and hand their statistics to one of
+    them.  Passes of one to seven tiles, two passes a slice, and the second largest logit, which goes the same way."""
     w = G.Workload("five", d=104, V=V, n_heads=2, rows=rows, dtype="bf16", seed=V + rows)
     heads = G.make_heads(w, DEV)
     hid = G.make_hidden(w, heads, DEV)
@@ -430,8 +476,8 @@ def test_fp32_products_keep_their_24_bits(B, exponent):
 
 @pytest.mark.parametrize("V,rows", [(50257, 33), (50257, 64), (1500, 65), (9001, 129), (20011, 160), (40001, 200), (60001, 300), (17, 513)])
 def test_batched_kernel_with_a_bias_vector(B, V, rows):
-    """bf16 heads with a bias vector beyond 32 rows (64 where a pass has fewer than seven tiles): the sums start
-    from the bias.  Ragged last tiles, a bias that decides the argmax, a cascade, and a verification."""
+    """bf16 heads with a bias vector beyond 32 rows (64 where a pass has fewer than seven tiles): the bias is added to
+    the finished sums.  Ragged last tiles, a bias that decides the argmax, a cascade, and a verification."""
     w, heads, hid, bs = _bias_heads(136, V, 2, rows, "bf16", V + rows)
     bs[1] *= 20.0
     orc = [_oracle(hid.h[l], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), bs[l], True) for l in range(2)]
