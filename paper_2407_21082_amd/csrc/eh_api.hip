@@ -102,6 +102,15 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // batched kernel took one, us, V = 50257, there / here: d = 768, 48 rows 30.3 / 27.3, 100 rows 41.4 / 28.3, 200 rows 65.1 / 37.1;
 // d = 1024, 300 rows 117 / 59, 512 rows 121 / 70.  Relative error of the entropies against 64 bits, mean of 12 sets: d = 768, 48 rows
 // 9.5e-8 / 9.5e-8, d = 2048, 200 rows 1.10e-7 / 1.14e-7.)
+// They still do where the batched kernel has too little to spread.  Small vocabularies leave it workgroups without a tile, or with one whose
+// k it does not split, while this kernel deals the workgroups to groups of 64 rows (bias_few; us, weights in memory, d = 2560, there / here:
+// V = 1000, 65 / 200 / 1000 rows 24.0 / 21.0, 27.7 / 22.2, 33.2 / 27.7; V = 4000, 128 / 256 / 512 rows 25.3 / 22.6, 30.3 / 25.2, 33.8 / 32.1;
+// V = 8000, 128 / 256 rows 30.9 / 28.6, 39.4 / 33.5; beyond the line V = 16000, 100 / 200 rows 39 / 39, 44 / 54, V = 4000, 1000 rows
+// 43 / 51, V = 8000, 512 rows 42.7 / 49.6).  Numbers of groups that are no power of two make this kernel slower (V = 4000, 320 rows
+// 29.1 / 37.3, V = 8000, 150 rows 33 / 37, V = 1000, 320 rows 26.1 / 24.7) and have a line of their own.
+// And one group of at most 64 rows on a vocabulary of seven tiles a pass with long k loops, whose weights fit no cache (there / here,
+// 48 rows of V = 50304: d = 3072 74.8 / 73.1, 3584 85.2 / 79.8, 4096 94 / 87; V = 57000 78.7 / 80.1, 90.9 / 90.0, 103 / 100; below the line
+// d = 2560 66 / 63 on weights met for the first time but 52 / 60 on a head called again).
 // fp32 beyond 32 rows goes where its products cost least: this kernel makes them of bf16 parts (ks_step), gemm_launch's
 // of fp32 matrix instructions, but with less to do at the end of a pass, of which a narrow head has many.  One
 // head of V = 50304, us, this kernel against that, 64 / 300 / 1000 rows: d = 64 22.5 / 60 / 141 against 16.9 / 46 / 114,
@@ -122,10 +131,18 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // Contexts of `wide` values (eh_internal.hpp) with a bias vector go there at any number of rows: its statistics test every
 // logit.  fp32 ones take its form on fp32 matrix instructions, and gemm_launch's kernel beyond 32 rows without one.
 constexpr int kF32Split = 256;
+constexpr int kBiasLongK = 3072;
+bool bias_few(const eh_ctx* c, int n_rows) {
+  const int groups = (n_rows + 63) / 64;
+  const int64_t tiles = (int64_t)c->VT * groups;
+  return c->VT <= 512 && tiles <= ((groups & (groups - 1)) == 0 ? 2048 : 512);
+}
 bool use_ksplit(const eh_ctx* c, int n_rows) {
-  if (n_rows <= 32 || (c->wide && !c->bias.empty())) return true;
-  if (c->dtype == EH_F32) return !c->bias.empty() || (c->d >= kF32Split && !c->wide);
-  return n_rows <= 64 && ksplit_pass_tiles(c) < 7;
+  const bool bias = !c->bias.empty();
+  if (n_rows <= 32 || (c->wide && bias)) return true;
+  if (c->dtype == EH_F32) return bias || (c->d >= kF32Split && !c->wide);
+  if (n_rows <= 64) return ksplit_pass_tiles(c) < 7 || (bias && c->d >= kBiasLongK);
+  return bias && bias_few(c, n_rows);
 }
 // Rows per block of the activations' operand order: 16 for gemm_launch's kernel, 32 for all others.
 int row_block(const eh_ctx* c, int n_rows) { return c->dtype == EH_BF16 || use_ksplit(c, n_rows) ? 32 : 16; }

@@ -474,11 +474,8 @@ def test_fp32_products_keep_their_24_bits(B, exponent):
         assert np.abs(lse.double().cpu().numpy() / z - 1.0).max() <= 2.0 ** -21 and bool((am == 0).all())
 
 
-@pytest.mark.parametrize("V,rows", [(50257, 33), (50257, 64), (1500, 65), (9001, 129), (20011, 160), (40001, 200), (60001, 300), (17, 513)])
-def test_batched_kernel_with_a_bias_vector(B, V, rows):
-    """bf16 heads with a bias vector beyond 32 rows (64 where a pass has fewer than seven tiles): the bias is added to
-    the finished sums.  Ragged last tiles, a bias that decides the argmax, a cascade, and a verification."""
-    w, heads, hid, bs = _bias_heads(136, V, 2, rows, "bf16", V + rows)
+def _check_bias_heads(B, d, V, rows):
+    w, heads, hid, bs = _bias_heads(d, V, 2, rows, "bf16", V + rows)
     bs[1] *= 20.0
     orc = [_oracle(hid.h[l], heads.gamma[l], heads.beta[l], P.f64(heads.W[l]), bs[l], True) for l in range(2)]
     tau = [float(np.median(orc[0][0])), float("inf")]
@@ -495,6 +492,22 @@ def test_batched_kernel_with_a_bias_vector(B, V, rows):
     clear = torch.from_numpy(orc[1][3] >= P.NEAR_TIE)
     assert torch.equal(tgt[0].cpu()[clear], torch.from_numpy(orc[1][2].astype(np.int32))[clear])
     B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("V,rows", [(50257, 33), (50257, 64), (1500, 65), (9001, 129), (20011, 160), (40001, 200), (60001, 300), (17, 513)])
+def test_batched_kernel_with_a_bias_vector(B, V, rows):
+    """bf16 heads with a bias vector beyond 32 rows (64 where a pass has fewer than seven tiles): the bias is added to
+    the finished sums.  Ragged last tiles, a bias that decides the argmax, a cascade, and a verification."""
+    _check_bias_heads(B, 136, V, rows)
+
+
+@pytest.mark.parametrize("d,V,rows", [
+    (136, 8192, 128), (136, 8193, 128), (136, 8192, 129), (136, 8192, 256), (136, 8192, 257), (136, 4096, 512), (136, 4096, 513),
+    (136, 2720, 190), (136, 2721, 190), (136, 16, 321), (3072, 50304, 33), (3064, 50304, 33), (3072, 49153, 64), (3072, 50304, 65)])
+def test_bias_heads_on_both_sides_of_their_lines(B, d, V, rows):
+    """Heads with a bias vector on few words for their rows, and of long k loops on up to 64 rows, run on the k-split kernel:
+    each line from both sides."""
+    _check_bias_heads(B, d, V, rows)
 
 
 @pytest.mark.parametrize("dtype,d,V,rows", [
@@ -654,6 +667,24 @@ def test_rows_do_not_depend_on_their_place_in_the_list(B, R, counts):
             other = _eval(B, ctx, 0, hid.h[0], R, row_idx=torch.cat([p, torch.arange(n, R)]).to(torch.int32).to(DEV), n_rows_dev=live)
             for a, b in zip(other, one):
                 assert torch.equal(a[:n], b[:n][p.to(DEV)])
+    B.eh_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype,d,V,R,counts", [("bf16", 136, 8001, 128, (33, 65, 90, 128)), ("bf16", 136, 20011, 200, (65, 150, 192)),
+                                                ("f32", 256, 20011, 200, (33, 65, 100, 161)), ("f32", 128, 20011, 100, (33, 65, 90))])
+def test_rows_of_bias_and_fp32_heads_do_not_depend_on_their_place(B, dtype, d, V, R, counts):
+    """The same for heads with a bias vector and fp32 heads with one, on the k-split kernel and the batched one: a group's last
+    block of rows alone or beside another, and lists of every number of groups."""
+    w, heads, hid, bs = _bias_heads(d, V, 1, R, dtype, V + R)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=R, bias=bs)
+    gen = torch.Generator().manual_seed(R)
+    for n in counts:
+        live = torch.tensor([n], dtype=torch.int32, device=DEV)
+        one = _eval(B, ctx, 0, hid.h[0], R, n_rows_dev=live)
+        p = torch.randperm(n, generator=gen)
+        other = _eval(B, ctx, 0, hid.h[0], R, row_idx=torch.cat([p, torch.arange(n, R)]).to(torch.int32).to(DEV), n_rows_dev=live)
+        for a, b in zip(other, one):
+            assert torch.equal(a[:n], b[:n][p.to(DEV)])
     B.eh_destroy(ctx)
 
 
