@@ -117,8 +117,12 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // d = 128 23.2 / 65 / 146 against 20.6 / 64 / 165, d = 192 28.3 / 87 / 203 against 24.9 / 83 / 215, d = 256 28.8 / 94 / 205
 // against 28.7 / 101 / 265, d = 384 34.0 / 120 / 267 against 36.0 / 138 / 362; d = 1024, 100 and 4096 rows 89 and 2412
 // against 123 and 3355.  The error against 64 bits is smaller (relative, entropies / log-sum-exps, this kernel against
-// that: d = 1024, 128 rows 1.3e-7 / 8e-8 against 6e-7 / 3e-7; against this kernel on fp32 matrix instructions, the mean of
-// 24 sets of 27 rows 1.4e-7 / 7e-8 against 1.6e-7 / 9e-8).
+// that: d = 1024, 128 rows 1.3e-7 / 8e-8 against 6e-7 / 3e-7, d = 288, 48 rows 8.8e-8 / 2.6e-8 against 3.3e-7 / 4.4e-8; against
+// this kernel on fp32 matrix instructions, the mean of 24 sets of 27 rows 1.4e-7 / 7e-8 against 1.6e-7 / 9e-8).  For that error the
+// line lies at d = 256 although this kernel works in steps of 128 of k, and widths well below the next multiple are slower
+// on vocabularies of seven tiles a pass (V = 50304, 48 / 130 rows on weights in memory: d = 256 32.2 / 60 against 30.7 / 60, d = 288
+// 36.3 / 72.6 against 33.2 / 65.3, d = 320 37.7 / 75.5 against 35.5 / 70.0, d = 384 38 / 77 against 39 / 80; V = 32000, d = 288 26 / 48 against
+// 27 / 48).
 // bf16 at 33 to 64 rows: with seven tiles a pass (V above 12 tiles of 16 a workgroup, 49152 on 256
 // compute units, up to 57344) two blocks of rows fill the register file, and the statistics behind a
 // pass spill; gemm32_launch's kernel is then the better one.  With six tiles and fewer it is the better one for a
