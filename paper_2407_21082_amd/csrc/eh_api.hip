@@ -229,7 +229,8 @@ bool use_decode(const eh_ctx* c, int n_rows) { return c->decode_grid > 0 && n_ro
 // A verification: its one head cannot hide the LayerNorm and the hand-over in front of its weights, and three launches
 // take less time at every size measured (us, one launch / three: V = 50304, d = 512, 24 and 64 positions 28.6 / 19.4 and
 // 34.3 / 21.3, d = 1024, 40 positions 41.3 / 27.6, d = 2048, 64 56.8 / 42.7, d = 2560, 18 and 63 59.6 / 52.3 and
-// 67.4 / 52.7; V = 32000, d = 1024, 60 32.9 / 22.3; V = 128256, d = 2048, 32 100 / 93).  Heads of less than kVerifySmall
+// 67.4 / 52.7; V = 32000, d = 1024, 60 32.9 / 22.3; V = 128256, d = 2048, 32 100 / 93; one sequence of 64, V = 32000, d = 256 26.6 / 19.2,
+// V = 50304, d = 2560 68.8 / 61.5).  Heads of less than kVerifySmall
 // elements still take one launch up to 64 positions, and not because it is the faster way (V = 20000, d = 256, 48
 // 23.3 / 14.8): the tests of a verification that gives up its bounded wait and is tried again run there.
 constexpr int64_t kVerifySmall = 6000000;
@@ -752,7 +753,7 @@ eh_status dssd_verify(eh_ctx* ctx, const void* f_final, const int32_t* draft, co
     launch_ln(ctx, fin, f_final, ctx->d, nullptr, nullptr, (int)rows, R_pad, ctx->yf, s);
     PartCount parts;
     EH_HIP(ctx, project(ctx, fin, 1, nullptr, (int)rows, true, ctx->yf, ctx->partials, &parts, s));
-    hipLaunchKernelGGL(verify_post_kernel, dim3(B), dim3(kWave * std::min(kVerifyWaves, k + 1)), (size_t)(k + 1) * sizeof(int), s, ctx->partials,
+    hipLaunchKernelGGL(verify_post_kernel, dim3(B), dim3(kWave * verify_waves(parts.n, k)), (size_t)(k + 1) * sizeof(int), s, ctx->partials,
                        parts.n, R_pad, draft, draft_len, k, target, accepted, next_token);
     EH_HIP(ctx, hipGetLastError());
     return EH_OK;

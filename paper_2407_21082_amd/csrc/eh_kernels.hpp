@@ -6,6 +6,8 @@
 #pragma once
 #include "eh_device.hpp"
 
+#include <algorithm>
+
 namespace eh {
 
 // A context's copy of a bias vector, by one workgroup.  Entries that mask a word (-infinity, the lowest float) are raised to
@@ -690,52 +692,113 @@ static __global__ void verify_compare_kernel(const int* __restrict__ draft, cons
 }
 
 // The same behind the batched projection in one launch: workgroup b merges the partial
-// argmax records of row b's k+1 positions (one wave per position, up to 16 at a time: with four, whose
-// records came one after the other, 9 positions took 8.5 us of a verification's 72), then
-// its first thread walks the prefix.  `target` (nullable) receives the merged argmaxes.
-constexpr int kVerifyWaves = 16;
+// argmax records of row b's k+1 positions, then its first wave finds the end of the prefix, 64 positions at a
+// time.  `target` (nullable) receives the merged argmaxes.
+//
+// What bounds it is how many cache lines one compute unit can ask for: records lie [part][row], so the lanes of a wave take
+// neighbouring positions of a part, and of as many parts as there is room for, and the waves share the parts.  (With a wave to a
+// position, whose lanes take a part and a line each, and a prefix walked by one thread, us, verification with V = 50304, all drafts
+// accepted: d = 512, one row of 32 / 64 / 200 positions 26.7 / 36.6 / 77.4 against 21.2 / 23.1 / 41.8 this way, d = 2560, 4 rows of 40
+// 66.9 / 59.2.)  Up to kVerifyFew positions, where that saves no line, a wave a position is the shorter way: no second
+// stage through LDS (d = 512, 64 rows of 2 positions 22.3 / 22.6, 32 of 3 21.6 / 22.2).
+constexpr int kVerifyWaves = 16;  // at most
+constexpr int kVerifyFew = 4;
+// As many waves as ask for all records at once, and as have sixteen lanes for every position of a turn.
+inline int verify_waves(int n_parts, int k) {
+  if (k < kVerifyFew) return k + 1;
+  const int sub = kWave / std::min(kWave, k + 1);
+  int waves = 4;
+  while (waves < kVerifyWaves && waves * 4 * sub < n_parts) waves *= 2;
+  return k < 4 * waves ? waves : kVerifyWaves;
+}
+__device__ __forceinline__ void argmax_take(float& zb, int& ib, float z, int i) {
+  if (z > zb || (z == zb && i < ib)) { zb = z; ib = i; }
+}
+// The records g0, g0 + step, ... of a position, four asked for at a time.
+__device__ __forceinline__ void argmax_records(const Stats* rec, int g0, int step, int n_parts, int R_pad, float& zb, int& ib) {
+  for (; g0 < n_parts; g0 += 4 * step) {
+    float z[4];
+    int i4[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // (the last record again where there are no more: no difference)
+      const Stats& q = rec[(int64_t)min(g0 + i * step, n_parts - 1) * R_pad];
+      z[i] = q.zb;
+      i4[i] = q.ib;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) argmax_take(zb, ib, z[i], i4[i]);
+  }
+}
 static __global__ __launch_bounds__(kVerifyWaves* kWave) void verify_post_kernel(
     const Stats* __restrict__ partials, int n_parts, int R_pad, const int* __restrict__ draft,
     const int* __restrict__ draft_len, int k, int* __restrict__ target, int* __restrict__ accepted,
     int* __restrict__ next_token) {
   extern __shared__ int verify_tgt[];  // k + 1 entries
-  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int j = wave; j <= k; j += (int)blockDim.x / kWave) {
-    const int p = b * (k + 1) + j;
+  __shared__ float wave_z[kVerifyWaves][kWave];
+  __shared__ int wave_i[kVerifyWaves][kWave];
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = (int)blockDim.x / kWave;
+  const int64_t p0 = (int64_t)b * (k + 1);
+  if (k < kVerifyFew) {
     float zb = -INFINITY;
     int ib = 0x7fffffff;
-    for (int g0 = lane; g0 < n_parts; g0 += 4 * kWave) {  // four records asked for at a time
-      float z[4];
-      int i4[4];
+    argmax_records(partials + p0 + wave, lane, kWave, n_parts, R_pad, zb, ib);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const Stats& q = partials[(int64_t)min(g0 + i * kWave, n_parts - 1) * R_pad + p];
-        z[i] = q.zb;
-        i4[i] = q.ib;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)  // (the last record again where there are no more: no difference)
-        if (z[i] > zb || (z[i] == zb && i4[i] < ib)) { zb = z[i]; ib = i4[i]; }
-    }
-#pragma unroll
-    for (int x = 32; x > 0; x >>= 1) {
-      const float oz = __shfl_xor(zb, x);
-      const int oi = __shfl_xor(ib, x);
-      if (oz > zb || (oz == zb && oi < ib)) { zb = oz; ib = oi; }
-    }
+    for (int x = kWave / 2; x > 0; x >>= 1) argmax_take(zb, ib, __shfl_xor(zb, x), __shfl_xor(ib, x));
     if (lane == 0) {
-      verify_tgt[j] = argmax_or_none(ib);
-      if (target) target[p] = argmax_or_none(ib);
+      verify_tgt[wave] = argmax_or_none(ib);
+      if (target) target[p0 + wave] = argmax_or_none(ib);
+    }
+    __syncthreads();
+  } else {
+    for (int c0 = 0; c0 <= k; c0 += kWave) {
+      const int n = min(kWave, k + 1 - c0);      // positions of this turn
+      const int sub = kWave / n, at = lane / n;  // parts a wave takes at once, and the lane's one
+      float zb = -INFINITY;
+      int ib = 0x7fffffff;
+      // (lanes without a part take the last one's too)
+      argmax_records(partials + p0 + c0 + (lane - at * n), wave * sub + min(at, sub - 1), waves * sub, n_parts, R_pad, zb, ib);
+      for (int h = kWave / 2; h > 0; h >>= 1) {
+        if (h >= sub) continue;  // (the same for all lanes)
+        const int from = at + h < sub ? lane + h * n : lane;
+        argmax_take(zb, ib, __shfl(zb, from), __shfl(ib, from));
+      }
+      if (lane < n) {
+        wave_z[wave][lane] = zb;
+        wave_i[wave][lane] = ib;
+      }
+      __syncthreads();
+      // sixteen neighbouring lanes to a position, the first with a wave's record each
+      const int pos = threadIdx.x / kVerifyWaves, of = min((int)threadIdx.x % kVerifyWaves, waves - 1);
+      zb = wave_z[of][min(pos, n - 1)];
+      ib = wave_i[of][min(pos, n - 1)];
+#pragma unroll
+      for (int x = kVerifyWaves / 2; x > 0; x >>= 1) {
+        if (x >= waves) continue;
+        argmax_take(zb, ib, __shfl_xor(zb, x), __shfl_xor(ib, x));
+      }
+      if (threadIdx.x % kVerifyWaves == 0 && pos < n) {
+        verify_tgt[c0 + pos] = argmax_or_none(ib);
+        if (target) target[p0 + c0 + pos] = argmax_or_none(ib);
+      }
+      __syncthreads();
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
+  if (wave == 0) {
     int len = k;
     if (draft_len) len = min(max(draft_len[b], 0), k);
     int n = 0;
-    while (n < len && draft[(int64_t)b * k + n] == verify_tgt[n]) ++n;
-    accepted[b] = n;
-    next_token[b] = verify_tgt[n];
+    for (;; n += kWave) {  // (ends: the lane at position len stops)
+      const int j = n + lane;
+      const unsigned long long stop = __ballot(j >= len || draft[(int64_t)b * k + j] != verify_tgt[j]);
+      if (stop) {
+        n += __ffsll(stop) - 1;
+        break;
+      }
+    }
+    if (lane == 0) {
+      accepted[b] = n;
+      next_token[b] = verify_tgt[n];
+    }
   }
 }
 

@@ -406,6 +406,34 @@ def test_verification_on_both_sides_of_small_heads(B, V, Bsz, k):
     B.eh_destroy(ctx)
 
 
+@pytest.mark.parametrize("Bsz,k", [(2, 1), (40, 3), (30, 4), (9, 8), (1, 15), (1, 16), (3, 17), (1, 31), (1, 32), (1, 63), (2, 64), (1, 65), (2, 130), (1, 200)])
+def test_verification_of_long_drafts(B, Bsz, k):
+    """One, two and four positions a wave and prefixes that end on both sides of 64 positions and of 128, by a mismatch, by the draft's
+    length or not at all.  Targets are the argmaxes of the same rows; the prefix rule by hand."""
+    d, rows = 320, Bsz * (k + 1)
+    w = G.Workload("long", d=d, V=20011, n_heads=1, rows=rows, dtype="bf16", seed=rows, kappa=0.6)
+    heads = G.make_heads(w, DEV)
+    hid = G.make_hidden(w, heads, DEV)
+    ctx = B.eh_create(heads.W, heads.gamma, heads.beta, [0.0], max_rows=rows)
+    want = _eval(B, ctx, 0, hid.h[0], rows)[2].reshape(Bsz, k + 1)
+    orc = _oracle(hid.h[0], heads.gamma[0], heads.beta[0], P.f64(heads.W[0]), None, True)
+    clear = torch.from_numpy(orc[3] >= P.NEAR_TIE)
+    assert torch.equal(want.reshape(-1).cpu()[clear], torch.from_numpy(orc[2].astype(np.int32))[clear])
+    f = hid.h[0].reshape(Bsz, k + 1, d).contiguous()
+    for stop in sorted({0, 1, k // 2, 62, 63, 64, 65, 127, 128, 129, k - 1, k} & set(range(k + 1))):
+        for by_length in (False, True):
+            draft, dlen = want[:, :k].clone(memory_format=torch.contiguous_format), None
+            if by_length:
+                dlen = torch.full((Bsz,), stop, dtype=torch.int32, device=DEV)
+            elif stop < k:
+                draft[:, stop] += 1
+                draft[:, stop + 1:] = -1
+            acc, nxt, tgt = _ints(Bsz), _ints(Bsz), _ints(Bsz, k + 1)
+            B.dssd_verify(ctx, f, draft, dlen, acc, nxt, tgt)
+            assert torch.equal(tgt, want) and bool((acc == stop).all()) and torch.equal(nxt, want[:, stop])
+    B.eh_destroy(ctx)
+
+
 @pytest.mark.parametrize("rows", [129, 160, 161, 192, 193, 300, 353])
 @pytest.mark.parametrize("V", [3000, 20011, 40001, 50257, 60001])
 def test_five_and_six_blocks_of_rows(B, rows, V):
