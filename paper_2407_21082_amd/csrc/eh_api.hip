@@ -347,27 +347,26 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
   const int Vp = c->VT * 16;
   c->Wf.resize(c->n_heads); c->gamma.resize(c->n_heads); c->beta.resize(c->n_heads);
   if (cfg->bias) c->bias.resize(c->n_heads);
-  int* wide = nullptr;
-  if ((e = dev_alloc(c, &wide, (size_t)1)) != hipSuccess) return bail(e, "hipMalloc(wide)");
-  if ((e = hipMemset(wide, 0, sizeof(int))) != hipSuccess) return bail(e, "memset wide");
+  // the status word both persistent kernels report a given-up wait in (read by eh_check), and what is found about the values
+  if ((e = dev_alloc(c, &c->dec_status, (size_t)4)) != hipSuccess) return bail(e, "hipMalloc(status)");
+  if ((e = hipMemset(c->dec_status, 0, 16)) != hipSuccess) return bail(e, "memset");
+  int* const wide = c->dec_status + 1;
   for (int l = 0; l < c->n_heads; ++l) {
     if ((e = dev_alloc(c, &c->Wf[l], wf_frags)) != hipSuccess) return bail(e, "hipMalloc(W)");
     if ((e = dev_alloc(c, &c->gamma[l], (size_t)c->d)) != hipSuccess) return bail(e, "hipMalloc(gamma)");
     if ((e = dev_alloc(c, &c->beta[l], (size_t)c->d)) != hipSuccess) return bail(e, "hipMalloc(beta)");
-    const unsigned blocks = (unsigned)((wf_frags + 255) / 256);
-    if (c->dtype == EH_BF16)
-      hipLaunchKernelGGL((repack_w_kernel<DtBf16>), dim3(blocks), dim3(256), 0, 0, cfg->W[l], c->V,
-                         c->d, c->VT, c->KS, c->Wf[l], wide);
-    else
-      hipLaunchKernelGGL((repack_w_kernel<DtF32>), dim3(blocks), dim3(256), 0, 0, cfg->W[l], c->V,
-                         c->d, c->VT, c->KS, c->Wf[l], wide);
-    if ((e = hipGetLastError()) != hipSuccess) return bail(e, "repack launch");
     if ((e = hipMemcpy(c->gamma[l], cfg->gamma[l], sizeof(float) * c->d, hipMemcpyDeviceToDevice)) != hipSuccess)
       return bail(e, "copy gamma");
     if ((e = hipMemcpy(c->beta[l], cfg->beta[l], sizeof(float) * c->d, hipMemcpyDeviceToDevice)) != hipSuccess)
       return bail(e, "copy beta");
-    hipLaunchKernelGGL(check_wide_kernel, dim3(1), dim3(256), 0, 0, c->gamma[l], c->beta[l], c->d, wide);
-    if ((e = hipGetLastError()) != hipSuccess) return bail(e, "check launch");
+    const unsigned blocks = (unsigned)((wf_frags + 255) / 256);
+    if (c->dtype == EH_BF16)
+      hipLaunchKernelGGL((repack_w_kernel<DtBf16>), dim3(blocks), dim3(256), 0, 0, cfg->W[l], c->V,
+                         c->d, c->VT, c->KS, c->Wf[l], c->gamma[l], c->beta[l], wide);
+    else
+      hipLaunchKernelGGL((repack_w_kernel<DtF32>), dim3(blocks), dim3(256), 0, 0, cfg->W[l], c->V,
+                         c->d, c->VT, c->KS, c->Wf[l], c->gamma[l], c->beta[l], wide);
+    if ((e = hipGetLastError()) != hipSuccess) return bail(e, "repack launch");
     if (cfg->bias) {
       if ((e = dev_alloc(c, &c->bias[l], (size_t)Vp)) != hipSuccess) return bail(e, "hipMalloc(bias)");
       if ((e = hipMemset(c->bias[l], 0, sizeof(float) * Vp)) != hipSuccess) return bail(e, "memset bias");
@@ -432,9 +431,6 @@ eh_status eh_create(const eh_config* cfg, eh_ctx** out) {
       if ((e = hipGetDeviceProperties(&prop, c->device)) != hipSuccess) return bail(e, "device properties");
       c->num_cu = prop.multiProcessorCount;
     }
-    // the status word both persistent kernels report a given-up wait in (read by eh_check)
-    if ((e = dev_alloc(c, &c->dec_status, (size_t)4)) != hipSuccess) return bail(e, "hipMalloc(status)");
-    if ((e = hipMemset(c->dec_status, 0, 16)) != hipSuccess) return bail(e, "memset");
     if (c->decode_grid > 0) {
       const size_t nrec = 2 * np * c->decode_grid * 16 * 5;
       if ((e = dev_alloc(c, &c->dec_records, nrec)) != hipSuccess) return bail(e, "hipMalloc(decode)");

@@ -40,17 +40,18 @@ static __global__ __launch_bounds__(kBiasThreads) void copy_bias_kernel(const fl
 
 // ---------------------------------------------------------------------------
 // Row-major W [V, d] -> fragment-major copy (done once, at context creation).
-// One thread per 16-byte chunk of the destination.  *wide is set if a value is not within 2^30.
+// One thread per 16-byte chunk of the destination.  *wide is set if a weight, or a value of gamma or beta, is not
+// within 2^30.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kWideBits = 0x4e800000u;  // 2^30
 __device__ __forceinline__ bool f32_is_wide(uint32_t bits) { return (bits & 0x7fffffffu) > kWideBits; }
-static __global__ void check_wide_kernel(const float* __restrict__ x, const float* __restrict__ y, int n, int* __restrict__ wide) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    if (f32_is_wide(__float_as_uint(x[i])) || f32_is_wide(__float_as_uint(y[i]))) *wide = 1;
-}
 template <typename DT>
 __global__ __launch_bounds__(256) void repack_w_kernel(const void* __restrict__ W, int V, int d,
-                                                       int VT, int KS, frag_t* __restrict__ Wf, int* __restrict__ wide) {
+                                                       int VT, int KS, frag_t* __restrict__ Wf, const float* __restrict__ gamma,
+                                                       const float* __restrict__ beta, int* __restrict__ wide) {
+  if (blockIdx.x == 0)  // (the context's copies, [d])
+    for (int i = threadIdx.x; i < d; i += blockDim.x)
+      if (f32_is_wide(__float_as_uint(gamma[i])) || f32_is_wide(__float_as_uint(beta[i]))) *wide = 1;
   const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t total = (int64_t)VT * KS * kWave;
   if (o >= total) return;
